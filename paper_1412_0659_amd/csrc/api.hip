@@ -52,7 +52,7 @@ void free_all(bh_ctx *c) {
         f(s.x64); f(s.y64); f(s.z64);
         f(c->sort.key[k]); f(c->sort.idx[k]);
     }
-    f(c->acc); f(c->xyzm); f(c->spill); f(c->box); f(c->box_part); f(c->status); f(c->work); f(c->totals);
+    f(c->acc); f(c->xyzm); f(c->pacc); f(c->pcnt); f(c->spill); f(c->box); f(c->box_part); f(c->status); f(c->work); f(c->totals);
     f(c->sort.counts); f(c->sort.scan_part);
     Cells &q = c->cells;
     f(q.prefix); f(q.level); f(q.begin); f(q.count); f(q.child0); f(q.nchild); f(q.parent);
@@ -292,15 +292,17 @@ size_t static_layout(bh_ctx *c, unsigned char *base) {
     take(&c->sort.counts, (size_t)c->sort.counts_len);
     take(&c->sort.scan_part, (size_t)c->sort.scan_part_len);
     take(&c->acc, n); take(&c->xyzm, n);
+    take(&c->pacc, (size_t)split_rows(c->nmax)); take(&c->pcnt, (size_t)split_rows(c->nmax));
     take(&c->spill, (size_t)c->walk_grid * kStackMax);
-    take(&c->box, 8); take(&c->box_part, 6 * 1024); take(&c->status, 4); take(&c->work, 8);
+    take(&c->box, 8); take(&c->box_part, 6 * 1024); take(&c->status, 4); take(&c->work, 8 * kWorkStride);
     take(&c->totals, 4);
     Cells &q = c->cells;
     take(&q.prefix, nc); take(&q.level, nc); take(&q.begin, nc); take(&q.count, nc);
     take(&q.child0, nc); take(&q.nchild, nc); take(&q.parent, nc); take(&q.ls, kLsSize);
     take(&q.part, kBuildGrid + 1); take(&q.lbt, ((size_t)1 << (3 * kTableLevel)) + 1);
     take(&q.cbnd, 8 * n);
-    take(&q.M, nc); take(&q.S, 3 * nc); take(&q.com, 3 * nc); take(&q.Q, 6 * nc);
+    take(&q.M, nc); take(&q.S, 3 * nc); take(&q.Q, 6 * nc);
+    q.com = nullptr;  // (only bh_export reads it)
     take(&q.wA, nc); take(&q.wN, nc); take(&q.P0, nc); take(&q.P1, nc); take(&q.P2, nc);
     take(&q.size, nc);
     Groups &g = c->groups;
@@ -415,9 +417,10 @@ int bh_create(bh_ctx **out, int64_t n_max, const bh_params *p) {
     }
     c->pair_groups = (uint32_t)prm.pair_groups;
     ok = ok && dalloc(&c->acc, n, err) && dalloc(&c->xyzm, n, err) &&
-         dalloc(&c->spill, (size_t)c->walk_grid * kStackMax, err) && dalloc(&c->box, 8, err) &&
+         dalloc(&c->pacc, (size_t)split_rows(n_max), err) &&
+         dalloc(&c->pcnt, (size_t)split_rows(n_max), err) && dalloc(&c->spill, (size_t)c->walk_grid * kStackMax, err) && dalloc(&c->box, 8, err) &&
          dalloc(&c->box_part, 6 * 1024, err) && dalloc(&c->status, 4, err) &&
-         dalloc(&c->work, 8, err) && dalloc(&c->totals, 4, err) &&
+         dalloc(&c->work, 8 * kWorkStride, err) && dalloc(&c->totals, 4, err) &&
          dalloc(&c->sort.counts, (size_t)c->sort.counts_len, err) &&
          dalloc(&c->sort.scan_part, (size_t)c->sort.scan_part_len, err) &&
          dalloc(&q.prefix, nc, err) && dalloc(&q.level, nc, err) && dalloc(&q.begin, nc, err) &&

@@ -21,6 +21,7 @@ constexpr int kBuildGrid = 2048;        // grid of the octree level kernels: 8 w
 constexpr int kTableLevel = 7;          // the build looks up the child bounds of levels < 7
 constexpr uint32_t kLeafBit = 0x80000000u;
 constexpr uint32_t kNone = 0xffffffffu;
+constexpr int kWorkStride = 32;         // a cache line per work counter of the walk
 constexpr int kStackMax = 2689;         // walk stack bound: 21 levels x 128 ranges + root
 // Adjoint: the cells of the top levels (the first kHotCells in level order) are hit by far
 // more groups than the rest, so their accumulators come in kHotCopies copies (4 per XCD).
@@ -142,11 +143,13 @@ struct bh_ctx {
     int cur = 0;
     float4 *acc = nullptr;  // sorted acceleration + potential
     float4 *xyzm = nullptr; // sorted position + mass, one record per particle
+    float4 *pacc = nullptr;     // split walks: partial sums, one row of n per wave of a group
+    uint2 *pcnt = nullptr;      // their interaction counts per group
     uint32_t *spill = nullptr;  // walk stack spill area, kStackMax per wave
     float *box = nullptr;   // [8]: lo xyz, side, scale
     float *box_part = nullptr;
     uint32_t *status = nullptr;
-    uint32_t *work = nullptr;                // [8] walk work counters
+    uint32_t *work = nullptr;                // [8][kWorkStride] walk work counters, one per line
     unsigned long long *totals = nullptr;    // [4] n_pp, n_pc, leaves
     bh::Sort sort{};
     bh::Cells cells{};
@@ -267,6 +270,27 @@ void launch_walk(bh_ctx *c, float eps, hipStream_t st);
 void launch_walk_view(bh_ctx *c, const SrcView &v, float eps, bool remote, bool accum,
                       hipStream_t st);
 int walk_blocks_per_cu();
+// A small set has fewer groups than the chip has wave slots, and the longest
+// walk (a wide group on the outskirts) sets the time, so 2^logw waves share
+// each group's walk.  Splitting costs throughput (every wave repeats the top
+// of the walk, lists are shorter), so fewer waves share as the groups become
+// more.  Measured, force of a disk + halo set at theta 0.4 in us by waves per
+// group (1 / 2 / 4 / 8): n = 1000: 77 / 58 / 49 / 48; 4096: 235 / 147 / 97 /
+// 90; 16384: 475 / 295 / 231 / 233; 32768: 581 / 429 / 407 / 448; 65536: 666 /
+// 601 / 564 / 663; 131072: 964 / 865 / 835 / 900; 262144: 1483 / 1393 / 1378;
+// at theta 0.6 two waves are as fast as one at 131072 (495 against 486) and 4%
+// slower at 262144, four 25% slower at 196608.
+constexpr int64_t kSplit8 = 4096, kSplit4 = 40960, kSplit2 = 147456;
+inline uint32_t split_logw(int64_t n) {
+    return n <= kSplit8 ? 3u : (n <= kSplit4 ? 2u : (n <= kSplit2 ? 1u : 0u));
+}
+// entries (one row of n per wave) of the partial sums of a context of n_max
+inline int64_t split_rows(int64_t n_max) {
+    const int64_t a = 8 * (n_max < kSplit8 ? n_max : kSplit8),
+                  b = n_max > kSplit8 ? 4 * (n_max < kSplit4 ? n_max : kSplit4) : 0,
+                  c = n_max > kSplit4 ? 2 * (n_max < kSplit2 ? n_max : kSplit2) : 0;
+    return a > b ? (a > c ? a : c) : (b > c ? b : c);
+}
 
 // integrate.hip
 void launch_ingest(bh_ctx *c, const float *pos, const float *vel, const float *mass, uint32_t n,

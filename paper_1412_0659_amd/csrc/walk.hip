@@ -28,6 +28,11 @@ struct WalkArgs {
     uint32_t ring;  // resident stack entries allowed: kRing, or 192 to exercise the spill path
     uint32_t remote;  // 1: the walked tree is another domain's (no self pair)
     uint32_t accum;   // 1: add to acc, npp, npc instead of overwriting them
+    // split walks: 2^logw waves per group; wave w's sums of sorted particle i
+    // at pacc[w * pstride + i], its counts (p-p, p-c) of group g at pcnt[w * pstride + g]
+    uint32_t logw, pstride;
+    float4 *pacc;
+    uint2 *pcnt;
 };
 
 __device__ __forceinline__ float rsq(float v) { return __builtin_amdgcn_rsqf(v); }
@@ -239,9 +244,15 @@ __device__ __forceinline__ void eval_chunk(Phase &ph, uint32_t n, const WalkLds 
     }
 }
 
-template <bool kEps0, bool kF16>
-__device__ void walk_group(const WalkArgs &a, uint32_t g, uint32_t lane, WalkLds &L,
-                           Far16Lds &S, uint32_t *spill) {
+// Walk group g (kSplit: as wave w of 2^a.logw, leaving the partial sums for
+// k_walk_combine).
+template <bool kEps0, bool kF16, bool kSplit>
+__device__ void walk_group(const WalkArgs &a, uint32_t g, uint32_t w, uint32_t lane, WalkLds &L,
+                           uint32_t *spill) {
+    // the FP16 pair records share the FP32 staging area: a flush uses one
+    // or the other, and each flush rewrites its null source
+    static_assert(sizeof(Far16Lds) <= sizeof(L.stage), "pair records exceed the staging area");
+    Far16Lds &S = *reinterpret_cast<Far16Lds *>(&L.stage[0][0]);
     const uint32_t gb = a.gbeg[g];
     const uint32_t gn = a.gbeg[g + 1] - gb;  // 1..64 by construction
     if (gn == 0u || gn > 64u) {
@@ -253,7 +264,7 @@ __device__ void walk_group(const WalkArgs &a, uint32_t g, uint32_t lane, WalkLds
     const bool own = lane < gn;
     const float4 me = a.xyzm[gb + (own ? lane : 0u)];
     const GroupBox b = group_box(me, own);
-    if (lane == 0) {
+    if (lane == 0 && w == 0u) {
         a.gbox[2 * (size_t)g] = make_float4(b.cx, b.cy, b.cz, 0.f);
         a.gbox[2 * (size_t)g + 1] = make_float4(b.hx, b.hy, b.hz, 0.f);
     }
@@ -307,9 +318,9 @@ __device__ void walk_group(const WalkArgs &a, uint32_t g, uint32_t lane, WalkLds
         }
         for (uint32_t base = 0; base < n; base += kChunk) {
             const uint32_t m = n - base < (uint32_t)kChunk ? n - base : (uint32_t)kChunk;
-            __syncthreads();
+            wave_sync();
             L.stage[0][lane] = r0; L.stage[1][lane] = r1; L.stage[2][lane] = r2;
-            __syncthreads();
+            wave_sync();
             if (base + kChunk < n) {
                 const uint32_t q = base + kChunk + lane;
                 const uint32_t c = L.T.pcidx[q < n ? q : base + kChunk];
@@ -318,7 +329,7 @@ __device__ void walk_group(const WalkArgs &a, uint32_t g, uint32_t lane, WalkLds
             eval_chunk<true, kEps0>(p1, m, L, a.eps2);
             if (two) eval_chunk<true, kEps0>(p2, m, L, a.eps2);
         }
-        __syncthreads();
+        wave_sync();
     };
     // FP16 far field: each chunk is staged as FP16 pair records; cells too
     // close to the group for FP16 leave a hole and their indices are moved
@@ -347,12 +358,12 @@ __device__ void walk_group(const WalkArgs &a, uint32_t g, uint32_t lane, WalkLds
             // near: box distance d with d s < 1/4, i.e. d^2 < 2^(2e - 4)
             const float d2 = fmaf(bx, bx, fmaf(by, by, bz * bz));
             const bool near = valid && !(d2 >= ldexpf(1.f, 2 * e - 4));
-            __syncthreads();
+            wave_sync();
             stage16(S, lane, valid && !near, r0, r1, r2, cx, cy, cz, e, eg, a.eps2);
             const uint64_t nm = ballot(near);
             if (near) L.T.pcidx[nnear + count_below(nm)] = cidx;
             nnear += (uint32_t)__popcll(nm);
-            __syncthreads();
+            wave_sync();
             if (base + kChunk < n) {
                 const uint32_t q = base + kChunk + lane;
                 const uint32_t c = L.T.pcidx[q < n ? q : base + kChunk];
@@ -362,7 +373,7 @@ __device__ void walk_group(const WalkArgs &a, uint32_t g, uint32_t lane, WalkLds
             eval16_chunk(p1, np, S);
             if (two) eval16_chunk(p2, np, S);
         }
-        __syncthreads();
+        wave_sync();
         if (nnear) flush_pc32(nnear);
     };
     auto flush_pc = [&](uint32_t n) {
@@ -374,9 +385,9 @@ __device__ void walk_group(const WalkArgs &a, uint32_t g, uint32_t lane, WalkLds
         float4 r0 = a.sxyzm[L.T.ppidx[lane < n ? lane : 0u]];
         for (uint32_t base = 0; base < n; base += kChunk) {
             const uint32_t m = n - base < (uint32_t)kChunk ? n - base : (uint32_t)kChunk;
-            __syncthreads();
+            wave_sync();
             L.stage[0][lane] = r0;
-            __syncthreads();
+            wave_sync();
             if (base + kChunk < n) {
                 const uint32_t q = base + kChunk + lane;
                 r0 = a.sxyzm[L.T.ppidx[q < n ? q : base + kChunk]];
@@ -384,31 +395,38 @@ __device__ void walk_group(const WalkArgs &a, uint32_t g, uint32_t lane, WalkLds
             eval_chunk<false, kEps0>(p1, m, L, a.eps2);
             if (two) eval_chunk<false, kEps0>(p2, m, L, a.eps2);
         }
-        __syncthreads();
+        wave_sync();
     };
 
     uint32_t cnt_pc, cnt_pp;
     const TreeView tv{a.wA, a.wN, a.ring, a.status};
-    traverse(tv, b, lane, L.T, spill, cnt_pc, cnt_pp, flush_pc, flush_pp);
+    traverse<false, kSplit>(tv, b, lane, L.T, spill, cnt_pc, cnt_pp, flush_pc, flush_pp,
+                            Share{w, a.logw});
 
     // ---- sum the slices of each target (staging area reused)
     float4 res = make_float4(0.f, 0.f, 0.f, 0.f);
     L.stage[0][lane] = p1.acc;
-    __syncthreads();
+    wave_sync();
     if (lane < p1.T)
         for (uint32_t k = 0; k < p1.r; ++k) {
             const float4 o = L.stage[0][lane + k * p1.T];
             res.x += o.x; res.y += o.y; res.z += o.z; res.w += o.w;
         }
     if (two) {
-        __syncthreads();
+        wave_sync();
         L.stage[0][lane] = p2.acc;
-        __syncthreads();
+        wave_sync();
         if (lane >= p1.T && lane < gn)
             for (uint32_t k = 0; k < p2.r; ++k) {
                 const float4 o = L.stage[0][lane - p1.T + k * p2.T];
                 res.x += o.x; res.y += o.y; res.z += o.z; res.w += o.w;
             }
+    }
+    if (kSplit) {
+        if (own) a.pacc[(size_t)w * a.pstride + gb + lane] = res;
+        if (lane == 0) a.pcnt[(size_t)w * a.pstride + g] = make_uint2(cnt_pp, cnt_pc);
+        wave_sync();
+        return;
     }
     if (own) {
         // the self pair was evaluated with r^2 = eps^2; take its potential out
@@ -423,36 +441,78 @@ __device__ void walk_group(const WalkArgs &a, uint32_t g, uint32_t lane, WalkLds
         a.npp[g] = (a.accum ? a.npp[g] : 0u) + cnt_pp;
         a.npc[g] = (a.accum ? a.npc[g] : 0u) + cnt_pc;
     }
-    __syncthreads();
+    wave_sync();
 }
 
-template <bool kEps0, bool kF16>
-__device__ __forceinline__ void walk_loop(const WalkArgs &a, WalkLds &L, Far16Lds &S) {
-    const uint32_t lane = threadIdx.x;
-    uint32_t *spill = a.spill + (size_t)blockIdx.x * kStackMax;
-    for_each_group(*a.ngroups, a.work, lane,
-                   [&](uint32_t g) { walk_group<kEps0, kF16>(a, g, lane, L, S, spill); });
-}
-
-template <bool kEps0, bool kF16>
+template <bool kEps0, bool kF16, bool kSplit>
 __global__ __launch_bounds__(64) void k_walk(WalkArgs a) {
     __shared__ WalkLds L;
-    // the FP16 pair records share the FP32 staging area: a flush uses one
-    // or the other, and each flush rewrites its null source
-    static_assert(sizeof(Far16Lds) <= sizeof(L.stage), "pair records exceed the staging area");
-    walk_loop<kEps0, kF16>(a, L, *reinterpret_cast<Far16Lds *>(&L.stage[0][0]));
+    const uint32_t lane = threadIdx.x;
+    uint32_t *spill = a.spill + (size_t)blockIdx.x * kStackMax;
+    for_each_group(*a.ngroups, a.work, lane, kSplit ? a.logw : 0u, [&](uint32_t g, uint32_t w) {
+        walk_group<kEps0, kF16, kSplit>(a, g, w, lane, L, spill);
+    });
+}
+
+// The partial sums and counts of a split walk, added in wave order.
+template <bool kEps0>
+__global__ __launch_bounds__(256) void k_walk_combine(WalkArgs a, uint32_t n) {
+    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    const uint32_t W = 1u << a.logw;
+    float4 res = a.pacc[i];
+    for (uint32_t w = 1; w < W; ++w) {
+        const float4 o = a.pacc[(size_t)w * a.pstride + i];
+        res.x += o.x; res.y += o.y; res.z += o.z; res.w += o.w;
+    }
+    if (!kEps0 && !a.remote) res.w += a.xyzm[i].w * rsq(a.eps2);  // the self pair
+    if (a.accum) {
+        const float4 o = a.acc[i];
+        res.x = o.x + res.x; res.y = o.y + res.y; res.z = o.z + res.z; res.w = o.w + res.w;
+    }
+    a.acc[i] = res;
+    if (i < *a.ngroups) {  // (at most n groups)
+        uint32_t pp = a.accum ? a.npp[i] : 0u, pc = a.accum ? a.npc[i] : 0u;
+        for (uint32_t w = 0; w < W; ++w) {
+            const uint2 c = a.pcnt[(size_t)w * a.pstride + i];
+            pp += c.x;
+            pc += c.y;
+        }
+        a.npp[i] = pp;
+        a.npc[i] = pc;
+    }
 }
 
 __global__ void k_reset_work(uint32_t *work) {
-    if (threadIdx.x < 8) work[threadIdx.x] = 0u;
+    if (threadIdx.x < 8) work[threadIdx.x * kWorkStride] = 0u;
 }
 
 int walk_blocks_per_cu() {
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_walk<false, false>, 64, 0) != hipSuccess ||
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (k_walk<false, false, false>), 64, 0) != hipSuccess ||
         nb < 1)
         nb = 4;
     return nb;
+}
+
+template <bool kSplit>
+static void launch_walk_k(bh_ctx *c, const WalkArgs &a, float eps, hipStream_t st) {
+    const dim3 grid(c->walk_grid), block(64);
+    const bool f16 = c->p.far_fp16 != 0;
+    if (eps == 0.f && f16)
+        hipLaunchKernelGGL((k_walk<true, true, kSplit>), grid, block, 0, st, a);
+    else if (eps == 0.f)
+        hipLaunchKernelGGL((k_walk<true, false, kSplit>), grid, block, 0, st, a);
+    else if (f16)
+        hipLaunchKernelGGL((k_walk<false, true, kSplit>), grid, block, 0, st, a);
+    else
+        hipLaunchKernelGGL((k_walk<false, false, kSplit>), grid, block, 0, st, a);
+    if (!kSplit) return;
+    const uint32_t n = (uint32_t)c->n;
+    if (eps == 0.f)
+        hipLaunchKernelGGL(k_walk_combine<true>, dim3(cdiv(n, 256)), dim3(256), 0, st, a, n);
+    else
+        hipLaunchKernelGGL(k_walk_combine<false>, dim3(cdiv(n, 256)), dim3(256), 0, st, a, n);
 }
 
 void launch_walk_view(bh_ctx *c, const SrcView &v, float eps, bool remote, bool accum,
@@ -473,15 +533,11 @@ void launch_walk_view(bh_ctx *c, const SrcView &v, float eps, bool remote, bool 
     hipLaunchKernelGGL(k_reset_work, dim3(1), dim3(64), 0, st, c->work);
     const bool own = !remote && !accum;  // the timed walk of the context's own tree
     if (own) record_event(c, 4, st);
-    const bool f16 = c->p.far_fp16 != 0;
-    if (eps == 0.f && f16)
-        hipLaunchKernelGGL((k_walk<true, true>), dim3(c->walk_grid), dim3(64), 0, st, a);
-    else if (eps == 0.f)
-        hipLaunchKernelGGL((k_walk<true, false>), dim3(c->walk_grid), dim3(64), 0, st, a);
-    else if (f16)
-        hipLaunchKernelGGL((k_walk<false, true>), dim3(c->walk_grid), dim3(64), 0, st, a);
-    else
-        hipLaunchKernelGGL((k_walk<false, false>), dim3(c->walk_grid), dim3(64), 0, st, a);
+    a.logw = split_logw(c->n);
+    a.pstride = (uint32_t)c->n;
+    a.pacc = c->pacc; a.pcnt = c->pcnt;
+    if (a.logw) launch_walk_k<true>(c, a, eps, st);
+    else launch_walk_k<false>(c, a, eps, st);
     if (own) record_event(c, 5, st);
 }
 

@@ -19,9 +19,9 @@
 //     (ballot + mbcnt) into two LDS index lists; no source data is read
 //     during the traversal.  The caller's flush functions evaluate a list
 //     when it fills, and once more at the end.
-// Groups are taken from eight contiguous ranges (one per XCD, blockIdx % 8)
-// through atomic counters, so neighbouring groups share an L2; every wave
-// leaves once all ranges are exhausted.
+// Groups are taken from eight contiguous ranges (one per XCD, blockIdx % 8),
+// so neighbouring groups share an L2; every wave leaves once all ranges are
+// exhausted.
 #pragma once
 
 #include "bh_internal.h"
@@ -34,6 +34,7 @@ constexpr int kPcCap = 752;  // particle-cell index list
 constexpr int kPcFlush = kPcCap - 128;  // a pass appends at most 128 cells
 constexpr int kPpCap = 512;  // particle-particle index list
 constexpr int kChunk = 64;   // sources staged per evaluation round
+constexpr uint32_t kDealRanges = 64;  // stack ranges at which the waves of a split walk part
 constexpr int kNull = kChunk;  // staging slot of the null source
 
 struct TravLds {
@@ -53,6 +54,15 @@ struct TreeView {
     uint32_t ring;      // resident stack entries allowed: kRing, or 192 to exercise the spill path
     uint32_t *status;
 };
+
+// Order the LDS accesses of one wave: the DS unit runs a wave's accesses in
+// program order, so only the compiler has to keep them in it (no barrier, no
+// wait; a workgroup may hold several waves that walk different groups).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 struct GroupBox {
     float cx, cy, cz, hx, hy, hz;
@@ -99,6 +109,21 @@ __device__ __forceinline__ float box_d2(const float4 &A, const GroupBox &b) {
     return d2;
 }
 
+// One of the 2^logw waves that walk the tree for one group.
+struct Share {
+    uint32_t w, logw;
+};
+
+// Split the waves' common entries: of the set flags of a (slot a of every
+// lane, then b) entry k goes to wave (dealt + k) mod 2^logw.
+__device__ __forceinline__ void deal(bool &a, bool &b, const Share &sh, uint32_t &dealt) {
+    const uint64_t ma = ballot(a), mb = ballot(b);
+    const uint32_t na = (uint32_t)__popcll(ma), wmask = (1u << sh.logw) - 1u;
+    a = a && ((dealt + count_below(ma)) & wmask) == sh.w;
+    b = b && ((dealt + na + count_below(mb)) & wmask) == sh.w;
+    dealt += na + (uint32_t)__popcll(mb);
+}
+
 // Walk the tree for one group.  flush_pc(n) / flush_pp(n) evaluate the first
 // n entries of L.pcidx / L.ppidx (called with n > 0, all lanes, after a
 // barrier); both lists are empty when traverse returns.  Counts: accepted
@@ -111,18 +136,28 @@ __device__ __forceinline__ float box_d2(const float4 &A, const GroupBox &b) {
 // and the barriers are shared by two opening tests and two cell loads are in
 // flight per lane.  Pop order is slot a's cells, then slot b's; every list
 // and the pushed children keep that order.
-template <bool kLeafCells = false, class FlushPc, class FlushPp>
+//
+// kSplit: 2^logw waves walk the tree for the same group, each calling
+// traverse with its own share.  They run the same passes until the stack
+// holds kDealRanges ranges, the accepted cells and opened leaves of those
+// passes dealt out in list order; then wave w keeps every 2^logw-th range and
+// walks those subtrees alone.  Which wave takes what depends only on the tree
+// and the group, so the sums do not depend on scheduling.
+template <bool kLeafCells = false, bool kSplit = false, class FlushPc, class FlushPp>
 __device__ __forceinline__ void traverse(const TreeView &tv, const GroupBox &b, uint32_t lane,
                                          TravLds &L, uint32_t *spill, uint32_t &cnt_pc,
                                          uint32_t &cnt_pp, FlushPc &&flush_pc,
-                                         FlushPp &&flush_pp) {
+                                         FlushPp &&flush_pp,
+                                         const Share sh = Share{0u, 0u}) {
     constexpr uint32_t rmask = (uint32_t)kRing - 1u;
     uint32_t pc_n = 0, pp_n = 0;
     uint32_t sp = 1, lo = 0;  // stack positions [lo, sp) are in the LDS ring
     cnt_pc = 0;
     cnt_pp = 0;
+    bool common = kSplit;          // the waves still walk the same cells
+    uint32_t dealt_pc = 0, dealt_pp = 0;  // entries dealt out so far
     if (lane == 0) L.ring[0] = 0u;  // the root: first cell 0, one cell
-    __syncthreads();
+    wave_sync();
 
     while (sp > 0) {
         // ---- refill the ring from the spill area when the top range is not resident
@@ -130,7 +165,7 @@ __device__ __forceinline__ void traverse(const TreeView &tv, const GroupBox &b, 
         if (sp - avail < lo) {
             lo -= 64u;
             L.ring[(lo + lane) & rmask] = spill[lo + lane];
-            __syncthreads();
+            wave_sync();
         }
         // ---- pop up to 128 cells from the top ranges (range lane = stack top - lane)
         uint32_t e = 0, ne = 0;
@@ -145,9 +180,9 @@ __device__ __forceinline__ void traverse(const TreeView &tv, const GroupBox &b, 
         const uint32_t total = tall < 128u ? tall : 128u;
         L.starts[lane] = 0u;
         L.starts[64u + lane] = 0u;
-        __syncthreads();
+        wave_sync();
         if (lane < avail && excl < 128u) L.starts[excl] = 1u;
-        __syncthreads();
+        wave_sync();
         const uint64_t sa = ballot(L.starts[lane] != 0u);
         const uint64_t sb = ballot(L.starts[64u + lane] != 0u);
         // range of each slot's cell (cell 0 starts range 0: both indices are in 0..63)
@@ -173,12 +208,17 @@ __device__ __forceinline__ void traverse(const TreeView &tv, const GroupBox &b, 
             Ab = tv.wA[cell_b];
             Nb = tv.wN[cell_b];
         }
-        const bool acc_a = have_a && box_d2(Aa, b) >= Aa.w;
-        const bool acc_b = have_b && box_d2(Ab, b) >= Ab.w;
-        const bool leaf_a = have_a && !acc_a && (Na.y & kLeafBit) != 0u;
-        const bool leaf_b = have_b && !acc_b && (Nb.y & kLeafBit) != 0u;
+        bool acc_a = have_a && box_d2(Aa, b) >= Aa.w;
+        bool acc_b = have_b && box_d2(Ab, b) >= Ab.w;
+        bool leaf_a = have_a && !acc_a && (Na.y & kLeafBit) != 0u;
+        bool leaf_b = have_b && !acc_b && (Nb.y & kLeafBit) != 0u;
         const bool open_a = have_a && !acc_a && (Na.y & kLeafBit) == 0u;
         const bool open_b = have_b && !acc_b && (Nb.y & kLeafBit) == 0u;
+
+        if (kSplit && common) {  // this wave's share of the entries, in list order
+            deal(acc_a, acc_b, sh, dealt_pc);
+            deal(leaf_a, leaf_b, sh, dealt_pp);
+        }
 
         // ---- accepted cells -> particle-cell index list
         const uint64_t ama = ballot(acc_a), amb = ballot(acc_b);
@@ -200,10 +240,10 @@ __device__ __forceinline__ void traverse(const TreeView &tv, const GroupBox &b, 
         }
         while (sp_new + npush > lo + tv.ring) {
             // spill the 64 lowest resident entries (all below sp_new when ring >= 192)
-            __syncthreads();
+            wave_sync();
             spill[lo + lane] = L.ring[(lo + lane) & rmask];
             lo += 64u;
-            __syncthreads();
+            wave_sync();
         }
         if (open_a) {
             const uint32_t above = lane == 63u ? 0u : (uint32_t)__popcll(oma >> (lane + 1u));
@@ -214,11 +254,22 @@ __device__ __forceinline__ void traverse(const TreeView &tv, const GroupBox &b, 
             L.ring[(sp_new + above) & rmask] = (Nb.x << 3) | (Nb.y - 1u);
         }
         sp = sp_new + npush;
+        if (kSplit && common && sp >= kDealRanges) {  // (at most 63 + 128 ranges, none spilled)
+            wave_sync();
+            const uint32_t j0 = sh.w + (lane << sh.logw), j1 = sh.w + ((64u + lane) << sh.logw);
+            const uint32_t e0 = j0 < sp ? L.ring[j0] : 0u;
+            const uint32_t e1 = j1 < sp ? L.ring[j1 & rmask] : 0u;
+            wave_sync();
+            L.ring[lane] = e0;
+            if (j1 < sp) L.ring[64u + lane] = e1;
+            sp = (sp - sh.w + (1u << sh.logw) - 1u) >> sh.logw;
+            common = false;
+        }
 
         // ---- opened leaves -> their cells (kLeafCells)
         if constexpr (kLeafCells) {
             if (pp_n + 128u > (uint32_t)kPpCap) {
-                __syncthreads();
+                wave_sync();
                 flush_pp(pp_n);
                 pp_n = 0;
             }
@@ -245,7 +296,7 @@ __device__ __forceinline__ void traverse(const TreeView &tv, const GroupBox &b, 
             L.offs[2u * lane + 1u] = o + ca;
             L.firsts[2u * lane] = Na.x;
             L.firsts[2u * lane + 1u] = Nb.x;
-            __syncthreads();
+            wave_sync();
             cnt_pp += P;
             for (uint32_t base = 0; base < P;) {
                 if (pp_n == (uint32_t)kPpCap) {
@@ -264,37 +315,56 @@ __device__ __forceinline__ void traverse(const TreeView &tv, const GroupBox &b, 
                 }
                 pp_n += take;
                 base += take;
-                __syncthreads();
+                wave_sync();
             }
         }
-        __syncthreads();
+        wave_sync();
         if (pc_n > (uint32_t)kPcFlush) {
             flush_pc(pc_n);
             pc_n = 0;
         }
     }
-    __syncthreads();
+    wave_sync();
     if (pc_n) flush_pc(pc_n);
     if (pp_n) flush_pp(pp_n);
-    __syncthreads();
+    wave_sync();
 }
 
-// Persistent group loop: groups come from eight contiguous ranges through
-// the atomic counters work[0..7]; fn(g) handles group g.
+// Persistent group loop: tasks (group, wave of the group) in eight contiguous
+// ranges of groups, one per XCD (blockIdx % 8); fn(g, w) handles group g as
+// wave w of 2^logw (waves of one group do not wait for each other).  A
+// block's first task is its place among the blocks of its range, the next
+// ones come from the range's counter; a block whose range is exhausted reads
+// all eight counters at once and goes on with a range that has tasks left, so
+// a launch of more blocks than tasks touches no counter but by that one load.
+// Each counter has a cache line of its own: eight in one line, each block
+// adding to all of them before it left, kept a grid of 4096 waves at 0.3 ms
+// however few the groups.
 template <class Fn>
 __device__ __forceinline__ void for_each_group(uint32_t ng, uint32_t *work, uint32_t lane,
-                                               Fn &&fn) {
-    for (uint32_t k = 0; k < 8; ++k) {
-        const uint32_t part = (blockIdx.x + k) & 7u;
+                                               uint32_t logw, Fn &&fn) {
+    const uint32_t q = lane & 7u;  // lane's range, for the look at all of them
+    const uint32_t qn = (uint32_t)((((uint64_t)ng * (q + 1)) >> 3) - (((uint64_t)ng * q) >> 3))
+                        << logw;
+    const uint32_t qb = (gridDim.x + 7u - q) >> 3;  // blocks that start in it
+    uint32_t part = blockIdx.x & 7u, t = blockIdx.x >> 3;
+    for (;;) {
         const uint32_t r0 = (uint32_t)(((uint64_t)ng * part) >> 3);
-        const uint32_t r1 = (uint32_t)(((uint64_t)ng * (part + 1)) >> 3);
-        for (;;) {
-            uint32_t t = 0;
-            if (lane == 0) t = atomicAdd(&work[part], 1u);
+        const uint32_t size = read_lane(qn, part), given = read_lane(qb, part);
+        while (t < size) {
+            fn(r0 + (t >> logw), t & ((1u << logw) - 1u));
+            if (lane == 0) t = given + atomicAdd(&work[part * kWorkStride], 1u);
             t = uniform(t);
-            if (t >= r1 - r0) break;
-            fn(r0 + t);
         }
+        const uint32_t seen = __hip_atomic_load(&work[q * kWorkStride], __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t left = (uint32_t)ballot(lane < 8u && qb + seen < qn);
+        if (left == 0u) return;
+        const uint32_t turn = ((left | (left << 8)) >> part) & 0xffu;  // ranges from part on
+        part = (part + (uint32_t)__builtin_ctz(turn)) & 7u;
+        const uint32_t first = read_lane(qb, part);
+        if (lane == 0) t = first + atomicAdd(&work[part * kWorkStride], 1u);
+        t = uniform(t);
     }
 }
 

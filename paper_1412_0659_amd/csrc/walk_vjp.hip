@@ -55,7 +55,7 @@ struct VjpArgs {
     const float4 *P0, *P1, *P2;
     const uint32_t *gbeg, *ngroups;
     uint32_t *work, *spill, *status;
-    uint32_t ring;
+    uint32_t ring, logw;  // logw: 2^logw waves per group (split walks)
     // copy 0 of kXcd accumulators; copy k at + k * lstride / gstride.  Field
     // major: cell adjoint q of cell c at lcell[q * cap + c], particle
     // adjoint q of particle j at gsrc[q * nmax + j], so that the lanes of one
@@ -198,8 +198,8 @@ __device__ __forceinline__ void vjp_targets(VPhase &ph, uint32_t n, const VjpLds
     }
 }
 
-template <bool kEps0>
-__device__ void vjp_group(const VjpArgs &a, uint32_t g, uint32_t lane, VjpLds &L,
+template <bool kEps0, bool kSplit>
+__device__ void vjp_group(const VjpArgs &a, uint32_t g, uint32_t w, uint32_t lane, VjpLds &L,
                           uint32_t *spill) {
     const uint32_t gb = a.gbeg[g];
     const uint32_t gn = a.gbeg[g + 1] - gb;
@@ -283,7 +283,7 @@ __device__ void vjp_group(const VjpArgs &a, uint32_t g, uint32_t lane, VjpLds &L
                 for (int q = 0; q < 6; ++q) add_l2(lc + (4 + q) * fs, (double)sQ[q]);
             }
         }
-        __syncthreads();
+        wave_sync();
     };
     auto flush_pp = [&](uint32_t n) {
         for (uint32_t base = 0; base < n; base += kChunk) {
@@ -291,10 +291,10 @@ __device__ void vjp_group(const VjpArgs &a, uint32_t g, uint32_t lane, VjpLds &L
             const bool valid = lane < m;
             const uint32_t j = L.T.ppidx[base + (valid ? lane : 0u)];
             const float4 P = a.xyzm[j];
-            __syncthreads();
+            wave_sync();
             L.stage[0][lane] = P;
             L.sidx[lane] = valid ? j : kNone;
-            __syncthreads();
+            wave_sync();
             vjp_targets<kEps0>(p1, m, L, a.eps2);
             if (two) vjp_targets<kEps0>(p2, m, L, a.eps2);
             float sx = 0.f, sy = 0.f, sz = 0.f, sm = 0.f;
@@ -313,26 +313,27 @@ __device__ void vjp_group(const VjpArgs &a, uint32_t g, uint32_t lane, VjpLds &L
                 add_l2(gs + 3 * a.nmax, (double)sm);
             }
         }
-        __syncthreads();
+        wave_sync();
     };
 
     uint32_t cnt_pc, cnt_pp;
     const TreeView tv{a.wA, a.wN, a.ring, a.status};
-    traverse(tv, b, lane, L.T, spill, cnt_pc, cnt_pp, flush_pc, flush_pp);
+    traverse<false, kSplit>(tv, b, lane, L.T, spill, cnt_pc, cnt_pp, flush_pc, flush_pp,
+                            Share{w, a.logw});
 
     // ---- sum the slices of each target and add the target terms
     float rx = 0.f, ry = 0.f, rz = 0.f;
     L.stage[0][lane] = make_float4(p1.gx, p1.gy, p1.gz, 0.f);
-    __syncthreads();
+    wave_sync();
     if (lane < p1.T)
         for (uint32_t k = 0; k < p1.r; ++k) {
             const float4 o = L.stage[0][lane + k * p1.T];
             rx += o.x; ry += o.y; rz += o.z;
         }
     if (two) {
-        __syncthreads();
+        wave_sync();
         L.stage[0][lane] = make_float4(p2.gx, p2.gy, p2.gz, 0.f);
-        __syncthreads();
+        wave_sync();
         if (lane >= p1.T && lane < gn)
             for (uint32_t k = 0; k < p2.r; ++k) {
                 const float4 o = L.stage[0][lane - p1.T + k * p2.T];
@@ -345,16 +346,17 @@ __device__ void vjp_group(const VjpArgs &a, uint32_t g, uint32_t lane, VjpLds &L
         add_l2(gs + a.nmax, (double)ry + (double)gty);
         add_l2(gs + 2 * a.nmax, (double)rz + (double)gtz);
     }
-    __syncthreads();
+    wave_sync();
 }
 
-template <bool kEps0>
+template <bool kEps0, bool kSplit>
 __global__ __launch_bounds__(64) void k_walk_vjp(VjpArgs a) {
     __shared__ VjpLds L;
     const uint32_t lane = threadIdx.x;
     uint32_t *spill = a.spill + (size_t)blockIdx.x * kStackMax;
-    for_each_group(*a.ngroups, a.work, lane,
-                   [&](uint32_t g) { vjp_group<kEps0>(a, g, lane, L, spill); });
+    for_each_group(*a.ngroups, a.work, lane, kSplit ? a.logw : 0u, [&](uint32_t g, uint32_t w) {
+        vjp_group<kEps0, kSplit>(a, g, w, lane, L, spill);
+    });
 }
 
 // ---- moments part, combination and unsorting --------------------------------
@@ -470,7 +472,27 @@ __global__ __launch_bounds__(256) void k_moments_vjp(Cells c, const float4 *__re
 }
 
 __global__ void k_reset_work_vjp(uint32_t *work) {
-    if (threadIdx.x < 8) work[threadIdx.x] = 0u;
+    if (threadIdx.x < 8) work[threadIdx.x * kWorkStride] = 0u;
+}
+
+// Waves per group of a split adjoint walk, as in the force walk; every wave
+// adds its targets' sums by atomics of its own, so two waves stop paying
+// earlier.  Disk + halo, theta 0.4, us by waves per group (1 / 2 / 4 / 8):
+// n = 1000: 289 / 184 / 137 / 101; 4096: 991 / 566 / 341 / 247; 16384: 1692 /
+// 1074 / 1034 / 923; 32768: 2156 / 1825 / 1659 / 1989; 65536: 2882 / 2647 /
+// 2925; at theta 0.6 two waves are as fast as one at 65536 and 17% slower at
+// 98304.
+static uint32_t vjp_logw(int64_t n) {
+    return n <= 8192 ? 3u : (n <= 24576 ? 2u : (n <= 65536 ? 1u : 0u));
+}
+
+template <bool kSplit>
+static void launch_vjp_k(bh_ctx *c, const VjpArgs &a, float eps, hipStream_t st) {
+    const dim3 grid(c->walk_grid), block(64);
+    if (eps == 0.f)
+        hipLaunchKernelGGL((k_walk_vjp<true, kSplit>), grid, block, 0, st, a);
+    else
+        hipLaunchKernelGGL((k_walk_vjp<false, kSplit>), grid, block, 0, st, a);
 }
 
 void launch_walk_vjp(bh_ctx *c, float eps, const float *u, float coef, float *g_pos,
@@ -503,10 +525,9 @@ void launch_walk_vjp(bh_ctx *c, float eps, const float *u, float coef, float *g_
     a.eps2 = eps * eps;
     hipLaunchKernelGGL(k_reset_work_vjp, dim3(1), dim3(64), 0, st, c->work);
     record_event(c, 8, st);
-    if (eps == 0.f)
-        hipLaunchKernelGGL(k_walk_vjp<true>, dim3(c->walk_grid), dim3(64), 0, st, a);
-    else
-        hipLaunchKernelGGL(k_walk_vjp<false>, dim3(c->walk_grid), dim3(64), 0, st, a);
+    a.logw = vjp_logw(c->n);
+    if (a.logw) launch_vjp_k<true>(c, a, eps, st);
+    else launch_vjp_k<false>(c, a, eps, st);
     record_event(c, 9, st);
     hipLaunchKernelGGL(k_fold_xcd, dim3(2048), dim3(256), 0, st, c->lcell, (uint64_t)0, 10u, cap,
                        lstride, ls);
