@@ -56,7 +56,7 @@ void free_all(bh_ctx *c) {
     f(c->sort.counts); f(c->sort.scan_part);
     Cells &q = c->cells;
     f(q.prefix); f(q.level); f(q.begin); f(q.count); f(q.child0); f(q.nchild); f(q.parent);
-    f(q.ls); f(q.part); f(q.lbt); f(q.cbnd); f(q.M); f(q.S); f(q.com); f(q.Q); f(q.wA); f(q.wN); f(q.P0); f(q.P1);
+    f(q.ls); f(q.lev); f(q.tcnt); f(q.ttot); f(q.M); f(q.S); f(q.com); f(q.Q); f(q.wA); f(q.wN); f(q.P0); f(q.P1);
     f(q.P2); f(q.size);
     Groups &g = c->groups;
     f(g.flag); f(g.scan); f(g.begin); f(g.count_dev); f(g.box); f(g.npp); f(g.npc);
@@ -119,8 +119,7 @@ void rebuild(bh_ctx *c, uint32_t n, hipStream_t s, bool fresh) {
     launch_radix_sort(c, n, s);
     launch_gather(c, n, s);
     record_event(c, 1, s);
-    launch_build(c, n, s, L);
-    launch_groups(c, n, s);
+    launch_build(c, n, s);
     record_event(c, 2, s);
     launch_moments(c, s, L);
     record_event(c, 3, s);
@@ -299,14 +298,15 @@ size_t static_layout(bh_ctx *c, unsigned char *base) {
     Cells &q = c->cells;
     take(&q.prefix, nc); take(&q.level, nc); take(&q.begin, nc); take(&q.count, nc);
     take(&q.child0, nc); take(&q.nchild, nc); take(&q.parent, nc); take(&q.ls, kLsSize);
-    take(&q.part, kBuildGrid + 1); take(&q.lbt, ((size_t)1 << (3 * kTableLevel)) + 1);
-    take(&q.cbnd, 8 * n);
+    take(&q.lev, n); take(&q.tcnt, (size_t)(kLevels + 1) * cdiv(n, kTreeTile));
+    take(&q.ttot, kLevels + 1);
     take(&q.M, nc); take(&q.S, 3 * nc); take(&q.Q, 6 * nc);
     q.com = nullptr;  // (only bh_export reads it)
     take(&q.wA, nc); take(&q.wN, nc); take(&q.P0, nc); take(&q.P1, nc); take(&q.P2, nc);
     take(&q.size, nc);
     Groups &g = c->groups;
-    take(&g.flag, n); take(&g.scan, n); take(&g.begin, n + 1); take(&g.count_dev, 1);
+    g.flag = g.scan = nullptr;  // (paired target sets only)
+    take(&g.begin, n + 1); take(&g.count_dev, 1);
     take(&g.box, 2 * n); take(&g.npp, n); take(&g.npc, n);
     return off;
 }
@@ -425,16 +425,16 @@ int bh_create(bh_ctx **out, int64_t n_max, const bh_params *p) {
          dalloc(&c->sort.scan_part, (size_t)c->sort.scan_part_len, err) &&
          dalloc(&q.prefix, nc, err) && dalloc(&q.level, nc, err) && dalloc(&q.begin, nc, err) &&
          dalloc(&q.count, nc, err) && dalloc(&q.child0, nc, err) && dalloc(&q.nchild, nc, err) &&
-         dalloc(&q.parent, nc, err) && dalloc(&q.ls, kLsSize, err) && dalloc(&q.cbnd, 8 * n, err) &&
-         dalloc(&q.part, kBuildGrid + 1, err) &&
-         dalloc(&q.lbt, ((size_t)1 << (3 * kTableLevel)) + 1, err) && dalloc(&q.M, nc, err) && dalloc(&q.S, 3 * nc, err) &&
+         dalloc(&q.parent, nc, err) && dalloc(&q.ls, kLsSize, err) && dalloc(&q.lev, n, err) &&
+         dalloc(&q.tcnt, (size_t)(kLevels + 1) * cdiv(n, kTreeTile), err) &&
+         dalloc(&q.ttot, kLevels + 1, err) && dalloc(&q.M, nc, err) && dalloc(&q.S, 3 * nc, err) &&
          dalloc(&q.com, 3 * nc, err) && dalloc(&q.Q, 6 * nc, err) && dalloc(&q.wA, nc, err) &&
          dalloc(&q.wN, nc, err) && dalloc(&q.P0, nc, err) && dalloc(&q.P1, nc, err) &&
-         dalloc(&q.P2, nc, err) && dalloc(&q.size, nc, err) && dalloc(&g.flag, n, err) &&
-         dalloc(&g.scan, n, err) && dalloc(&g.begin, n + 1, err) &&
+         dalloc(&q.P2, nc, err) && dalloc(&q.size, nc, err) && dalloc(&g.begin, n + 1, err) &&
          dalloc(&g.count_dev, 1, err) && dalloc(&g.box, 2 * n, err) && dalloc(&g.npp, n, err) &&
          dalloc(&g.npc, n, err) && dalloc(&c->cic, 65536, err) && dalloc(&c->inv, n, err) &&
          dalloc(&c->diag, (size_t)(kDiagBlocks + 1) * kDiagN, err);
+    if (ok && prm.pair_groups) ok = dalloc(&g.flag, n, err) && dalloc(&g.scan, n, err);
     if (ok && prm.adjoint)
         ok = dalloc(&c->lcell, 8 * 10 * nc, err) && dalloc(&c->gsrc, 8 * 4 * n, err) &&
              dalloc(&c->lhot, (size_t)kHotCopies * kHotCopy, err) &&

@@ -17,8 +17,7 @@ constexpr int kKeyBits = 21;            // bits per axis of a Morton key
 constexpr int kLevels = 22;             // levels 0..21
 constexpr int kLsSize = 24;             // level_start entries (23 used)
 constexpr int kGrid = 1024;             // fixed grid of the per-level moment, box and flag kernels
-constexpr int kBuildGrid = 2048;        // grid of the octree level kernels: 8 waves per SIMD
-constexpr int kTableLevel = 7;          // the build looks up the child bounds of levels < 7
+constexpr int kTreeTile = 1024;         // particles per block of the octree build
 constexpr uint32_t kLeafBit = 0x80000000u;
 constexpr uint32_t kNone = 0xffffffffu;
 constexpr int kWorkStride = 32;         // a cache line per work counter of the walk
@@ -53,10 +52,9 @@ struct Cells {
     uint64_t *prefix;  // key >> 3 (21 - level)
     uint32_t *level, *begin, *count, *child0, *nchild, *parent;
     uint32_t *ls;      // [kLsSize] level_start on the device
-    uint32_t *part;    // [kBuildGrid + 1] per-block partials of the level scans
-    uint32_t *lbt;     // [8^kTableLevel + 1] first sorted slot of every level-kTableLevel prefix
-    uint32_t *cbnd;    // [n_max][8] child bounds 1..8 of the cells of the level being split
-                       // (level-local index), from the count pass to the write pass
+    uint16_t *lev;     // [n_max] levels of the cells that start at / hold each particle
+    uint32_t *tcnt;    // [kLevels + 1][tiles] cells of each level (and groups) starting before a tile
+    uint32_t *ttot;    // [kLevels + 1] their totals
     // FP64 moments of the upward pass
     double *M, *S, *com, *Q;  // [c], [c][3], [c][3], [c][6]; com = S / M, filled for export
     // records read by the walk
@@ -69,7 +67,7 @@ struct Cells {
 };
 
 struct Groups {
-    uint32_t *flag, *scan;  // [n] group-start flags and their exclusive scan
+    uint32_t *flag, *scan;  // [n] first groups of paired target sets and their exclusive scan
     uint32_t *begin;        // [n + 1]
     uint32_t *count_dev;    // [1] number of groups
     float4 *box;            // [2 * n] centre, half size
@@ -174,7 +172,7 @@ struct bh_ctx {
     bh::Let let{};
     bh::Cut cut{};
 
-    // level starts of a recent build, written by k_build_tail into pinned host
+    // level starts of a recent build, written by k_tree_write into pinned host
     // memory: [0] build number (written first), [1] build number (written
     // last), [2 ..] ls[0 .. kLevels]
     uint32_t *hint_host = nullptr;
@@ -233,8 +231,7 @@ void launch_exclusive_scan(const uint32_t *in, uint32_t *out, uint32_t n, uint32
                            hipStream_t st);
 
 // build.hip
-void launch_build(bh_ctx *c, uint32_t n, hipStream_t st, int grid_levels);
-void launch_groups(bh_ctx *c, uint32_t n, hipStream_t st);
+void launch_build(bh_ctx *c, uint32_t n, hipStream_t st);  // cells and groups
 
 // moments.hip
 void launch_moments(bh_ctx *c, hipStream_t st, int grid_levels);

@@ -1,434 +1,383 @@
-// Octree construction from sorted Morton keys, level by level (Sec. I.A:
-// octants are split until a cell holds at most nleaf particles; Table II
-// "Tree-construction"), and the target groups of the walk.
+// Octree construction from the sorted keys (Sec. I.A: octants are split until
+// a cell holds at most nleaf particles; Table II "Tree-construction"), and
+// the target groups of the walk.
 //
-// Cells are numbered breadth first: the cells of level l, in key order,
-// then those of level l + 1.  A cell (l, P) with more than nleaf particles
-// and l < 21 gets one child per non-empty 3-bit digit d, found by binary
-// search for the key bound (8 P + d) << 3 (20 - l) inside the cell's range.
-// Each level takes three launches over a fixed grid that reads the level's
-// cell range from device memory (count children / scan block totals / write
-// children), so the build never waits on the host.  On the top levels the
-// searches are replaced by a table: for every key prefix q of level
-// kTableLevel, lbt[q] is the first sorted slot whose key is >= q shifted to a
-// full key (a lower bound over all keys, so inside a cell it is exactly the
-// bound the search would find); one launch of 8^kTableLevel independent
-// searches fills it per build.
+// Cells are numbered breadth first: the cells of level l, in key order, then
+// those of level l + 1.  No level waits for the one above it: which cells a
+// particle lies in follows from the keys next to its own.  With common(a, b)
+// the number of leading 3-bit digits two keys share,
+//   * the cell of level l holding sorted particle i has more than m particles
+//     iff l <= D_m(i) = max over j in [i - m, i] of common(key[j], key[j + m])
+//     (m + 1 consecutive keys around i share the level's prefix);
+//   * so i lies in cells of the levels 0 .. hi(i) = min(D_nleaf(i) + 1, 21),
+//     all but the last of them split;
+//   * the cells whose first particle is i are those of the levels
+//     lo(i) = common(key[i - 1], key[i]) + 1 .. hi(i) (lo(0) = 0), and the
+//     cells whose last particle is i those of the levels lo(i + 1) .. hi(i);
+//   * the number of a cell is its level's start plus the number of cells of
+//     that level that start before it, its parent is the last cell of the
+//     level above that starts at or before it, its children begin with the
+//     cell of the next level that starts with it and end with the one that
+//     ends with it.
+// Three launches: per tile of particles the levels of each particle and the
+// cells that start in the tile per level (k_tree_levels), the running sums of
+// those counts over the tiles (k_tree_scan), and the cells (k_tree_write),
+// ranked inside the tile by a bit mask per level.  The build never waits on
+// the host and does not depend on the depth of the tree.
+//
+// Bound: memory, 16 B of keys and 4 B of levels per particle and 36 B per
+// cell; on small sets the latency of the three launches.  Measured at 13M
+// (disk + halo): 0.23 ms (levels 97, sums 14, cells 122 us), where splitting
+// level by level with binary searches (three launches per level) took 0.76 ms;
+// at 16384: 42 against 260 us.
+//
+// A cell is a group iff (count <= ncrit or it is a leaf) and (it is the root
+// or its parent holds more than ncrit), so the group of particle i is the
+// cell of level g(i) = min(D_ncrit(i) + 1, hi(i)); groups are numbered in key
+// order as one more level.  A group cell larger than ncrit (a leaf, for
+// nleaf > ncrit or coincident keys) is cut into chunks of ncrit.
 #include "bh_internal.h"
 #include "wave.h"
 
 namespace bh {
 
-constexpr int kBuildThreads = 256;
-constexpr uint32_t kFewCells = 16384;  // levels with fewer cells are latency bound
+constexpr int kTreeThreads = 256;
+constexpr int kTreeItems = kTreeTile / kTreeThreads;
+constexpr int kTreeWords = kTreeTile / 64;
+constexpr int kHalo = 64;               // nleaf, ncrit <= 64
+constexpr int kGroupCh = kLevels;       // the groups' channel of the tile counts
+
+// levels of a particle, packed: lo (5 bits), hi (5 bits), its group cell's
+// level (5 bits), first of a group
+__device__ __forceinline__ uint32_t lv_lo(uint32_t v) { return v & 31u; }
+__device__ __forceinline__ uint32_t lv_hi(uint32_t v) { return (v >> 5) & 31u; }
+__device__ __forceinline__ uint32_t lv_glev(uint32_t v) { return (v >> 10) & 31u; }
+__device__ __forceinline__ bool lv_group(uint32_t v) { return (v >> 15) & 1u; }
+
+// leading 3-bit digits (of 21) that two 63-bit keys share
+__device__ __forceinline__ int common_digits(uint64_t a, uint64_t b) {
+    const uint64_t x = a ^ b;
+    return x == 0ull ? kKeyBits : (__clzll((long long)x) - 1) / 3;
+}
 
 __device__ __forceinline__ uint32_t key_lower_bound(const uint64_t *__restrict__ k, uint32_t lo,
                                                     uint32_t hi, uint64_t v) {
     while (lo < hi) {
-        uint32_t mid = lo + ((hi - lo) >> 1);
+        const uint32_t mid = lo + ((hi - lo) >> 1);
         if (k[mid] < v) lo = mid + 1;
         else hi = mid;
     }
     return lo;
 }
 
-// digit boundaries of the children of cell c (level l): bnd[0] = begin,
-// bnd[8] = end; child d holds [bnd[d], bnd[d+1]).  On a level of few cells
-// (latency bound: the top of the tree) a large range runs the seven
-// searches in lock step over the whole range, so their loads overlap
-// instead of waiting on each other; otherwise the searches are chained,
-// each starting at the previous bound (fewer loads).
-__device__ __forceinline__ void child_bounds(const uint64_t *__restrict__ key,
-                                             const uint32_t *__restrict__ lbt, uint64_t P,
-                                             uint32_t b, uint32_t e, int l, bool few,
-                                             uint32_t bnd[9]) {
-    uint32_t shift = 3u * (kKeyBits - 1 - l);
-    bnd[0] = b;
-    bnd[8] = e;
-    if (l < kTableLevel) {  // children on a level <= kTableLevel: look the bounds up
-        const uint32_t up = 3u * (uint32_t)(kTableLevel - 1 - l);
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
 #pragma unroll
-        for (uint32_t d = 1; d < 8; ++d) bnd[d] = lbt[((P << 3) | d) << up];
-        return;
+    for (int d = 32; d >= 1; d >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, d, 64));
+    return v;
+}
+
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+
+// Levels of every particle and, per tile, the number of cells of each level
+// (and of groups) that start in it.  Window maxima by doubling: entry j holds
+// max over [j, j + 2^k) of common(key[j], key[j + m]) + 1, for m = nleaf and
+// m = ncrit in the two halves of a word.
+__global__ __launch_bounds__(kTreeThreads) void k_tree_levels(const uint64_t *__restrict__ key,
+                                                              uint32_t n, uint32_t nleaf,
+                                                              uint32_t ncrit, uint32_t ntiles,
+                                                              uint16_t *__restrict__ lev,
+                                                              uint32_t *__restrict__ tcnt) {
+    constexpr int kSpan = kTreeTile + kHalo;  // entries j = t0 - kHalo .. t0 + kTreeTile - 1
+    __shared__ uint64_t k[kTreeTile + 2 * kHalo];
+    __shared__ u16x2 win[2][kSpan];
+    __shared__ uint32_t cnt[kLevels + 1];
+    const int64_t t0 = (int64_t)blockIdx.x * kTreeTile;
+    for (int q = threadIdx.x; q < kTreeTile + 2 * kHalo; q += kTreeThreads) {
+        const int64_t j = t0 - kHalo + q;
+        k[q] = j >= 0 && j < (int64_t)n ? key[j] : 0ull;
     }
-    if (few && e - b >= 256u) {
-        uint32_t base[8];
-#pragma unroll
-        for (uint32_t d = 1; d < 8; ++d) base[d] = b;
-        uint32_t len = e - b;
-        while (len > 1u) {
-            const uint32_t half = len >> 1;
-#pragma unroll
-            for (uint32_t d = 1; d < 8; ++d)
-                base[d] = key[base[d] + half] < (((P << 3) | d) << shift) ? base[d] + half
-                                                                          : base[d];
-            len -= half;
+    if (threadIdx.x <= kLevels) cnt[threadIdx.x] = 0u;
+    __syncthreads();
+    for (int q = threadIdx.x; q < kSpan; q += kTreeThreads) {
+        const int64_t j = t0 - kHalo + q;
+        u16x2 v = {0, 0};
+        if (j >= 0) {
+            if (j + nleaf < (int64_t)n) v.x = (unsigned short)(common_digits(k[q], k[q + nleaf]) + 1);
+            if (j + ncrit < (int64_t)n) v.y = (unsigned short)(common_digits(k[q], k[q + ncrit]) + 1);
         }
-#pragma unroll
-        for (uint32_t d = 1; d < 8; ++d)
-            bnd[d] = base[d] + (key[base[d]] < (((P << 3) | d) << shift) ? 1u : 0u);
-        return;
+        win[0][q] = v;
     }
+    __syncthreads();
+    const int kl = 31 - __clz((int)nleaf + 1), kc = 31 - __clz((int)ncrit + 1);
+    const int steps = max(kl, kc);
+    uint32_t dl[kTreeItems], dc[kTreeItems];  // D + 1 of this thread's particles
+    for (int s = 0; s <= steps; ++s) {
+        const u16x2 *w = win[s & 1];
+        if (s == kl || s == kc) {
 #pragma unroll
-    for (uint32_t d = 1; d < 8; ++d)
-        bnd[d] = key_lower_bound(key, bnd[d - 1], e, ((P << 3) | d) << shift);
-}
-
-__global__ void k_build_init(Cells c, uint32_t n) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        c.prefix[0] = 0;
-        c.level[0] = 0;
-        c.begin[0] = 0;
-        c.count[0] = n;
-        c.child0[0] = kNone;
-        c.nchild[0] = 0;
-        c.parent[0] = kNone;
-    }
-    if (blockIdx.x == 0 && threadIdx.x < kLsSize) c.ls[threadIdx.x] = threadIdx.x == 0 ? 0u : 1u;
-}
-
-__device__ __forceinline__ void level_chunk(const Cells &c, int l, uint32_t &cs, uint32_t &ce) {
-    uint32_t first = c.ls[l], last = c.ls[l + 1];
-    uint32_t chunk = (last - first + gridDim.x - 1) / gridDim.x;
-    cs = first + blockIdx.x * chunk;
-    ce = min(last, cs + chunk);
-    if (cs > ce) cs = ce;
-}
-
-__global__ __launch_bounds__(kBuildThreads) void k_build_count(Cells c,
-                                                               const uint64_t *__restrict__ key,
-                                                               int l, uint32_t nleaf,
-                                                               uint32_t nmax) {
-    __shared__ uint32_t lds[4];
-    uint32_t cs, ce;
-    level_chunk(c, l, cs, ce);
-    const uint32_t first = c.ls[l];
-    const bool few = c.ls[l + 1] - first < kFewCells;
-    uint32_t sum = 0;
-    for (uint32_t i = cs + threadIdx.x; i < ce; i += kBuildThreads) {
-        uint32_t nch = 0;
-        uint32_t cnt = c.count[i];
-        if (cnt > nleaf) {
-            uint32_t bnd[9];
-            uint32_t b = c.begin[i];
-            child_bounds(key, c.lbt, c.prefix[i], b, b + cnt, l, few, bnd);
-#pragma unroll
-            for (int d = 0; d < 8; ++d) nch += bnd[d + 1] > bnd[d];
-            // kept for the write pass (a level holds at most nmax cells)
-            if (i - first < nmax) {
-                uint4 *cb = reinterpret_cast<uint4 *>(c.cbnd + 8 * (size_t)(i - first));
-                cb[0] = make_uint4(bnd[1], bnd[2], bnd[3], bnd[4]);
-                cb[1] = make_uint4(bnd[5], bnd[6], bnd[7], bnd[8]);
+            for (int r = 0; r < kTreeItems; ++r) {
+                const int q = kHalo + r * kTreeThreads + (int)threadIdx.x;
+                if (s == kl)
+                    dl[r] = max((uint32_t)w[q - (int)nleaf].x, (uint32_t)w[q - (1 << kl) + 1].x);
+                if (s == kc)
+                    dc[r] = max((uint32_t)w[q - (int)ncrit].y, (uint32_t)w[q - (1 << kc) + 1].y);
             }
         }
-        c.nchild[i] = nch;
-        sum += nch;
-    }
-    sum = wave_sum(sum);
-    if (lane_id() == 0) lds[threadIdx.x >> 6] = sum;
-    __syncthreads();
-    if (threadIdx.x == 0) c.part[blockIdx.x] = lds[0] + lds[1] + lds[2] + lds[3];
-}
-
-// exclusive scan of the kBuildGrid block totals; sets the end of level l + 1
-__global__ __launch_bounds__(kBuildThreads) void k_build_scan(Cells c, int l, uint32_t cap,
-                                                              uint32_t *status) {
-    __shared__ uint32_t lds[4];
-    constexpr int per = kBuildGrid / kBuildThreads;
-    uint32_t v[per], s = 0;
-#pragma unroll
-    for (int k = 0; k < per; ++k) {
-        v[k] = c.part[threadIdx.x * per + k];
-        s += v[k];
-    }
-    uint32_t lane = lane_id(), w = threadIdx.x >> 6;
-    uint32_t inc = wave_incl_scan(s, lane);
-    if (lane == 63) lds[w] = inc;
-    __syncthreads();
-    uint32_t off = 0, tot = 0;
-    for (uint32_t k = 0; k < 4; ++k) {
-        if (k < w) off += lds[k];
-        tot += lds[k];
-    }
-    off += inc - s;
-#pragma unroll
-    for (int k = 0; k < per; ++k) {
-        c.part[threadIdx.x * per + k] = off;
-        off += v[k];
-    }
-    if (threadIdx.x == 0) {
-        uint32_t end = c.ls[l + 1] + tot;
-        if (end > cap) {
-            atomicOr(status, kStOverflow);
-            end = cap;
-        }
-        c.ls[l + 2] = end;
-    }
-}
-
-__global__ __launch_bounds__(kBuildThreads) void k_build_write(Cells c,
-                                                               const uint64_t *__restrict__ key,
-                                                               int l, uint32_t cap,
-                                                               uint32_t nmax) {
-    __shared__ uint32_t lds[4];
-    uint32_t cs, ce;
-    level_chunk(c, l, cs, ce);
-    const uint32_t first = c.ls[l];
-    const bool few = c.ls[l + 1] - first < kFewCells;
-    uint32_t carry = c.ls[l + 1] + c.part[blockIdx.x];
-    uint32_t lane = lane_id(), w = threadIdx.x >> 6;
-    for (uint32_t base = cs; base < ce; base += kBuildThreads) {
-        uint32_t i = base + threadIdx.x;
-        uint32_t v = i < ce ? c.nchild[i] : 0u;
-        uint32_t inc = wave_incl_scan(v, lane);
-        if (lane == 63) lds[w] = inc;
-        __syncthreads();
-        uint32_t off = 0, tot = 0;
-        for (uint32_t k = 0; k < 4; ++k) {
-            if (k < w) off += lds[k];
-            tot += lds[k];
+        if (s == steps) break;
+        u16x2 *o = win[(s + 1) & 1];
+        for (int q = threadIdx.x; q < kSpan; q += kTreeThreads) {
+            const u16x2 a = w[q], b = q + (1 << s) < kSpan ? w[q + (1 << s)] : a;
+            o[q] = __builtin_elementwise_max(a, b);
         }
         __syncthreads();
-        if (v > 0) {
-            uint32_t ch = carry + off + inc - v;
-            c.child0[i] = ch;
-            uint32_t b = c.begin[i];
-            uint64_t P = c.prefix[i];
-            uint32_t bnd[9];
-            if (i - first < nmax) {  // the bounds the count pass found
-                const uint4 *cb = reinterpret_cast<const uint4 *>(c.cbnd + 8 * (size_t)(i - first));
-                const uint4 u = cb[0], w = cb[1];
-                bnd[0] = b;
-                bnd[1] = u.x; bnd[2] = u.y; bnd[3] = u.z; bnd[4] = u.w;
-                bnd[5] = w.x; bnd[6] = w.y; bnd[7] = w.z; bnd[8] = w.w;
-            } else {
-                child_bounds(key, c.lbt, P, b, b + c.count[i], l, few, bnd);
-            }
-            for (uint32_t d = 0; d < 8; ++d) {
-                if (bnd[d + 1] > bnd[d]) {
-                    if (ch < cap) {
-                        c.prefix[ch] = (P << 3) | d;
-                        c.level[ch] = (uint32_t)(l + 1);
-                        c.begin[ch] = bnd[d];
-                        c.count[ch] = bnd[d + 1] - bnd[d];
-                        c.child0[ch] = kNone;
-                        c.nchild[ch] = 0;
-                        c.parent[ch] = i;
-                    }
-                    ++ch;
-                }
-            }
-        } else if (i < ce) {
-            c.child0[i] = kNone;
-        }
-        carry += tot;
     }
+    const uint32_t lane = lane_id();
+#pragma unroll
+    for (int r = 0; r < kTreeItems; ++r) {
+        const int q = kHalo + r * kTreeThreads + (int)threadIdx.x;
+        const int64_t i = t0 + q - kHalo;
+        const bool valid = i < (int64_t)n;
+        uint32_t lo = 31u, hi = 0u;
+        bool gs = false;
+        if (valid) {
+            lo = i == 0 ? 0u : (uint32_t)common_digits(k[q - 1], k[q]) + 1u;
+            hi = min(dl[r], (uint32_t)(kLevels - 1));
+            const uint32_t g = min(dc[r], hi);
+            gs = lo <= g;
+            if (dc[r] > g) {  // the group's cell holds more than ncrit: chunks of ncrit
+                const uint32_t sh = 3u * (kKeyBits - g);
+                const uint64_t p = g == 0u ? 0ull : (k[q] >> sh) << sh;
+                const uint32_t b = gs ? (uint32_t)i : key_lower_bound(key, 0u, (uint32_t)i, p);
+                gs = ((uint32_t)i - b) % ncrit == 0u;
+            }
+            lev[i] = (uint16_t)(lo | (hi << 5) | (g << 10) | (gs ? 1u << 15 : 0u));
+        }
+        const uint64_t gm = ballot(gs);
+        if (lane == 0 && gm) atomicAdd(&cnt[kGroupCh], (uint32_t)__popcll(gm));
+        const bool starts = valid && lo <= hi;
+        if (ballot(starts) == 0ull) continue;
+        const uint32_t l1 = wave_max_u32(starts ? hi : 0u),
+                       l0 = 31u - wave_max_u32(starts ? 31u - lo : 0u);
+        for (uint32_t l = l0; l <= l1; ++l) {
+            const uint64_t m = ballot(starts && lo <= l && l <= hi);
+            if (lane == 0 && m) atomicAdd(&cnt[l], (uint32_t)__popcll(m));
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x <= kLevels) tcnt[(size_t)threadIdx.x * ntiles + blockIdx.x] = cnt[threadIdx.x];
 }
 
-// lbt[q] for q in [0, 8^kTableLevel]: the first of the n sorted keys that is
-// >= q << 3 (21 - kTableLevel); lbt[8^kTableLevel] = n
-__global__ __launch_bounds__(256) void k_lb_table(const uint64_t *__restrict__ key, uint32_t n,
-                                                  uint32_t *__restrict__ lbt) {
-    constexpr uint32_t kQ = 1u << (3 * kTableLevel);
-    const uint32_t q = blockIdx.x * 256u + threadIdx.x;
-    if (q > kQ) return;
-    lbt[q] = q == kQ ? n
-                     : key_lower_bound(key, 0u, n, (uint64_t)q << (3 * (kKeyBits - kTableLevel)));
-}
-
-// Levels l0 .. 20 in one workgroup: the deep end of the tree, where a level
-// holds few cells (or none) and three launches per level would cost more
-// than the work.  Per level: each round of 1024 cells finds its children's
-// bounds, a block scan numbers the children in cell order, and the children
-// are written, exactly as the three grid kernels would.  Any level size is
-// handled (only more slowly), so the split between grid and tail levels
-// affects the time, never the tree.  Then publishes the level starts and the
-// build's number to the host (pinned memory, tagged before and after).
-constexpr int kTailThreads = 1024;
-
-__global__ __launch_bounds__(kTailThreads) void k_build_tail(Cells c,
-                                                             const uint64_t *__restrict__ key,
-                                                             int l0, uint32_t nleaf, uint32_t cap,
-                                                             uint32_t *status,
-                                                             volatile uint32_t *hint,
-                                                             uint32_t gen) {
-    __shared__ uint32_t wtot[kTailThreads / 64];
+// One block per level (and one for the groups): exclusive running sums of its
+// counts over the tiles, in place; the total into tot[channel].
+__global__ __launch_bounds__(1024) void k_tree_scan(uint32_t *__restrict__ tcnt, uint32_t ntiles,
+                                                    uint32_t *__restrict__ tot) {
+    __shared__ uint32_t ws[16];
+    uint32_t *row = tcnt + (size_t)blockIdx.x * ntiles;
     const uint32_t lane = lane_id(), w = threadIdx.x >> 6;
-    uint32_t first = 0, last = 0;
-    if (l0 < kLevels - 1) {
-        first = c.ls[l0];
-        last = c.ls[l0 + 1];
-    }
-    for (int l = l0; l < kLevels - 1; ++l) {
-        const bool few = last - first < kFewCells;
-        uint32_t next = last;  // the next level is built at [last, next)
-        for (uint32_t base = first; base < last; base += kTailThreads) {
-            const uint32_t i = base + threadIdx.x;
-            uint32_t bnd[9];
-            uint32_t nch = 0, b = 0;
-            uint64_t P = 0;
-            if (i < last) {
-                const uint32_t cnt = c.count[i];
-                if (cnt > nleaf) {
-                    b = c.begin[i];
-                    P = c.prefix[i];
-                    child_bounds(key, c.lbt, P, b, b + cnt, l, few, bnd);
+    constexpr uint32_t kPer = 8;
+    uint32_t carry = 0;
+    for (uint32_t base = 0; base < ntiles; base += 1024u * kPer) {
+        uint32_t v[kPer], s = 0;
 #pragma unroll
-                    for (int d = 0; d < 8; ++d) nch += bnd[d + 1] > bnd[d];
-                }
-                c.nchild[i] = nch;
-            }
-            const uint32_t inc = wave_incl_scan(nch, lane);
-            if (lane == 63) wtot[w] = inc;
-            __syncthreads();
-            uint32_t off = 0, tot = 0;
-            for (uint32_t k = 0; k < (uint32_t)(kTailThreads / 64); ++k) {
-                if (k < w) off += wtot[k];
-                tot += wtot[k];
-            }
-            __syncthreads();
-            if (i < last) {
-                if (nch > 0) {
-                    uint32_t ch = next + off + inc - nch;
-                    c.child0[i] = ch;
-                    for (uint32_t d = 0; d < 8; ++d) {
-                        if (bnd[d + 1] > bnd[d]) {
-                            if (ch < cap) {
-                                c.prefix[ch] = (P << 3) | d;
-                                c.level[ch] = (uint32_t)(l + 1);
-                                c.begin[ch] = bnd[d];
-                                c.count[ch] = bnd[d + 1] - bnd[d];
-                                c.child0[ch] = kNone;
-                                c.nchild[ch] = 0;
-                                c.parent[ch] = i;
-                            }
-                            ++ch;
-                        }
-                    }
-                } else {
-                    c.child0[i] = kNone;
-                }
-            }
-            next += tot;
+        for (uint32_t q = 0; q < kPer; ++q) {
+            const uint32_t i = base + threadIdx.x * kPer + q;
+            v[q] = i < ntiles ? row[i] : 0u;
+            s += v[q];
         }
-        if (next > cap) {
-            if (threadIdx.x == 0) atomicOr(status, kStOverflow);
-            next = cap;
+        const uint32_t inc = wave_incl_scan(s, lane);
+        if (lane == 63) ws[w] = inc;
+        __syncthreads();
+        uint32_t off = carry + inc - s, all = 0;
+#pragma unroll
+        for (uint32_t q = 0; q < 16; ++q) {
+            if (q < w) off += ws[q];
+            all += ws[q];
         }
-        if (threadIdx.x == 0) c.ls[l + 2] = next;
-        __syncthreads();  // the new level's cells are read by the whole block next
-        first = last;
-        last = next;
+        __syncthreads();
+#pragma unroll
+        for (uint32_t q = 0; q < kPer; ++q) {
+            const uint32_t i = base + threadIdx.x * kPer + q;
+            if (i < ntiles) row[i] = off;
+            off += v[q];
+        }
+        carry += all;
+    }
+    if (threadIdx.x == 0) tot[blockIdx.x] = carry;
+}
+
+// The cells and groups that start or end in the tile.  A cell's end (one past
+// its last particle) is left in count and the end of its children (0 for a
+// leaf) in nchild: its first and last particle may lie in different tiles.
+// The moment pass turns both into counts.
+__global__ __launch_bounds__(kTreeThreads) void k_tree_write(
+    Cells c, const uint64_t *__restrict__ key, const uint16_t *__restrict__ lev, uint32_t n,
+    uint32_t ntiles, const uint32_t *__restrict__ tcnt, const uint32_t *__restrict__ tot,
+    uint32_t cap, uint32_t *__restrict__ gbeg, uint32_t gcap, uint32_t *__restrict__ gpar,
+    uint32_t *ngroups, uint32_t *status, volatile uint32_t *hint, uint32_t gen) {
+    __shared__ uint64_t mask[kLevels + 1][kTreeWords];
+    __shared__ uint32_t pre[kLevels + 1][kTreeWords];  // starts of the level before the word
+    const uint32_t lane = lane_id(), w = threadIdx.x >> 6;
+    const uint32_t t0 = blockIdx.x * kTreeTile;
+    for (uint32_t q = threadIdx.x; q < (kLevels + 1) * kTreeWords; q += kTreeThreads)
+        (&mask[0][0])[q] = 0ull;
+    // level starts (every wave for itself; lane l holds level l's)
+    const uint32_t lt = lane < kLevels ? tot[lane] : 0u;
+    const uint32_t lend = wave_incl_scan(lt, lane), lstart = lend - lt;
+    if (blockIdx.x == 0 && threadIdx.x <= kLevels) {
+        c.ls[threadIdx.x] = min(lstart, cap);  // (lane kLevels: the cell count)
+        if (threadIdx.x == kLevels) {
+            if (lstart > cap) atomicOr(status, kStOverflow);
+            *ngroups = tot[kGroupCh];
+            if (tot[kGroupCh] < gcap) gbeg[tot[kGroupCh]] = n;
+        }
     }
     __syncthreads();
-    if (threadIdx.x == 0 && hint) {
+    uint32_t lv[kTreeItems], ln[kTreeItems];
+#pragma unroll
+    for (int r = 0; r < kTreeItems; ++r) {
+        const uint32_t i = t0 + r * kTreeThreads + threadIdx.x;
+        lv[r] = i < n ? lev[i] : 31u;           // no cell
+        ln[r] = i + 1u < n ? lv_lo(lev[i + 1u]) : 0u;  // every cell ends with the last particle
+        const uint32_t lo = lv_lo(lv[r]), hi = lv_hi(lv[r]);
+        const uint32_t word = r * (kTreeThreads / 64) + w;
+        const uint64_t gm = ballot(i < n && lv_group(lv[r]));
+        if (lane == 0) mask[kGroupCh][word] = gm;
+        const bool starts = lo <= hi;
+        if (ballot(starts) == 0ull) continue;
+        const uint32_t l1 = wave_max_u32(starts ? hi : 0u),
+                       l0 = 31u - wave_max_u32(starts ? 31u - lo : 0u);
+        for (uint32_t l = l0; l <= l1; ++l) {
+            const uint64_t m = ballot(starts && lo <= l && l <= hi);
+            if (lane == 0) mask[l][word] = m;
+        }
+    }
+    __syncthreads();
+    for (uint32_t q = threadIdx.x; q < (kLevels + 1) * kTreeWords; q += kTreeThreads) {
+        const uint32_t l = q / kTreeWords, word = q % kTreeWords;
+        uint32_t s = tcnt[(size_t)l * ntiles + blockIdx.x];
+        for (uint32_t k = 0; k < word; ++k) s += (uint32_t)__popcll(mask[l][k]);
+        pre[l][word] = s;
+    }
+    __syncthreads();
+    // numbers of the cells of level l: those that start before particle
+    // (word, lane), and the start of the level
+    auto before = [&](uint32_t l, uint32_t word) {
+        return pre[l][word] + (uint32_t)__popcll(mask[l][word] & mask_lt(lane));
+    };
+    auto upto = [&](uint32_t l, uint32_t word) {
+        return pre[l][word] + (uint32_t)__popcll(mask[l][word] & mask_le(lane));
+    };
+#pragma unroll
+    for (int r = 0; r < kTreeItems; ++r) {
+        const uint32_t i = t0 + r * kTreeThreads + threadIdx.x;
+        const uint32_t word = r * (kTreeThreads / 64) + w;
+        const uint32_t lo = lv_lo(lv[r]), hi = lv_hi(lv[r]);
+        const bool valid = i < n;
+        const uint64_t ky = valid ? key[i] : 0ull;
+        const bool grp = valid && lv_group(lv[r]);
+        const uint32_t gn = before(kGroupCh, word);
+        if (grp) gbeg[gn] = i;
+        if (gpar && ballot(grp) != 0ull) {  // the parent of the group's cell
+            const uint32_t gl = lv_glev(lv[r]), up = gl ? gl - 1u : 0u;
+            const uint32_t s = shfl(lstart, (int)up);
+            if (grp) gpar[gn] = gl ? s + upto(up, word) - 1u : kNone;
+        }
+        const bool starts = valid && lo <= hi, ends = valid && ln[r] <= hi;
+        if (ballot(starts || ends) == 0ull) continue;
+        const uint32_t first = min(starts ? lo : 31u, ends ? ln[r] : 31u);
+        const uint32_t l1 = wave_max_u32(starts || ends ? hi : 0u), l0 = 31u - wave_max_u32(31u - first);
+        for (uint32_t l = l0; l <= l1; ++l) {
+            const uint32_t s0 = read_lane(lstart, l);
+            const uint32_t s1 = read_lane(lend, l);  // the start of level l + 1
+            const uint32_t sp = read_lane(lstart, l ? l - 1u : 0u);
+            if (starts && lo <= l && l <= hi) {
+                const uint32_t ch = s0 + before(l, word);
+                if (ch < cap) {
+                    c.prefix[ch] = l == 0u ? 0ull : ky >> (3u * (kKeyBits - l));
+                    c.level[ch] = l;
+                    c.begin[ch] = i;
+                    c.child0[ch] = l < hi ? s1 + before(l + 1u, word) : kNone;
+                    c.parent[ch] = l == 0u ? kNone : sp + upto(l - 1u, word) - 1u;
+                }
+            }
+            if (ends && ln[r] <= l && l <= hi) {
+                const uint32_t e = s0 + upto(l, word) - 1u;
+                if (e < cap) {
+                    c.count[e] = i + 1u;
+                    c.nchild[e] = l < hi ? s1 + upto(l + 1u, word) : 0u;
+                }
+            }
+        }
+    }
+    if (hint && blockIdx.x == 0 && threadIdx.x == 0) {
         hint[0] = gen;
         __threadfence_system();
-        for (int k = 0; k < kLevels + 1; ++k) hint[2 + k] = c.ls[k];
+        for (uint32_t k = 0; k <= (uint32_t)kLevels; ++k) hint[2 + k] = min(read_lane(lstart, k), cap);
         __threadfence_system();
         hint[1] = gen;
     }
 }
 
-// Levels 0 .. grid_levels - 1 are split by the grid kernels, the rest by
-// k_build_tail.
-void launch_build(bh_ctx *ctx, uint32_t n, hipStream_t st, int grid_levels) {
-    Cells &c = ctx->cells;
-    constexpr uint32_t kQ = 1u << (3 * kTableLevel);
-    hipLaunchKernelGGL(k_lb_table, dim3((kQ + 1 + 255) / 256), dim3(256), 0, st,
-                       (const uint64_t *)ctx->sort.key[0], n, c.lbt);
-    hipLaunchKernelGGL(k_build_init, dim3(1), dim3(64), 0, st, c, n);
-    uint32_t cap = (uint32_t)ctx->cap_cells;
-    const int L = grid_levels < 0 ? 0 : (grid_levels > kLevels - 1 ? kLevels - 1 : grid_levels);
-    for (int l = 0; l < L; ++l) {
-        hipLaunchKernelGGL(k_build_count, dim3(kBuildGrid), dim3(kBuildThreads), 0, st, c,
-                           (const uint64_t *)ctx->sort.key[0], l, (uint32_t)ctx->p.nleaf,
-                           (uint32_t)ctx->nmax);
-        hipLaunchKernelGGL(k_build_scan, dim3(1), dim3(kBuildThreads), 0, st, c, l, cap,
-                           ctx->status);
-        hipLaunchKernelGGL(k_build_write, dim3(kBuildGrid), dim3(kBuildThreads), 0, st, c,
-                           (const uint64_t *)ctx->sort.key[0], l, cap, (uint32_t)ctx->nmax);
+// Paired target sets (bh_params.pair_groups = cap, off by default): groups
+// 2k and 2k + 1 that are siblings (group cells with one parent, gpar) and hold
+// at most cap particles together become one target set, walked once against
+// the box of their union.  flag[j] = 1 where group j stays the first of a set.
+__global__ __launch_bounds__(256) void k_pair_flags(const uint32_t *__restrict__ gbeg,
+                                                    const uint32_t *__restrict__ ngroups,
+                                                    const uint32_t *__restrict__ gpar, uint32_t n,
+                                                    uint32_t cap, uint32_t *__restrict__ flag) {
+    const uint32_t j = blockIdx.x * 256 + threadIdx.x;
+    if (j >= n) return;
+    const uint32_t ng = *ngroups;
+    bool keep = j < ng;
+    if (keep && (j & 1u)) {
+        const uint32_t end = j + 1u < ng ? gbeg[j + 1u] : n;
+        keep = !(end - gbeg[j - 1u] <= cap && gpar[j - 1u] == gpar[j] && gpar[j] != kNone);
     }
-    hipLaunchKernelGGL(k_build_tail, dim3(1), dim3(kTailThreads), 0, st, c,
-                       (const uint64_t *)ctx->sort.key[0], L, (uint32_t)ctx->p.nleaf, cap,
-                       ctx->status, (volatile uint32_t *)ctx->hint_dev, ctx->build_gen);
+    flag[j] = keep ? 1u : 0u;
 }
 
-// ---- groups -----------------------------------------------------------------
-//
-// A cell is a group iff (count <= ncrit or it is a leaf) and (it is the root
-// or its parent holds more than ncrit).  Groups partition the sorted
-// particles; a group cell larger than ncrit (a level-21 leaf of coincident
-// keys) is cut into chunks of ncrit.  Group numbers follow key order: flag
-// each group's first particle, scan the flags.
-
-__global__ __launch_bounds__(256) void k_group_flags(Cells c, uint32_t ncrit, uint32_t *flag,
-                                                     uint32_t *gpar) {
-    uint32_t nc = c.ls[kLevels];
-    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < nc; i += gridDim.x * 256) {
-        uint32_t cnt = c.count[i];
-        bool small = cnt <= ncrit || c.nchild[i] == 0;
-        bool top = i == 0 || c.count[c.parent[i]] > ncrit;
-        if (small && top) {
-            uint32_t b = c.begin[i];
-            for (uint32_t s = 0; s < cnt; s += ncrit) {
-                flag[b + s] = 1u;
-                if (gpar) gpar[b + s] = i == 0 ? kNone : c.parent[i];
-            }
-        }
-    }
-}
-
-__global__ __launch_bounds__(256) void k_group_fill(const uint32_t *__restrict__ flag,
-                                                    const uint32_t *__restrict__ scan, uint32_t n,
-                                                    uint32_t *gbeg, uint32_t *ngroups) {
-    uint32_t i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    if (flag[i]) gbeg[scan[i]] = i;
-    if (i == n - 1) {
-        uint32_t ng = scan[i] + flag[i];
+__global__ __launch_bounds__(256) void k_pair_fill(const uint32_t *__restrict__ gbeg0,
+                                                   const uint32_t *__restrict__ flag,
+                                                   const uint32_t *__restrict__ scan, uint32_t n,
+                                                   uint32_t *__restrict__ gbeg,
+                                                   uint32_t *ngroups) {
+    const uint32_t j = blockIdx.x * 256 + threadIdx.x;
+    if (j >= n) return;
+    if (flag[j]) gbeg[scan[j]] = gbeg0[j];
+    if (j == n - 1u) {
+        const uint32_t ng = scan[j] + flag[j];
         *ngroups = ng;
         gbeg[ng] = n;
     }
 }
 
-// Paired target sets (bh_params.pair_groups = cap, off by default): groups
-// 2k and 2k + 1 that are siblings (group cells with one parent; gpar holds
-// it at each group's first particle) and hold at most cap particles together
-// become one target set, walked once against the box of their union, by
-// clearing the start flag of group 2k + 1.
-__global__ __launch_bounds__(256) void k_pair_flags(const uint32_t *__restrict__ gbeg,
-                                                    const uint32_t *__restrict__ ngroups,
-                                                    const uint32_t *__restrict__ gpar,
-                                                    uint32_t cap, uint32_t *flag) {
-    const uint32_t ng = *ngroups;
-    for (uint32_t j = 2 * (blockIdx.x * 256 + threadIdx.x) + 1; j < ng;
-         j += 2 * gridDim.x * 256) {
-        const uint32_t a = gbeg[j - 1], b = gbeg[j];
-        if (gbeg[j + 1] - a <= cap && gpar[a] == gpar[b] && gpar[a] != kNone) flag[b] = 0u;
-    }
-}
-
-void launch_groups(bh_ctx *ctx, uint32_t n, hipStream_t st) {
+// Cells (count and nchild completed by the moment pass) and groups.
+void launch_build(bh_ctx *ctx, uint32_t n, hipStream_t st) {
+    Cells &c = ctx->cells;
     Groups &g = ctx->groups;
-    launch_fill_u32(g.flag, 0u, n, st);
-    // paired target sets: each group's parent cell is kept in npp until the walk
+    const uint64_t *key = ctx->sort.key[0];
+    const uint32_t nt = cdiv(n, kTreeTile);
+    hipLaunchKernelGGL(k_tree_levels, dim3(nt), dim3(kTreeThreads), 0, st, key, n,
+                       (uint32_t)ctx->p.nleaf, (uint32_t)ctx->p.ncrit, nt, c.lev, c.tcnt);
+    hipLaunchKernelGGL(k_tree_scan, dim3(kLevels + 1), dim3(1024), 0, st, c.tcnt, nt, c.ttot);
+    // paired target sets: the groups first go to the sort's second index
+    // buffer, each group's parent cell to npp
+    uint32_t *gbeg0 = ctx->pair_groups ? ctx->sort.idx[1] : g.begin;
     uint32_t *gpar = ctx->pair_groups ? g.npp : nullptr;
-    hipLaunchKernelGGL(k_group_flags, dim3(kGrid), dim3(256), 0, st, ctx->cells,
-                       (uint32_t)ctx->p.ncrit, g.flag, gpar);
+    hipLaunchKernelGGL(k_tree_write, dim3(nt), dim3(kTreeThreads), 0, st, c, key,
+                       (const uint16_t *)c.lev, n, nt, (const uint32_t *)c.tcnt,
+                       (const uint32_t *)c.ttot, (uint32_t)ctx->cap_cells, gbeg0,
+                       ctx->pair_groups ? n : n + 1u, gpar, g.count_dev, ctx->status,
+                       (volatile uint32_t *)ctx->hint_dev, ctx->build_gen);
+    if (!ctx->pair_groups) return;
+    hipLaunchKernelGGL(k_pair_flags, dim3(cdiv(n, 256)), dim3(256), 0, st,
+                       (const uint32_t *)gbeg0, (const uint32_t *)g.count_dev,
+                       (const uint32_t *)gpar, n, ctx->pair_groups, g.flag);
     launch_exclusive_scan(g.flag, g.scan, n, ctx->sort.scan_part, st);
-    hipLaunchKernelGGL(k_group_fill, dim3(cdiv(n, 256)), dim3(256), 0, st,
-                       (const uint32_t *)g.flag, (const uint32_t *)g.scan, n, g.begin,
-                       g.count_dev);
-    if (ctx->pair_groups) {
-        hipLaunchKernelGGL(k_pair_flags, dim3(kGrid), dim3(256), 0, st,
-                           (const uint32_t *)g.begin, (const uint32_t *)g.count_dev,
-                           (const uint32_t *)gpar, ctx->pair_groups, g.flag);
-        launch_exclusive_scan(g.flag, g.scan, n, ctx->sort.scan_part, st);
-        hipLaunchKernelGGL(k_group_fill, dim3(cdiv(n, 256)), dim3(256), 0, st,
-                           (const uint32_t *)g.flag, (const uint32_t *)g.scan, n, g.begin,
-                           g.count_dev);
-    }
+    hipLaunchKernelGGL(k_pair_fill, dim3(cdiv(n, 256)), dim3(256), 0, st,
+                       (const uint32_t *)gbeg0, (const uint32_t *)g.flag,
+                       (const uint32_t *)g.scan, n, g.begin, g.count_dev);
 }
 
 }  // namespace bh

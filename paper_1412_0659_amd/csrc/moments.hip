@@ -178,9 +178,13 @@ template <bool kStaged>
 __device__ __forceinline__ void cell_pass(const MomArgs &a, uint32_t i, uint32_t lev) {
     const Cells &c = a.c;
     // the cell's topology in one round of loads (every field is defined for
-    // every cell; child0 is only used by parents, begin and count by leaves)
-    const uint32_t nch = c.nchild[i], b0 = c.begin[i], n0 = c.count[i], k0 = c.child0[i];
+    // every cell; child0 is only used by parents, begin and count by leaves);
+    // the build left the ends of its particles and children, made counts here
+    const uint32_t kend = c.nchild[i], b0 = c.begin[i], n0 = c.count[i] - b0, k0 = c.child0[i];
     const uint64_t prefix = c.prefix[i];
+    const uint32_t nch = kend ? kend - k0 : 0u;
+    c.count[i] = n0;
+    c.nchild[i] = nch;
     Mom r;
     double c0, c1, c2;
     uint32_t first, cnt;
