@@ -18,6 +18,7 @@ constexpr int kLevels = 22;             // levels 0..21
 constexpr int kLsSize = 24;             // level_start entries (23 used)
 constexpr int kGrid = 1024;             // fixed grid of the per-level moment, box and flag kernels
 constexpr int kTreeTile = 1024;         // particles per block of the octree build
+constexpr int kSpanTiles = 128;         // tiles per block of the moment pass over tile ends
 constexpr uint32_t kLeafBit = 0x80000000u;
 constexpr uint32_t kNone = 0xffffffffu;
 constexpr int kWorkStride = 32;         // a cache line per work counter of the walk
@@ -172,14 +173,6 @@ struct bh_ctx {
     bh::Let let{};
     bh::Cut cut{};
 
-    // level starts of a recent build, written by k_tree_write into pinned host
-    // memory: [0] build number (written first), [1] build number (written
-    // last), [2 ..] ls[0 .. kLevels]
-    uint32_t *hint_host = nullptr;
-    uint32_t *hint_dev = nullptr;  // the same memory as the device addresses it
-    uint32_t build_gen = 0;     // builds launched so far
-    uint32_t hint_gen_min = 1;  // first build of the current particle set
-
     bool built = false, have_acc = false;
     bool counts_valid = false;  // npp / npc / totals describe a walk of the current groups
     bool fixed_box = false;     // keys relative to a caller-given box (bh_set_box)
@@ -187,7 +180,6 @@ struct bh_ctx {
     float acc_theta = 0.f, acc_eps = 0.f;
     int walk_grid = 0;
     bool walk_small_stack = false;  // test hook: at most 192 resident stack entries
-    int forced_grid_levels = -1;    // test hook: levels split by the grid kernels
     uint32_t pair_groups = 0;       // sibling groups of together <= this many walk as one (0: off)
 
     // events: build start, after sort, after octree+groups, after moments,
@@ -234,7 +226,7 @@ void launch_exclusive_scan(const uint32_t *in, uint32_t *out, uint32_t n, uint32
 void launch_build(bh_ctx *c, uint32_t n, hipStream_t st);  // cells and groups
 
 // moments.hip
-void launch_moments(bh_ctx *c, hipStream_t st, int grid_levels);
+void launch_moments(bh_ctx *c, uint32_t n, hipStream_t st);
 void launch_com(bh_ctx *c, hipStream_t st);
 void launch_walk_prep(bh_ctx *c, float theta, hipStream_t st);
 
@@ -315,6 +307,13 @@ inline void record_event(bh_ctx *c, int k, hipStream_t st) {
     (void)hipEventRecord(c->ev[k], st);
     c->ev_rec[k] = true;
 }
+
+// levels of a particle, packed: lo (5 bits), hi (5 bits), its group cell's
+// level (5 bits), first of a group
+__device__ __forceinline__ uint32_t lv_lo(uint32_t v) { return v & 31u; }
+__device__ __forceinline__ uint32_t lv_hi(uint32_t v) { return (v >> 5) & 31u; }
+__device__ __forceinline__ uint32_t lv_glev(uint32_t v) { return (v >> 10) & 31u; }
+__device__ __forceinline__ bool lv_group(uint32_t v) { return (v >> 15) & 1u; }
 
 // Peano-Hilbert curve (the curve of Sec. III.B.1), after J. Skilling,
 // "Programming the Hilbert curve", AIP Conf. Proc. 707, 381 (2004): integer

@@ -47,13 +47,6 @@ constexpr int kTreeWords = kTreeTile / 64;
 constexpr int kHalo = 64;               // nleaf, ncrit <= 64
 constexpr int kGroupCh = kLevels;       // the groups' channel of the tile counts
 
-// levels of a particle, packed: lo (5 bits), hi (5 bits), its group cell's
-// level (5 bits), first of a group
-__device__ __forceinline__ uint32_t lv_lo(uint32_t v) { return v & 31u; }
-__device__ __forceinline__ uint32_t lv_hi(uint32_t v) { return (v >> 5) & 31u; }
-__device__ __forceinline__ uint32_t lv_glev(uint32_t v) { return (v >> 10) & 31u; }
-__device__ __forceinline__ bool lv_group(uint32_t v) { return (v >> 15) & 1u; }
-
 // leading 3-bit digits (of 21) that two 63-bit keys share
 __device__ __forceinline__ int common_digits(uint64_t a, uint64_t b) {
     const uint64_t x = a ^ b;
@@ -213,7 +206,7 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_write(
     Cells c, const uint64_t *__restrict__ key, const uint16_t *__restrict__ lev, uint32_t n,
     uint32_t ntiles, const uint32_t *__restrict__ tcnt, const uint32_t *__restrict__ tot,
     uint32_t cap, uint32_t *__restrict__ gbeg, uint32_t gcap, uint32_t *__restrict__ gpar,
-    uint32_t *ngroups, uint32_t *status, volatile uint32_t *hint, uint32_t gen) {
+    uint32_t *ngroups, uint32_t *status) {
     __shared__ uint64_t mask[kLevels + 1][kTreeWords];
     __shared__ uint32_t pre[kLevels + 1][kTreeWords];  // starts of the level before the word
     const uint32_t lane = lane_id(), w = threadIdx.x >> 6;
@@ -309,13 +302,6 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_write(
             }
         }
     }
-    if (hint && blockIdx.x == 0 && threadIdx.x == 0) {
-        hint[0] = gen;
-        __threadfence_system();
-        for (uint32_t k = 0; k <= (uint32_t)kLevels; ++k) hint[2 + k] = min(read_lane(lstart, k), cap);
-        __threadfence_system();
-        hint[1] = gen;
-    }
 }
 
 // Paired target sets (bh_params.pair_groups = cap, off by default): groups
@@ -368,8 +354,7 @@ void launch_build(bh_ctx *ctx, uint32_t n, hipStream_t st) {
     hipLaunchKernelGGL(k_tree_write, dim3(nt), dim3(kTreeThreads), 0, st, c, key,
                        (const uint16_t *)c.lev, n, nt, (const uint32_t *)c.tcnt,
                        (const uint32_t *)c.ttot, (uint32_t)ctx->cap_cells, gbeg0,
-                       ctx->pair_groups ? n : n + 1u, gpar, g.count_dev, ctx->status,
-                       (volatile uint32_t *)ctx->hint_dev, ctx->build_gen);
+                       ctx->pair_groups ? n : n + 1u, gpar, g.count_dev, ctx->status);
     if (!ctx->pair_groups) return;
     hipLaunchKernelGGL(k_pair_flags, dim3(cdiv(n, 256)), dim3(256), 0, st,
                        (const uint32_t *)gbeg0, (const uint32_t *)g.count_dev,

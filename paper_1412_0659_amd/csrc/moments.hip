@@ -9,28 +9,45 @@
 //
 // Each cell is one thread summing in a fixed order (a leaf over its
 // particles in sorted order, a parent over its children in child order),
-// with contraction off, so the result does not depend on the launch.  Level
-// by level from the deepest, leaves and parents of a level in one pass that
-// also writes the cell's walk records.  The FP64 record of a cell is M, S
-// and Q (80 bytes, read once more by its parent); com = S / M is recomputed
-// where needed.  The walk reads FP32 copies: com and the opening radius
-// r_open = l / theta + |com - geometric centre| (l = cell size) for the
-// opening test, and (com, M, -3 Q, tr Q / 2, -3 tr Q / 2) for the
-// particle-cell terms.
+// with contraction off, so the result does not depend on the launch.  The
+// FP64 record of a cell is M, S and Q (80 bytes); com = S / M is recomputed
+// where needed.  The walk reads FP32 copies, written as soon as the moments
+// are known: com and the opening radius r_open = l / theta + |com - geometric
+// centre| (l = cell size) for the opening test, and (com, M, -3 Q, tr Q / 2,
+// -3 tr Q / 2) for the particle-cell terms.
+//
+// The cells that start and end inside one tile of kTreeTile particles are
+// summed by the tile's block (k_moments_tile): its leaves first, all levels
+// at once, then its parents from the deepest level up, each level's moments
+// kept in LDS for the next.  A cell across a tile's end is the last one of
+// its level to start in the tile, so at most one per tile and level is left
+// over; those inside a span of kSpanTiles tiles are summed by one block per
+// span (k_moments_span, eight lanes per tile end, level by level), the rest by
+// one block (k_moments_top, eight lanes per span end): three launches for any
+// number of particles and levels (one to kTreeTile particles, two to a span).
+//
+// Bound: memory, 16 B per particle and 200 B per cell; on small sets the
+// chain of levels (4 us a level in the spans).  Measured: 0.38 ms at 13M (tiles
+// 263, spans 52, top 67 us), 0.105 ms at 1M, where one launch per level took
+// 0.42 and 0.135 ms (22 launches on a new particle set); 16384: 50 against 95
+// us, 1000: 22 against 67.  Also measured: one lane per parent in the spans and
+// the top (its 27 FP64 divisions in a row): 54 and 135 us at 13M; eight parents
+// a wave with the sums by shuffles: 101 and 191 us; topology loaded again on
+// every level and records written from inside it: tiles 422 us.
 #include "bh_internal.h"
+#include "wave.h"
 
 namespace bh {
 
-// Leaves of at most kStage particles are read once into registers (the loads
-// issue together instead of one trip at a time) and summed from there; larger
-// leaves (nleaf > kStage) and the leaves of the single-workgroup tail read
-// their particles twice.  The sums run in the same order either way.
-constexpr uint32_t kStage = 16;
+// A leaf's particles are read kBatch at a time (the loads of a batch issue
+// together), once for the mass and centre and once more, from the cache, for
+// the quadrupole: holding 16 particles in registers instead halved the waves
+// in flight.
+constexpr uint32_t kBatch = 8;
 
 struct MomArgs {
     Cells c;
-    const float *x, *y, *z, *m;
-    const float4 *xyzm;  // the same particles as (x, y, z, m) records, one load each
+    const float4 *xyzm;  // sorted particles as (x, y, z, m) records
     const float *box;  // lo xyz, side
     int curve;
 };
@@ -39,115 +56,75 @@ struct Mom {
     double M, s0, s1, s2, q0, q1, q2, q3, q4, q5;
 };
 
-template <bool kStaged>
 __device__ __forceinline__ void leaf_sums(const MomArgs &a, uint32_t b, uint32_t cnt, Mom &r,
                                           double &c0, double &c1, double &c2) {
-    const uint32_t e = b + cnt;
-    double mm = 0.0, s0 = 0.0, s1 = 0.0, s2 = 0.0;
-    double q0 = 0, q1 = 0, q2 = 0, q3 = 0, q4 = 0, q5 = 0;
-    if (kStaged && cnt <= kStage) {
-        float px[kStage], py[kStage], pz[kStage], pm[kStage];
+    r = Mom{0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    float4 p[kBatch];
+#pragma unroll 1
+    for (uint32_t o = 0; o < cnt; o += kBatch) {
 #pragma unroll
-        for (uint32_t k = 0; k < kStage; ++k) {
-            const float4 p = a.xyzm[k < cnt ? b + k : b];
-            px[k] = p.x; py[k] = p.y; pz[k] = p.z; pm[k] = p.w;
-        }
+        for (uint32_t k = 0; k < kBatch; ++k) p[k] = a.xyzm[o + k < cnt ? b + o + k : b];
 #pragma unroll
-        for (uint32_t k = 0; k < kStage; ++k) {
-            if (k < cnt) {
-                const double mj = pm[k];
-                mm = mm + mj;
-                s0 = s0 + mj * (double)px[k];
-                s1 = s1 + mj * (double)py[k];
-                s2 = s2 + mj * (double)pz[k];
+        for (uint32_t k = 0; k < kBatch; ++k) {
+            if (o + k < cnt) {
+                const double mj = p[k].w;
+                r.M = r.M + mj;
+                r.s0 = r.s0 + mj * (double)p[k].x;
+                r.s1 = r.s1 + mj * (double)p[k].y;
+                r.s2 = r.s2 + mj * (double)p[k].z;
             }
-        }
-        c0 = s0 / mm; c1 = s1 / mm; c2 = s2 / mm;
-#pragma unroll
-        for (uint32_t k = 0; k < kStage; ++k) {
-            if (k < cnt) {
-                const double mj = pm[k];
-                const double d0 = (double)px[k] - c0, d1 = (double)py[k] - c1,
-                             d2 = (double)pz[k] - c2;
-                q0 = q0 + (mj * d0) * d0;
-                q1 = q1 + (mj * d1) * d1;
-                q2 = q2 + (mj * d2) * d2;
-                q3 = q3 + (mj * d0) * d1;
-                q4 = q4 + (mj * d0) * d2;
-                q5 = q5 + (mj * d1) * d2;
-            }
-        }
-    } else {
-        for (uint32_t j = b; j < e; ++j) {
-            double mj = a.m[j];
-            mm = mm + mj;
-            s0 = s0 + mj * (double)a.x[j];
-            s1 = s1 + mj * (double)a.y[j];
-            s2 = s2 + mj * (double)a.z[j];
-        }
-        c0 = s0 / mm; c1 = s1 / mm; c2 = s2 / mm;
-        for (uint32_t j = b; j < e; ++j) {
-            double mj = a.m[j];
-            double d0 = (double)a.x[j] - c0, d1 = (double)a.y[j] - c1, d2 = (double)a.z[j] - c2;
-            q0 = q0 + (mj * d0) * d0;
-            q1 = q1 + (mj * d1) * d1;
-            q2 = q2 + (mj * d2) * d2;
-            q3 = q3 + (mj * d0) * d1;
-            q4 = q4 + (mj * d0) * d2;
-            q5 = q5 + (mj * d1) * d2;
         }
     }
-    r = Mom{mm, s0, s1, s2, q0, q1, q2, q3, q4, q5};
+    c0 = r.s0 / r.M; c1 = r.s1 / r.M; c2 = r.s2 / r.M;
+#pragma unroll 1
+    for (uint32_t o = 0; o < cnt; o += kBatch) {
+        if (cnt > kBatch) {
+#pragma unroll
+            for (uint32_t k = 0; k < kBatch; ++k) p[k] = a.xyzm[o + k < cnt ? b + o + k : b];
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < kBatch; ++k) {
+            if (o + k < cnt) {
+                const double mj = p[k].w;
+                const double d0 = (double)p[k].x - c0, d1 = (double)p[k].y - c1,
+                             d2 = (double)p[k].z - c2;
+                r.q0 = r.q0 + (mj * d0) * d0;
+                r.q1 = r.q1 + (mj * d1) * d1;
+                r.q2 = r.q2 + (mj * d2) * d2;
+                r.q3 = r.q3 + (mj * d0) * d1;
+                r.q4 = r.q4 + (mj * d0) * d2;
+                r.q5 = r.q5 + (mj * d1) * d2;
+            }
+        }
+    }
 }
 
-// A parent reads the mass, first and second moments (and with kStaged the
-// quadrupoles) of its (at most eight) children at once, then sums them in
-// child order; a child's centre of mass is its S / M, the same division that
-// made it.
-template <bool kStaged>
+// A parent from its children in memory, in child order; a child's centre of
+// mass is its S / M, the same division that made it.
 __device__ __forceinline__ void parent_sums(const Cells &c, uint32_t k0, uint32_t nch, Mom &r,
                                             double &c0, double &c1, double &c2) {
-    double cm[8], cs0[8], cs1[8], cs2[8];
-    double2 cq[8][3];  // the six quadrupole entries as three 16-byte loads
-    const double2 *Q2 = reinterpret_cast<const double2 *>(c.Q);  // 16-byte aligned
-#pragma unroll
-    for (uint32_t k = 0; k < 8; ++k) {
-        const uint32_t j = k0 + (k < nch ? k : 0u);
-        cm[k] = c.M[j]; cs0[k] = c.S[3 * j]; cs1[k] = c.S[3 * j + 1]; cs2[k] = c.S[3 * j + 2];
-        if (kStaged) {
-            cq[k][0] = Q2[3 * (size_t)j]; cq[k][1] = Q2[3 * (size_t)j + 1];
-            cq[k][2] = Q2[3 * (size_t)j + 2];
-        }
+    r = Mom{0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+    for (size_t j = k0; j < (size_t)k0 + nch; ++j) {
+        r.M = r.M + c.M[j];
+        r.s0 = r.s0 + c.S[3 * j];
+        r.s1 = r.s1 + c.S[3 * j + 1];
+        r.s2 = r.s2 + c.S[3 * j + 2];
     }
-    double mm = 0.0, s0 = 0.0, s1 = 0.0, s2 = 0.0;
-#pragma unroll
-    for (uint32_t k = 0; k < 8; ++k) {
-        if (k < nch) {
-            mm = mm + cm[k];
-            s0 = s0 + cs0[k];
-            s1 = s1 + cs1[k];
-            s2 = s2 + cs2[k];
-        }
+    c0 = r.s0 / r.M; c1 = r.s1 / r.M; c2 = r.s2 / r.M;
+#pragma unroll 1
+    for (size_t j = k0; j < (size_t)k0 + nch; ++j) {
+        const double mk = c.M[j];
+        const double d0 = c.S[3 * j] / mk - c0, d1 = c.S[3 * j + 1] / mk - c1,
+                     d2 = c.S[3 * j + 2] / mk - c2;
+        const double *Q = c.Q + 6 * j;
+        r.q0 = r.q0 + (Q[0] + (mk * d0) * d0);
+        r.q1 = r.q1 + (Q[1] + (mk * d1) * d1);
+        r.q2 = r.q2 + (Q[2] + (mk * d2) * d2);
+        r.q3 = r.q3 + (Q[3] + (mk * d0) * d1);
+        r.q4 = r.q4 + (Q[4] + (mk * d0) * d2);
+        r.q5 = r.q5 + (Q[5] + (mk * d1) * d2);
     }
-    c0 = s0 / mm; c1 = s1 / mm; c2 = s2 / mm;
-    double q0 = 0, q1 = 0, q2 = 0, q3 = 0, q4 = 0, q5 = 0;
-#pragma unroll
-    for (uint32_t k = 0; k < 8; ++k) {
-        if (k < nch) {
-            const double mk = cm[k];
-            const double d0 = cs0[k] / mk - c0, d1 = cs1[k] / mk - c1, d2 = cs2[k] / mk - c2;
-            const size_t j = k0 + k;
-            const double2 qa = kStaged ? cq[k][0] : Q2[3 * j], qb = kStaged ? cq[k][1] : Q2[3 * j + 1],
-                          qc = kStaged ? cq[k][2] : Q2[3 * j + 2];
-            q0 = q0 + (qa.x + (mk * d0) * d0);
-            q1 = q1 + (qa.y + (mk * d1) * d1);
-            q2 = q2 + (qb.x + (mk * d2) * d2);
-            q3 = q3 + (qb.y + (mk * d0) * d1);
-            q4 = q4 + (qc.x + (mk * d0) * d2);
-            q5 = q5 + (qc.y + (mk * d1) * d2);
-        }
-    }
-    r = Mom{mm, s0, s1, s2, q0, q1, q2, q3, q4, q5};
 }
 
 // every third bit of v (bits 0, 3, 6, ...) gathered into the low 21 bits
@@ -162,41 +139,22 @@ __device__ __forceinline__ uint32_t every_third_bit(uint64_t v) {
 }
 
 // corner coordinates of a cell from its key prefix (x the high bit of each
-// 3-bit digit, the first digit the most significant); lev only bounds the
-// prefix, whose higher bits are zero
-__device__ __forceinline__ void cell_coords(uint64_t prefix, uint32_t lev, uint32_t p[3]) {
-    (void)lev;
+// 3-bit digit, the first digit the most significant)
+__device__ __forceinline__ void cell_coords(uint64_t prefix, uint32_t p[3]) {
     p[0] = every_third_bit(prefix >> 2);
     p[1] = every_third_bit(prefix >> 1);
     p[2] = every_third_bit(prefix);
 }
 
-// Cell i of level lev: its FP64 moments (M, S, Q; the centre of mass is
-// S / M wherever it is needed) and its walk records.  kStaged: small leaves
-// through registers (more VGPRs).
-template <bool kStaged>
-__device__ __forceinline__ void cell_pass(const MomArgs &a, uint32_t i, uint32_t lev) {
+// Write cell i's moments and walk records; the build left the ends of its
+// particles and children, made counts here.
+__device__ __forceinline__ void cell_out(const MomArgs &a, uint32_t i, uint32_t lev,
+                                         uint64_t prefix, uint32_t b0, uint32_t n0, uint32_t k0,
+                                         uint32_t nch, const Mom &r, double c0, double c1,
+                                         double c2) {
     const Cells &c = a.c;
-    // the cell's topology in one round of loads (every field is defined for
-    // every cell; child0 is only used by parents, begin and count by leaves);
-    // the build left the ends of its particles and children, made counts here
-    const uint32_t kend = c.nchild[i], b0 = c.begin[i], n0 = c.count[i] - b0, k0 = c.child0[i];
-    const uint64_t prefix = c.prefix[i];
-    const uint32_t nch = kend ? kend - k0 : 0u;
     c.count[i] = n0;
     c.nchild[i] = nch;
-    Mom r;
-    double c0, c1, c2;
-    uint32_t first, cnt;
-    if (nch == 0) {
-        first = b0;
-        cnt = n0;
-        leaf_sums<kStaged>(a, first, cnt, r, c0, c1, c2);
-    } else {
-        first = k0;
-        cnt = nch;
-        parent_sums<kStaged>(c, first, nch, r, c0, c1, c2);
-    }
     c.M[i] = r.M;
     c.S[3 * i] = r.s0; c.S[3 * i + 1] = r.s1; c.S[3 * i + 2] = r.s2;
     double2 *q = reinterpret_cast<double2 *>(c.Q) + 3 * (size_t)i;
@@ -207,7 +165,7 @@ __device__ __forceinline__ void cell_pass(const MomArgs &a, uint32_t i, uint32_t
     // walk records: com (FP32), opening-radius terms, particle-cell record
     const double lo0 = a.box[0], lo1 = a.box[1], lo2 = a.box[2], side = a.box[3];
     uint32_t p[3];
-    cell_coords(prefix, lev, p);          // the digits, deinterleaved
+    cell_coords(prefix, p);          // the digits, deinterleaved
     if (a.curve == 1) ph_decode(p, (int)lev);  // Peano-Hilbert prefix -> octant
     const double lc = side * (1.0 / (double)(1u << lev));
     const double e0 = c0 - (lo0 + ((double)p[0] + 0.5) * lc);
@@ -221,47 +179,332 @@ __device__ __forceinline__ void cell_pass(const MomArgs &a, uint32_t i, uint32_t
                           (float)(-3.0 * r.q3));
     c.P2[i] = make_float4((float)(-3.0 * r.q4), (float)(-3.0 * r.q5), (float)(0.5 * tr),
                           (float)(-1.5 * tr));
-    c.wN[i] = nch ? make_uint2(first, cnt) : make_uint2(first, cnt | kLeafBit);
+    c.wN[i] = nch ? make_uint2(k0, nch) : make_uint2(b0, n0 | kLeafBit);
     c.size[i] = make_float2((float)lc, (float)dl);
 }
 
-__global__ __launch_bounds__(256) void k_moments_level(MomArgs a, int l) {
-    const uint32_t first = a.c.ls[l], last = a.c.ls[l + 1];
-    for (uint32_t i = first + blockIdx.x * 256 + threadIdx.x; i < last; i += gridDim.x * 256)
-        cell_pass<true>(a, i, (uint32_t)l);
+// Cell i of level lev on its own, a parent's children read from memory.
+__device__ __forceinline__ void cell_pass(const MomArgs &a, uint32_t i, uint32_t lev) {
+    const Cells &c = a.c;
+    // the topology in one round of loads (child0 is only used by parents)
+    const uint32_t kend = c.nchild[i], b0 = c.begin[i], n0 = c.count[i] - b0, k0 = c.child0[i];
+    const uint64_t prefix = c.prefix[i];
+    const uint32_t nch = kend ? kend - k0 : 0u;
+    Mom r;
+    double c0, c1, c2;
+    if (nch == 0) leaf_sums(a, b0, n0, r, c0, c1, c2);
+    else parent_sums(c, k0, nch, r, c0, c1, c2);
+    cell_out(a, i, lev, prefix, b0, n0, k0, nch, r, c0, c1, c2);
 }
 
-// Levels l0 down to l1 in one workgroup (the deep end of the tree, few or no
-// cells), the same per-cell sums as k_moments_level (leaves read twice).
-__global__ __launch_bounds__(1024) void k_moments_tail(MomArgs a, int l0, int l1) {
-    for (int l = l0; l >= l1; --l) {
-        const uint32_t first = a.c.ls[l], last = a.c.ls[l + 1];
-        for (uint32_t i = first + threadIdx.x; i < last; i += 1024)
-            cell_pass<false>(a, i, (uint32_t)l);
-        __syncthreads();  // the next level up reads these cells
+// The cells of level l that start before tile t (the total for t = tiles).
+__device__ __forceinline__ uint32_t starts_before(const Cells &c, uint32_t ntiles, uint32_t l,
+                                                  uint32_t t) {
+    return t < ntiles ? c.tcnt[(size_t)l * ntiles + t] : c.ttot[l];
+}
+
+// The levels l < levels_across(i) are those whose cells hold both particle
+// i - 1 and i.
+__device__ __forceinline__ uint32_t levels_across(const Cells &c, uint32_t i) {
+    return min(lv_hi(c.lev[i - 1u]) + 1u, lv_lo(c.lev[i]));
+}
+
+constexpr int kMomThreads = 256;
+constexpr int kMomCells = 384;  // cells of a tile whose moments fit in LDS (235 on average)
+
+__global__ __launch_bounds__(kMomThreads, 4) void k_moments_tile(MomArgs a, uint32_t n,
+                                                              uint32_t ntiles) {
+    // M, S xyz, com xyz, Q xx yy zz xy xz yz of the tile's cells
+    __shared__ double mo[13][kMomCells];
+    __shared__ uint32_t first[kLevels], ofs[kLevels + 1], inside[kLevels];
+    const Cells &c = a.c;
+    const uint32_t lane = lane_id();
+    if (threadIdx.x < 64) {
+        const uint32_t l = min(lane, (uint32_t)kLevels - 1u);
+        const uint32_t s0 = starts_before(c, ntiles, l, blockIdx.x),
+                       s1 = starts_before(c, ntiles, l, blockIdx.x + 1u);
+        const uint32_t cnt = lane < kLevels ? s1 - s0 : 0u;
+        const uint32_t end = (blockIdx.x + 1u) * kTreeTile;
+        const uint32_t across = end < n ? levels_across(c, end) : 0u;
+        const uint32_t inc = wave_incl_scan(cnt, lane);
+        if (lane <= kLevels) ofs[lane] = inc - cnt;
+        if (lane < kLevels) {
+            first[lane] = c.ls[lane] + s0;
+            // the last cell to start is left out where it holds the tile's end
+            inside[lane] = cnt && lane < across ? cnt - 1u : cnt;
+        }
+    }
+    __syncthreads();
+    const uint32_t total = ofs[kLevels];
+    if (total > (uint32_t)kMomCells) {  // (tiny leaves, chains of coincident particles)
+        for (int l = kLevels - 1; l >= 0; --l) {
+            const uint32_t m = inside[l];
+            for (uint32_t q = threadIdx.x; q < m; q += kMomThreads)
+                cell_pass(a, first[l] + q, (uint32_t)l);
+            if (m) __syncthreads();  // the next level up reads these cells
+        }
+        return;
+    }
+    auto keep = [&](uint32_t q, const Mom &r, double c0, double c1, double c2) {
+        mo[0][q] = r.M;
+        mo[1][q] = r.s0; mo[2][q] = r.s1; mo[3][q] = r.s2;
+        mo[4][q] = c0; mo[5][q] = c1; mo[6][q] = c2;
+        mo[7][q] = r.q0; mo[8][q] = r.q1; mo[9][q] = r.q2;
+        mo[10][q] = r.q3; mo[11][q] = r.q4; mo[12][q] = r.q5;
+    };
+    // ---- this thread's cells: topology, and the moments of the leaves
+    constexpr int kOwn = (kMomCells + kMomThreads - 1) / kMomThreads;
+    uint32_t lev[kOwn], ci[kOwn], b0[kOwn], n0[kOwn], k0[kOwn], nch[kOwn];
+    uint64_t prefix[kOwn];
+#pragma unroll
+    for (int s = 0; s < kOwn; ++s) {
+        const uint32_t q = threadIdx.x + s * kMomThreads;
+        uint32_t l = 0;
+        lev[s] = kNone;  // no cell
+        if (q >= total) continue;
+        while (q >= ofs[l + 1u]) ++l;
+        if (q - ofs[l] >= inside[l]) continue;
+        lev[s] = l;
+        const uint32_t i = first[l] + (q - ofs[l]);
+        ci[s] = i;
+        const uint32_t kend = c.nchild[i];
+        b0[s] = c.begin[i];
+        n0[s] = c.count[i] - b0[s];
+        k0[s] = c.child0[i];
+        prefix[s] = c.prefix[i];
+        nch[s] = kend ? kend - k0[s] : 0u;
+    }
+#pragma unroll
+    for (int s = 0; s < kOwn; ++s) {
+        if (lev[s] == kNone || nch[s] != 0u) continue;
+        Mom r;
+        double c0, c1, c2;
+        leaf_sums(a, b0[s], n0[s], r, c0, c1, c2);
+        keep(threadIdx.x + s * kMomThreads, r, c0, c1, c2);
+    }
+    // ---- the parents, from the deepest level up
+    for (uint32_t l = kLevels - 1; l-- > 0u;) {
+        if (ofs[l + 1u] == ofs[l + 2u] || inside[l] == 0u) continue;  // no child starts here
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < kOwn; ++s) {
+            if (lev[s] != l || nch[s] == 0u) continue;
+            const uint32_t q0 = ofs[l + 1u] + (k0[s] - first[l + 1u]);
+            Mom r{0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+            double vm[8], v0[8], v1[8], v2[8];
+#pragma unroll
+            for (uint32_t k = 0; k < 8; ++k) {
+                const uint32_t j = q0 + (k < nch[s] ? k : 0u);
+                vm[k] = mo[0][j]; v0[k] = mo[1][j]; v1[k] = mo[2][j]; v2[k] = mo[3][j];
+            }
+#pragma unroll
+            for (uint32_t k = 0; k < 8; ++k) {
+                if (k < nch[s]) {
+                    r.M = r.M + vm[k];
+                    r.s0 = r.s0 + v0[k];
+                    r.s1 = r.s1 + v1[k];
+                    r.s2 = r.s2 + v2[k];
+                }
+            }
+            const double c0 = r.s0 / r.M, c1 = r.s1 / r.M, c2 = r.s2 / r.M;
+#pragma unroll 4
+            for (uint32_t k = 0; k < 8; ++k) {
+                const uint32_t j = q0 + (k < nch[s] ? k : 0u);
+                const double mk = mo[0][j];
+                const double d0 = mo[4][j] - c0, d1 = mo[5][j] - c1, d2 = mo[6][j] - c2;
+                const double t0 = mo[7][j] + (mk * d0) * d0, t1 = mo[8][j] + (mk * d1) * d1,
+                             t2 = mo[9][j] + (mk * d2) * d2, t3 = mo[10][j] + (mk * d0) * d1,
+                             t4 = mo[11][j] + (mk * d0) * d2, t5 = mo[12][j] + (mk * d1) * d2;
+                if (k < nch[s]) {
+                    r.q0 = r.q0 + t0;
+                    r.q1 = r.q1 + t1;
+                    r.q2 = r.q2 + t2;
+                    r.q3 = r.q3 + t3;
+                    r.q4 = r.q4 + t4;
+                    r.q5 = r.q5 + t5;
+                }
+            }
+            keep(threadIdx.x + s * kMomThreads, r, c0, c1, c2);
+        }
+    }
+    // ---- all of them written (each thread reads back its own)
+#pragma unroll
+    for (int s = 0; s < kOwn; ++s) {
+        if (lev[s] == kNone) continue;
+        const uint32_t q = threadIdx.x + s * kMomThreads;
+        const Mom r{mo[0][q], mo[1][q], mo[2][q], mo[3][q], mo[7][q],
+                    mo[8][q], mo[9][q], mo[10][q], mo[11][q], mo[12][q]};
+        cell_out(a, ci[s], lev[s], prefix[s], b0[s], n0[s], k0[s], nch[s], r, mo[4][q], mo[5][q],
+                 mo[6][q]);
     }
 }
 
-// One pass per level from the deepest (leaves from their particles, parents
-// from their children, each cell's walk records as soon as its moments are
-// known): the levels above grid_levels by one grid launch each, levels 21
-// down to grid_levels by k_moments_tail (level 21 by a grid launch too when
-// grid_levels is 21: no recent tree said the deep levels are sparse).
-void launch_moments(bh_ctx *ctx, hipStream_t st, int grid_levels) {
-    const State &s = ctx->st[ctx->cur];
+struct Across {
+    uint32_t i, b0, n0, k0, nch;  // i = kNone: none
+    uint32_t p0, p1;              // prefix
+};
+
+constexpr int kAcrossThreads = 1024;
+constexpr int kAcrossUnits = kAcrossThreads / 8;
+constexpr int kAcrossRow = kAcrossThreads + 2;  // (the eight lanes' rows in different banks)
+static_assert(kAcrossUnits >= kSpanTiles, "a span's tiles in one round");
+
+// A parent across an end, by eight lanes of a wave (have: these eight have
+// one): lane k reads child k, then each sum over the children runs in child
+// order in one lane, through the LDS rows ch.
+__device__ __forceinline__ void group_parent(const MomArgs &a, uint32_t lev, bool have,
+                                             const Across &o, double (*ch)[kAcrossRow]) {
+    const Cells &c = a.c;
+    const uint32_t t = threadIdx.x, k = t & 7u, b = t & ~7u;
+    const double2 *Q2 = reinterpret_cast<const double2 *>(c.Q);
+    const uint32_t nch = have ? o.nch : 0u;
+    double cm = 0.0, s0 = 0.0, s1 = 0.0, s2 = 0.0;
+    double2 qa = make_double2(0.0, 0.0), qb = qa, qc = qa;
+    if (k < nch) {
+        const size_t j = (size_t)o.k0 + k;
+        cm = c.M[j];
+        s0 = c.S[3 * j]; s1 = c.S[3 * j + 1]; s2 = c.S[3 * j + 2];
+        qa = Q2[3 * j]; qb = Q2[3 * j + 1]; qc = Q2[3 * j + 2];
+    }
+    ch[0][t] = cm; ch[1][t] = s0; ch[2][t] = s1; ch[3][t] = s2;
+    wave_sync();
+    if (k < 4u) {
+        double v = 0.0;
+        for (uint32_t j = 0; j < nch; ++j) v = v + ch[k][b + j];
+        ch[k][b] = v;
+    }
+    wave_sync();
+    Mom r;
+    r.M = ch[0][b]; r.s0 = ch[1][b]; r.s1 = ch[2][b]; r.s2 = ch[3][b];
+    const double c0 = r.s0 / r.M, c1 = r.s1 / r.M, c2 = r.s2 / r.M;
+    const double d0 = s0 / cm - c0, d1 = s1 / cm - c1, d2 = s2 / cm - c2;
+    ch[4][t] = qa.x + (cm * d0) * d0;
+    ch[5][t] = qa.y + (cm * d1) * d1;
+    ch[6][t] = qb.x + (cm * d2) * d2;
+    ch[7][t] = qb.y + (cm * d0) * d1;
+    ch[8][t] = qc.x + (cm * d0) * d2;
+    ch[9][t] = qc.y + (cm * d1) * d2;
+    wave_sync();
+    if (k < 6u) {
+        double v = 0.0;
+        for (uint32_t j = 0; j < nch; ++j) v = v + ch[4u + k][b + j];
+        ch[4u + k][b] = v;
+    }
+    wave_sync();
+    if (have && k == 0u) {
+        r.q0 = ch[4][b]; r.q1 = ch[5][b]; r.q2 = ch[6][b];
+        r.q3 = ch[7][b]; r.q4 = ch[8][b]; r.q5 = ch[9][b];
+        cell_out(a, o.i, lev, ((uint64_t)o.p1 << 32) | o.p0, o.b0, o.n0, o.k0, o.nch, r, c0, c1,
+                 c2);
+    }
+    wave_sync();
+}
+
+// The cells across the ends of consecutive units of `tiles` tiles (unit u
+// ends at particle (u + 1) tiles kTreeTile): those that end by `limit`, of the
+// units u0 .. u0 + units - 1.  Eight lanes per unit; first each lane looks up
+// the cells of its unit on every eighth level (and finishes a leaf, of which
+// there is at most one), then level by level from the deepest the eight sum
+// the unit's parent.
+__device__ __forceinline__ void across_pass(const MomArgs &a, uint32_t ntiles, uint32_t u0,
+                                            uint32_t units, uint32_t tiles, uint32_t limit) {
+    __shared__ double ch[10][kAcrossRow];
+    __shared__ uint32_t levels;  // bit l: some unit has a parent on level l
+    constexpr int kOwn = (kLevels + 7) / 8;
+    static_assert(kOwn == 3, "levels a lane looks up");
+    const Cells &c = a.c;
+    const uint32_t len = tiles * kTreeTile;
+    const uint32_t uu = threadIdx.x >> 3, k = threadIdx.x & 7u;
+    if (units <= (uint32_t)kAcrossUnits) {
+        if (threadIdx.x == 0) levels = 0u;
+        __syncthreads();
+        const uint32_t across = uu < units ? levels_across(c, (u0 + uu + 1u) * len) : 0u;
+        uint32_t leaf = kNone, leaf_level = 0;
+        // (an array per field, so that they stay in registers)
+        uint32_t wi[kOwn], wb[kOwn], wn[kOwn], wk[kOwn], wc[kOwn], wp0[kOwn], wp1[kOwn];
+#pragma unroll
+        for (int s = 0; s < kOwn; ++s) {
+            const uint32_t l = k + 8u * (uint32_t)s;
+            wi[s] = kNone;
+            wb[s] = wn[s] = wk[s] = wc[s] = wp0[s] = wp1[s] = 0u;
+            if (l >= across) continue;
+            const uint32_t s1 = starts_before(c, ntiles, l, (u0 + uu + 1u) * tiles);
+            if (s1 == starts_before(c, ntiles, l, (u0 + uu) * tiles)) continue;
+            const uint32_t i = c.ls[l] + s1 - 1u;
+            const uint32_t end = c.count[i];  // (still the end of its particles)
+            const uint32_t kend = c.nchild[i], k0 = c.child0[i], b0 = c.begin[i];
+            const uint64_t pre = c.prefix[i];
+            if (end > limit) continue;
+            if (kend == 0u) {
+                leaf = i;
+                leaf_level = l;
+                continue;
+            }
+            wi[s] = i;
+            wb[s] = b0; wn[s] = end - b0;
+            wk[s] = k0; wc[s] = kend - k0;
+            wp0[s] = (uint32_t)pre; wp1[s] = (uint32_t)(pre >> 32);
+            atomicOr(&levels, 1u << l);
+        }
+        if (leaf != kNone) cell_pass(a, leaf, leaf_level);
+        __syncthreads();
+        uint32_t todo = levels;
+        while (todo) {
+            const uint32_t l = 31u - (uint32_t)__clz((int)todo);
+            todo &= ~(1u << l);
+            const int src = (int)((lane_id() & ~7u) + (l & 7u));
+            auto pick = [&](uint32_t v0, uint32_t v1, uint32_t v2) {
+                return shfl(l < 8u ? v0 : (l < 16u ? v1 : v2), src);
+            };
+            Across o{pick(wi[0], wi[1], wi[2]), 0u, 0u, 0u, 0u, 0u, 0u};
+            if (ballot(o.i != kNone) != 0ull) {
+                o.b0 = pick(wb[0], wb[1], wb[2]); o.n0 = pick(wn[0], wn[1], wn[2]);
+                o.k0 = pick(wk[0], wk[1], wk[2]); o.nch = pick(wc[0], wc[1], wc[2]);
+                o.p0 = pick(wp0[0], wp0[1], wp0[2]); o.p1 = pick(wp1[0], wp1[1], wp1[2]);
+                group_parent(a, l, o.i != kNone, o, ch);
+            }
+            __syncthreads();  // the next level up reads these cells
+        }
+        return;
+    }
+    // more units than lanes (sets of more than 16 million particles): every
+    // level over all of them before the next
+    for (int l = kLevels - 1; l >= 0; --l) {
+        for (uint32_t u = threadIdx.x; u < units; u += (uint32_t)kAcrossThreads) {
+            if ((uint32_t)l >= levels_across(c, (u0 + u + 1u) * len)) continue;
+            const uint32_t s1 = starts_before(c, ntiles, (uint32_t)l, (u0 + u + 1u) * tiles);
+            if (s1 == starts_before(c, ntiles, (uint32_t)l, (u0 + u) * tiles)) continue;
+            const uint32_t i = c.ls[l] + s1 - 1u;
+            if (c.count[i] <= limit) cell_pass(a, i, (uint32_t)l);
+        }
+        __syncthreads();
+    }
+}
+
+// The cells across a tile's end that end inside its span of kSpanTiles tiles.
+__global__ __launch_bounds__(kAcrossThreads) void k_moments_span(MomArgs a, uint32_t ntiles) {
+    const uint32_t u0 = blockIdx.x * kSpanTiles;
+    const uint32_t ends = min((uint32_t)kSpanTiles, ntiles - 1u - u0);  // tile ends below n
+    across_pass(a, ntiles, u0, ends, 1u, (blockIdx.x + 1u) * (kSpanTiles * kTreeTile));
+}
+
+// The cells across a span's end, by one block.
+__global__ __launch_bounds__(kAcrossThreads) void k_moments_top(MomArgs a, uint32_t n,
+                                                                uint32_t ntiles,
+                                                                uint32_t nspans) {
+    across_pass(a, ntiles, 0u, nspans - 1u, kSpanTiles, n);
+}
+
+void launch_moments(bh_ctx *ctx, uint32_t n, hipStream_t st) {
     MomArgs a;
     a.c = ctx->cells;
-    a.x = s.x; a.y = s.y; a.z = s.z; a.m = s.m;
     a.xyzm = ctx->xyzm;
     a.box = ctx->box;
     a.curve = (int)ctx->p.curve;
-    const int L = grid_levels < 0 ? 0 : (grid_levels > kLevels - 1 ? kLevels - 1 : grid_levels);
-    if (L < kLevels - 1)
-        hipLaunchKernelGGL(k_moments_tail, dim3(1), dim3(1024), 0, st, a, kLevels - 1, L);
-    else
-        hipLaunchKernelGGL(k_moments_level, dim3(kGrid), dim3(256), 0, st, a, kLevels - 1);
-    for (int l = L - 1; l >= 0; --l)
-        hipLaunchKernelGGL(k_moments_level, dim3(kGrid), dim3(256), 0, st, a, l);
+    const uint32_t nt = cdiv(n, kTreeTile), ns = cdiv(nt, kSpanTiles);
+    hipLaunchKernelGGL(k_moments_tile, dim3(nt), dim3(kMomThreads), 0, st, a, n, nt);
+    if (nt > 1) hipLaunchKernelGGL(k_moments_span, dim3(ns), dim3(kAcrossThreads), 0, st, a, nt);
+    if (ns > 1) hipLaunchKernelGGL(k_moments_top, dim3(1), dim3(kAcrossThreads), 0, st, a, n, nt, ns);
 }
 
 // com = S / M of every cell (FP64), for export

@@ -55,15 +55,6 @@ struct TreeView {
     uint32_t *status;
 };
 
-// Order the LDS accesses of one wave: the DS unit runs a wave's accesses in
-// program order, so only the compiler has to keep them in it (no barrier, no
-// wait; a workgroup may hold several waves that walk different groups).
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 struct GroupBox {
     float cx, cy, cz, hx, hy, hz;
 };

@@ -67,6 +67,15 @@ __device__ __forceinline__ float wave_max(float v) {
     return v;
 }
 
+// Order the LDS accesses of one wave: the DS unit runs a wave's accesses in
+// program order, so only the compiler has to keep them in it (no barrier, no
+// wait; a workgroup may hold several waves that walk different groups).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // uniform value from lane 0 held in a scalar register
 __device__ __forceinline__ uint32_t uniform(uint32_t v) {
     return __builtin_amdgcn_readfirstlane(v);

@@ -33,3 +33,47 @@ def test_build_at_tile_edges(oracle, n, kind, nleaf, ncrit, curve):
     for arr in ("mom_M", "mom_com", "mom_Q"):
         assert np.array_equal(t.export(arr), ot.mom[arr[4:]])
     t.close()
+
+
+def test_moments_of_more_spans_than_one_block_round():
+    """More than 128 spans of 131072 particles (the top of the moment pass in
+    rounds): every parent's count and moments follow from its children's, in
+    child order, bit for bit, and the leaves' masses from their particles."""
+    import torch
+    from gpu_util import device
+    from paper_1412_0659_amd import Tree
+    n = 16_900_000
+    g = torch.Generator(device=device())
+    g.manual_seed(5)
+    pos = torch.randn(n, 3, generator=g, device="cuda")
+    mass = torch.rand(n, generator=g, device="cuda") + 0.5
+    t = Tree(n)
+    t.build(pos, mass)
+    t.sync()
+    nch = t.export("cell_nchild").astype(np.int64)
+    cnt = t.export("cell_count").astype(np.int64)
+    beg = t.export("cell_begin").astype(np.int64)
+    ch0 = t.export("cell_child0").astype(np.int64)
+    M, com, Q = t.export("mom_M"), t.export("mom_com"), t.export("mom_Q")
+    perm = t.export("perm")
+    t.close()
+    assert cnt[0] == n and beg[0] == 0
+    par = np.nonzero(nch)[0]
+    sums = {"cnt": np.zeros(len(par), np.int64), "M": np.zeros(len(par)),
+            "Q": np.zeros((len(par), 6))}
+    pairs = ((0, 0), (1, 1), (2, 2), (0, 1), (0, 2), (1, 2))
+    for k in range(8):
+        has = nch[par] > k
+        c = ch0[par[has]] + k
+        sums["cnt"][has] += cnt[c]
+        sums["M"][has] += M[c]
+        d = com[c] - com[par[has]]
+        for q, (i, j) in enumerate(pairs):
+            sums["Q"][has, q] += Q[c, q] + (M[c] * d[:, i]) * d[:, j]
+    assert np.array_equal(sums["cnt"], cnt[par])
+    assert np.array_equal(sums["M"], M[par])
+    assert np.array_equal(sums["Q"], Q[par])
+    leaf = np.nonzero(nch == 0)[0]
+    ms = np.concatenate([[0.0], np.cumsum(mass.cpu().numpy().astype(np.float64)[perm])])
+    ref = ms[beg[leaf] + cnt[leaf]] - ms[beg[leaf]]
+    assert np.allclose(M[leaf], ref, rtol=1e-7)  # (differences of 1e7-long running sums)
