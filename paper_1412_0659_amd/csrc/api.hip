@@ -88,8 +88,7 @@ int check_status(bh_ctx *c) {
 void rebuild(bh_ctx *c, uint32_t n, hipStream_t s) {
     record_event(c, 0, s);
     launch_bbox(c, c->st[c->cur], n, s);
-    launch_keys(c, c->st[c->cur], n, s);
-    launch_radix_sort(c, n, s);
+    launch_sort(c, c->st[c->cur], n, s);
     launch_gather(c, n, s);
     record_event(c, 1, s);
     launch_build(c, n, s);

@@ -212,8 +212,8 @@ void launch_direct(bh_ctx *c, const int64_t *tgt, uint32_t nt, float eps, double
 
 // keys_sort.hip
 void launch_bbox(bh_ctx *c, const State &s, uint32_t n, hipStream_t st);
-void launch_keys(bh_ctx *c, const State &s, uint32_t n, hipStream_t st);
-void launch_radix_sort(bh_ctx *c, uint32_t n, hipStream_t st);  // result in key[0], idx[0]
+// keys of s and their sort: result in key[0], idx[0]
+void launch_sort(bh_ctx *c, const State &s, uint32_t n, hipStream_t st);
 void launch_gather(bh_ctx *c, uint32_t n, hipStream_t st);      // st[cur] -> st[cur ^ 1]
 int64_t sort_counts_len(int64_t nmax);
 int64_t scan_part_len(int64_t n);

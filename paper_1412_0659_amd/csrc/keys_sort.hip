@@ -116,8 +116,20 @@ __device__ __forceinline__ uint32_t quantise(float v, float lo, float scale) {
     return q > 0x1fffffu ? 0x1fffffu : q;
 }
 
-// 63-bit keys: the quantised coordinates interleaved (Morton), or their
-// Peano-Hilbert transposed index interleaved the same way
+// 63-bit key of a position: the quantised coordinates interleaved (Morton), or
+// their Peano-Hilbert transposed index interleaved the same way
+struct KeyBox {
+    float lo0, lo1, lo2, scale;
+};
+
+template <bool kPH>
+__device__ __forceinline__ uint64_t key_of(float x, float y, float z, const KeyBox &b) {
+    uint32_t X[3] = {quantise(x, b.lo0, b.scale), quantise(y, b.lo1, b.scale),
+                     quantise(z, b.lo2, b.scale)};
+    if (kPH) ph_encode(X, kKeyBits);
+    return (spread3(X[0]) << 2) | (spread3(X[1]) << 1) | spread3(X[2]);
+}
+
 template <bool kPH>
 __global__ __launch_bounds__(256) void k_keys(const float *__restrict__ x,
                                               const float *__restrict__ y,
@@ -127,15 +139,11 @@ __global__ __launch_bounds__(256) void k_keys(const float *__restrict__ x,
                                               uint32_t *__restrict__ idx) {
     uint32_t i = blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
-    float lo0 = box[0], lo1 = box[1], lo2 = box[2], scale = box[4];
-    uint32_t X[3] = {quantise(x[i], lo0, scale), quantise(y[i], lo1, scale),
-                     quantise(z[i], lo2, scale)};
-    if (kPH) ph_encode(X, kKeyBits);
-    key[i] = (spread3(X[0]) << 2) | (spread3(X[1]) << 1) | spread3(X[2]);
+    key[i] = key_of<kPH>(x[i], y[i], z[i], KeyBox{box[0], box[1], box[2], box[4]});
     idx[i] = i;
 }
 
-void launch_keys(bh_ctx *c, const State &s, uint32_t n, hipStream_t st) {
+static void launch_keys(bh_ctx *c, const State &s, uint32_t n, hipStream_t st) {
     if (c->p.curve == 1)
         hipLaunchKernelGGL(k_keys<true>, dim3(cdiv(n, 256)), dim3(256), 0, st, s.x, s.y, s.z, n,
                            (const float *)c->box, c->sort.key[0], c->sort.idx[0]);
@@ -144,8 +152,231 @@ void launch_keys(bh_ctx *c, const State &s, uint32_t n, hipStream_t st) {
                            n, (const float *)c->box, c->sort.key[0], c->sort.idx[0]);
 }
 
+// ---- block sort and merges ------------------------------------------------
+//
+// Sets of up to kMergeMax particles.  k_sort_block computes the keys of a tile
+// of 1024 kRounds particles and sorts them in LDS, all eight digits in one
+// launch (stable, least significant first: the order of equal keys is input
+// order); k_sort_merge then merges pairs of sorted runs, ties from the earlier
+// run first.  A block of a merge takes kMergeTile consecutive outputs, finds
+// where they begin and end in both runs by a 64-way search on the diagonal
+// (one wave per end), and merges them in LDS.
+//
+// Bound: latency on small sets (one launch up to 8192 particles, one more per
+// doubling, where the radix passes over memory below take five launches per
+// digit), 24 B per particle and merge on larger ones.  Measured, bounding box,
+// keys, sort and gather of a set in random order, in us, these against the
+// radix passes: n = 1000: 25 / 135; 4096: 45 / 148; 16384: 79 / 186; 65536: 97
+// / 213; 262144: 135 / 243; 1M: 290 / 374; 2M: 499 / 567; 4M: 1009 / 1011; 8M:
+// 2061 / 1936.
+constexpr uint32_t kMergeMax = 3u << 20;
+
+constexpr int kSortThreads = 1024;
+constexpr int kSortWaves = kSortThreads / 64;
+
+template <bool kPH, int kRounds>
+__global__ __launch_bounds__(kSortThreads) void k_sort_block(
+    const float *__restrict__ x, const float *__restrict__ y, const float *__restrict__ z,
+    uint32_t n, const float *__restrict__ box, uint64_t *__restrict__ key_out,
+    uint32_t *__restrict__ idx_out) {
+    constexpr uint32_t kTile = kSortThreads * kRounds;
+    __shared__ uint64_t skey[kTile];
+    __shared__ uint16_t sidx[kTile];
+    __shared__ uint32_t cnt[kSortWaves][256];
+    __shared__ uint32_t wsum[4];
+    const uint32_t w = threadIdx.x >> 6, lane = lane_id();
+    const uint32_t t0 = blockIdx.x * kTile;
+    const uint32_t p0 = w * 64u * kRounds + lane;  // this wave's positions: p0 + 64 r
+    const KeyBox kb{box[0], box[1], box[2], box[4]};
+    const uint64_t lt = mask_lt(lane);
+    uint64_t kk[kRounds];
+    uint32_t vv[kRounds];
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        const uint32_t i = t0 + p0 + 64u * r;
+        // past the end: a key above all others, so it stays behind them
+        kk[r] = i < n ? key_of<kPH>(x[i], y[i], z[i], kb) : ~0ull;
+        vv[r] = p0 + 64u * r;
+    }
+    for (uint32_t shift = 0; shift < 64u; shift += 8u) {
+        for (uint32_t k = threadIdx.x; k < kSortWaves * 256u; k += kSortThreads) (&cnt[0][0])[k] = 0u;
+        __syncthreads();
+        uint32_t rk[kRounds];
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) {
+            const uint32_t d = (uint32_t)(kk[r] >> shift) & 255u;
+            uint64_t peers = ~0ull;  // lanes of this round holding the same digit
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                const bool bit = (d >> b) & 1u;
+                const uint64_t m = ballot(bit);
+                peers &= bit ? m : ~m;
+            }
+            const uint32_t before = (uint32_t)__popcll(peers & lt);
+            const uint32_t run = cnt[w][d];
+            wave_sync();
+            if (before == 0) cnt[w][d] = run + (uint32_t)__popcll(peers);
+            wave_sync();
+            rk[r] = run + before;
+        }
+        __syncthreads();
+        uint32_t tot = 0, inc = 0;
+        if (threadIdx.x < 256) {  // waves 0..3: one digit per thread
+#pragma unroll
+            for (int k = 0; k < kSortWaves; ++k) tot += cnt[k][threadIdx.x];
+            inc = wave_incl_scan(tot, lane);
+            if (lane == 63) wsum[w] = inc;
+        }
+        __syncthreads();
+        if (threadIdx.x < 256) {
+            uint32_t run = inc - tot;
+            for (uint32_t k = 0; k < w; ++k) run += wsum[k];
+#pragma unroll
+            for (int k = 0; k < kSortWaves; ++k) {
+                const uint32_t c = cnt[k][threadIdx.x];
+                cnt[k][threadIdx.x] = run;
+                run += c;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) {
+            const uint32_t lp = cnt[w][(uint32_t)(kk[r] >> shift) & 255u] + rk[r];
+            skey[lp] = kk[r];
+            sidx[lp] = (uint16_t)vv[r];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) {
+            kk[r] = skey[p0 + 64u * r];
+            vv[r] = sidx[p0 + 64u * r];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        const uint32_t i = t0 + p0 + 64u * r;
+        if (i < n) {
+            key_out[i] = kk[r];
+            idx_out[i] = t0 + vv[r];
+        }
+    }
+}
+
+constexpr int kMergeThreads = 256;
+constexpr int kMergeItems = 8;
+constexpr int kMergeTile = kMergeThreads * kMergeItems;
+
+// Of the first d outputs of the merge of A (na keys) and B (nb keys), ties
+// from A first: how many come from A.  One wave, 64 probes a round.
+__device__ __forceinline__ uint32_t merge_split(const uint64_t *__restrict__ A, uint32_t na,
+                                                const uint64_t *__restrict__ B, uint32_t nb,
+                                                uint32_t d, uint32_t lane) {
+    uint32_t lo = d > nb ? d - nb : 0u, hi = d < na ? d : na;  // the answer is in [lo, hi]
+    while (lo < hi) {
+        const uint32_t len = hi - lo, step = (len + 63u) >> 6;
+        const uint32_t i = lo + lane * step;  // probe: does output d take A[i]?
+        const bool take = i < hi && A[i] <= B[d - 1u - i];
+        const uint32_t k = (uint32_t)__popcll(ballot(take));  // (true for the first k probes)
+        if (k == 0u) return lo;
+        lo = lo + (k - 1u) * step + 1u;
+        hi = k < 64u && lo - 1u + step < hi ? lo - 1u + step : hi;
+    }
+    return lo;
+}
+
+// Merge runs of `run` keys in pairs.
+__global__ __launch_bounds__(kMergeThreads) void k_sort_merge(
+    const uint64_t *__restrict__ key, const uint32_t *__restrict__ idx, uint32_t n, uint32_t run,
+    uint64_t *__restrict__ key_out, uint32_t *__restrict__ idx_out) {
+    __shared__ uint64_t sk[kMergeTile];
+    __shared__ uint32_t si[kMergeTile];
+    __shared__ uint32_t split[2];
+    const uint32_t o0 = blockIdx.x * kMergeTile;
+    const uint32_t a0 = o0 / (2u * run) * (2u * run);  // (run is a multiple of the tile)
+    const uint32_t na = min(run, n - a0), nb = min(run, n - a0 - na);
+    const uint32_t d0 = o0 - a0, d1 = min(d0 + (uint32_t)kMergeTile, na + nb);
+    const uint64_t *A = key + a0, *B = A + na;
+    const uint32_t lane = lane_id(), w = threadIdx.x >> 6;
+    if (w < 2) {
+        const uint32_t s = merge_split(A, na, B, nb, w ? d1 : d0, lane);
+        if (lane == 0) split[w] = s;
+    }
+    __syncthreads();
+    const uint32_t i0 = split[0], ca = split[1] - i0, j0 = d0 - i0, m = d1 - d0, cb = m - ca;
+    for (uint32_t t = threadIdx.x; t < m; t += kMergeThreads) {
+        const uint32_t s = a0 + (t < ca ? i0 + t : na + j0 + (t - ca));
+        sk[t] = key[s];
+        si[t] = idx[s];
+    }
+    __syncthreads();
+    // this thread's outputs [d, d + kMergeItems) of the m: A part at sk[0, ca), B part behind it
+    const uint32_t d = min(threadIdx.x * (uint32_t)kMergeItems, m);
+    uint32_t lo = d > cb ? d - cb : 0u, hi = d < ca ? d : ca;
+    while (lo < hi) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (sk[mid] <= sk[ca + d - 1u - mid]) lo = mid + 1u;
+        else hi = mid;
+    }
+    uint32_t i = lo, j = ca + d - lo;
+    uint64_t ok[kMergeItems];
+    uint32_t oi[kMergeItems];
+#pragma unroll
+    for (int t = 0; t < kMergeItems; ++t) {
+        const bool va = i < ca, vb = j < m;
+        const uint64_t x = va ? sk[i] : ~0ull, y = vb ? sk[j] : ~0ull;
+        const bool ta = va && (!vb || x <= y);
+        const uint32_t s = ta ? i : (vb ? j : 0u);
+        ok[t] = ta ? x : y;
+        oi[t] = si[s];
+        if (ta) ++i;
+        else ++j;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < kMergeItems; ++t) {
+        const uint32_t o = threadIdx.x * kMergeItems + t;
+        if (o < m) {
+            sk[o] = ok[t];
+            si[o] = oi[t];
+        }
+    }
+    __syncthreads();
+    for (uint32_t t = threadIdx.x; t < m; t += kMergeThreads) {
+        key_out[o0 + t] = sk[t];
+        idx_out[o0 + t] = si[t];
+    }
+}
+
+template <int kRounds>
+static void launch_sort_block(bh_ctx *c, const State &s, uint32_t n, int dst, hipStream_t st) {
+    const dim3 grid(cdiv(n, (uint64_t)kSortThreads * kRounds));
+    if (c->p.curve == 1)
+        hipLaunchKernelGGL((k_sort_block<true, kRounds>), grid, dim3(kSortThreads), 0, st, s.x,
+                           s.y, s.z, n, (const float *)c->box, c->sort.key[dst], c->sort.idx[dst]);
+    else
+        hipLaunchKernelGGL((k_sort_block<false, kRounds>), grid, dim3(kSortThreads), 0, st, s.x,
+                           s.y, s.z, n, (const float *)c->box, c->sort.key[dst], c->sort.idx[dst]);
+}
+
+// Sorted keys and indices into key[0], idx[0].
+static void launch_merge_sort(bh_ctx *c, const State &s, uint32_t n, hipStream_t st) {
+    constexpr uint32_t kTile = kSortThreads * 8;
+    int passes = 0;
+    while (((uint64_t)kTile << passes) < n) ++passes;
+    int src = passes & 1;
+    if (n <= 1024u) launch_sort_block<1>(c, s, n, src, st);
+    else if (n <= 2048u) launch_sort_block<2>(c, s, n, src, st);
+    else if (n <= 4096u) launch_sort_block<4>(c, s, n, src, st);
+    else launch_sort_block<8>(c, s, n, src, st);
+    for (int p = 0; p < passes; ++p, src ^= 1)
+        hipLaunchKernelGGL(k_sort_merge, dim3(cdiv(n, kMergeTile)), dim3(kMergeThreads), 0, st,
+                           (const uint64_t *)c->sort.key[src], (const uint32_t *)c->sort.idx[src],
+                           n, kTile << p, c->sort.key[src ^ 1], c->sort.idx[src ^ 1]);
+}
+
 // ---- LSD radix sort, 8 bits per pass -------------------------------------
 //
+// Sets of more than kMergeMax particles.
 // A tile is 8192 keys handled by 1024 threads (16 waves x 8 rounds x 64
 // lanes); wave w owns the contiguous keys [512 w, 512 w + 512) of the tile,
 // in rounds of 64 consecutive keys, so (wave, round, lane) order is input
@@ -155,8 +386,6 @@ void launch_keys(bh_ctx *c, const State &s, uint32_t n, hipStream_t st) {
 // mostly whole cache lines (the tile and its reorder buffer, 112 KB of LDS,
 // fit one workgroup of gfx950).
 
-constexpr int kSortThreads = 1024;
-constexpr int kSortWaves = kSortThreads / 64;
 constexpr int kSortRounds = 8;
 constexpr int kSortTile = kSortThreads * kSortRounds;
 
@@ -271,7 +500,9 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(
     }
 }
 
-void launch_radix_sort(bh_ctx *c, uint32_t n, hipStream_t st) {
+void launch_sort(bh_ctx *c, const State &s, uint32_t n, hipStream_t st) {
+    if (n <= kMergeMax) return launch_merge_sort(c, s, n, st);
+    launch_keys(c, s, n, st);
     uint32_t ntiles = cdiv(n, kSortTile);
     uint32_t len = 256u * ntiles;
     int src = 0;
