@@ -85,11 +85,11 @@ int check_status(bh_ctx *c) {
     return fail(c, BH_ECAPACITY, "cell or stack capacity exceeded");
 }
 
-void rebuild(bh_ctx *c, uint32_t n, hipStream_t s) {
+// Sort and tree of the n particles of src; the sorted state becomes c's.
+void rebuild(bh_ctx *c, const Source &src, uint32_t n, hipStream_t s) {
     record_event(c, 0, s);
-    launch_bbox(c, c->st[c->cur], n, s);
-    launch_sort(c, c->st[c->cur], n, s);
-    launch_gather(c, n, s);
+    launch_sort(c, src, n, s);
+    launch_gather(c, src, n, s);
     record_event(c, 1, s);
     launch_build(c, n, s);
     record_event(c, 2, s);
@@ -100,6 +100,47 @@ void rebuild(bh_ctx *c, uint32_t n, hipStream_t s) {
     c->counts_valid = false;
     c->bnd.valid = false;
     c->let.valid = false;
+}
+
+// The caller's arrays ([n][3] positions and velocities; vel null: zero).
+Source caller_source(const float *pos, const float *vel, const float *mass) {
+    Source r;
+    r.x = pos; r.y = pos + 1; r.z = pos + 2;
+    r.ps = 3;
+    if (vel) {
+        r.vx = vel; r.vy = vel + 1; r.vz = vel + 2;
+        r.vs = 3;
+    }
+    r.m = mass;
+    r.check = true;
+    return r;
+}
+
+// Whether a kernel of c can read or write a snapshot at p: memory of c's
+// device, aligned for its widest field (else it is copied field by field).
+bool in_place(const bh_ctx *c, const void *p) {
+    if (reinterpret_cast<uintptr_t>(p) % sizeof(double)) return false;
+    hipPointerAttribute_t at{};
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return at.type == hipMemoryTypeDevice && at.device == c->device;
+}
+
+// Copy a snapshot of n particles to (out) or from st, field by field.
+hipError_t copy_snapshot(const State &st, size_t n, char *p, bool out, hipStream_t s) {
+    void *const field[11] = {st.x, st.y, st.z, st.m, st.vx, st.vy, st.vz, st.cid,
+                             st.x64, st.y64, st.z64};
+    for (int k = 0; k < 11; ++k) {
+        if (!field[k]) continue;  // (no FP64 master)
+        const size_t bytes = n * (k < 8 ? 4 : 8);
+        const hipError_t e = out ? hipMemcpyAsync(p, field[k], bytes, hipMemcpyDeviceToDevice, s)
+                                 : hipMemcpyAsync(field[k], p, bytes, hipMemcpyDeviceToDevice, s);
+        if (e != hipSuccess) return e;
+        p += bytes;
+    }
+    return hipSuccess;
 }
 
 void force(bh_ctx *c, float theta, float eps, hipStream_t s) {
@@ -222,7 +263,7 @@ void weight_cuts(std::vector<std::pair<uint64_t, int64_t>> smp, int32_t pieces,
 namespace {
 
 constexpr int64_t kStaticMaxN = BH_STATIC_MAX_N;
-constexpr int kStaticWalkGrid = 1024;          // persistent walk waves (stack spill per wave)
+constexpr int kStaticWalkGrid = 2048;          // persistent walk waves (stack spill per wave)
 constexpr size_t kStaticBytes = size_t(64) << 20;
 constexpr int kMaxDevices = 64;
 
@@ -250,11 +291,10 @@ size_t static_layout(bh_ctx *c, unsigned char *base) {
         off += sizeof(T) * std::max<size_t>(count, 1);
     };
     const size_t n = (size_t)c->nmax, nc = (size_t)c->cap_cells;
+    c->st[0] = State{};
+    c->st[1] = State{};  // no state is kept beside xyzm, only the caller indices
+    take(&c->st[1].cid, n);
     for (int k = 0; k < 2; ++k) {
-        State &st = c->st[k];
-        take(&st.x, n); take(&st.y, n); take(&st.z, n); take(&st.m, n);
-        take(&st.vx, n); take(&st.vy, n); take(&st.vz, n); take(&st.cid, n);
-        st.x64 = st.y64 = st.z64 = nullptr;
         take(&c->sort.key[k], n);
         take(&c->sort.idx[k], n);
     }
@@ -438,9 +478,7 @@ int bh_set_state(bh_ctx *c, const float *pos, const float *vel, const float *mas
     int rc = check_n(c, n);
     if (rc) return rc;
     c->n = n;
-    c->cur = 0;
-    launch_ingest(c, pos, vel, mass, (uint32_t)n, s);
-    rebuild(c, (uint32_t)n, s);
+    rebuild(c, caller_source(pos, vel, mass), (uint32_t)n, s);
     c->ev_rec[6] = c->ev_rec[7] = false;
     BH_HIP(c, hipGetLastError());
     return BH_OK;
@@ -467,7 +505,7 @@ int leapfrog_step(bh_ctx *c, float dt, float theta, float eps, hipStream_t s) {
     record_event(c, 6, s);
     if (!c->have_acc || theta != c->acc_theta || eps != c->acc_eps) force(c, theta, eps, s);
     launch_kick_drift(c, 0.5f * dt, dt, n, s);
-    rebuild(c, n, s);
+    rebuild(c, source_of(c->st[c->cur]), n, s);
     force(c, theta, eps, s);
     launch_kick(c, 0.5f * dt, n, s);
     record_event(c, 7, s);
@@ -744,23 +782,14 @@ int bh_save_state(bh_ctx *c, void *dst, hipStream_t s) {
     if (!c) return BH_EINVAL;
     if (!dst) return fail(c, BH_EINVAL, "null destination");
     if (!c->built) return fail(c, BH_ESTATE, "no state");
-    const size_t n = (size_t)c->n;
     const State &st = c->st[c->cur];
-    char *p = static_cast<char *>(dst);
-    float *const fa[7] = {st.x, st.y, st.z, st.m, st.vx, st.vy, st.vz};
-    for (float *f : fa) {
-        BH_HIP(c, hipMemcpyAsync(p, f, n * sizeof(float), hipMemcpyDeviceToDevice, s));
-        p += n * sizeof(float);
+    const size_t n = (size_t)c->n;
+    if (in_place(c, dst)) {
+        launch_save(st, (uint32_t)n, static_cast<char *>(dst), s);
+        BH_HIP(c, hipGetLastError());
+        return BH_OK;
     }
-    BH_HIP(c, hipMemcpyAsync(p, st.cid, n * sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
-    p += n * sizeof(uint32_t);
-    if (c->p.pos_fp64) {
-        double *const da[3] = {st.x64, st.y64, st.z64};
-        for (double *d : da) {
-            BH_HIP(c, hipMemcpyAsync(p, d, n * sizeof(double), hipMemcpyDeviceToDevice, s));
-            p += n * sizeof(double);
-        }
-    }
+    BH_HIP(c, copy_snapshot(st, n, static_cast<char *>(dst), true, s));
     return BH_OK;
 }
 
@@ -771,23 +800,21 @@ int bh_load_state(bh_ctx *c, const void *src, int64_t n64, hipStream_t s) {
     if (rc) return rc;
     const size_t n = (size_t)n64;
     c->n = n64;
-    State &st = c->st[c->cur];
-    const char *p = static_cast<const char *>(src);
-    float *const fa[7] = {st.x, st.y, st.z, st.m, st.vx, st.vy, st.vz};
-    for (float *f : fa) {
-        BH_HIP(c, hipMemcpyAsync(f, p, n * sizeof(float), hipMemcpyDeviceToDevice, s));
-        p += n * sizeof(float);
-    }
-    BH_HIP(c, hipMemcpyAsync(st.cid, p, n * sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
-    p += n * sizeof(uint32_t);
-    if (c->p.pos_fp64) {
-        double *const da[3] = {st.x64, st.y64, st.z64};
-        for (double *d : da) {
-            BH_HIP(c, hipMemcpyAsync(d, p, n * sizeof(double), hipMemcpyDeviceToDevice, s));
-            p += n * sizeof(double);
+    Source r = source_of(c->st[c->cur]);
+    if (in_place(c, src)) {
+        const float *f = static_cast<const float *>(src);
+        r.x = f; r.y = f + n; r.z = f + 2 * n; r.m = f + 3 * n;
+        r.vx = f + 4 * n; r.vy = f + 5 * n; r.vz = f + 6 * n;
+        r.cid = reinterpret_cast<const uint32_t *>(f + 7 * n);
+        if (c->p.pos_fp64) {
+            const double *d = reinterpret_cast<const double *>(f + 8 * n);
+            r.x64 = d; r.y64 = d + n; r.z64 = d + 2 * n;
         }
+    } else {
+        BH_HIP(c, copy_snapshot(c->st[c->cur], n, static_cast<char *>(const_cast<void *>(src)),
+                                false, s));
     }
-    rebuild(c, (uint32_t)n, s);
+    rebuild(c, r, (uint32_t)n, s);
     c->ev_rec[6] = c->ev_rec[7] = false;
     BH_HIP(c, hipGetLastError());
     return BH_OK;
@@ -1203,8 +1230,7 @@ int tree_force_static(const float *pos, const float *mass, int64_t n, float thet
     c.cur = 0;
     // the array keeps the previous call's contents: clear the status words
     launch_fill_u32(c.status, 0u, 4, s);
-    launch_ingest(&c, pos, nullptr, mass, (uint32_t)n, s);
-    rebuild(&c, (uint32_t)n, s);
+    rebuild(&c, caller_source(pos, nullptr, mass), (uint32_t)n, s);
     force(&c, theta, eps, s);
     if (acc || pot) launch_unsort(&c, acc, pot, (uint32_t)n, s);
     if (status) {

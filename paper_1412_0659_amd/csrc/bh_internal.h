@@ -48,6 +48,26 @@ struct State {
     double *x64, *y64, *z64;  // FP64 master positions (pos_fp64 contexts), else null
 };
 
+// Particles to be sorted, read in place: the context's own state, the caller's
+// arrays (positions and velocities [n][3]) or a snapshot.
+struct Source {
+    const float *x = nullptr, *y = nullptr, *z = nullptr;     // every ps-th value
+    const float *vx = nullptr, *vy = nullptr, *vz = nullptr;  // every vs-th; null: zero
+    const float *m = nullptr;
+    uint32_t ps = 1, vs = 1;
+    const uint32_t *cid = nullptr;  // null: the index
+    const double *x64 = nullptr, *y64 = nullptr, *z64 = nullptr;  // null: the FP32 positions
+    bool check = false;  // latch bad masses and velocities (the caller's data)
+};
+inline Source source_of(const State &s) {
+    Source r;
+    r.x = s.x; r.y = s.y; r.z = s.z; r.m = s.m;
+    r.vx = s.vx; r.vy = s.vy; r.vz = s.vz;
+    r.cid = s.cid;
+    r.x64 = s.x64; r.y64 = s.y64; r.z64 = s.z64;
+    return r;
+}
+
 // Octree cells, breadth-first order (level, then key).
 struct Cells {
     uint64_t *prefix;  // key >> 3 (21 - level)
@@ -211,10 +231,9 @@ void launch_direct(bh_ctx *c, const int64_t *tgt, uint32_t nt, float eps, double
                    double *pot, hipStream_t st);
 
 // keys_sort.hip
-void launch_bbox(bh_ctx *c, const State &s, uint32_t n, hipStream_t st);
-// keys of s and their sort: result in key[0], idx[0]
-void launch_sort(bh_ctx *c, const State &s, uint32_t n, hipStream_t st);
-void launch_gather(bh_ctx *c, uint32_t n, hipStream_t st);      // st[cur] -> st[cur ^ 1]
+// bounding box and keys of s and their sort: result in key[0], idx[0], box
+void launch_sort(bh_ctx *c, const Source &s, uint32_t n, hipStream_t st);
+void launch_gather(bh_ctx *c, const Source &s, uint32_t n, hipStream_t st);  // s -> st[cur ^ 1]
 int64_t sort_counts_len(int64_t nmax);
 int64_t scan_part_len(int64_t n);
 
@@ -282,8 +301,7 @@ inline int64_t split_rows(int64_t n_max) {
 }
 
 // integrate.hip
-void launch_ingest(bh_ctx *c, const float *pos, const float *vel, const float *mass, uint32_t n,
-                   hipStream_t st);
+void launch_save(const State &s, uint32_t n, char *dst, hipStream_t st);
 void launch_kick(bh_ctx *c, float h, uint32_t n, hipStream_t st);
 void launch_kick_drift(bh_ctx *c, float h, float dt, uint32_t n, hipStream_t st);
 void launch_unsort(bh_ctx *c, float *acc, float *pot, uint32_t n, hipStream_t st,

@@ -20,43 +20,31 @@ void launch_fill_u32(uint32_t *p, uint32_t v, uint64_t n, hipStream_t st) {
     hipLaunchKernelGGL(k_fill_u32, dim3(nb), dim3(256), 0, st, p, v, n);
 }
 
-// caller [n][3] positions / velocities and [n] masses -> state (caller order)
-__global__ __launch_bounds__(256) void k_ingest(const float *__restrict__ pos,
-                                                const float *__restrict__ vel,
-                                                const float *__restrict__ mass, uint32_t n,
-                                                State s, uint32_t *status) {
-    uint32_t i = blockIdx.x * 256 + threadIdx.x;
+// The state as held -> a snapshot: x y z m vx vy vz cid, then the FP64
+// positions if kept, [n] each.
+__global__ __launch_bounds__(256) void k_save(State s, uint32_t n, char *__restrict__ dst) {
+    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
-    const float px = pos[3 * (size_t)i], py = pos[3 * (size_t)i + 1], pz = pos[3 * (size_t)i + 2];
-    s.x[i] = px;
-    s.y[i] = py;
-    s.z[i] = pz;
+    float *f = reinterpret_cast<float *>(dst);
+    const size_t N = n;
+    f[i] = s.x[i];
+    f[N + i] = s.y[i];
+    f[2 * N + i] = s.z[i];
+    f[3 * N + i] = s.m[i];
+    f[4 * N + i] = s.vx[i];
+    f[5 * N + i] = s.vy[i];
+    f[6 * N + i] = s.vz[i];
+    reinterpret_cast<uint32_t *>(dst)[7 * N + i] = s.cid[i];
     if (s.x64) {
-        s.x64[i] = px;
-        s.y64[i] = py;
-        s.z64[i] = pz;
+        double *d = reinterpret_cast<double *>(dst + 32 * N);
+        d[i] = s.x64[i];
+        d[N + i] = s.y64[i];
+        d[2 * N + i] = s.z64[i];
     }
-    float mi = mass[i];
-    s.m[i] = mi;
-    if (!(mi > 0.f) || !isfinite(mi)) atomicOr(status, kStMass);
-    if (vel) {
-        float a = vel[3 * (size_t)i], b = vel[3 * (size_t)i + 1], c = vel[3 * (size_t)i + 2];
-        if (!(isfinite(a) && isfinite(b) && isfinite(c))) atomicOr(status, kStNonFinite);
-        s.vx[i] = a;
-        s.vy[i] = b;
-        s.vz[i] = c;
-    } else {
-        s.vx[i] = 0.f;
-        s.vy[i] = 0.f;
-        s.vz[i] = 0.f;
-    }
-    s.cid[i] = i;
 }
 
-void launch_ingest(bh_ctx *c, const float *pos, const float *vel, const float *mass, uint32_t n,
-                   hipStream_t st) {
-    hipLaunchKernelGGL(k_ingest, dim3(cdiv(n, 256)), dim3(256), 0, st, pos, vel, mass, n,
-                       c->st[c->cur], c->status);
+void launch_save(const State &s, uint32_t n, char *dst, hipStream_t st) {
+    hipLaunchKernelGGL(k_save, dim3(cdiv(n, 256)), dim3(256), 0, st, s, n, dst);
 }
 
 // v += a h

@@ -15,86 +15,138 @@ namespace bh {
 constexpr int kBoxThreads = 256;
 constexpr int kBoxBlocks = 1024;
 
-__global__ __launch_bounds__(kBoxThreads) void k_bbox_partial(const float *__restrict__ x,
-                                                              const float *__restrict__ y,
-                                                              const float *__restrict__ z,
-                                                              uint32_t n, float *part,
+struct Extent {
+    float lo[3], hi[3];
+};
+
+__device__ __forceinline__ Extent no_extent() {
+    return Extent{{INFINITY, INFINITY, INFINITY}, {-INFINITY, -INFINITY, -INFINITY}};
+}
+
+// Particle i of s joins e; bit mask of what is wrong with it.
+__device__ __forceinline__ uint32_t join_particle(const Source &s, uint32_t i, Extent &e,
+                                                  float p[3]) {
+    const size_t o = (size_t)i * s.ps;
+    p[0] = s.x[o]; p[1] = s.y[o]; p[2] = s.z[o];
+    uint32_t bad = isfinite(p[0]) && isfinite(p[1]) && isfinite(p[2]) ? 0u : kStNonFinite;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        e.lo[k] = fminf(e.lo[k], p[k]);
+        e.hi[k] = fmaxf(e.hi[k], p[k]);
+    }
+    if (s.check) {
+        const float m = s.m[i];
+        if (!(m > 0.f) || !isfinite(m)) bad |= kStMass;
+        if (s.vx) {
+            const size_t v = (size_t)i * s.vs;
+            if (!(isfinite(s.vx[v]) && isfinite(s.vy[v]) && isfinite(s.vz[v]))) bad |= kStNonFinite;
+        }
+    }
+    return bad;
+}
+
+__device__ __forceinline__ void wave_extent(Extent &e) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        e.lo[k] = wave_min(e.lo[k]);
+        e.hi[k] = wave_max(e.hi[k]);
+    }
+}
+
+__global__ __launch_bounds__(kBoxThreads) void k_bbox_partial(Source s, uint32_t n, float *part,
                                                               uint32_t *status) {
-    __shared__ float lds[4][6];
-    float lo0 = INFINITY, lo1 = INFINITY, lo2 = INFINITY;
-    float hi0 = -INFINITY, hi1 = -INFINITY, hi2 = -INFINITY;
-    bool bad = false;
+    __shared__ Extent lds[kBoxThreads / 64];
+    Extent e = no_extent();
+    uint32_t bad = 0;
     for (uint32_t i = blockIdx.x * kBoxThreads + threadIdx.x; i < n;
          i += gridDim.x * kBoxThreads) {
-        float a = x[i], b = y[i], c = z[i];
-        bad |= !(isfinite(a) && isfinite(b) && isfinite(c));
-        lo0 = fminf(lo0, a); hi0 = fmaxf(hi0, a);
-        lo1 = fminf(lo1, b); hi1 = fmaxf(hi1, b);
-        lo2 = fminf(lo2, c); hi2 = fmaxf(hi2, c);
+        float p[3];
+        bad |= join_particle(s, i, e, p);
     }
-    if (bad) atomicOr(status, kStNonFinite);
-    lo0 = wave_min(lo0); lo1 = wave_min(lo1); lo2 = wave_min(lo2);
-    hi0 = wave_max(hi0); hi1 = wave_max(hi1); hi2 = wave_max(hi2);
-    uint32_t w = threadIdx.x >> 6;
-    if (lane_id() == 0) {
-        lds[w][0] = lo0; lds[w][1] = lo1; lds[w][2] = lo2;
-        lds[w][3] = hi0; lds[w][4] = hi1; lds[w][5] = hi2;
-    }
+    if (bad) atomicOr(status, bad);
+    wave_extent(e);
+    if (lane_id() == 0) lds[threadIdx.x >> 6] = e;
     __syncthreads();
     if (threadIdx.x < 6) {
-        float v = lds[0][threadIdx.x];
-        for (int k = 1; k < 4; ++k)
-            v = threadIdx.x < 3 ? fminf(v, lds[k][threadIdx.x]) : fmaxf(v, lds[k][threadIdx.x]);
+        const uint32_t k = threadIdx.x % 3u;
+        const bool lo = threadIdx.x < 3u;
+        float v = lo ? lds[0].lo[k] : lds[0].hi[k];
+        for (int w = 1; w < kBoxThreads / 64; ++w)
+            v = lo ? fminf(v, lds[w].lo[k]) : fmaxf(v, lds[w].hi[k]);
         part[blockIdx.x * 6 + threadIdx.x] = v;
     }
 }
 
-// Reduce the block partials.  fixed == 0: the cube of side = largest
-// extent at the minimum corner.  fixed == 1: the caller's box (flo, fside),
-// and kStOutside is latched when on some axis a particle lies below flo or
-// has fl32(x - flo) > fside (the difference the keys quantise).
-__global__ __launch_bounds__(64) void k_bbox_final(const float *__restrict__ part, uint32_t nb,
-                                                   float *box, int fixed, float flo0, float flo1,
-                                                   float flo2, float fside, uint32_t *status) {
-    float lo0 = INFINITY, lo1 = INFINITY, lo2 = INFINITY;
-    float hi0 = -INFINITY, hi1 = -INFINITY, hi2 = -INFINITY;
-    for (uint32_t b = threadIdx.x; b < nb; b += 64) {
-        lo0 = fminf(lo0, part[6 * b + 0]); lo1 = fminf(lo1, part[6 * b + 1]);
-        lo2 = fminf(lo2, part[6 * b + 2]); hi0 = fmaxf(hi0, part[6 * b + 3]);
-        hi1 = fmaxf(hi1, part[6 * b + 4]); hi2 = fmaxf(hi2, part[6 * b + 5]);
-    }
-    lo0 = wave_min(lo0); lo1 = wave_min(lo1); lo2 = wave_min(lo2);
-    hi0 = wave_max(hi0); hi1 = wave_max(hi1); hi2 = wave_max(hi2);
-    if (threadIdx.x == 0) {
-        if (fixed) {
-            bool out = lo0 < flo0 || lo1 < flo1 || lo2 < flo2 || hi0 - flo0 > fside ||
-                       hi1 - flo1 > fside || hi2 - flo2 > fside;
-            if (out) atomicOr(status, kStOutside);
-            box[0] = flo0; box[1] = flo1; box[2] = flo2;
-            box[3] = fside;
-            box[4] = (float)(2097152.0 / (double)fside);
-            return;
+// The key box (lo xyz, side, scale) of particles of extent e.  fixed == 0: the
+// cube of side = largest extent at the minimum corner.  fixed == 1: the
+// caller's box (flo, fside), and kStOutside is latched (by the thread that is
+// asked to) when on some axis a particle lies below flo or has
+// fl32(x - flo) > fside (the difference the keys quantise).
+struct FixedBox {
+    int fixed;
+    float lo[3], side;
+};
+
+__device__ __forceinline__ void key_box(const Extent &e, const FixedBox &f, bool latch,
+                                        uint32_t *status, float box[5]) {
+    if (f.fixed) {
+        bool out = false;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            out = out || e.lo[k] < f.lo[k] || e.hi[k] - f.lo[k] > f.side;
+            box[k] = f.lo[k];
         }
-        float side = 0.f, e;
-        e = hi0 - lo0; if (e > side) side = e;
-        e = hi1 - lo1; if (e > side) side = e;
-        e = hi2 - lo2; if (e > side) side = e;
+        if (latch && out) atomicOr(status, kStOutside);
+        box[3] = f.side;
+    } else {
+        float side = 0.f;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const float d = e.hi[k] - e.lo[k];
+            if (d > side) side = d;
+            box[k] = e.lo[k];
+        }
         if (side == 0.f) side = 1.f;
-        box[0] = lo0; box[1] = lo1; box[2] = lo2;
         box[3] = side;
-        box[4] = (float)(2097152.0 / (double)side);
+    }
+    box[4] = (float)(2097152.0 / (double)box[3]);
+}
+
+// The extent of the nb partials, by one wave.
+__device__ __forceinline__ Extent join_partials(const float *__restrict__ part, uint32_t nb,
+                                                uint32_t lane) {
+    Extent e = no_extent();
+    for (uint32_t b = lane; b < nb; b += 64) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            e.lo[k] = fminf(e.lo[k], part[6 * b + k]);
+            e.hi[k] = fmaxf(e.hi[k], part[6 * b + 3 + k]);
+        }
+    }
+    wave_extent(e);
+    return e;
+}
+
+__global__ __launch_bounds__(64) void k_bbox_final(const float *__restrict__ part, uint32_t nb,
+                                                   float *box, FixedBox f, uint32_t *status) {
+    const Extent e = join_partials(part, nb, threadIdx.x);
+    if (threadIdx.x == 0) {
+        float b[5];
+        key_box(e, f, true, status, b);
+        for (int k = 0; k < 5; ++k) box[k] = b[k];
     }
 }
 
-void launch_bbox(bh_ctx *c, const State &s, uint32_t n, hipStream_t st) {
+static FixedBox fixed_box(const bh_ctx *c) {
+    return FixedBox{c->fixed_box ? 1 : 0, {c->box_lo[0], c->box_lo[1], c->box_lo[2]}, c->box_side};
+}
+
+static uint32_t launch_bbox_partial(bh_ctx *c, const Source &s, uint32_t n, hipStream_t st) {
     uint32_t nb = cdiv(n, kBoxThreads * 8);
     if (nb > kBoxBlocks) nb = kBoxBlocks;
-    if (nb < 1) nb = 1;
-    hipLaunchKernelGGL(k_bbox_partial, dim3(nb), dim3(kBoxThreads), 0, st, s.x, s.y, s.z, n,
-                       c->box_part, c->status);
-    hipLaunchKernelGGL(k_bbox_final, dim3(1), dim3(64), 0, st, (const float *)c->box_part, nb,
-                       c->box, c->fixed_box ? 1 : 0, c->box_lo[0], c->box_lo[1], c->box_lo[2],
-                       c->box_side, c->status);
+    hipLaunchKernelGGL(k_bbox_partial, dim3(nb), dim3(kBoxThreads), 0, st, s, n, c->box_part,
+                       c->status);
+    return nb;
 }
 
 // 21 bits -> every third bit of a 63-bit word
@@ -131,25 +183,23 @@ __device__ __forceinline__ uint64_t key_of(float x, float y, float z, const KeyB
 }
 
 template <bool kPH>
-__global__ __launch_bounds__(256) void k_keys(const float *__restrict__ x,
-                                              const float *__restrict__ y,
-                                              const float *__restrict__ z, uint32_t n,
-                                              const float *__restrict__ box,
+__global__ __launch_bounds__(256) void k_keys(Source s, uint32_t n, const float *__restrict__ box,
                                               uint64_t *__restrict__ key,
                                               uint32_t *__restrict__ idx) {
     uint32_t i = blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
-    key[i] = key_of<kPH>(x[i], y[i], z[i], KeyBox{box[0], box[1], box[2], box[4]});
+    const size_t o = (size_t)i * s.ps;
+    key[i] = key_of<kPH>(s.x[o], s.y[o], s.z[o], KeyBox{box[0], box[1], box[2], box[4]});
     idx[i] = i;
 }
 
-static void launch_keys(bh_ctx *c, const State &s, uint32_t n, hipStream_t st) {
+static void launch_keys(bh_ctx *c, const Source &s, uint32_t n, hipStream_t st) {
     if (c->p.curve == 1)
-        hipLaunchKernelGGL(k_keys<true>, dim3(cdiv(n, 256)), dim3(256), 0, st, s.x, s.y, s.z, n,
+        hipLaunchKernelGGL(k_keys<true>, dim3(cdiv(n, 256)), dim3(256), 0, st, s, n,
                            (const float *)c->box, c->sort.key[0], c->sort.idx[0]);
     else
-        hipLaunchKernelGGL(k_keys<false>, dim3(cdiv(n, 256)), dim3(256), 0, st, s.x, s.y, s.z,
-                           n, (const float *)c->box, c->sort.key[0], c->sort.idx[0]);
+        hipLaunchKernelGGL(k_keys<false>, dim3(cdiv(n, 256)), dim3(256), 0, st, s, n,
+                           (const float *)c->box, c->sort.key[0], c->sort.idx[0]);
 }
 
 // ---- block sort and merges ------------------------------------------------
@@ -174,28 +224,66 @@ constexpr uint32_t kMergeMax = 3u << 20;
 constexpr int kSortThreads = 1024;
 constexpr int kSortWaves = kSortThreads / 64;
 
+// nb == 0: the only tile, which also finds the bounding box (and checks the
+// particles); else every block folds the nb partials.  Block 0 writes box.
 template <bool kPH, int kRounds>
 __global__ __launch_bounds__(kSortThreads) void k_sort_block(
-    const float *__restrict__ x, const float *__restrict__ y, const float *__restrict__ z,
-    uint32_t n, const float *__restrict__ box, uint64_t *__restrict__ key_out,
-    uint32_t *__restrict__ idx_out) {
+    Source s, uint32_t n, const float *__restrict__ part, uint32_t nb, FixedBox fb, float *box,
+    uint32_t *status, uint64_t *__restrict__ key_out, uint32_t *__restrict__ idx_out) {
     constexpr uint32_t kTile = kSortThreads * kRounds;
     __shared__ uint64_t skey[kTile];
     __shared__ uint16_t sidx[kTile];
     __shared__ uint32_t cnt[kSortWaves][256];
     __shared__ uint32_t wsum[4];
+    __shared__ Extent ext[kSortWaves];
     const uint32_t w = threadIdx.x >> 6, lane = lane_id();
     const uint32_t t0 = blockIdx.x * kTile;
     const uint32_t p0 = w * 64u * kRounds + lane;  // this wave's positions: p0 + 64 r
-    const KeyBox kb{box[0], box[1], box[2], box[4]};
     const uint64_t lt = mask_lt(lane);
+    float px[kRounds], py[kRounds], pz[kRounds];
+    Extent e = no_extent();
+    uint32_t bad = 0;
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        const uint32_t i = t0 + p0 + 64u * r;
+        px[r] = py[r] = pz[r] = 0.f;
+        if (i < n) {
+            if (nb == 0) {
+                float p[3];
+                bad |= join_particle(s, i, e, p);
+                px[r] = p[0]; py[r] = p[1]; pz[r] = p[2];
+            } else {
+                const size_t o = (size_t)i * s.ps;
+                px[r] = s.x[o]; py[r] = s.y[o]; pz[r] = s.z[o];
+            }
+        }
+    }
+    if (nb == 0) {
+        if (bad) atomicOr(status, bad);
+        wave_extent(e);
+        if (lane == 0) ext[w] = e;
+        __syncthreads();
+        e = ext[lane % kSortWaves];
+        wave_extent(e);
+    } else {
+        if (w == 0) {
+            e = join_partials(part, nb, lane);
+            if (lane == 0) ext[0] = e;
+        }
+        __syncthreads();
+        e = ext[0];
+    }
+    float b[5];
+    key_box(e, fb, blockIdx.x == 0 && threadIdx.x == 0, status, b);
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        for (int k = 0; k < 5; ++k) box[k] = b[k];
+    const KeyBox kb{b[0], b[1], b[2], b[4]};
     uint64_t kk[kRounds];
     uint32_t vv[kRounds];
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
-        const uint32_t i = t0 + p0 + 64u * r;
         // past the end: a key above all others, so it stays behind them
-        kk[r] = i < n ? key_of<kPH>(x[i], y[i], z[i], kb) : ~0ull;
+        kk[r] = t0 + p0 + 64u * r < n ? key_of<kPH>(px[r], py[r], pz[r], kb) : ~0ull;
         vv[r] = p0 + 64u * r;
     }
     for (uint32_t shift = 0; shift < 64u; shift += 8u) {
@@ -348,26 +436,30 @@ __global__ __launch_bounds__(kMergeThreads) void k_sort_merge(
 }
 
 template <int kRounds>
-static void launch_sort_block(bh_ctx *c, const State &s, uint32_t n, int dst, hipStream_t st) {
+static void launch_sort_block(bh_ctx *c, const Source &s, uint32_t n, uint32_t nb, int dst,
+                              hipStream_t st) {
     const dim3 grid(cdiv(n, (uint64_t)kSortThreads * kRounds));
     if (c->p.curve == 1)
-        hipLaunchKernelGGL((k_sort_block<true, kRounds>), grid, dim3(kSortThreads), 0, st, s.x,
-                           s.y, s.z, n, (const float *)c->box, c->sort.key[dst], c->sort.idx[dst]);
+        hipLaunchKernelGGL((k_sort_block<true, kRounds>), grid, dim3(kSortThreads), 0, st, s, n,
+                           (const float *)c->box_part, nb, fixed_box(c), c->box, c->status,
+                           c->sort.key[dst], c->sort.idx[dst]);
     else
-        hipLaunchKernelGGL((k_sort_block<false, kRounds>), grid, dim3(kSortThreads), 0, st, s.x,
-                           s.y, s.z, n, (const float *)c->box, c->sort.key[dst], c->sort.idx[dst]);
+        hipLaunchKernelGGL((k_sort_block<false, kRounds>), grid, dim3(kSortThreads), 0, st, s, n,
+                           (const float *)c->box_part, nb, fixed_box(c), c->box, c->status,
+                           c->sort.key[dst], c->sort.idx[dst]);
 }
 
 // Sorted keys and indices into key[0], idx[0].
-static void launch_merge_sort(bh_ctx *c, const State &s, uint32_t n, hipStream_t st) {
+static void launch_merge_sort(bh_ctx *c, const Source &s, uint32_t n, hipStream_t st) {
     constexpr uint32_t kTile = kSortThreads * 8;
     int passes = 0;
     while (((uint64_t)kTile << passes) < n) ++passes;
     int src = passes & 1;
-    if (n <= 1024u) launch_sort_block<1>(c, s, n, src, st);
-    else if (n <= 2048u) launch_sort_block<2>(c, s, n, src, st);
-    else if (n <= 4096u) launch_sort_block<4>(c, s, n, src, st);
-    else launch_sort_block<8>(c, s, n, src, st);
+    const uint32_t nb = n > kTile ? launch_bbox_partial(c, s, n, st) : 0u;
+    if (n <= 1024u) launch_sort_block<1>(c, s, n, nb, src, st);
+    else if (n <= 2048u) launch_sort_block<2>(c, s, n, nb, src, st);
+    else if (n <= 4096u) launch_sort_block<4>(c, s, n, nb, src, st);
+    else launch_sort_block<8>(c, s, n, nb, src, st);
     for (int p = 0; p < passes; ++p, src ^= 1)
         hipLaunchKernelGGL(k_sort_merge, dim3(cdiv(n, kMergeTile)), dim3(kMergeThreads), 0, st,
                            (const uint64_t *)c->sort.key[src], (const uint32_t *)c->sort.idx[src],
@@ -500,8 +592,11 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(
     }
 }
 
-void launch_sort(bh_ctx *c, const State &s, uint32_t n, hipStream_t st) {
+void launch_sort(bh_ctx *c, const Source &s, uint32_t n, hipStream_t st) {
     if (n <= kMergeMax) return launch_merge_sort(c, s, n, st);
+    const uint32_t nb = launch_bbox_partial(c, s, n, st);
+    hipLaunchKernelGGL(k_bbox_final, dim3(1), dim3(64), 0, st, (const float *)c->box_part, nb,
+                       c->box, fixed_box(c), c->status);
     launch_keys(c, s, n, st);
     uint32_t ntiles = cdiv(n, kSortTile);
     uint32_t len = 256u * ntiles;
@@ -522,32 +617,41 @@ void launch_sort(bh_ctx *c, const State &s, uint32_t n, hipStream_t st) {
 
 // ---- gather the state into sorted order ------------------------------------
 
+// Particle idx[i] of s becomes sorted particle i of b.  Read from the caller's
+// arrays a particle in random order costs two or three cache lines instead of
+// the eight of a copy as separate arrays.
 __global__ __launch_bounds__(256) void k_gather(const uint32_t *__restrict__ idx, uint32_t n,
-                                                State a, State b, float4 *__restrict__ xyzm) {
+                                                Source a, State b, float4 *__restrict__ xyzm) {
     uint32_t i = blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
-    uint32_t s = idx[i];
-    float px = a.x[s], py = a.y[s], pz = a.z[s], pm = a.m[s];
+    const uint32_t s = idx[i];
+    const size_t o = (size_t)s * a.ps;
+    const float px = a.x[o], py = a.y[o], pz = a.z[o], pm = a.m[s];
+    float vx = 0.f, vy = 0.f, vz = 0.f;
+    if (a.vx) {
+        const size_t v = (size_t)s * a.vs;
+        vx = a.vx[v]; vy = a.vy[v]; vz = a.vz[v];
+    }
+    xyzm[i] = make_float4(px, py, pz, pm);
+    b.cid[i] = a.cid ? a.cid[s] : s;
+    if (!b.x) return;  // (tree_force_static keeps no state)
     b.x[i] = px;
     b.y[i] = py;
     b.z[i] = pz;
     b.m[i] = pm;
-    xyzm[i] = make_float4(px, py, pz, pm);
-    b.vx[i] = a.vx[s];
-    b.vy[i] = a.vy[s];
-    b.vz[i] = a.vz[s];
-    b.cid[i] = a.cid[s];
-    if (a.x64) {
-        b.x64[i] = a.x64[s];
-        b.y64[i] = a.y64[s];
-        b.z64[i] = a.z64[s];
+    b.vx[i] = vx;
+    b.vy[i] = vy;
+    b.vz[i] = vz;
+    if (b.x64) {
+        b.x64[i] = a.x64 ? a.x64[s] : (double)px;
+        b.y64[i] = a.y64 ? a.y64[s] : (double)py;
+        b.z64[i] = a.z64 ? a.z64[s] : (double)pz;
     }
 }
 
-void launch_gather(bh_ctx *c, uint32_t n, hipStream_t st) {
+void launch_gather(bh_ctx *c, const Source &s, uint32_t n, hipStream_t st) {
     hipLaunchKernelGGL(k_gather, dim3(cdiv(n, 256)), dim3(256), 0, st,
-                       (const uint32_t *)c->sort.idx[0], n, c->st[c->cur], c->st[c->cur ^ 1],
-                       c->xyzm);
+                       (const uint32_t *)c->sort.idx[0], n, s, c->st[c->cur ^ 1], c->xyzm);
     c->cur ^= 1;
 }
 
