@@ -89,7 +89,6 @@ int check_status(bh_ctx *c) {
 void rebuild(bh_ctx *c, const Source &src, uint32_t n, hipStream_t s) {
     record_event(c, 0, s);
     launch_sort(c, src, n, s);
-    launch_gather(c, src, n, s);
     record_event(c, 1, s);
     launch_build(c, n, s);
     record_event(c, 2, s);

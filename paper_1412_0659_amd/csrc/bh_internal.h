@@ -231,9 +231,9 @@ void launch_direct(bh_ctx *c, const int64_t *tgt, uint32_t nt, float eps, double
                    double *pot, hipStream_t st);
 
 // keys_sort.hip
-// bounding box and keys of s and their sort: result in key[0], idx[0], box
+// bounding box (-> box), keys of s, their sort (-> key[0]), and the particles
+// in that order (-> st[cur ^ 1], xyzm; cur is flipped)
 void launch_sort(bh_ctx *c, const Source &s, uint32_t n, hipStream_t st);
-void launch_gather(bh_ctx *c, const Source &s, uint32_t n, hipStream_t st);  // s -> st[cur ^ 1]
 int64_t sort_counts_len(int64_t nmax);
 int64_t scan_part_len(int64_t n);
 

@@ -202,30 +202,75 @@ static void launch_keys(bh_ctx *c, const Source &s, uint32_t n, hipStream_t st) 
                            (const float *)c->box, c->sort.key[0], c->sort.idx[0]);
 }
 
+// ---- gather the state into sorted order ------------------------------------
+
+// Particle s of a becomes sorted particle i of b.  Read from the caller's
+// arrays a particle in random order costs two or three cache lines instead of
+// the eight of a copy as separate arrays.
+__device__ __forceinline__ void move_particle(const Source &a, uint32_t s, const State &b,
+                                              uint32_t i, float4 *__restrict__ xyzm) {
+    const size_t o = (size_t)s * a.ps;
+    const float px = a.x[o], py = a.y[o], pz = a.z[o], pm = a.m[s];
+    float vx = 0.f, vy = 0.f, vz = 0.f;
+    if (a.vx) {
+        const size_t v = (size_t)s * a.vs;
+        vx = a.vx[v]; vy = a.vy[v]; vz = a.vz[v];
+    }
+    xyzm[i] = make_float4(px, py, pz, pm);
+    b.cid[i] = a.cid ? a.cid[s] : s;
+    if (!b.x) return;  // (tree_force_static keeps no state)
+    b.x[i] = px;
+    b.y[i] = py;
+    b.z[i] = pz;
+    b.m[i] = pm;
+    b.vx[i] = vx;
+    b.vy[i] = vy;
+    b.vz[i] = vz;
+    if (b.x64) {
+        b.x64[i] = a.x64 ? a.x64[s] : (double)px;
+        b.y64[i] = a.y64 ? a.y64[s] : (double)py;
+        b.z64[i] = a.z64 ? a.z64[s] : (double)pz;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_gather(const uint32_t *__restrict__ idx, uint32_t n,
+                                                Source a, State b, float4 *__restrict__ xyzm) {
+    uint32_t i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) move_particle(a, idx[i], b, i, xyzm);
+}
+
+static void launch_gather(bh_ctx *c, const Source &s, uint32_t n, hipStream_t st) {
+    hipLaunchKernelGGL(k_gather, dim3(cdiv(n, 256)), dim3(256), 0, st,
+                       (const uint32_t *)c->sort.idx[0], n, s, c->st[c->cur ^ 1], c->xyzm);
+    c->cur ^= 1;
+}
+
 // ---- block sort and merges ------------------------------------------------
 //
 // Sets of up to kMergeMax particles.  k_sort_block computes the keys of a tile
 // of 1024 kRounds particles and sorts them in LDS, all eight digits in one
 // launch (stable, least significant first: the order of equal keys is input
-// order); k_sort_merge then merges pairs of sorted runs, ties from the earlier
-// run first.  A block of a merge takes kMergeTile consecutive outputs, finds
-// where they begin and end in both runs by a 64-way search on the diagonal
-// (one wave per end), and merges them in LDS.
+// order).  Up to kRankMax particles k_sort_rank then finds every particle's
+// place among all tiles at once and moves it there; above, k_sort_merge merges
+// pairs of sorted runs, ties from the earlier run first.  A block of a merge
+// takes kMergeTile consecutive outputs, finds where they begin and end in both
+// runs by a 64-way search on the diagonal (one wave per end), and merges them
+// in LDS.
 //
-// Bound: latency on small sets (one launch up to 8192 particles, one more per
-// doubling, where the radix passes over memory below take five launches per
-// digit), 24 B per particle and merge on larger ones.  Measured, bounding box,
-// keys, sort and gather of a set in random order, in us, these against the
-// radix passes: n = 1000: 25 / 135; 4096: 45 / 148; 16384: 79 / 186; 65536: 97
-// / 213; 262144: 135 / 243; 1M: 290 / 374; 2M: 499 / 567; 4M: 1009 / 1011; 8M:
-// 2061 / 1936.
+// Bound: latency on small sets (two launches up to 8192 particles, then one
+// per doubling, where the radix passes over memory below take five launches
+// per digit), 24 B per particle and merge on larger ones.  Measured, bounding
+// box, keys, sort and gather of a set in random order, in us, these against
+// the radix passes: n = 1000: 23 / 135; 4096: 32 / 148; 16384: 54 / 192; 65536:
+// 73 / 213; 500000: 136 / 257; 1M: 192 / 297; 2M: 312 / 373; 3M: 460 / 529; 4M:
+// 625 / 615; 8M: 1235 / 1105.
 constexpr uint32_t kMergeMax = 3u << 20;
 
 constexpr int kSortThreads = 1024;
 constexpr int kSortWaves = kSortThreads / 64;
 
-// nb == 0: the only tile, which also finds the bounding box (and checks the
-// particles); else every block folds the nb partials.  Block 0 writes box.
+// nb == 0: every block finds the bounding box of all particles itself (and
+// block 0 checks them); else it folds the nb partials.  Block 0 writes box.
 template <bool kPH, int kRounds>
 __global__ __launch_bounds__(kSortThreads) void k_sort_block(
     Source s, uint32_t n, const float *__restrict__ part, uint32_t nb, FixedBox fb, float *box,
@@ -241,25 +286,27 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_block(
     const uint32_t p0 = w * 64u * kRounds + lane;  // this wave's positions: p0 + 64 r
     const uint64_t lt = mask_lt(lane);
     float px[kRounds], py[kRounds], pz[kRounds];
-    Extent e = no_extent();
-    uint32_t bad = 0;
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
         const uint32_t i = t0 + p0 + 64u * r;
         px[r] = py[r] = pz[r] = 0.f;
         if (i < n) {
-            if (nb == 0) {
-                float p[3];
-                bad |= join_particle(s, i, e, p);
-                px[r] = p[0]; py[r] = p[1]; pz[r] = p[2];
-            } else {
-                const size_t o = (size_t)i * s.ps;
-                px[r] = s.x[o]; py[r] = s.y[o]; pz[r] = s.z[o];
-            }
+            const size_t o = (size_t)i * s.ps;
+            px[r] = s.x[o]; py[r] = s.y[o]; pz[r] = s.z[o];
+        }
+    }
+    Extent e = no_extent();
+    uint32_t bad = 0;
+    if (nb == 0) {
+        Source all = s;
+        all.check = s.check && blockIdx.x == 0;
+        for (uint32_t i = threadIdx.x; i < n; i += kSortThreads) {
+            float p[3];
+            bad |= join_particle(all, i, e, p);
         }
     }
     if (nb == 0) {
-        if (bad) atomicOr(status, bad);
+        if (bad && blockIdx.x == 0) atomicOr(status, bad);
         wave_extent(e);
         if (lane == 0) ext[w] = e;
         __syncthreads();
@@ -449,21 +496,69 @@ static void launch_sort_block(bh_ctx *c, const Source &s, uint32_t n, uint32_t n
                            c->sort.key[dst], c->sort.idx[dst]);
 }
 
-// Sorted keys and indices into key[0], idx[0].
+// Sets of up to kRankMax particles: the place of every particle among all runs
+// of 1024 in one launch, its place in its own run plus the keys before it in
+// each other run (ties from the earlier run first), found by binary searches
+// that do not wait for each other; the particle is moved there at once.
+constexpr uint32_t kRankRun = 1024;
+constexpr uint32_t kRankMax = 8 * kRankRun;
+
+__global__ __launch_bounds__(256) void k_sort_rank(const uint64_t *__restrict__ key,
+                                                   const uint32_t *__restrict__ idx, uint32_t n,
+                                                   Source a, State b, float4 *__restrict__ xyzm,
+                                                   uint64_t *__restrict__ key_out) {
+    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+    const uint32_t own = blockIdx.x * 256 / kRankRun, runs = (n + kRankRun - 1u) / kRankRun;
+    if (i >= n) return;
+    const uint64_t k = key[i];
+    uint32_t rank = i - own * kRankRun;
+    for (uint32_t q0 = 0; q0 < runs; q0 += 4u) {
+        uint32_t pos[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (uint32_t step = kRankRun; step > 0u; step >>= 1) {
+#pragma unroll
+            for (uint32_t q = 0; q < 4u; ++q) {
+                const uint32_t r = q0 + q, base = r * kRankRun;
+                if (r >= runs || r == own) continue;
+                const uint32_t len = min(kRankRun, n - base), e = pos[q] + step;
+                const uint64_t v = key[base + min(e, len) - 1u];
+                if (e <= len && (r < own ? v <= k : v < k)) pos[q] = e;
+            }
+        }
+        rank += pos[0] + pos[1] + pos[2] + pos[3];
+    }
+    key_out[rank] = k;
+    move_particle(a, idx[i], b, rank, xyzm);
+}
+
+// Sorted keys into key[0], the particles into st[cur ^ 1].
 static void launch_merge_sort(bh_ctx *c, const Source &s, uint32_t n, hipStream_t st) {
-    constexpr uint32_t kTile = kSortThreads * 8;
+    if (n <= kRankMax) {
+        const int src = n > kRankRun ? 1 : 0;
+        launch_sort_block<1>(c, s, n, 0u, src, st);
+        if (src == 0) return launch_gather(c, s, n, st);
+        hipLaunchKernelGGL(k_sort_rank, dim3(cdiv(n, 256)), dim3(256), 0, st,
+                           (const uint64_t *)c->sort.key[1], (const uint32_t *)c->sort.idx[1], n,
+                           s, c->st[c->cur ^ 1], c->xyzm, c->sort.key[0]);
+        c->cur ^= 1;
+        return;
+    }
+    // 65536 particles take 73 us with tiles of 2048, 77 with 4096, 95 with 8192
+    // (a tile's sort grows with its size, a merge costs 7 us); 1M: 200 / 192 /
+    // 203; 3M: 489 / 460 / 479
+    const bool small = n <= (1u << 19);
+    const uint32_t tile = kSortThreads * (small ? 2u : 4u);
     int passes = 0;
-    while (((uint64_t)kTile << passes) < n) ++passes;
+    while (((uint64_t)tile << passes) < n) ++passes;
     int src = passes & 1;
-    const uint32_t nb = n > kTile ? launch_bbox_partial(c, s, n, st) : 0u;
-    if (n <= 1024u) launch_sort_block<1>(c, s, n, nb, src, st);
-    else if (n <= 2048u) launch_sort_block<2>(c, s, n, nb, src, st);
-    else if (n <= 4096u) launch_sort_block<4>(c, s, n, nb, src, st);
-    else launch_sort_block<8>(c, s, n, nb, src, st);
+    const uint32_t nb = launch_bbox_partial(c, s, n, st);
+    if (small) launch_sort_block<2>(c, s, n, nb, src, st);
+    else launch_sort_block<4>(c, s, n, nb, src, st);
     for (int p = 0; p < passes; ++p, src ^= 1)
         hipLaunchKernelGGL(k_sort_merge, dim3(cdiv(n, kMergeTile)), dim3(kMergeThreads), 0, st,
                            (const uint64_t *)c->sort.key[src], (const uint32_t *)c->sort.idx[src],
-                           n, kTile << p, c->sort.key[src ^ 1], c->sort.idx[src ^ 1]);
+                           n, tile << p, c->sort.key[src ^ 1], c->sort.idx[src ^ 1]);
+    launch_gather(c, s, n, st);
 }
 
 // ---- LSD radix sort, 8 bits per pass -------------------------------------
@@ -613,46 +708,7 @@ void launch_sort(bh_ctx *c, const Source &s, uint32_t n, hipStream_t st) {
         src ^= 1;
     }
     // 8 passes: the result is back in buffer 0
-}
-
-// ---- gather the state into sorted order ------------------------------------
-
-// Particle idx[i] of s becomes sorted particle i of b.  Read from the caller's
-// arrays a particle in random order costs two or three cache lines instead of
-// the eight of a copy as separate arrays.
-__global__ __launch_bounds__(256) void k_gather(const uint32_t *__restrict__ idx, uint32_t n,
-                                                Source a, State b, float4 *__restrict__ xyzm) {
-    uint32_t i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const uint32_t s = idx[i];
-    const size_t o = (size_t)s * a.ps;
-    const float px = a.x[o], py = a.y[o], pz = a.z[o], pm = a.m[s];
-    float vx = 0.f, vy = 0.f, vz = 0.f;
-    if (a.vx) {
-        const size_t v = (size_t)s * a.vs;
-        vx = a.vx[v]; vy = a.vy[v]; vz = a.vz[v];
-    }
-    xyzm[i] = make_float4(px, py, pz, pm);
-    b.cid[i] = a.cid ? a.cid[s] : s;
-    if (!b.x) return;  // (tree_force_static keeps no state)
-    b.x[i] = px;
-    b.y[i] = py;
-    b.z[i] = pz;
-    b.m[i] = pm;
-    b.vx[i] = vx;
-    b.vy[i] = vy;
-    b.vz[i] = vz;
-    if (b.x64) {
-        b.x64[i] = a.x64 ? a.x64[s] : (double)px;
-        b.y64[i] = a.y64 ? a.y64[s] : (double)py;
-        b.z64[i] = a.z64 ? a.z64[s] : (double)pz;
-    }
-}
-
-void launch_gather(bh_ctx *c, const Source &s, uint32_t n, hipStream_t st) {
-    hipLaunchKernelGGL(k_gather, dim3(cdiv(n, 256)), dim3(256), 0, st,
-                       (const uint32_t *)c->sort.idx[0], n, s, c->st[c->cur ^ 1], c->xyzm);
-    c->cur ^= 1;
+    launch_gather(c, s, n, st);
 }
 
 }  // namespace bh
