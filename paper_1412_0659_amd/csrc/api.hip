@@ -142,14 +142,22 @@ hipError_t copy_snapshot(const State &st, size_t n, char *p, bool out, hipStream
     return hipSuccess;
 }
 
-void force(bh_ctx *c, float theta, float eps, hipStream_t s) {
-    launch_walk_prep(c, theta, s);
-    launch_walk(c, eps, s);
-    launch_totals(c, (uint32_t)c->n, s);
+// Forces from the current tree: sorted into c->acc and on to `out`.
+void force(bh_ctx *c, float theta, float eps, const WalkOut &out, hipStream_t s) {
+    launch_walk_prep(c, theta, c, true, s);
+    launch_walk_view(c, own_view(c), eps, false, false, out, s);
     c->have_acc = true;
     c->counts_valid = true;
     c->acc_theta = theta;
     c->acc_eps = eps;
+}
+
+WalkOut to_caller(float *acc, float *pot, const uint32_t *rows = nullptr) {
+    WalkOut o;
+    o.acc = acc;
+    o.pot = pot;
+    o.rows = rows;
+    return o;
 }
 
 // lazily sized device buffers of the multi-domain calls
@@ -304,7 +312,7 @@ size_t static_layout(bh_ctx *c, unsigned char *base) {
     take(&c->acc, n); take(&c->xyzm, n);
     take(&c->pacc, (size_t)split_rows(c->nmax)); take(&c->pcnt, (size_t)split_rows(c->nmax));
     take(&c->spill, (size_t)c->walk_grid * kStackMax);
-    take(&c->box, 8); take(&c->box_part, 6 * 1024); take(&c->status, 4); take(&c->work, 8 * kWorkStride);
+    take(&c->box, 8); take(&c->box_part, 6 * 1024); take(&c->status, 4); take(&c->work, 16 * kWorkStride);
     take(&c->totals, 4);
     Cells &q = c->cells;
     take(&q.prefix, nc); take(&q.level, nc); take(&q.begin, nc); take(&q.count, nc);
@@ -427,7 +435,7 @@ int bh_create(bh_ctx **out, int64_t n_max, const bh_params *p) {
          dalloc(&c->pacc, (size_t)split_rows(n_max), err) &&
          dalloc(&c->pcnt, (size_t)split_rows(n_max), err) && dalloc(&c->spill, (size_t)c->walk_grid * kStackMax, err) && dalloc(&c->box, 8, err) &&
          dalloc(&c->box_part, 6 * 1024, err) && dalloc(&c->status, 4, err) &&
-         dalloc(&c->work, 8 * kWorkStride, err) && dalloc(&c->totals, 4, err) &&
+         dalloc(&c->work, 16 * kWorkStride, err) && dalloc(&c->totals, 4, err) &&
          dalloc(&c->sort.counts, (size_t)c->sort.counts_len, err) &&
          dalloc(&c->sort.scan_part, (size_t)c->sort.scan_part_len, err) &&
          dalloc(&q.prefix, nc, err) && dalloc(&q.level, nc, err) && dalloc(&q.begin, nc, err) &&
@@ -488,8 +496,7 @@ int tree_force(bh_ctx *c, float theta, float eps, float *acc, float *pot, hipStr
     if (!valid_theta(theta)) return fail(c, BH_EINVAL, "theta must be in (0, 1]");
     if (!valid_eps(eps)) return fail(c, BH_EINVAL, "eps must be finite and >= 0");
     if (!c->built) return fail(c, BH_ESTATE, "tree_force before tree_build");
-    force(c, theta, eps, s);
-    if (acc || pot) launch_unsort(c, acc, pot, (uint32_t)c->n, s);
+    force(c, theta, eps, to_caller(acc, pot), s);
     BH_HIP(c, hipGetLastError());
     return BH_OK;
 }
@@ -502,11 +509,14 @@ int leapfrog_step(bh_ctx *c, float dt, float theta, float eps, hipStream_t s) {
     if (!c->built) return fail(c, BH_ESTATE, "leapfrog_step before tree_build");
     uint32_t n = (uint32_t)c->n;
     record_event(c, 6, s);
-    if (!c->have_acc || theta != c->acc_theta || eps != c->acc_eps) force(c, theta, eps, s);
+    if (!c->have_acc || theta != c->acc_theta || eps != c->acc_eps)
+        force(c, theta, eps, WalkOut{}, s);
     launch_kick_drift(c, 0.5f * dt, dt, n, s);
     rebuild(c, source_of(c->st[c->cur]), n, s);
-    force(c, theta, eps, s);
-    launch_kick(c, 0.5f * dt, n, s);
+    WalkOut out;
+    out.kick = true;
+    out.kick_h = 0.5f * dt;
+    force(c, theta, eps, out, s);
     record_event(c, 7, s);
     BH_HIP(c, hipGetLastError());
     return BH_OK;
@@ -696,7 +706,7 @@ int tree_force_vjp(bh_ctx *c, float theta, float eps, const float *u, float coef
     if (!c->p.adjoint) return fail(c, BH_EINVAL, "context created without adjoint = 1");
     if (!c->built) return fail(c, BH_ESTATE, "tree_force_vjp before tree_build");
     if (!g_pos && !g_mass) return BH_OK;
-    launch_walk_prep(c, theta, s);
+    launch_walk_prep(c, theta, c, false, s);
     launch_walk_vjp(c, eps, u, coef, g_pos, g_mass, s);
     BH_HIP(c, hipGetLastError());
     return BH_OK;
@@ -984,8 +994,10 @@ int tree_force_add(bh_ctx *c, bh_ctx *src, float theta, float eps, float *acc, f
     if (!valid_eps(eps)) return fail(c, BH_EINVAL, "eps must be finite and >= 0");
     if (!c->built || !src->built) return fail(c, BH_ESTATE, "tree_force_add before tree_build");
     if (src->device != c->device) return fail(c, BH_EINVAL, "contexts on different devices");
-    launch_walk_prep(src, theta, s);
-    launch_walk_view(c, own_view(src), eps, true, false, s);
+    launch_walk_prep(src, theta, c, false, s);
+    WalkOut sorted;
+    sorted.totals = false;
+    launch_walk_view(c, own_view(src), eps, true, false, sorted, s);
     if (acc || pot) launch_unsort_add(c, acc, pot, (uint32_t)c->n, s);
     c->have_acc = false;
     c->counts_valid = false;
@@ -1128,7 +1140,7 @@ int bh_let_build(bh_ctx *c, bh_ctx *const *srcs, int32_t nsrc, float theta, int6
     for (int32_t k = 0; k < nsrc; ++k) {
         bh_ctx *src = srcs[k];
         const uint32_t nc = ncs[(size_t)k];
-        launch_walk_prep(src, theta, s);
+        launch_walk_prep(src, theta, nullptr, false, s);
         launch_let_mark(c, src, nc, s);
         uint32_t word = 0;
         BH_HIP(c, hipStreamSynchronize(s));
@@ -1187,16 +1199,19 @@ int tree_force_let(bh_ctx *c, float theta, float eps, const uint32_t *rows, floa
     if (!c->built) return fail(c, BH_ESTATE, "tree_force_let before tree_build");
     if (!c->let.valid) return fail(c, BH_ESTATE, "tree_force_let before bh_let_build");
     if (theta != c->let.theta) return fail(c, BH_EINVAL, "theta differs from the LET's");
-    force(c, theta, eps, s);
-    SrcView v;
-    v.wA = c->let.wA; v.wN = c->let.wN;
-    v.P0 = c->let.P0; v.P1 = c->let.P1; v.P2 = c->let.P2;
-    v.xyzm = c->let.xyzm;
+    WalkOut out = to_caller(acc, pot, rows);
     if (c->let.ncell) {
-        launch_walk_view(c, v, eps, true, true, s);
-        launch_totals(c, (uint32_t)c->n, s);
+        WalkOut own;
+        own.totals = false;  // counted with the LET's
+        force(c, theta, eps, own, s);
+        SrcView v;
+        v.wA = c->let.wA; v.wN = c->let.wN;
+        v.P0 = c->let.P0; v.P1 = c->let.P1; v.P2 = c->let.P2;
+        v.xyzm = c->let.xyzm;
+        launch_walk_view(c, v, eps, true, true, out, s);
+    } else {
+        force(c, theta, eps, out, s);
     }
-    if (acc || pot) launch_unsort(c, acc, pot, (uint32_t)c->n, s, rows);
     c->have_acc = false;  // acc holds local + remote forces
     BH_HIP(c, hipGetLastError());
     return BH_OK;
@@ -1230,8 +1245,7 @@ int tree_force_static(const float *pos, const float *mass, int64_t n, float thet
     // the array keeps the previous call's contents: clear the status words
     launch_fill_u32(c.status, 0u, 4, s);
     rebuild(&c, caller_source(pos, nullptr, mass), (uint32_t)n, s);
-    force(&c, theta, eps, s);
-    if (acc || pot) launch_unsort(&c, acc, pot, (uint32_t)n, s);
+    force(&c, theta, eps, to_caller(acc, pot), s);
     if (status) {
         hipError_t e = hipMemcpyAsync(status, c.status, sizeof(uint32_t), hipMemcpyDeviceToDevice, s);
         if (e != hipSuccess) {

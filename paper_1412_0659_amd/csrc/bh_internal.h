@@ -168,7 +168,7 @@ struct bh_ctx {
     float *box = nullptr;   // [8]: lo xyz, side, scale
     float *box_part = nullptr;
     uint32_t *status = nullptr;
-    uint32_t *work = nullptr;                // [8][kWorkStride] walk work counters, one per line
+    uint32_t *work = nullptr;                // [2][8][kWorkStride] walk work counters, one per line
     unsigned long long *totals = nullptr;    // [4] n_pp, n_pc, leaves
     bh::Sort sort{};
     bh::Cells cells{};
@@ -247,7 +247,9 @@ void launch_build(bh_ctx *c, uint32_t n, hipStream_t st);  // cells and groups
 // moments.hip
 void launch_moments(bh_ctx *c, uint32_t n, hipStream_t st);
 void launch_com(bh_ctx *c, hipStream_t st);
-void launch_walk_prep(bh_ctx *c, float theta, hipStream_t st);
+// opening radii of c's cells for theta; also the work counters of walker (which
+// is about to walk; null: none) to zero, and its interaction totals if totals
+void launch_walk_prep(bh_ctx *c, float theta, bh_ctx *walker, bool totals, hipStream_t st);
 
 // let.hip: boundary trees and local essential trees (Sec. III.B.2); nc is
 // the cell count of the tree the launcher reads (cell_count)
@@ -272,11 +274,20 @@ struct SrcView {
     const float4 *xyzm;  // particles the leaves index
 };
 SrcView own_view(const bh_ctx *c);
-void launch_walk(bh_ctx *c, float eps, hipStream_t st);
+// What becomes of the forces beside c->acc: written to caller-order outputs
+// (row rows[i] of caller index i, or row i), and a kick v += a kick_h.
+struct WalkOut {
+    float *acc = nullptr, *pot = nullptr;
+    const uint32_t *rows = nullptr;
+    bool kick = false;
+    float kick_h = 0.f;
+    bool totals = true;  // sum up the interactions (the last walk of an evaluation)
+};
 // c's groups walk the tree v; remote: no self pairs (v is not c's own tree);
-// accum: forces and counts add to c->acc, npp, npc
+// accum: forces and counts add to c->acc, npp, npc.  The own tree's walk and a
+// remote one have work counters of their own (both reset by launch_walk_prep).
 void launch_walk_view(bh_ctx *c, const SrcView &v, float eps, bool remote, bool accum,
-                      hipStream_t st);
+                      const WalkOut &out, hipStream_t st);
 int walk_blocks_per_cu();
 // A small set has fewer groups than the chip has wave slots, and the longest
 // walk (a wide group on the outskirts) sets the time, so 2^logw waves share
@@ -302,10 +313,7 @@ inline int64_t split_rows(int64_t n_max) {
 
 // integrate.hip
 void launch_save(const State &s, uint32_t n, char *dst, hipStream_t st);
-void launch_kick(bh_ctx *c, float h, uint32_t n, hipStream_t st);
 void launch_kick_drift(bh_ctx *c, float h, float dt, uint32_t n, hipStream_t st);
-void launch_unsort(bh_ctx *c, float *acc, float *pot, uint32_t n, hipStream_t st,
-                   const uint32_t *rows = nullptr);
 void launch_unsort_add(bh_ctx *c, float *acc, float *pot, uint32_t n, hipStream_t st);
 void launch_state_out(bh_ctx *c, float *pos, float *vel, uint32_t n, hipStream_t st);
 void launch_range_out(bh_ctx *c, uint32_t lo, uint32_t cnt, float *pos, float *vel, float *mass,

@@ -47,17 +47,6 @@ void launch_save(const State &s, uint32_t n, char *dst, hipStream_t st) {
     hipLaunchKernelGGL(k_save, dim3(cdiv(n, 256)), dim3(256), 0, st, s, n, dst);
 }
 
-// v += a h
-__global__ __launch_bounds__(256) void k_kick(State s, const float4 *__restrict__ acc, uint32_t n,
-                                              float h) {
-    uint32_t i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    float4 a = acc[i];
-    s.vx[i] = fmaf(a.x, h, s.vx[i]);
-    s.vy[i] = fmaf(a.y, h, s.vy[i]);
-    s.vz[i] = fmaf(a.z, h, s.vz[i]);
-}
-
 // v += a h; x += v dt.  With an FP64 master copy the drift is done in FP64
 // and the FP32 positions the tree is built from are its rounding.
 __global__ __launch_bounds__(256) void k_kick_drift(State s, const float4 *__restrict__ acc,
@@ -86,34 +75,9 @@ __global__ __launch_bounds__(256) void k_kick_drift(State s, const float4 *__res
     }
 }
 
-void launch_kick(bh_ctx *c, float h, uint32_t n, hipStream_t st) {
-    hipLaunchKernelGGL(k_kick, dim3(cdiv(n, 256)), dim3(256), 0, st, c->st[c->cur],
-                       (const float4 *)c->acc, n, h);
-}
-
 void launch_kick_drift(bh_ctx *c, float h, float dt, uint32_t n, hipStream_t st) {
     hipLaunchKernelGGL(k_kick_drift, dim3(cdiv(n, 256)), dim3(256), 0, st, c->st[c->cur],
                        (const float4 *)c->acc, n, h, dt);
-}
-
-// sorted acceleration + potential -> caller order (rows: output row of each
-// caller index, or null for the identity)
-__global__ __launch_bounds__(256) void k_unsort(const float4 *__restrict__ acc,
-                                                const uint32_t *__restrict__ cid, uint32_t n,
-                                                const uint32_t *__restrict__ rows,
-                                                float *__restrict__ out_acc,
-                                                float *__restrict__ out_pot) {
-    uint32_t i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    float4 a = acc[i];
-    uint32_t p = cid[i];
-    if (rows) p = rows[p];
-    if (out_acc) {
-        out_acc[3 * (size_t)p] = a.x;
-        out_acc[3 * (size_t)p + 1] = a.y;
-        out_acc[3 * (size_t)p + 2] = a.z;
-    }
-    if (out_pot) out_pot[p] = a.w;
 }
 
 // sorted acceleration + potential added to caller-order outputs
@@ -136,12 +100,6 @@ __global__ __launch_bounds__(256) void k_unsort_add(const float4 *__restrict__ a
 void launch_unsort_add(bh_ctx *c, float *acc, float *pot, uint32_t n, hipStream_t st) {
     hipLaunchKernelGGL(k_unsort_add, dim3(cdiv(n, 256)), dim3(256), 0, st,
                        (const float4 *)c->acc, (const uint32_t *)c->st[c->cur].cid, n, acc, pot);
-}
-
-void launch_unsort(bh_ctx *c, float *acc, float *pot, uint32_t n, hipStream_t st,
-                   const uint32_t *rows) {
-    hipLaunchKernelGGL(k_unsort, dim3(cdiv(n, 256)), dim3(256), 0, st, (const float4 *)c->acc,
-                       (const uint32_t *)c->st[c->cur].cid, n, rows, acc, pot);
 }
 
 __global__ __launch_bounds__(256) void k_state_out(State s, uint32_t n, float *__restrict__ pos,
@@ -256,7 +214,8 @@ void launch_diagnostics(bh_ctx *c, hipStream_t st) {
                        c->diag + (size_t)kDiagBlocks * kDiagN);
 }
 
-// sum over groups of npp * size and npc * size (integers: order-free)
+// sum over groups of npp * size and npc * size (integers: order-free), added to
+// tot, which launch_walk_prep zeroed
 __global__ __launch_bounds__(256) void k_totals(const uint32_t *__restrict__ gbeg,
                                                 const uint32_t *__restrict__ ngroups,
                                                 const uint32_t *__restrict__ npp,
@@ -309,12 +268,7 @@ void launch_count_leaves(bh_ctx *c, hipStream_t st) {
     hipLaunchKernelGGL(k_count_leaves, dim3(512), dim3(256), 0, st, c->cells, c->totals);
 }
 
-__global__ void k_zero_totals(unsigned long long *tot) {
-    if (threadIdx.x < 2) tot[threadIdx.x] = 0ull;
-}
-
 void launch_totals(bh_ctx *c, uint32_t n, hipStream_t st) {
-    hipLaunchKernelGGL(k_zero_totals, dim3(1), dim3(64), 0, st, c->totals);
     uint32_t nb = cdiv(n, 256 * 64);
     if (nb > 256) nb = 256;
     if (nb < 1) nb = 1;

@@ -522,8 +522,15 @@ void launch_com(bh_ctx *ctx, hipStream_t st) {
     hipLaunchKernelGGL(k_com, dim3(kGrid * 2), dim3(256), 0, st, ctx->cells);
 }
 
-// r_open^2 = (fl32(l / theta) + delta)^2 in FP32, stored in wA.w
-__global__ __launch_bounds__(256) void k_walk_prep(Cells c, float theta) {
+// r_open^2 = (fl32(l / theta) + delta)^2 in FP32, stored in wA.w; the first
+// block also zeroes the walk's counters.
+__global__ __launch_bounds__(256) void k_walk_prep(Cells c, float theta, uint32_t *work,
+                                                   unsigned long long *totals) {
+    if (blockIdx.x == 0) {
+        if (work)
+            for (uint32_t k = threadIdx.x; k < 16u; k += 256u) work[k * kWorkStride] = 0u;
+        if (totals && threadIdx.x < 2u) totals[threadIdx.x] = 0ull;
+    }
     uint32_t nc = c.ls[kLevels];
     for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < nc; i += gridDim.x * 256) {
         float2 sz = c.size[i];
@@ -532,8 +539,12 @@ __global__ __launch_bounds__(256) void k_walk_prep(Cells c, float theta) {
     }
 }
 
-void launch_walk_prep(bh_ctx *ctx, float theta, hipStream_t st) {
-    hipLaunchKernelGGL(k_walk_prep, dim3(kGrid * 2), dim3(256), 0, st, ctx->cells, theta);
+void launch_walk_prep(bh_ctx *ctx, float theta, bh_ctx *walker, bool totals, hipStream_t st) {
+    // (a cell per particle at most in sets worth more than a few blocks)
+    const uint32_t nb = cdiv((uint64_t)ctx->n, 256);
+    hipLaunchKernelGGL(k_walk_prep, dim3(nb < kGrid * 2u ? nb : kGrid * 2u), dim3(256), 0, st,
+                       ctx->cells, theta, walker ? walker->work : nullptr,
+                       walker && totals ? walker->totals : nullptr);
 }
 
 }  // namespace bh

@@ -33,6 +33,12 @@ struct WalkArgs {
     uint32_t logw, pstride;
     float4 *pacc;
     uint2 *pcnt;
+    // caller-order outputs (null: none), kick of the velocities (null: none)
+    float *out_acc, *out_pot;
+    const uint32_t *cid, *rows;
+    float *vx, *vy, *vz;
+    float kick_h;
+    unsigned long long *totals;  // split walks: interaction totals to add to (null: none)
 };
 
 __device__ __forceinline__ float rsq(float v) { return __builtin_amdgcn_rsqf(v); }
@@ -244,6 +250,35 @@ __device__ __forceinline__ void eval_chunk(Phase &ph, uint32_t n, const WalkLds 
     }
 }
 
+// Target i's forces from the walked tree: the self pair's potential out (it
+// was evaluated with r^2 = eps^2), an earlier walk's added, then stored and
+// passed on to whoever takes them (a separate launch for each of these cost
+// 4 us on small sets and 30 + 16 B per particle of traffic on large ones).
+template <bool kEps0>
+__device__ __forceinline__ void finish_target(const WalkArgs &a, uint32_t i, float m, float4 res) {
+    if (!kEps0 && !a.remote) res.w += m * rsq(a.eps2);
+    if (a.accum) {
+        const float4 o = a.acc[i];
+        res.x = o.x + res.x; res.y = o.y + res.y; res.z = o.z + res.z; res.w = o.w + res.w;
+    }
+    a.acc[i] = res;
+    if (a.out_acc || a.out_pot) {
+        uint32_t p = a.cid[i];
+        if (a.rows) p = a.rows[p];
+        if (a.out_acc) {
+            a.out_acc[3 * (size_t)p] = res.x;
+            a.out_acc[3 * (size_t)p + 1] = res.y;
+            a.out_acc[3 * (size_t)p + 2] = res.z;
+        }
+        if (a.out_pot) a.out_pot[p] = res.w;
+    }
+    if (a.vx) {
+        a.vx[i] = fmaf(res.x, a.kick_h, a.vx[i]);
+        a.vy[i] = fmaf(res.y, a.kick_h, a.vy[i]);
+        a.vz[i] = fmaf(res.z, a.kick_h, a.vz[i]);
+    }
+}
+
 // Walk group g (kSplit: as wave w of 2^a.logw, leaving the partial sums for
 // k_walk_combine).
 template <bool kEps0, bool kF16, bool kSplit>
@@ -428,15 +463,7 @@ __device__ void walk_group(const WalkArgs &a, uint32_t g, uint32_t w, uint32_t l
         wave_sync();
         return;
     }
-    if (own) {
-        // the self pair was evaluated with r^2 = eps^2; take its potential out
-        if (!kEps0 && !a.remote) res.w += me.w * rsq(a.eps2);
-        if (a.accum) {
-            const float4 o = a.acc[gb + lane];
-            res.x = o.x + res.x; res.y = o.y + res.y; res.z = o.z + res.z; res.w = o.w + res.w;
-        }
-        a.acc[gb + lane] = res;
-    }
+    if (own) finish_target<kEps0>(a, gb + lane, me.w, res);
     if (lane == 0) {
         a.npp[g] = (a.accum ? a.npp[g] : 0u) + cnt_pp;
         a.npc[g] = (a.accum ? a.npc[g] : 0u) + cnt_pc;
@@ -444,8 +471,10 @@ __device__ void walk_group(const WalkArgs &a, uint32_t g, uint32_t w, uint32_t l
     wave_sync();
 }
 
+// Four waves per SIMD by registers (three would do: asked for at least four,
+// the compiler schedules for five and the 13M walk takes 59.4 instead of 57.6 ms).
 template <bool kEps0, bool kF16, bool kSplit>
-__global__ __launch_bounds__(64) void k_walk(WalkArgs a) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 4))) void k_walk(WalkArgs a) {
     __shared__ WalkLds L;
     const uint32_t lane = threadIdx.x;
     uint32_t *spill = a.spill + (size_t)blockIdx.x * kStackMax;
@@ -454,23 +483,22 @@ __global__ __launch_bounds__(64) void k_walk(WalkArgs a) {
     });
 }
 
-// The partial sums and counts of a split walk, added in wave order.
+// The partial sums and counts of a split walk, added in wave order; the
+// interaction totals.
 template <bool kEps0>
 __global__ __launch_bounds__(256) void k_walk_combine(WalkArgs a, uint32_t n) {
+    __shared__ unsigned long long part[4][2];
     const uint32_t i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
     const uint32_t W = 1u << a.logw;
-    float4 res = a.pacc[i];
-    for (uint32_t w = 1; w < W; ++w) {
-        const float4 o = a.pacc[(size_t)w * a.pstride + i];
-        res.x += o.x; res.y += o.y; res.z += o.z; res.w += o.w;
+    if (i < n) {
+        float4 res = a.pacc[i];
+        for (uint32_t w = 1; w < W; ++w) {
+            const float4 o = a.pacc[(size_t)w * a.pstride + i];
+            res.x += o.x; res.y += o.y; res.z += o.z; res.w += o.w;
+        }
+        finish_target<kEps0>(a, i, a.xyzm[i].w, res);
     }
-    if (!kEps0 && !a.remote) res.w += a.xyzm[i].w * rsq(a.eps2);  // the self pair
-    if (a.accum) {
-        const float4 o = a.acc[i];
-        res.x = o.x + res.x; res.y = o.y + res.y; res.z = o.z + res.z; res.w = o.w + res.w;
-    }
-    a.acc[i] = res;
+    unsigned long long spp = 0, spc = 0;
     if (i < *a.ngroups) {  // (at most n groups)
         uint32_t pp = a.accum ? a.npp[i] : 0u, pc = a.accum ? a.npc[i] : 0u;
         for (uint32_t w = 0; w < W; ++w) {
@@ -480,11 +508,24 @@ __global__ __launch_bounds__(256) void k_walk_combine(WalkArgs a, uint32_t n) {
         }
         a.npp[i] = pp;
         a.npc[i] = pc;
+        const unsigned long long size = a.gbeg[i + 1] - a.gbeg[i];
+        spp = size * pp;
+        spc = size * pc;
     }
-}
-
-__global__ void k_reset_work(uint32_t *work) {
-    if (threadIdx.x < 8) work[threadIdx.x * kWorkStride] = 0u;
+    if (!a.totals || blockIdx.x * 256u >= *a.ngroups) return;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        spp += __shfl_xor(spp, d, 64);
+        spc += __shfl_xor(spc, d, 64);
+    }
+    if (lane_id() == 0) {
+        part[threadIdx.x >> 6][0] = spp;
+        part[threadIdx.x >> 6][1] = spc;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2)
+        atomicAdd(&a.totals[threadIdx.x], part[0][threadIdx.x] + part[1][threadIdx.x] +
+                                              part[2][threadIdx.x] + part[3][threadIdx.x]);
 }
 
 int walk_blocks_per_cu() {
@@ -516,21 +557,28 @@ static void launch_walk_k(bh_ctx *c, const WalkArgs &a, float eps, hipStream_t s
 }
 
 void launch_walk_view(bh_ctx *c, const SrcView &v, float eps, bool remote, bool accum,
-                      hipStream_t st) {
+                      const WalkOut &out, hipStream_t st) {
     WalkArgs a;
     a.xyzm = c->xyzm;
     a.sxyzm = v.xyzm;
     a.wA = v.wA; a.wN = v.wN;
     a.P0 = v.P0; a.P1 = v.P1; a.P2 = v.P2;
     a.gbeg = c->groups.begin; a.ngroups = c->groups.count_dev;
-    a.work = c->work; a.spill = c->spill;
+    a.work = c->work + (remote ? 8 * kWorkStride : 0);
+    a.spill = c->spill;
     a.acc = c->acc; a.gbox = c->groups.box;
     a.npp = c->groups.npp; a.npc = c->groups.npc; a.status = c->status;
     a.eps2 = eps * eps;
     a.ring = c->walk_small_stack ? 192u : (uint32_t)kRing;
     a.remote = remote ? 1u : 0u;
     a.accum = accum ? 1u : 0u;
-    hipLaunchKernelGGL(k_reset_work, dim3(1), dim3(64), 0, st, c->work);
+    const State &s = c->st[c->cur];
+    a.out_acc = out.acc; a.out_pot = out.pot;
+    a.cid = s.cid; a.rows = out.rows;
+    a.vx = out.kick ? s.vx : nullptr;
+    a.vy = s.vy; a.vz = s.vz;
+    a.kick_h = out.kick_h;
+    a.totals = out.totals ? c->totals : nullptr;
     const bool own = !remote && !accum;  // the timed walk of the context's own tree
     if (own) record_event(c, 4, st);
     a.logw = split_logw(c->n);
@@ -539,6 +587,7 @@ void launch_walk_view(bh_ctx *c, const SrcView &v, float eps, bool remote, bool 
     if (a.logw) launch_walk_k<true>(c, a, eps, st);
     else launch_walk_k<false>(c, a, eps, st);
     if (own) record_event(c, 5, st);
+    if (!a.logw && out.totals) launch_totals(c, (uint32_t)c->n, st);
 }
 
 SrcView own_view(const bh_ctx *c) {
@@ -547,10 +596,6 @@ SrcView own_view(const bh_ctx *c) {
     v.P0 = c->cells.P0; v.P1 = c->cells.P1; v.P2 = c->cells.P2;
     v.xyzm = c->xyzm;
     return v;
-}
-
-void launch_walk(bh_ctx *c, float eps, hipStream_t st) {
-    launch_walk_view(c, own_view(c), eps, false, false, st);
 }
 
 }  // namespace bh

@@ -471,10 +471,6 @@ __global__ __launch_bounds__(256) void k_moments_vjp(Cells c, const float4 *__re
     if (g_mass) g_mass[o] += (float)(coef * gm);
 }
 
-__global__ void k_reset_work_vjp(uint32_t *work) {
-    if (threadIdx.x < 8) work[threadIdx.x * kWorkStride] = 0u;
-}
-
 // Waves per group of a split adjoint walk, as in the force walk; every wave
 // adds its targets' sums by atomics of its own, so two waves stop paying
 // earlier.  Disk + halo, theta 0.4, us by waves per group (1 / 2 / 4 / 8):
@@ -523,7 +519,6 @@ void launch_walk_vjp(bh_ctx *c, float eps, const float *u, float coef, float *g_
     a.lstride = lstride; a.gstride = gstride;
     a.cap = cap; a.nmax = nmax;
     a.eps2 = eps * eps;
-    hipLaunchKernelGGL(k_reset_work_vjp, dim3(1), dim3(64), 0, st, c->work);
     record_event(c, 8, st);
     a.logw = vjp_logw(c->n);
     if (a.logw) launch_vjp_k<true>(c, a, eps, st);
