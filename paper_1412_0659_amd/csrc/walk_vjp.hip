@@ -11,29 +11,42 @@
 //               dM/dm_k = 1, dcom/dm_k = s / M, dQ/dm_k = s s^T (the centre of
 //               mass dependence of Q cancels because sum m s = 0).
 // The walk (walk_common.h) is repeated exactly, so the lists are those of the
-// force evaluation.  Particle-cell chunks: lane = cell, looping over the
-// group's targets; each pair's J^T u is added to the cell's adjoint and, summed
-// over the lanes with DPP, subtracted from the target's.  Particle-particle
-// chunks: pass A (lane = target, slice) accumulates the target terms in
-// registers, pass B (lane = source) loops over the targets for the source
-// terms.  Source terms reach FP64 accumulators with one atomic per source
-// and group.  The self pair (zero separation by construction) contributes
-// nothing.
+// force evaluation.  Both lists are taken in chunks of 64 sources, lane =
+// source, looping over the group's targets; each pair's J^T u is added to the
+// source's running sums and, summed over the lanes, subtracted from the
+// target's.  That second sum runs on the matrix cores: a 16 x 16 x 4 FP32
+// product of a matrix whose row t % 16 is one and the other rows zero with the
+// 64 lanes' values adds four lanes' sum to each of 16 columns of the target's
+// row (exact products, FP32 sums), so a trip issues three of them instead of 21
+// dependent DPP adds and three lane reads; the columns are added once per list
+// flush.  A value that is not finite would reach the other rows as 0 x inf:
+// such a flush is seen by its sums and its target side taken again with the
+// lane sums.
 //
-// The accumulators are field-major (cell adjoint q of cell c at q * cap + c),
-// so the lanes of one atomic instruction, neighbouring cells or the
-// particles of one leaf, share a few cache lines; and they come in kXcd
-// copies, one per XCD: a wave adds into the copy of the XCD it runs on (read
-// from the hardware XCC id), so no cache line is updated from two XCDs.  The
-// cells of the top levels are accepted by far more groups than deeper ones
-// (a few cache lines of them take a quarter of all the atomics), so the first
-// kHotCells cells get kHotCopies copies, kHotCopies / kXcd per XCD chosen by
-// the workgroup.  The copies are summed after the walk.
+// Source terms reach FP64 accumulators with one atomic per value, source and
+// group.  They come in kXcd copies, one per XCD: a wave adds into the copy of
+// the XCD it runs on (read from the hardware XCC id), so no cache line is
+// updated from two XCDs.  The cells of the top levels are accepted by far more
+// groups than deeper ones (a few cache lines of them take a quarter of all the
+// atomics), so the first kHotCells cells get kHotCopies copies, kHotCopies /
+// kXcd per XCD chosen by the workgroup.  The copies are summed after the walk.
+// A cell's (particle's) values lie together, and a chunk's sums are turned
+// through LDS so that the lanes of one atomic instruction add to consecutive
+// addresses: the cells of a list come in runs of siblings, and 64 cells of ten
+// values are 40 to 60 cache lines instead of ten times the 15 or so runs.
+//
+// Bound: the L2's atomics, which go at 2.35e10 requests of 64 bytes per second
+// (1.9e11 adds where eight lanes fill a request): 2.0e9 adds of the cells at 1M
+// (theta 0.4) take 18.5 ms with the pairs left out, everything but the adds 13.9
+// ms (84 VALU instructions and a reciprocal root per particle-cell pair).
+// Measured at 1M, theta 0.4: 19.9 ms, where lane sums by DPP, accumulators
+// field by field and particle pairs evaluated once per side took 23.0.
 #include "walk_common.h"
 
 namespace bh {
 
 constexpr uint32_t kXcd = 8;
+constexpr uint32_t kCellAdj = 10;  // a cell's adjoints: M, com xyz, Q xx yy zz xy xz yz
 
 // XCD (XCC) that runs the calling wave.
 __device__ __forceinline__ uint32_t xcc_id() {
@@ -56,69 +69,71 @@ struct VjpArgs {
     const uint32_t *gbeg, *ngroups;
     uint32_t *work, *spill, *status;
     uint32_t ring, logw;  // logw: 2^logw waves per group (split walks)
-    // copy 0 of kXcd accumulators; copy k at + k * lstride / gstride.  Field
-    // major: cell adjoint q of cell c at lcell[q * cap + c], particle
-    // adjoint q of particle j at gsrc[q * nmax + j], so that the lanes of one
-    // atomic instruction (neighbouring cells or particles) share cache lines
+    // copy 0 of kXcd accumulators; copy k at + k * lstride / gstride: cell
+    // adjoint q of cell c at lcell[kCellAdj * c + q], particle adjoint q of
+    // particle j at gsrc[4 * j + q]
     double *lcell, *gsrc;
-    uint64_t lstride, gstride, cap, nmax;
+    uint64_t lstride, gstride;
     // kHotCopies copies of the first kHotCells cells' adjoints, copy k at
-    // lhot + k * kHotCopy, field q of cell c at + q * kHotField + c
+    // lhot + k * kHotCopy
     double *lhot;
     float eps2;
 };
 
 __device__ __forceinline__ float rsqv(float v) { return __builtin_amdgcn_rsqf(v); }
 
-// Adjoint of one particle-cell term (records as in the force walk:
-// A = (com, M), B = -3 (Qxx, Qyy, Qzz, Qxy), C = (-3 Qxz, -3 Qyz, tr/2, -3 tr/2)).
-// Returns w = J^T u and adds the cell-side terms to running sums.  With
-// B = -3 Q, ctr = -3 tr / 2, ud = u.d:
-//   w = u [M r^-3 + ctr r^-5 - 5/2 dBd r^-7]
-//     + d [-3 M ud r^-5 - 5 ctr ud r^-7 - 5 uBd r^-7 + 35/2 dBd ud r^-9]
-//     + Bu r^-5 - 5 ud Bd r^-7
-// dF/dM . u = ud r^-3 (added to sM).  dF/dQ . u for the six stored entries:
-// with v = r^-5 u - 5/2 ud r^-7 d,
+// Adjoint of one particle-cell term.  A = (com, M); B = (xx, yy, zz, xy) and
+// C = (xz, yz, e) of the trace-free B' = -3 Q + tr(Q) I with e = tr(Q) eps^2,
+// in which the force is F = M d r^-3 + q r^-5 - 5/2 s d r^-7, q = B'd, s = d.q +
+// e (Eq. (2) with the trace taken into the quadrupole term).  Returns
+//   w = J^T u = u (M r^-3 - 5/2 s r^-7) + B'u r^-5 - 5 ud r^-7 q
+//       + d [ud (-3 M r^-5 + 35/2 s r^-9) - 5 uq r^-7],
+// ud = u.d, uq = u.q, and adds the cell-side terms to running sums:
+// dF/dM . u = ud r^-3 to sM.  dF/dQ . u for the six stored entries: with v =
+// r^-5 u - 5/2 ud r^-7 d,
 //   diagonal  -3 v_a d_a - 3/2 ud r^-5,   off-diagonal  -3 (v_a d_b + v_b d_a);
 // sQ collects the v-terms unscaled (diagonal v_a d_a, off-diagonal
 // v_a d_b + v_b d_a) and st the ud r^-5, so that the factors -3 and -3/2 are
 // applied once per sum (pc_adj_finish).
-__device__ __forceinline__ void pc_adj(const float4 &T, const float4 &U, const float4 &A,
-                                       const float4 &B, const float4 &C, float eps2, float &wx,
-                                       float &wy, float &wz, float &sM, float *sQ, float &st) {
-    const float dx = A.x - T.x, dy = A.y - T.y, dz = A.z - T.z;
+struct CellSums {
+    float w[3], M, Q[6], t;
+};
+
+__device__ __forceinline__ void pc_adj(const float *T, const float *U, const float4 &A,
+                                       const float4 &B, const float4 &C, float eps2, float w[3],
+                                       CellSums &c) {
+    const float dx = A.x - T[0], dy = A.y - T[1], dz = A.z - T[2];
     const float r2 = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, eps2)));
     const float ri = rsqv(r2);
     const float ri2 = ri * ri, ri3 = ri * ri2, ri5 = ri3 * ri2, ri7 = ri5 * ri2;
-    const float ud = fmaf(U.x, dx, fmaf(U.y, dy, U.z * dz));
-    const float bdx = fmaf(B.x, dx, fmaf(B.w, dy, C.x * dz));
-    const float bdy = fmaf(B.w, dx, fmaf(B.y, dy, C.y * dz));
-    const float bdz = fmaf(C.x, dx, fmaf(C.y, dy, B.z * dz));
-    const float bux = fmaf(B.x, U.x, fmaf(B.w, U.y, C.x * U.z));
-    const float buy = fmaf(B.w, U.x, fmaf(B.y, U.y, C.y * U.z));
-    const float buz = fmaf(C.x, U.x, fmaf(C.y, U.y, B.z * U.z));
-    const float q2 = fmaf(dx, bdx, fmaf(dy, bdy, dz * bdz)) * ri2;  // dBd / r^2
-    const float uBd = fmaf(U.x, bdx, fmaf(U.y, bdy, U.z * bdz));
-    const float M = A.w, ctr = C.w;
-    const float cu = fmaf(fmaf(-2.5f, q2, ctr), ri5, M * ri3);
-    const float udr7 = ud * ri7;
-    const float cd =
-        fmaf(ud, fmaf(-3.f * M, ri5, fmaf(17.5f, q2, -5.f * ctr) * ri7), -5.f * uBd * ri7);
-    const float cb = -5.f * udr7;
-    wx = fmaf(cu, U.x, fmaf(cd, dx, fmaf(bux, ri5, cb * bdx)));
-    wy = fmaf(cu, U.y, fmaf(cd, dy, fmaf(buy, ri5, cb * bdy)));
-    wz = fmaf(cu, U.z, fmaf(cd, dz, fmaf(buz, ri5, cb * bdz)));
-    sM = fmaf(ud, ri3, sM);
-    st = fmaf(ud, ri5, st);
-    const float h = -2.5f * udr7;
-    const float vx = fmaf(h, dx, ri5 * U.x), vy = fmaf(h, dy, ri5 * U.y),
-                vz = fmaf(h, dz, ri5 * U.z);
-    sQ[0] = fmaf(vx, dx, sQ[0]);
-    sQ[1] = fmaf(vy, dy, sQ[1]);
-    sQ[2] = fmaf(vz, dz, sQ[2]);
-    sQ[3] = fmaf(vx, dy, fmaf(vy, dx, sQ[3]));
-    sQ[4] = fmaf(vx, dz, fmaf(vz, dx, sQ[4]));
-    sQ[5] = fmaf(vy, dz, fmaf(vz, dy, sQ[5]));
+    const float ud = fmaf(U[0], dx, fmaf(U[1], dy, U[2] * dz));
+    const float qx = fmaf(B.x, dx, fmaf(B.w, dy, C.x * dz));
+    const float qy = fmaf(B.w, dx, fmaf(B.y, dy, C.y * dz));
+    const float qz = fmaf(C.x, dx, fmaf(C.y, dy, B.z * dz));
+    const float bux = fmaf(B.x, U[0], fmaf(B.w, U[1], C.x * U[2]));
+    const float buy = fmaf(B.w, U[0], fmaf(B.y, U[1], C.y * U[2]));
+    const float buz = fmaf(C.x, U[0], fmaf(C.y, U[1], B.z * U[2]));
+    const float s7 = fmaf(dx, qx, fmaf(dy, qy, fmaf(dz, qz, C.z))) * ri7;
+    const float uq = fmaf(U[0], qx, fmaf(U[1], qy, U[2] * qz));
+    const float m3 = A.w * ri3;
+    const float cu = fmaf(-2.5f, s7, m3);
+    const float cb = -5.f * (ud * ri7);
+    const float cd = fmaf(ud, fmaf(-3.f, m3, 17.5f * s7) * ri2, -5.f * (uq * ri7));
+    w[0] = fmaf(cu, U[0], fmaf(cd, dx, fmaf(bux, ri5, cb * qx)));
+    w[1] = fmaf(cu, U[1], fmaf(cd, dy, fmaf(buy, ri5, cb * qy)));
+    w[2] = fmaf(cu, U[2], fmaf(cd, dz, fmaf(buz, ri5, cb * qz)));
+    c.w[0] += w[0]; c.w[1] += w[1]; c.w[2] += w[2];
+    c.M = fmaf(ud, ri3, c.M);
+    c.t = fmaf(ud, ri5, c.t);
+    const float h = 0.5f * cb;
+    const float vx = fmaf(h, dx, ri5 * U[0]), vy = fmaf(h, dy, ri5 * U[1]),
+                vz = fmaf(h, dz, ri5 * U[2]);
+    c.Q[0] = fmaf(vx, dx, c.Q[0]);
+    c.Q[1] = fmaf(vy, dy, c.Q[1]);
+    c.Q[2] = fmaf(vz, dz, c.Q[2]);
+    c.Q[3] = fmaf(vx, dy, fmaf(vy, dx, c.Q[3]));
+    c.Q[4] = fmaf(vx, dz, fmaf(vz, dx, c.Q[4]));
+    c.Q[5] = fmaf(vy, dz, fmaf(vz, dy, c.Q[5]));
 }
 
 // dL/dQ of the six stored entries from the sums of pc_adj.
@@ -134,18 +149,18 @@ __device__ __forceinline__ void pc_adj_finish(float *sQ, float st) {
 
 // Adjoint of one particle-particle term: F = m d r^-3, J = m (I r^-3 - 3 d d^T r^-5).
 template <bool kEps0>
-__device__ __forceinline__ void pp_adj(const float4 &T, const float4 &U, const float4 &P,
-                                       float eps2, float &wx, float &wy, float &wz, float &gm) {
-    const float dx = P.x - T.x, dy = P.y - T.y, dz = P.z - T.z;
+__device__ __forceinline__ void pp_adj(const float *T, const float *U, const float4 &P,
+                                       float eps2, float w[3], float &gm) {
+    const float dx = P.x - T[0], dy = P.y - T[1], dz = P.z - T[2];
     const float r2 = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, eps2)));
     float ri = rsqv(r2);
     if (kEps0) ri = r2 > 0.f ? ri : 0.f;
     const float ri2 = ri * ri, ri3 = ri * ri2, ri5 = ri3 * ri2;
-    const float ud = fmaf(U.x, dx, fmaf(U.y, dy, U.z * dz));
+    const float ud = fmaf(U[0], dx, fmaf(U[1], dy, U[2] * dz));
     const float c1 = P.w * ri3, c2 = -3.f * P.w * ud * ri5;
-    wx = fmaf(c1, U.x, c2 * dx);
-    wy = fmaf(c1, U.y, c2 * dy);
-    wz = fmaf(c1, U.z, c2 * dz);
+    w[0] = fmaf(c1, U[0], c2 * dx);
+    w[1] = fmaf(c1, U[1], c2 * dy);
+    w[2] = fmaf(c1, U[2], c2 * dz);
     gm = ud * ri3;
 }
 
@@ -166,36 +181,78 @@ __device__ __forceinline__ float wave_total(float v) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
+constexpr uint32_t kTile = 16;            // targets of one accumulator tile
+constexpr uint32_t kTiles = 2;            // tiles taken at once
+constexpr uint32_t kTurn = 32 * kCellAdj; // values turned through LDS at once
+
 struct VjpLds {
-    float4 stage[1][kChunk + 1];  // particle sources of one chunk + the null source
-    uint32_t sidx[kChunk + 1];    // particle index of staged particle sources
-    float4 tp[64], tu[64];        // the group's targets: position + mass, cotangent
-    uint32_t tidx[64];
+    float4 tp[64];  // the group's targets: position, u_x
+    float2 tu[64];  // u_y, u_z
+    union {
+        float turn[kTurn];              // sums of a chunk on their way to the atomics
+        float4 tsum[kTile * kTiles];    // target sums of a flush
+    };
     TravLds T;
 };
 
-struct VPhase {
-    uint32_t T, r, slice, tidx;
-    bool act;
-    float4 tgt, u;
-    float gx, gy, gz;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// Target sums of up to kTiles x kTile targets: d[tile][k] is component k, row
+// t of a tile in lanes 16 (t / 4) .. + 15, register t % 4.
+struct TargetSums {
+    f32x4 d[kTiles][3];
 };
 
-// Target terms of one staged chunk of particle sources for one phase.
-template <bool kEps0>
-__device__ __forceinline__ void vjp_targets(VPhase &ph, uint32_t n, const VjpLds &L, float eps2) {
-    const uint32_t r = ph.r;
-    const uint32_t rounds = (n + r - 1u) / r;
-    uint32_t k = ph.slice;
-    for (uint32_t j = 0; j < rounds; ++j, k += r) {
-        const uint32_t kk = k < n ? k : (uint32_t)kNull;
-        float wx, wy, wz, gm;
-        pp_adj<kEps0>(ph.tgt, ph.u, L.stage[0][kk], eps2, wx, wy, wz, gm);
-        if (L.sidx[kk] == ph.tidx) wx = wy = wz = 0.f;
-        ph.gx -= wx;
-        ph.gy -= wy;
-        ph.gz -= wz;
+// w of target `row` of the tile (sel: one in the lanes of that row, else zero)
+__device__ __forceinline__ void add_target(f32x4 d[3], float sel, const float w[3]) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) d[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(sel, w[k], d[k], 0, 0, 0);
+}
+
+// sel of the next row: its lanes rotated by one inside each row of 16
+__device__ __forceinline__ float next_row(float sel) {
+    return __int_as_float(
+        __builtin_amdgcn_update_dpp(0, __float_as_int(sel), 0x121, 0xf, 0xf, false));
+}
+
+// Whether every sum is finite.
+__device__ __forceinline__ bool sums_finite(const TargetSums &s) {
+    float z = 0.f;
+#pragma unroll
+    for (uint32_t i = 0; i < kTiles; ++i)
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) z = fmaf(s.d[i][k][r], 0.f, z);
+    return ballot(!(z == 0.f)) == 0ull;
+}
+
+// Sum over the 16 lanes of a DPP row, in its last lane.
+__device__ __forceinline__ float row_total(float v) {
+    v = dpp_add<0x111, 0xf>(v);
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    return dpp_add<0x118, 0xf>(v);
+}
+
+// Take the sums from lane tb + t's target terms g, t < kTiles kTile.
+__device__ __forceinline__ void take_targets(const TargetSums &s, VjpLds &L, uint32_t lane,
+                                             uint32_t tb, float g[3]) {
+#pragma unroll
+    for (uint32_t i = 0; i < kTiles; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float x = row_total(s.d[i][0][r]), y = row_total(s.d[i][1][r]),
+                        z = row_total(s.d[i][2][r]);
+            if ((lane & 15u) == 15u)
+                L.tsum[i * kTile + (lane >> 4) * 4u + (uint32_t)r] = make_float4(x, y, z, 0.f);
+        }
+    wave_sync();
+    if (lane - tb < kTiles * kTile) {
+        const float4 o = L.tsum[lane - tb];
+        g[0] -= o.x; g[1] -= o.y; g[2] -= o.z;
     }
+    wave_sync();
 }
 
 template <bool kEps0, bool kSplit>
@@ -216,101 +273,160 @@ __device__ void vjp_group(const VjpArgs &a, uint32_t g, uint32_t w, uint32_t lan
     const uint32_t ti = gb + (own ? lane : 0u);
     const float4 me = a.xyzm[ti];
     const GroupBox b = group_box(me, own);
-    L.tp[lane] = own ? me : make_float4(1e30f, 1e30f, 1e30f, 0.f);
-    L.tu[lane] = own ? a.u[ti] : make_float4(0.f, 0.f, 0.f, 0.f);
-    L.tidx[lane] = own ? ti : kNone;
-    if (lane == 0) {
-        L.stage[0][kNull] = make_float4(1e30f, 1e30f, 1e30f, 0.f);
-        L.sidx[kNull] = kNone;
-    }
+    const float4 mu = a.u[ti];
+    L.tp[lane] = make_float4(me.x, me.y, me.z, mu.x);
+    L.tu[lane] = make_float2(mu.y, mu.z);
+    float gt[3] = {0.f, 0.f, 0.f};  // target terms of lane t's target
 
-    VPhase p1, p2;
-    plan_phases(gn, p1.T, p1.r, p2.T, p2.r);
-    p1.act = lane < p1.T * p1.r;
-    p1.slice = p1.act ? lane / p1.T : 0u;
-    p1.tidx = gb + (p1.act ? lane % p1.T : 0u);
-    p1.tgt = a.xyzm[p1.tidx];
-    p1.u = a.u[p1.tidx];
-    p1.gx = p1.gy = p1.gz = 0.f;
-    p2.act = p2.T && lane < p2.T * p2.r;
-    p2.slice = p2.act ? lane / p2.T : 0u;
-    p2.tidx = gb + (p2.act ? p1.T + lane % p2.T : 0u);
-    p2.tgt = a.xyzm[p2.tidx];
-    p2.u = a.u[p2.tidx];
-    p2.gx = p2.gy = p2.gz = 0.f;
-    const bool two = p2.T != 0u;
-
-    // particle-cell lists: lane = cell (a null cell, zero mass and moments, far
-    // away, on lanes past the list), looping over the group's targets; each
-    // pair's J^T u serves both sides: summed over targets into the cell's
-    // adjoint, and over the lanes (a DPP sum) into the target's
-    float gtx = 0.f, gty = 0.f, gtz = 0.f;  // target side of lane t's target
-    auto flush_pc = [&](uint32_t n) {
-        for (uint32_t base = 0; base < n; base += kChunk) {
-            const uint32_t m = n - base < (uint32_t)kChunk ? n - base : (uint32_t)kChunk;
-            const bool valid = lane < m;
-            const uint32_t c = L.T.pcidx[base + (valid ? lane : 0u)];
-            float4 r0 = make_float4(1e18f, 1e18f, 1e18f, 0.f), r1 = make_float4(0.f, 0.f, 0.f, 0.f),
-                   r2 = r1;
-            if (valid) {
-                r0 = a.P0[c];
-                r1 = a.P1[c];
-                r2 = a.P2[c];
-            }
-            float sw[3] = {0.f, 0.f, 0.f}, sM = 0.f, st = 0.f;
-            float sQ[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            for (uint32_t t = 0; t < gn; ++t) {
-                float wx, wy, wz;
-                pc_adj(L.tp[t], L.tu[t], r0, r1, r2, a.eps2, wx, wy, wz, sM, sQ, st);
-                sw[0] += wx; sw[1] += wy; sw[2] += wz;
-                const float tx = wave_total(wx), ty = wave_total(wy), tz = wave_total(wz);
-                if (lane == t) {
-                    gtx -= tx;
-                    gty -= ty;
-                    gtz -= tz;
-                }
-            }
-            pc_adj_finish(sQ, st);
-            if (valid) {
-                const bool hot = c < kHotCells;
-                double *lc = hot ? lhx + c : lcx + c;
-                const uint64_t fs = hot ? kHotField : a.cap;
-                add_l2(lc, (double)sM);
-                add_l2(lc + fs, (double)sw[0]);
-                add_l2(lc + 2 * fs, (double)sw[1]);
-                add_l2(lc + 3 * fs, (double)sw[2]);
+    // one trip: target t's position and cotangent
+    auto target = [&](uint32_t t, float T[3], float U[3]) {
+        const float4 p = L.tp[t];
+        const float2 q = L.tu[t];
+        T[0] = p.x; T[1] = p.y; T[2] = p.z;
+        U[0] = p.w; U[1] = q.x; U[2] = q.y;
+    };
+    // all trips of targets [tb, tb + kTiles kTile): pair(t, w) evaluates one
+    auto trips = [&](uint32_t tb, TargetSums &ts, auto &&pair) {
 #pragma unroll
-                for (int q = 0; q < 6; ++q) add_l2(lc + (4 + q) * fs, (double)sQ[q]);
+        for (uint32_t i = 0; i < kTiles; ++i) {
+            const uint32_t t0 = tb + i * kTile, t1 = gn < t0 + kTile ? gn : t0 + kTile;
+            float sel = (lane & 15u) == 0u ? 1.f : 0.f;
+            for (uint32_t t = t0; t < t1; ++t) {
+                float wv[3];
+                pair(t, wv);
+                add_target(ts.d[i], sel, wv);
+                sel = next_row(sel);
+            }
+        }
+    };
+    // the target side of a flush whose sums are not all finite, by lane sums
+    auto lane_sums = [&](uint32_t tb, auto &&pair) {
+        for (uint32_t t = tb; t < gn && t < tb + kTiles * kTile; ++t) {
+            float wv[3];
+            pair(t, wv);
+            const float x = wave_total(wv[0]), y = wave_total(wv[1]), z = wave_total(wv[2]);
+            if (lane == t) {
+                gt[0] -= x; gt[1] -= y; gt[2] -= z;
+            }
+        }
+    };
+
+    // particle-cell list; lanes past it hold a null cell (zero mass and
+    // moments, far away)
+    auto flush_pc = [&](uint32_t n) {
+        float4 A, B, C;
+        auto load = [&](uint32_t base) {
+            A = make_float4(1e18f, 1e18f, 1e18f, 0.f);
+            B = C = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (base + lane < n) {
+                const uint32_t c = L.T.pcidx[base + lane];
+                A = a.P0[c];
+                B = a.P1[c];
+                C = a.P2[c];
+                const float tr = 2.f * C.z;  // the trace into the quadrupole
+                B.x += tr; B.y += tr; B.z += tr;
+                C.z = tr * a.eps2;
+            }
+        };
+        for (uint32_t tb = 0; tb < gn; tb += kTiles * kTile) {
+            TargetSums ts{};
+            for (uint32_t base = 0; base < n; base += kChunk) {
+                const uint32_t m = n - base < (uint32_t)kChunk ? n - base : (uint32_t)kChunk;
+                load(base);
+                CellSums cs{};
+                trips(tb, ts, [&](uint32_t t, float wv[3]) {
+                    float T[3], U[3];
+                    target(t, T, U);
+                    pc_adj(T, U, A, B, C, a.eps2, wv, cs);
+                });
+                pc_adj_finish(cs.Q, cs.t);
+                const float v[kCellAdj] = {cs.M,    cs.w[0], cs.w[1], cs.w[2], cs.Q[0],
+                                           cs.Q[1], cs.Q[2], cs.Q[3], cs.Q[4], cs.Q[5]};
+                for (uint32_t half = 0; half < m; half += 32u) {
+                    wave_sync();
+                    if ((lane & 32u) == half) {
+#pragma unroll
+                        for (uint32_t q = 0; q < kCellAdj; ++q)
+                            L.turn[(lane & 31u) * kCellAdj + q] = v[q];
+                    }
+                    wave_sync();
+#pragma unroll
+                    for (uint32_t r = 0; r < kTurn / 64u; ++r) {
+                        const uint32_t f = r * 64u + lane, k = f / kCellAdj, q = f - k * kCellAdj;
+                        if (half + k < m) {
+                            const uint32_t c = L.T.pcidx[base + half + k];
+                            double *lc = c < kHotCells ? lhx : lcx;
+                            add_l2(lc + (size_t)c * kCellAdj + q, (double)L.turn[f]);
+                        }
+                    }
+                }
+                wave_sync();
+            }
+            if (sums_finite(ts)) {
+                take_targets(ts, L, lane, tb, gt);
+            } else {
+                for (uint32_t base = 0; base < n; base += kChunk) {
+                    load(base);
+                    CellSums cs{};
+                    lane_sums(tb, [&](uint32_t t, float wv[3]) {
+                        float T[3], U[3];
+                        target(t, T, U);
+                        pc_adj(T, U, A, B, C, a.eps2, wv, cs);
+                    });
+                }
             }
         }
         wave_sync();
     };
+    // particle-particle list; the self pair contributes nothing
     auto flush_pp = [&](uint32_t n) {
-        for (uint32_t base = 0; base < n; base += kChunk) {
-            const uint32_t m = n - base < (uint32_t)kChunk ? n - base : (uint32_t)kChunk;
-            const bool valid = lane < m;
-            const uint32_t j = L.T.ppidx[base + (valid ? lane : 0u)];
-            const float4 P = a.xyzm[j];
-            wave_sync();
-            L.stage[0][lane] = P;
-            L.sidx[lane] = valid ? j : kNone;
-            wave_sync();
-            vjp_targets<kEps0>(p1, m, L, a.eps2);
-            if (two) vjp_targets<kEps0>(p2, m, L, a.eps2);
-            float sx = 0.f, sy = 0.f, sz = 0.f, sm = 0.f;
-            for (uint32_t t = 0; t < gn; ++t) {
-                float wx, wy, wz, gm;
-                pp_adj<kEps0>(L.tp[t], L.tu[t], P, a.eps2, wx, wy, wz, gm);
-                if (L.tidx[t] != j) {
-                    sx += wx; sy += wy; sz += wz; sm += gm;
-                }
+        float4 P;
+        uint32_t j;
+        auto load = [&](uint32_t base) {
+            P = make_float4(1e18f, 1e18f, 1e18f, 0.f);
+            j = kNone;
+            if (base + lane < n) {
+                j = L.T.ppidx[base + lane];
+                P = a.xyzm[j];
             }
-            if (valid) {
-                double *gs = gsx + j;
-                add_l2(gs, (double)sx);
-                add_l2(gs + a.nmax, (double)sy);
-                add_l2(gs + 2 * a.nmax, (double)sz);
-                add_l2(gs + 3 * a.nmax, (double)sm);
+        };
+        for (uint32_t tb = 0; tb < gn; tb += kTiles * kTile) {
+            TargetSums ts{};
+            for (uint32_t base = 0; base < n; base += kChunk) {
+                const uint32_t m = n - base < (uint32_t)kChunk ? n - base : (uint32_t)kChunk;
+                load(base);
+                float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+                auto pair = [&](uint32_t t, float wv[3]) {
+                    float T[3], U[3], gm;
+                    target(t, T, U);
+                    pp_adj<kEps0>(T, U, P, a.eps2, wv, gm);
+                    if (gb + t == j) wv[0] = wv[1] = wv[2] = gm = 0.f;
+                    s.x += wv[0]; s.y += wv[1]; s.z += wv[2]; s.w += gm;
+                };
+                trips(tb, ts, pair);
+                wave_sync();
+                reinterpret_cast<float4 *>(L.turn)[lane] = s;
+                wave_sync();
+#pragma unroll
+                for (uint32_t r = 0; r < 4u; ++r) {
+                    const uint32_t f = r * 64u + lane, k = f >> 2;
+                    if (k < m)
+                        add_l2(gsx + 4ull * L.T.ppidx[base + k] + (f & 3u), (double)L.turn[f]);
+                }
+                wave_sync();
+            }
+            if (sums_finite(ts)) {
+                take_targets(ts, L, lane, tb, gt);
+            } else {
+                for (uint32_t base = 0; base < n; base += kChunk) {
+                    load(base);
+                    lane_sums(tb, [&](uint32_t t, float wv[3]) {
+                        float T[3], U[3], gm;
+                        target(t, T, U);
+                        pp_adj<kEps0>(T, U, P, a.eps2, wv, gm);
+                        if (gb + t == j) wv[0] = wv[1] = wv[2] = 0.f;
+                    });
+                }
             }
         }
         wave_sync();
@@ -320,37 +436,16 @@ __device__ void vjp_group(const VjpArgs &a, uint32_t g, uint32_t w, uint32_t lan
     const TreeView tv{a.wA, a.wN, a.ring, a.status};
     traverse<false, kSplit>(tv, b, lane, L.T, spill, cnt_pc, cnt_pp, flush_pc, flush_pp,
                             Share{w, a.logw});
-
-    // ---- sum the slices of each target and add the target terms
-    float rx = 0.f, ry = 0.f, rz = 0.f;
-    L.stage[0][lane] = make_float4(p1.gx, p1.gy, p1.gz, 0.f);
-    wave_sync();
-    if (lane < p1.T)
-        for (uint32_t k = 0; k < p1.r; ++k) {
-            const float4 o = L.stage[0][lane + k * p1.T];
-            rx += o.x; ry += o.y; rz += o.z;
-        }
-    if (two) {
-        wave_sync();
-        L.stage[0][lane] = make_float4(p2.gx, p2.gy, p2.gz, 0.f);
-        wave_sync();
-        if (lane >= p1.T && lane < gn)
-            for (uint32_t k = 0; k < p2.r; ++k) {
-                const float4 o = L.stage[0][lane - p1.T + k * p2.T];
-                rx += o.x; ry += o.y; rz += o.z;
-            }
-    }
     if (own) {
-        double *gs = gsx + ti;
-        add_l2(gs, (double)rx + (double)gtx);
-        add_l2(gs + a.nmax, (double)ry + (double)gty);
-        add_l2(gs + 2 * a.nmax, (double)rz + (double)gtz);
+        double *gs = gsx + 4ull * ti;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) add_l2(gs + k, (double)gt[k]);
     }
     wave_sync();
 }
 
 template <bool kEps0, bool kSplit>
-__global__ __launch_bounds__(64) void k_walk_vjp(VjpArgs a) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_walk_vjp(VjpArgs a) {
     __shared__ VjpLds L;
     const uint32_t lane = threadIdx.x;
     uint32_t *spill = a.spill + (size_t)blockIdx.x * kStackMax;
@@ -379,54 +474,38 @@ __global__ __launch_bounds__(256) void k_usort(const float *__restrict__ u,
     us[i] = make_float4(u[3 * p], u[3 * p + 1], u[3 * p + 2], 0.f);
 }
 
-// Zero `copies` copies (copy k at k * stride) of F fields of cnt entries each
-// (field q at q * fs; cnt = the cell count of the current tree when ls is
-// given, at most `lim`).
+// Zero `copies` copies (copy k at k * stride) of cnt entries of F values each
+// (cnt = the cell count of the current tree when ls is given, at most lim).
 __global__ __launch_bounds__(256) void k_zero_xcd(double *p, uint64_t cnt, uint32_t F,
-                                                  uint64_t fs, uint64_t stride, uint32_t copies,
+                                                  uint64_t stride, uint32_t copies,
                                                   const uint32_t *ls, uint64_t lim) {
     if (ls) cnt = ls[kLevels] < lim ? ls[kLevels] : lim;
     const uint64_t total = cnt * F;
     for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < total;
-         i += (uint64_t)gridDim.x * 256) {
-        const uint64_t q = i / cnt, e = i - q * cnt;
-        for (uint32_t k = 0; k < copies; ++k) p[q * fs + e + k * stride] = 0.0;
-    }
+         i += (uint64_t)gridDim.x * 256)
+        for (uint32_t k = 0; k < copies; ++k) p[i + k * stride] = 0.0;
 }
 
-
-// Fold the kXcd copies (same layout as k_zero_xcd) into copy 0.
+// Fold the kXcd copies (same layout as k_zero_xcd) into copy 0; with hot, the
+// first kHotCells cells instead from their kHotCopies copies.
 __global__ __launch_bounds__(256) void k_fold_xcd(double *p, uint64_t cnt, uint32_t F,
-                                                  uint64_t fs, uint64_t stride,
-                                                  const uint32_t *ls) {
+                                                  uint64_t stride, const uint32_t *ls,
+                                                  const double *__restrict__ hot) {
     if (ls) cnt = ls[kLevels];
     const uint64_t total = cnt * F;
     for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < total;
          i += (uint64_t)gridDim.x * 256) {
-        const uint64_t q = i / cnt, e = i - q * cnt, o = q * fs + e;
-        double v = p[o];
-#pragma unroll
-        for (uint32_t k = 1; k < kXcd; ++k) v += p[o + k * stride];
-        p[o] = v;
-    }
-}
-
-// Add the kHotCopies copies of the first kHotCells cells' adjoints (copy k at
-// k * kHotCopy, field q at q * kHotField) to copy 0 of the cell accumulators
-// (field q of cell c at q * cap + c).
-__global__ __launch_bounds__(256) void k_fold_hot(const double *__restrict__ hot, double *lcell,
-                                                  uint64_t cap, const uint32_t *ls) {
-    const uint32_t nc = ls[kLevels] < kHotCells ? ls[kLevels] : kHotCells;
-    const uint32_t total = nc * 10u;
-    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < total; i += gridDim.x * 256) {
-        const uint32_t q = i / nc, e = i - q * nc;
-        const double *h = hot + q * kHotField + e;
         double v = 0.0;
-        for (uint32_t k = 0; k < kHotCopies; ++k) v += h[k * kHotCopy];
-        lcell[q * cap + e] += v;
+        if (hot && i < (uint64_t)kHotCells * F) {
+#pragma unroll 8
+            for (uint32_t k = 0; k < kHotCopies; ++k) v += hot[i + k * kHotCopy];
+        } else {
+#pragma unroll
+            for (uint32_t k = 0; k < kXcd; ++k) v += p[i + k * stride];
+        }
+        p[i] = v;
     }
 }
-
 
 // Each particle adds the adjoints of the cells holding it (its leaf and the
 // leaf's ancestors), then the total is scaled and added to the caller-order
@@ -436,18 +515,18 @@ __global__ __launch_bounds__(256) void k_moments_vjp(Cells c, const float4 *__re
                                                      const uint32_t *__restrict__ cid,
                                                      const double *__restrict__ lcell,
                                                      const double *__restrict__ gsrc,
-                                                     uint64_t cap, uint64_t nmax, uint32_t n,
-                                                     float coef, float *g_pos, float *g_mass) {
+                                                     uint32_t n, float coef, float *g_pos,
+                                                     float *g_mass) {
     const uint32_t k = blockIdx.x * 256 + threadIdx.x;
     if (k >= n) return;
     const float4 p = xyzm[k];
     const double xk = p.x, yk = p.y, zk = p.z, mk = p.w;
-    double gx = gsrc[k], gy = gsrc[k + nmax], gz = gsrc[k + 2 * nmax], gm = gsrc[k + 3 * nmax];
+    const double *gk = gsrc + 4ull * k;
+    double gx = gk[0], gy = gk[1], gz = gk[2], gm = gk[3];
     for (uint32_t cc = leafof[k]; cc != kNone; cc = c.parent[cc]) {
-        const double *l = lcell + cc;
-        const double lM = l[0], lx = l[cap], ly = l[2 * cap], lz = l[3 * cap];
-        const double qxx = l[4 * cap], qyy = l[5 * cap], qzz = l[6 * cap], qxy = l[7 * cap],
-                     qxz = l[8 * cap], qyz = l[9 * cap];
+        const double *l = lcell + (size_t)cc * kCellAdj;
+        const double lM = l[0], lx = l[1], ly = l[2], lz = l[3];
+        const double qxx = l[4], qyy = l[5], qzz = l[6], qxy = l[7], qxz = l[8], qyz = l[9];
         const double M = c.M[cc];
         const double sx = xk - c.S[3 * (size_t)cc] / M, sy = yk - c.S[3 * (size_t)cc + 1] / M,
                      sz = zk - c.S[3 * (size_t)cc + 2] / M;
@@ -471,15 +550,15 @@ __global__ __launch_bounds__(256) void k_moments_vjp(Cells c, const float4 *__re
     if (g_mass) g_mass[o] += (float)(coef * gm);
 }
 
-// Waves per group of a split adjoint walk, as in the force walk; every wave
-// adds its targets' sums by atomics of its own, so two waves stop paying
-// earlier.  Disk + halo, theta 0.4, us by waves per group (1 / 2 / 4 / 8):
-// n = 1000: 289 / 184 / 137 / 101; 4096: 991 / 566 / 341 / 247; 16384: 1692 /
-// 1074 / 1034 / 923; 32768: 2156 / 1825 / 1659 / 1989; 65536: 2882 / 2647 /
-// 2925; at theta 0.6 two waves are as fast as one at 65536 and 17% slower at
-// 98304.
+// Waves per group of a split adjoint walk, as in the force walk, but its sums
+// leave by atomics, which a split does not multiply, so it pays up to larger
+// sets.  Disk + halo, theta 0.4 / 0.6, whole calls in us by waves per group:
+// n = 1000: 1 220 / 210, 8 88 / 96; 16384: 1 1433 / 745, 4 736 / 383, 8 575 /
+// 343; 65536: 1 2667 / 1287, 4 1818 / 892, 8 1840 / 897; 131072: 1 3957 / 1934,
+// 4 3122 / 1722, 8 3138 / 1708; 262144: 1 6323 / 3123, 4 5536 / 3270; 1M: 1 20506
+// / 9955, 4 21548 / 12058.
 static uint32_t vjp_logw(int64_t n) {
-    return n <= 8192 ? 3u : (n <= 24576 ? 2u : (n <= 65536 ? 1u : 0u));
+    return n <= 98304 ? 3u : (n <= 229376 ? 2u : 0u);
 }
 
 template <bool kSplit>
@@ -496,15 +575,16 @@ void launch_walk_vjp(bh_ctx *c, float eps, const float *u, float coef, float *g_
     const uint32_t n = (uint32_t)c->n;
     const uint32_t nb = cdiv(n, 256);
     const uint32_t grid = nb < 4096u ? (nb ? nb : 1u) : 4096u;
-    const uint64_t cap = (uint64_t)c->cap_cells, nmax = (uint64_t)c->nmax;
-    const uint64_t lstride = 10ull * cap, gstride = 4ull * nmax;
+    const uint64_t cap = (uint64_t)c->cap_cells;
+    const uint64_t lstride = kCellAdj * cap, gstride = 4ull * (uint64_t)c->nmax;
     const uint32_t *ls = c->cells.ls;
-    hipLaunchKernelGGL(k_zero_xcd, dim3(2048), dim3(256), 0, st, c->lcell, (uint64_t)0, 10u, cap,
+    // (cells in the hot copies leave their first copies unused)
+    hipLaunchKernelGGL(k_zero_xcd, dim3(2048), dim3(256), 0, st, c->lcell, (uint64_t)0, kCellAdj,
                        lstride, kXcd, ls, cap);
-    hipLaunchKernelGGL(k_zero_xcd, dim3(grid), dim3(256), 0, st, c->gsrc, (uint64_t)n, 4u, nmax,
+    hipLaunchKernelGGL(k_zero_xcd, dim3(grid), dim3(256), 0, st, c->gsrc, (uint64_t)n, 4u,
                        gstride, kXcd, (const uint32_t *)nullptr, (uint64_t)n);
-    hipLaunchKernelGGL(k_zero_xcd, dim3(640), dim3(256), 0, st, c->lhot, (uint64_t)0, 10u,
-                       kHotField, kHotCopy, kHotCopies, ls, (uint64_t)kHotCells);
+    hipLaunchKernelGGL(k_zero_xcd, dim3(640), dim3(256), 0, st, c->lhot, (uint64_t)0, kCellAdj,
+                       kHotCopy, kHotCopies, ls, (uint64_t)kHotCells);
     hipLaunchKernelGGL(k_leafof, dim3(kGrid * 2), dim3(256), 0, st, c->cells, c->leafof);
     hipLaunchKernelGGL(k_usort, dim3(nb), dim3(256), 0, st, u,
                        (const uint32_t *)c->st[c->cur].cid, n, c->usort);
@@ -517,23 +597,20 @@ void launch_walk_vjp(bh_ctx *c, float eps, const float *u, float coef, float *g_
     a.ring = c->walk_small_stack ? 192u : (uint32_t)kRing;
     a.lcell = c->lcell; a.gsrc = c->gsrc; a.lhot = c->lhot;
     a.lstride = lstride; a.gstride = gstride;
-    a.cap = cap; a.nmax = nmax;
     a.eps2 = eps * eps;
     record_event(c, 8, st);
     a.logw = vjp_logw(c->n);
     if (a.logw) launch_vjp_k<true>(c, a, eps, st);
     else launch_vjp_k<false>(c, a, eps, st);
     record_event(c, 9, st);
-    hipLaunchKernelGGL(k_fold_xcd, dim3(2048), dim3(256), 0, st, c->lcell, (uint64_t)0, 10u, cap,
-                       lstride, ls);
-    hipLaunchKernelGGL(k_fold_hot, dim3(640), dim3(256), 0, st, (const double *)c->lhot, c->lcell,
-                       cap, ls);
-    hipLaunchKernelGGL(k_fold_xcd, dim3(grid), dim3(256), 0, st, c->gsrc, (uint64_t)n, 4u, nmax,
-                       gstride, (const uint32_t *)nullptr);
+    hipLaunchKernelGGL(k_fold_xcd, dim3(2048), dim3(256), 0, st, c->lcell, (uint64_t)0, kCellAdj,
+                       lstride, ls, (const double *)c->lhot);
+    hipLaunchKernelGGL(k_fold_xcd, dim3(grid), dim3(256), 0, st, c->gsrc, (uint64_t)n, 4u,
+                       gstride, (const uint32_t *)nullptr, (const double *)nullptr);
     hipLaunchKernelGGL(k_moments_vjp, dim3(nb), dim3(256), 0, st, c->cells,
                        (const float4 *)c->xyzm, (const uint32_t *)c->leafof,
                        (const uint32_t *)c->st[c->cur].cid, (const double *)c->lcell,
-                       (const double *)c->gsrc, cap, nmax, n, coef, g_pos, g_mass);
+                       (const double *)c->gsrc, n, coef, g_pos, g_mass);
 }
 
 // y += a x over n [3]-vectors (the drift's transpose in the adjoint step)
