@@ -64,7 +64,7 @@ void free_all(bh_ctx *c) {
     f(b.flag); f(b.scan); f(b.ids); f(b.box); f(b.cmin); f(b.cmax); f(b.lvl); f(b.part);
     Let &t = c->let;
     f(t.wA); f(t.P0); f(t.P1); f(t.P2); f(t.xyzm); f(t.wN); f(t.origin);
-    f(t.cmark); f(t.omark); f(t.cscan); f(t.pmark); f(t.pscan); f(t.spart); f(t.word);
+    f(t.marks); f(t.keep); f(t.spart); f(t.info);
     f(c->cut.S); f(c->cut.cuts); f(c->seg);
     for (auto &e : c->ev)
         if (e) (void)hipEventDestroy(e);
@@ -1055,6 +1055,7 @@ int bh_boundary(bh_ctx *c, int32_t max_cells, int32_t *level, int64_t *nterm, hi
     BH_HIP(c, hipGetLastError());
     b.level = L;
     b.nterm = nt;
+    b.ncell = nc;
     b.valid = true;
     if (level) *level = L;
     if (nterm) *nterm = nt;
@@ -1065,7 +1066,7 @@ int bh_boundary(bh_ctx *c, int32_t max_cells, int32_t *level, int64_t *nterm, hi
 int bh_let_build(bh_ctx *c, bh_ctx *const *srcs, int32_t nsrc, float theta, int64_t *info,
                  hipStream_t s) {
     if (!c) return BH_EINVAL;
-    if ((!srcs && nsrc) || nsrc < 0 || nsrc > 64)
+    if ((!srcs && nsrc) || nsrc < 0 || nsrc > kLetMaxSrc)
         return fail(c, BH_EINVAL, "need 0 <= nsrc <= 64 sources");
     if (!valid_theta(theta)) return fail(c, BH_EINVAL, "theta must be in (0, 1]");
     if (!c->built || !c->bnd.valid) return fail(c, BH_ESTATE, "target needs a boundary tree");
@@ -1098,20 +1099,16 @@ int bh_let_build(bh_ctx *c, bh_ctx *const *srcs, int32_t nsrc, float theta, int6
     }
     int64_t nv = 0;
     for (int q = 0; q + 1 < nlv; ++q) nv += lv[q];
-    // sizes
-    std::vector<uint32_t> ncs((size_t)nsrc);
-    int64_t need_c = nv, need_p = 0, max_c = 0, max_p = 0;
+    // sizes (a boundary tree knows its tree's cell count)
+    int64_t need_c = nv, need_p = 0;
     for (int32_t k = 0; k < nsrc; ++k) {
-        ncs[(size_t)k] = cell_count(srcs[k], s);
-        need_c += ncs[(size_t)k];
+        need_c += srcs[k]->bnd.ncell;
         need_p += srcs[k]->n;
-        max_c = std::max<int64_t>(max_c, ncs[(size_t)k]);
-        max_p = std::max<int64_t>(max_p, srcs[k]->n);
     }
     if (need_c >= (int64_t(1) << 29) || need_p >= (int64_t(1) << 31))
         return fail(c, BH_ECAPACITY, "local essential tree too large");
     std::string err;
-    int64_t cc = t.cell_cap, c2 = cc, c3 = cc, c4 = cc, c5 = cc, c6 = cc, c7 = 2 * cc;
+    int64_t cc = t.cell_cap, c2 = cc, c3 = cc, c4 = cc, c5 = cc, c7 = 2 * cc;
     int64_t pc = t.part_cap;
     if (!grow(&t.wA, cc, need_c, err) || !grow(&t.P0, c2, need_c, err) ||
         !grow(&t.P1, c3, need_c, err) || !grow(&t.P2, c4, need_c, err) ||
@@ -1120,71 +1117,25 @@ int bh_let_build(bh_ctx *c, bh_ctx *const *srcs, int32_t nsrc, float theta, int6
         t.cell_cap = t.part_cap = 0;
         return fail(c, BH_ENOMEM, err);
     }
-    (void)c6;
-    t.cell_cap = need_c;
-    t.part_cap = std::max<int64_t>(need_p, 1);
-    int64_t s1 = t.scr_cells, s2 = s1, s0 = s1, s3 = t.scr_parts, s4 = s3, s5 = t.part_len, s6 = 1;
-    const int64_t plen = scan_part_len(std::max(max_c, max_p) + 1);
-    if (!grow(&t.cmark, s1, max_c + 1, err) || !grow(&t.omark, s0, max_c + 1, err) ||
-        !grow(&t.cscan, s2, max_c + 1, err) ||
-        !grow(&t.pmark, s3, max_p + 1, err) || !grow(&t.pscan, s4, max_p + 1, err) ||
-        !grow(&t.spart, s5, plen, err) || (!t.word && !grow(&t.word, s6, 1, err))) {
-        t.scr_cells = t.scr_parts = t.part_len = 0;
+    t.cell_cap = cc;
+    t.part_cap = pc;
+    const int64_t sum_c = need_c - nv;
+    if (!grow(&t.marks, t.marks_cap, 2 * sum_c + need_p + nsrc, err) ||
+        !grow(&t.keep, t.keep_cap, sum_c + need_p + 1, err) ||
+        !grow(&t.spart, t.spart_cap, scan_part_len(sum_c + need_p + 1), err) ||
+        !grow(&t.info, t.info_cap, 3 * kLetMaxSrc + 2, err))
         return fail(c, BH_ENOMEM, err);
-    }
-    t.scr_cells = max_c + 1;
-    t.scr_parts = max_p + 1;
-    t.part_len = plen;
 
-    uint32_t cbase = (uint32_t)(nv + nsrc), pbase = 0;
-    for (int32_t k = 0; k < nsrc; ++k) {
-        bh_ctx *src = srcs[k];
-        const uint32_t nc = ncs[(size_t)k];
-        launch_walk_prep(src, theta, nullptr, false, s);
-        launch_let_mark(c, src, nc, s);
-        uint32_t word = 0;
-        BH_HIP(c, hipStreamSynchronize(s));
-        BH_HIP(c, hipMemcpy(&word, t.word, sizeof(word), hipMemcpyDeviceToHost));
-        const bool boundary_only = word == 0u;
-        launch_let_keep(c, src, nc, boundary_only, s);
-        uint32_t kc = 0, kp = 0;
-        BH_HIP(c, hipStreamSynchronize(s));
-        BH_HIP(c, hipMemcpy(&kc, t.cscan + nc, sizeof(kc), hipMemcpyDeviceToHost));
-        BH_HIP(c, hipMemcpy(&kp, t.pscan + src->n, sizeof(kp), hipMemcpyDeviceToHost));
-        launch_let_emit(c, src, nc, k, boundary_only, (uint32_t)(nv + k), cbase, pbase, s);
-        BH_HIP(c, hipGetLastError());
-        if (info) {
-            info[3 * k] = boundary_only ? 1 : 0;
-            info[3 * k + 1] = kc;
-            info[3 * k + 2] = kp;
-        }
-        cbase += kc - 1u;
-        pbase += kp;
-    }
-    // the virtual cells: never accepted (r_open^2 = +inf), children contiguous
-    std::vector<float4> vA((size_t)nv), vz((size_t)nv);
-    std::vector<uint2> vN((size_t)nv);
-    std::vector<uint32_t> vo(2 * (size_t)nv, kNone);
-    int64_t off = 0;
-    for (int q = 0; q + 1 < nlv; ++q) {
-        const int64_t next = off + lv[q];
-        for (int64_t i = 0; i < lv[q]; ++i) {
-            const int64_t f = 8 * i, cnt = std::min<int64_t>(8, lv[q + 1] - f);
-            vA[(size_t)(off + i)] = make_float4(0.f, 0.f, 0.f, INFINITY);
-            vz[(size_t)(off + i)] = make_float4(0.f, 0.f, 0.f, 0.f);
-            vN[(size_t)(off + i)] = make_uint2((uint32_t)(next + f), (uint32_t)cnt);
-        }
-        off = next;
-    }
+    launch_let(c, srcs, nsrc, theta, lv, nlv, (uint32_t)nv, s);
+    BH_HIP(c, hipGetLastError());
+    uint32_t got[3 * kLetMaxSrc + 2];
+    BH_HIP(c, hipMemcpyAsync(got, t.info, (3 * (size_t)nsrc + 2) * sizeof(uint32_t),
+                             hipMemcpyDeviceToHost, s));
     BH_HIP(c, hipStreamSynchronize(s));
-    BH_HIP(c, hipMemcpy(t.wA, vA.data(), 16 * (size_t)nv, hipMemcpyHostToDevice));
-    BH_HIP(c, hipMemcpy(t.P0, vz.data(), 16 * (size_t)nv, hipMemcpyHostToDevice));
-    BH_HIP(c, hipMemcpy(t.P1, vz.data(), 16 * (size_t)nv, hipMemcpyHostToDevice));
-    BH_HIP(c, hipMemcpy(t.P2, vz.data(), 16 * (size_t)nv, hipMemcpyHostToDevice));
-    BH_HIP(c, hipMemcpy(t.wN, vN.data(), 8 * (size_t)nv, hipMemcpyHostToDevice));
-    BH_HIP(c, hipMemcpy(t.origin, vo.data(), 8 * (size_t)nv, hipMemcpyHostToDevice));
-    t.ncell = cbase;
-    t.npart = pbase;
+    if (info)
+        for (int32_t k = 0; k < 3 * nsrc; ++k) info[k] = got[k];
+    t.ncell = (uint32_t)nv + got[3 * nsrc];
+    t.npart = got[3 * nsrc + 1];
     t.nsrc = nsrc;
     t.theta = theta;
     t.valid = true;

@@ -102,6 +102,7 @@ struct Boundary {
     bool valid = false;
     int level = -1;
     uint32_t nterm = 0;
+    uint32_t ncell = 0;        // cells of the tree
     float margin = 0.f;        // widening of the terminal boxes
     uint32_t *flag = nullptr;  // [cap_cells + 1] bit 0: in the boundary tree, bit 1: terminal
     uint32_t *scan = nullptr;  // [cap_cells + 1] exclusive scan of the terminal bits
@@ -123,15 +124,11 @@ struct Let {
     float4 *wA = nullptr, *P0 = nullptr, *P1 = nullptr, *P2 = nullptr, *xyzm = nullptr;
     uint2 *wN = nullptr;
     uint32_t *origin = nullptr;  // [cell_cap][2] (source, source cell); kNone for virtual
-    // per-source scratch, sized to the largest source
-    int64_t scr_cells = 0, scr_parts = 0, part_len = 0;
-    uint32_t *cmark = nullptr;  // [cells + 1] bit 0 accepted, 1 opened, 2 reached
-    uint32_t *omark = nullptr;  // [cells + 1] leaves some box opened
-    uint32_t *cscan = nullptr;  // [cells + 1] kept cells, scanned
-    uint32_t *pmark = nullptr;  // [parts + 1] particles of opened leaves
-    uint32_t *pscan = nullptr;  // [parts + 1]
-    uint32_t *spart = nullptr;  // scan partials
-    uint32_t *word = nullptr;   // [1] a terminal boundary cell was opened
+    // scratch of the construction, over all sources one after another: per cell
+    // accepted and opened marks, per particle marks, per source a word (zeroed
+    // together), then kept cells and particles and their exclusive scan
+    uint32_t *marks = nullptr, *keep = nullptr, *spart = nullptr, *info = nullptr;
+    int64_t marks_cap = 0, keep_cap = 0, spart_cap = 0, info_cap = 0;
 };
 
 // Device buffers of the domain cut: group-start costs and the cuts.
@@ -255,12 +252,13 @@ void launch_walk_prep(bh_ctx *c, float theta, bh_ctx *walker, bool totals, hipSt
 void launch_bnd_flags(bh_ctx *c, hipStream_t st);                // -> bnd.flag bit 0, bnd.lvl
 void launch_bnd_terminal(bh_ctx *c, int level, hipStream_t st);  // -> flag bit 1, scan input
 void launch_bnd_boxes(bh_ctx *c, uint32_t nc, uint32_t nterm, hipStream_t st);  // -> ids, box
-void launch_let_mark(bh_ctx *tgt, const bh_ctx *src, uint32_t nc, hipStream_t st);
-void launch_let_keep(bh_ctx *tgt, const bh_ctx *src, uint32_t nc, bool boundary_only,
-                     hipStream_t st);
-void launch_let_emit(bh_ctx *tgt, const bh_ctx *src, uint32_t nc, int src_index,
-                     bool boundary_only, uint32_t root_slot, uint32_t cbase, uint32_t pbase,
-                     hipStream_t st);
+constexpr int kLetMaxSrc = 64;
+// All of the LETs of tgt: opening radii of the sources for theta, marks, the
+// kept cells and particles below the nv virtual cells (of the level sizes lv);
+// then per source (boundary tree sufficed, cells, particles) and the totals of
+// both to let.info [3 nsrc + 2].
+void launch_let(bh_ctx *tgt, bh_ctx *const *srcs, int nsrc, float theta, const int64_t lv[4],
+                int nlv, uint32_t nv, hipStream_t st);
 uint32_t cell_count(const bh_ctx *c, hipStream_t st);  // synchronises st, reads the count
 
 // walk.hip

@@ -12,17 +12,26 @@
 // widened by a margin, stand for the domain's targets.
 //
 // LET of a source tree for a target domain: every target box walks the
-// source tree with the force walk's own traversal and opening test.  Cells
-// the boxes accept and the leaves they open are marked; a pass up the
-// levels then gives, per cell, whether some box opened it and whether some
-// box reached it, and marks the particles of opened leaves.  Any target group lies inside one terminal
-// box, and the margin keeps its FP32 box distance to any cell at least the
-// box's, so a group opens only cells that its box opens: the reached cells
-// (opened cells with all their children, opened leaves with their particles)
-// are exactly what the group walks need, and walking them gives bit for bit
-// the interaction lists of the full source tree.  When no box opens a
-// terminal cell of the source's boundary tree, the boundary tree itself
-// serves as the LET.
+// source tree with the force walk's own traversal and opening test, and marks
+// the cells it accepts and those it opens.  Any target group lies inside one
+// terminal box, and the margin keeps its FP32 box distance to any cell at
+// least the box's, so a group opens only cells that its box opens: the reached
+// cells (opened cells with all their children, opened leaves with their
+// particles) are exactly what the group walks need, and walking them gives bit
+// for bit the interaction lists of the full source tree.  When no box opens a
+// terminal cell of the source's boundary tree, the boundary tree itself serves
+// as the LET.
+//
+// All sources of a target go through each step together (a source is a grid
+// row), their cells and particles one after another in the scratch arrays, so
+// that one scan numbers the kept cells and particles of all of them and the
+// host waits once: 12 launches for up to 16 sources.  Source by source, with a
+// pass up the levels to find the opened cells, it took 40 launches and two
+// waits per source.  Four domains of a 262144-particle disk, trees and forces:
+// 5.87 -> 2.51 ms, the construction now about 0.2 ms per target, half of it
+// k_let_mark (97 us, a walk whose longest box bounds it).
+#include <algorithm>
+
 #include "walk_common.h"
 
 namespace bh {
@@ -173,74 +182,87 @@ void launch_bnd_boxes(bh_ctx *c, uint32_t nc, uint32_t nterm, hipStream_t st) {
 
 // ---- local essential tree ---------------------------------------------------
 
-// One wave per target box (grid-stride): the force walk's traversal of the
-// source tree; accepted cells (cmark) and opened leaves (omark) are marked.
-__global__ __launch_bounds__(64) void k_let_mark(TreeView tv, const float4 *__restrict__ tbox,
-                                                 uint32_t nbox, uint32_t *cmark, uint32_t *omark,
-                                                 uint32_t *spill_base) {
+// A source as the kernels see it, and where its cells and particles lie in the
+// scratch arrays.
+struct LetSrc {
+    float4 *wA;
+    const float2 *size;
+    const uint2 *wN;
+    const float4 *P0, *P1, *P2, *xyzm;
+    const uint32_t *begin, *count, *child0, *nchild, *bflag;
+    uint32_t nc, n, c0, p0;
+};
+constexpr int kLetBatch = 16;
+struct LetBatch {
+    LetSrc s[kLetBatch];
+    uint32_t first, nsrc;  // this batch's first source, sources of all batches
+    uint32_t cells, parts; // of all sources
+    uint32_t *acc, *opn, *pmark, *word;  // [cells], [cells], [parts], [nsrc]
+    uint32_t *keep;                      // [cells + parts + 1], then its scan
+};
+
+// opening radii of the batch's sources for theta
+__global__ __launch_bounds__(256) void k_let_prep(LetBatch b, float theta) {
+    const LetSrc &s = b.s[blockIdx.y];
+    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < s.nc; i += gridDim.x * 256) {
+        const float2 sz = s.size[i];
+        const float r = sz.x / theta + sz.y;
+        s.wA[i].w = r * r;
+    }
+}
+
+// One wave per (source, target box): the force walk's traversal of the
+// source tree; accepted and opened cells are marked.
+__global__ __launch_bounds__(64) void k_let_mark(LetBatch b, uint32_t batch,
+                                                 const float4 *__restrict__ tbox, uint32_t nbox,
+                                                 uint32_t *spill_base, uint32_t *status) {
     __shared__ TravLds L;
     const uint32_t lane = threadIdx.x;
     uint32_t *spill = spill_base + (size_t)blockIdx.x * kStackMax;
-    for (uint32_t k = blockIdx.x; k < nbox; k += gridDim.x) {
+    for (uint32_t task = blockIdx.x; task < batch * nbox; task += gridDim.x) {
+        const uint32_t q = task / nbox, k = task - q * nbox;
+        const LetSrc &s = b.s[q];
+        uint32_t *acc = b.acc + s.c0, *opn = b.opn + s.c0;
+        const TreeView tv{s.wA, s.wN, (uint32_t)kRing, status, opn};
         const float4 bc = tbox[2 * (size_t)k], bh = tbox[2 * (size_t)k + 1];
-        GroupBox b;
-        b.cx = bc.x; b.cy = bc.y; b.cz = bc.z;
-        b.hx = bh.x; b.hy = bh.y; b.hz = bh.z;
+        GroupBox g;
+        g.cx = bc.x; g.cy = bc.y; g.cz = bc.z;
+        g.hx = bh.x; g.hy = bh.y; g.hz = bh.z;
         uint32_t npc = 0, npp = 0;
         traverse<true>(
-            tv, b, lane, L, spill, npc, npp,
+            tv, g, lane, L, spill, npc, npp,
             [&](uint32_t n) {
-                for (uint32_t i = lane; i < n; i += 64u) cmark[L.pcidx[i]] = 1u;
+                for (uint32_t i = lane; i < n; i += 64u) acc[L.pcidx[i]] = 1u;
             },
             [&](uint32_t n) {
-                for (uint32_t i = lane; i < n; i += 64u) omark[L.ppidx[i]] = 1u;
+                for (uint32_t i = lane; i < n; i += 64u) opn[L.ppidx[i]] = 1u;
             });
     }
 }
 
-// Level l, after level l + 1: opened = a marked leaf or an internal cell
-// with a reached child; reached = accepted or opened.  The particles of an
-// opened leaf are marked in pmark.
-__global__ __launch_bounds__(256) void k_let_up(Cells c, int l, uint32_t *cmark,
-                                                const uint32_t *__restrict__ omark,
-                                                uint32_t *__restrict__ pmark,
-                                                const uint32_t *__restrict__ bflag,
-                                                uint32_t *word) {
-    const uint32_t first = c.ls[l], last = c.ls[l + 1];
-    for (uint32_t i = first + blockIdx.x * 256 + threadIdx.x; i < last; i += gridDim.x * 256) {
-        const uint32_t acc = cmark[i] & 1u;
-        const uint32_t nch = c.nchild[i];
-        bool opn = false;
-        if (nch == 0u) {
-            opn = omark[i] != 0u;
-            if (opn) {
-                const uint32_t b = c.begin[i], e = b + c.count[i];
-                for (uint32_t j = b; j < e; ++j) pmark[j] = 1u;
-            }
-        } else {
-            const uint32_t k0 = c.child0[i];
-            for (uint32_t k = k0; k < k0 + nch; ++k) opn = opn || (cmark[k] & 4u) != 0u;
-        }
-        const bool vis = acc != 0u || opn;
-        cmark[i] = acc | (opn ? 2u : 0u) | (vis ? 4u : 0u);
-        if (opn && (bflag[i] & 2u)) atomicOr(word, 1u);
+// Marks of the opened leaves' particles; word of a source: some box opened a
+// terminal cell of its boundary tree.
+__global__ __launch_bounds__(256) void k_let_opened(LetBatch b) {
+    const LetSrc &s = b.s[blockIdx.y];
+    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < s.nc; i += gridDim.x * 256) {
+        if (!b.opn[s.c0 + i]) continue;
+        if (s.bflag[i] & 2u) b.word[b.first + blockIdx.y] = 1u;
+        if (s.nchild[i] != 0u) continue;
+        const uint32_t j0 = s.p0 + s.begin[i], j1 = j0 + s.count[i];
+        for (uint32_t j = j0; j < j1; ++j) b.pmark[j] = 1u;
     }
 }
 
-__global__ __launch_bounds__(256) void k_let_keep(uint32_t nc, const uint32_t *__restrict__ cmark,
-                                                  const uint32_t *__restrict__ bflag,
-                                                  uint32_t boundary_only, uint32_t *cscan) {
-    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i <= nc; i += gridDim.x * 256) {
-        uint32_t keep = 0u;
-        if (i < nc) keep = boundary_only ? (bflag[i] & 1u) : ((cmark[i] >> 2) & 1u);
-        cscan[i] = keep;
-    }
-}
-
-__global__ __launch_bounds__(256) void k_copy_flags(uint32_t n, const uint32_t *__restrict__ in,
-                                                    uint32_t *out) {
-    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i <= n; i += gridDim.x * 256)
-        out[i] = i < n ? in[i] : 0u;
+__global__ __launch_bounds__(256) void k_let_keep(LetBatch b) {
+    const LetSrc &s = b.s[blockIdx.y];
+    const bool boundary_only = b.word[b.first + blockIdx.y] == 0u;
+    const uint32_t step = gridDim.x * 256, i0 = blockIdx.x * 256 + threadIdx.x;
+    for (uint32_t i = i0; i < s.nc; i += step)
+        b.keep[s.c0 + i] =
+            boundary_only ? (s.bflag[i] & 1u) : (b.acc[s.c0 + i] | b.opn[s.c0 + i]);
+    for (uint32_t j = i0; j < s.n; j += step)
+        b.keep[b.cells + s.p0 + j] = boundary_only ? 0u : b.pmark[s.p0 + j];
+    if (i0 == 0u) b.keep[b.cells + b.parts] = 0u;
 }
 
 struct LetOut {
@@ -250,106 +272,140 @@ struct LetOut {
     float4 *xyzm;
 };
 
-// Kept source cells -> LET slots: the root at root_slot, cell i at
-// cbase + rank(i) - 1.  An expanded cell keeps its children (internal) or
-// its particles (leaf); every other kept cell becomes a leaf with none.
-__global__ __launch_bounds__(256) void k_let_emit(Cells c, uint32_t nc,
-                                                  const uint32_t *__restrict__ cmark,
-                                                  const uint32_t *__restrict__ bflag,
-                                                  const uint32_t *__restrict__ cscan,
-                                                  const uint32_t *__restrict__ pscan,
-                                                  uint32_t boundary_only, uint32_t src_index,
-                                                  uint32_t root_slot, uint32_t cbase,
-                                                  uint32_t pbase, LetOut o) {
-    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < nc; i += gridDim.x * 256) {
-        const uint32_t keep = boundary_only ? (bflag[i] & 1u) : ((cmark[i] >> 2) & 1u);
+// Virtual cells above the sources' roots: levels of lv cells each.
+struct LetVirtual {
+    uint32_t lv[4];
+    uint32_t nlv, nv;
+};
+
+// Kept source cells -> LET slots: the root of source k at nv + k, the other
+// cells behind all roots in scan order.  An expanded cell keeps its children
+// (internal) or its particles (leaf); every other kept cell becomes a leaf
+// with none.
+__global__ __launch_bounds__(256) void k_let_emit(LetBatch b, LetVirtual v, LetOut o) {
+    const LetSrc &s = b.s[blockIdx.y];
+    const uint32_t src = b.first + blockIdx.y;
+    const bool boundary_only = b.word[src] == 0u;
+    const uint32_t *scan = b.keep, *pscan = b.keep + b.cells;
+    const uint32_t r0 = scan[s.c0], kept = scan[b.cells];
+    // (scan counts the earlier sources' roots, this one's and the cell itself)
+    auto slot_of = [&](uint32_t rank) { return v.nv + b.nsrc + rank - (src + 1u); };
+    const uint32_t step = gridDim.x * 256, i0 = blockIdx.x * 256 + threadIdx.x;
+    for (uint32_t i = i0; i < s.nc; i += step) {
+        const bool opn = b.opn[s.c0 + i] != 0u;
+        const bool keep = boundary_only ? (s.bflag[i] & 1u) != 0u : opn || b.acc[s.c0 + i] != 0u;
         if (!keep) continue;
-        const uint32_t r = cscan[i];
-        const uint32_t slot = r == 0u ? root_slot : cbase + r - 1u;
-        const bool expand = boundary_only ? (bflag[i] & 3u) == 1u : (cmark[i] & 2u) != 0u;
-        const uint32_t nch = c.nchild[i];
+        const uint32_t r = scan[s.c0 + i];
+        const uint32_t slot = r == r0 ? v.nv + src : slot_of(r);
+        const bool expand = boundary_only ? (s.bflag[i] & 3u) == 1u : opn;
+        const uint32_t nch = s.nchild[i];
         uint2 N = make_uint2(0u, kLeafBit);
-        if (expand && nch) N = make_uint2(cbase + cscan[c.child0[i]] - 1u, nch);
-        else if (expand) N = make_uint2(pbase + pscan[c.begin[i]], c.count[i] | kLeafBit);
-        o.wA[slot] = c.wA[i];
-        o.P0[slot] = c.P0[i];
-        o.P1[slot] = c.P1[i];
-        o.P2[slot] = c.P2[i];
+        if (expand && nch) N = make_uint2(slot_of(scan[s.c0 + s.child0[i]]), nch);
+        else if (expand) N = make_uint2(pscan[s.p0 + s.begin[i]] - kept, s.count[i] | kLeafBit);
+        o.wA[slot] = s.wA[i];
+        o.P0[slot] = s.P0[i];
+        o.P1[slot] = s.P1[i];
+        o.P2[slot] = s.P2[i];
         o.wN[slot] = N;
-        o.origin[2 * (size_t)slot] = src_index;
+        o.origin[2 * (size_t)slot] = src;
         o.origin[2 * (size_t)slot + 1] = i;
     }
-}
-
-__global__ __launch_bounds__(256) void k_let_parts(uint32_t n, const float4 *__restrict__ sxyzm,
-                                                   const uint32_t *__restrict__ pmark,
-                                                   const uint32_t *__restrict__ pscan,
-                                                   uint32_t pbase, float4 *__restrict__ out) {
-    for (uint32_t j = blockIdx.x * 256 + threadIdx.x; j < n; j += gridDim.x * 256)
-        if (pmark[j]) out[pbase + pscan[j]] = sxyzm[j];
-}
-
-static uint32_t grid_for(uint64_t n) {
-    uint32_t nb = cdiv(n, 256);
-    if (nb > 4096) nb = 4096;
-    return nb < 1 ? 1 : nb;
-}
-
-void launch_let_mark(bh_ctx *tgt, const bh_ctx *src, uint32_t nc, hipStream_t st) {
-    Let &t = tgt->let;
-    const uint32_t n = (uint32_t)src->n;
-    launch_fill_u32(t.cmark, 0u, (uint64_t)nc + 1, st);
-    launch_fill_u32(t.omark, 0u, (uint64_t)nc + 1, st);
-    launch_fill_u32(t.pmark, 0u, (uint64_t)n + 1, st);
-    launch_fill_u32(t.word, 0u, 1, st);
-    const uint32_t nbox = tgt->bnd.nterm;
-    if (nbox) {
-        TreeView tv;
-        tv.wA = src->cells.wA;
-        tv.wN = src->cells.wN;
-        tv.ring = (uint32_t)kRing;
-        tv.status = tgt->status;
-        const uint32_t grid = nbox < (uint32_t)tgt->walk_grid ? nbox : (uint32_t)tgt->walk_grid;
-        hipLaunchKernelGGL(k_let_mark, dim3(grid), dim3(64), 0, st, tv,
-                           (const float4 *)tgt->bnd.box, nbox, t.cmark, t.omark, tgt->spill);
-    }
-    for (int l = kLevels - 1; l >= 0; --l)
-        hipLaunchKernelGGL(k_let_up, dim3(kGrid), dim3(256), 0, st, src->cells, l, t.cmark,
-                           (const uint32_t *)t.omark, t.pmark, (const uint32_t *)src->bnd.flag,
-                           t.word);
-}
-
-void launch_let_keep(bh_ctx *tgt, const bh_ctx *src, uint32_t nc, bool boundary_only,
-                     hipStream_t st) {
-    Let &t = tgt->let;
-    const uint32_t n = (uint32_t)src->n;
-    hipLaunchKernelGGL(k_let_keep, dim3(grid_for((uint64_t)nc + 1)), dim3(256), 0, st, nc,
-                       (const uint32_t *)t.cmark, (const uint32_t *)src->bnd.flag,
-                       boundary_only ? 1u : 0u, t.cscan);
-    launch_exclusive_scan(t.cscan, t.cscan, nc + 1, t.spart, st);
-    if (boundary_only) {
-        launch_fill_u32(t.pscan, 0u, (uint64_t)n + 1, st);
-    } else {
-        hipLaunchKernelGGL(k_copy_flags, dim3(grid_for((uint64_t)n + 1)), dim3(256), 0, st, n,
-                           (const uint32_t *)t.pmark, t.pscan);
-        launch_exclusive_scan(t.pscan, t.pscan, n + 1, t.spart, st);
-    }
-}
-
-void launch_let_emit(bh_ctx *tgt, const bh_ctx *src, uint32_t nc, int src_index,
-                     bool boundary_only, uint32_t root_slot, uint32_t cbase, uint32_t pbase,
-                     hipStream_t st) {
-    Let &t = tgt->let;
-    const uint32_t n = (uint32_t)src->n;
-    LetOut o{t.wA, t.P0, t.P1, t.P2, t.wN, t.origin, t.xyzm};
-    hipLaunchKernelGGL(k_let_emit, dim3(grid_for(nc)), dim3(256), 0, st, src->cells, nc,
-                       (const uint32_t *)t.cmark, (const uint32_t *)src->bnd.flag,
-                       (const uint32_t *)t.cscan, (const uint32_t *)t.pscan,
-                       boundary_only ? 1u : 0u, (uint32_t)src_index, root_slot, cbase, pbase, o);
     if (!boundary_only)
-        hipLaunchKernelGGL(k_let_parts, dim3(grid_for(n)), dim3(256), 0, st, n,
-                           (const float4 *)src->xyzm, (const uint32_t *)t.pmark,
-                           (const uint32_t *)t.pscan, pbase, t.xyzm);
+        for (uint32_t j = i0; j < s.n; j += step)
+            if (b.pmark[s.p0 + j]) o.xyzm[pscan[s.p0 + j] - kept] = s.xyzm[j];
+    if (src != 0u) return;
+    // the virtual cells: never accepted (r_open^2 = +inf), children contiguous
+    uint32_t off = 0;
+    for (uint32_t q = 0; q + 1u < v.nlv; ++q) {
+        const uint32_t next = off + v.lv[q];
+        for (uint32_t i = i0; i < v.lv[q]; i += step) {
+            const uint32_t slot = off + i;
+            o.wA[slot] = make_float4(0.f, 0.f, 0.f, INFINITY);
+            o.P0[slot] = o.P1[slot] = o.P2[slot] = make_float4(0.f, 0.f, 0.f, 0.f);
+            o.wN[slot] = make_uint2(next + 8u * i, min(8u, v.lv[q + 1u] - 8u * i));
+            o.origin[2 * (size_t)slot] = kNone;
+            o.origin[2 * (size_t)slot + 1] = kNone;
+        }
+        off = next;
+    }
+}
+
+// per source: boundary tree sufficed, cells, particles; then the totals
+__global__ __launch_bounds__(64) void k_let_info(LetBatch b, uint32_t batch, uint32_t *info) {
+    const uint32_t *scan = b.keep, *pscan = b.keep + b.cells;
+    if (threadIdx.x < batch) {
+        const LetSrc &s = b.s[threadIdx.x];
+        const uint32_t k = b.first + threadIdx.x;
+        info[3 * k] = b.word[k] == 0u ? 1u : 0u;
+        info[3 * k + 1] = scan[s.c0 + s.nc] - scan[s.c0];
+        info[3 * k + 2] = pscan[s.p0 + s.n] - pscan[s.p0];
+    }
+    if (threadIdx.x == 0) {
+        info[3 * b.nsrc] = scan[b.cells];
+        info[3 * b.nsrc + 1] = pscan[b.parts] - scan[b.cells];
+    }
+}
+
+void launch_let(bh_ctx *tgt, bh_ctx *const *srcs, int nsrc, float theta, const int64_t lv[4],
+                int nlv, uint32_t nv, hipStream_t st) {
+    Let &t = tgt->let;
+    uint32_t cells = 0, parts = 0, most = 1;
+    for (int k = 0; k < nsrc; ++k) {
+        cells += srcs[k]->bnd.ncell;
+        parts += (uint32_t)srcs[k]->n;
+        most = std::max({most, srcs[k]->bnd.ncell, (uint32_t)srcs[k]->n});
+    }
+    launch_fill_u32(t.marks, 0u, 2ull * cells + parts + (uint32_t)nsrc, st);
+    const dim3 block(256);
+    const uint32_t rows = std::min(cdiv(most, 256), 1024u);
+    auto each_batch = [&](auto &&step) {
+        uint32_t c0 = 0, p0 = 0;
+        for (int first = 0; first < nsrc; first += kLetBatch) {
+            LetBatch b{};
+            const uint32_t batch = (uint32_t)std::min(kLetBatch, nsrc - first);
+            for (uint32_t k = 0; k < batch; ++k) {
+                const bh_ctx *s = srcs[first + (int)k];
+                const Cells &q = s->cells;
+                b.s[k] = LetSrc{q.wA, q.size, q.wN, q.P0, q.P1, q.P2, s->xyzm, q.begin, q.count,
+                                q.child0, q.nchild, s->bnd.flag, s->bnd.ncell, (uint32_t)s->n,
+                                c0, p0};
+                c0 += s->bnd.ncell;
+                p0 += (uint32_t)s->n;
+            }
+            b.first = (uint32_t)first;
+            b.nsrc = (uint32_t)nsrc;
+            b.cells = cells;
+            b.parts = parts;
+            b.acc = t.marks;
+            b.opn = b.acc + cells;
+            b.pmark = b.opn + cells;
+            b.word = b.pmark + parts;
+            b.keep = t.keep;
+            step(b, batch);
+        }
+    };
+    const uint32_t nbox = tgt->bnd.nterm;
+    each_batch([&](const LetBatch &b, uint32_t batch) {
+        hipLaunchKernelGGL(k_let_prep, dim3(rows, batch), block, 0, st, b, theta);
+        const uint64_t tasks = (uint64_t)batch * nbox;
+        if (tasks)
+            hipLaunchKernelGGL(k_let_mark,
+                               dim3((uint32_t)std::min<uint64_t>(tasks, (uint64_t)tgt->walk_grid)),
+                               dim3(64), 0, st, b, batch, (const float4 *)tgt->bnd.box, nbox,
+                               tgt->spill, tgt->status);
+        hipLaunchKernelGGL(k_let_opened, dim3(rows, batch), block, 0, st, b);
+        hipLaunchKernelGGL(k_let_keep, dim3(rows, batch), block, 0, st, b);
+    });
+    launch_exclusive_scan(t.keep, t.keep, cells + parts + 1u, t.spart, st);
+    LetVirtual v{};
+    for (int q = 0; q < 4; ++q) v.lv[q] = (uint32_t)lv[q];
+    v.nlv = (uint32_t)nlv;
+    v.nv = nv;
+    const LetOut o{t.wA, t.P0, t.P1, t.P2, t.wN, t.origin, t.xyzm};
+    each_batch([&](const LetBatch &b, uint32_t batch) {
+        hipLaunchKernelGGL(k_let_emit, dim3(rows, batch), block, 0, st, b, v, o);
+        hipLaunchKernelGGL(k_let_info, dim3(1), dim3(64), 0, st, b, batch, t.info);
+    });
 }
 
 }  // namespace bh

@@ -53,6 +53,7 @@ struct TreeView {
     const uint2 *wN;    // (first, n | leaf bit)
     uint32_t ring;      // resident stack entries allowed: kRing, or 192 to exercise the spill path
     uint32_t *status;
+    uint32_t *opened = nullptr;  // kLeafCells: opened internal cells are marked here
 };
 
 struct GroupBox {
@@ -120,7 +121,7 @@ __device__ __forceinline__ void deal(bool &a, bool &b, const Share &sh, uint32_t
 // barrier); both lists are empty when traverse returns.  Counts: accepted
 // cells and particles of opened leaves.  kLeafCells: L.ppidx lists the
 // opened leaf cells themselves instead of their particles (and the second
-// count is of those leaves).
+// count is of those leaves), and opened internal cells are marked in tv.opened.
 //
 // A pass pops up to 128 cells from the top 64 ranges: lane l takes cells l
 // (slot a) and 64 + l (slot b) of their concatenation, so the pop, the scan
@@ -235,6 +236,10 @@ __device__ __forceinline__ void traverse(const TreeView &tv, const GroupBox &b, 
             spill[lo + lane] = L.ring[(lo + lane) & rmask];
             lo += 64u;
             wave_sync();
+        }
+        if constexpr (kLeafCells) {
+            if (open_a) tv.opened[cell_a] = 1u;
+            if (open_b) tv.opened[cell_b] = 1u;
         }
         if (open_a) {
             const uint32_t above = lane == 63u ? 0u : (uint32_t)__popcll(oma >> (lane + 1u));
