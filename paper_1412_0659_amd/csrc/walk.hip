@@ -9,6 +9,16 @@
 // LDS (the next chunk's loads are issued before the current chunk is
 // evaluated), then lane = (target, slice) evaluates the chunk, slice s
 // taking entries s, s + r, ...; the slices are summed at the end.
+//
+// Bound, large sets: power.  At 13M (theta 0.4) the vector units issue an
+// instruction every 2.8 cycles of a SIMD and the clock is held at 2.1 GHz
+// (2.45 in the other kernels), so what pays is work not done at all: lanes
+// without a target or without an entry left are switched off (57.1 ms) where
+// they repeated a slice or read a null source (57.6 ms).  Neither five waves
+// per SIMD instead of four (58.8), nor two targets per lane and half the LDS
+// reads (56.9, but 5% slower with the FP16 far field, which it leaves three
+// waves), nor d and Q d by 4 x 4 x 1 matrix products (75.4; they do not
+// overlap the vector units) does better.
 #include "walk_common.h"
 
 namespace bh {
@@ -115,19 +125,18 @@ __device__ __forceinline__ h2 as_h2(uint32_t u) { return __builtin_bit_cast(h2, 
 // that it is read with four 16-byte loads and one 4-byte load.
 enum { kDx, kDy, kDz, kRho, kE2, kBxx, kByy, kBzz, kBxy, kBxz, kByz, kHtr, kCtr, kH };
 constexpr int kFa = kH, kFphi = kH + 2, kRec = 20;
-constexpr int kNullPair = kChunk / 2;
 
 struct Far16Lds {
-    uint32_t rec[kChunk / 2 + 1][kRec];
+    uint32_t rec[kChunk / 2][kRec];
 };
 
 struct WalkLds {
-    float4 stage[3][kChunk + 1];  // source records of one chunk + the null source
+    float4 stage[3][kChunk];  // source records of one chunk
     TravLds T;
 };
 
 // Target roles of a lane in one evaluation phase: T targets, r slices;
-// lanes >= T * r are idle (they repeat slice 0 and are ignored).
+// lanes >= T * r are idle.
 struct Phase {
     uint32_t T, r, slice;
     bool act;
@@ -175,13 +184,14 @@ __device__ __forceinline__ void pc16_pair(const h2 ti[3], const Far16Lds &S, uin
     acc.w = fmaf((float)ph.y, fphi1, acc.w);
 }
 
-// Evaluate n staged pairs for one phase (null pair past the end).
+// Evaluate n staged pairs for one phase.
 __device__ __forceinline__ void eval16_chunk(Phase &ph, uint32_t n, const Far16Lds &S) {
     const uint32_t r = ph.r;
     const uint32_t full = n / r, rem = n - full * r;
+    if (!ph.act) return;
     uint32_t k = ph.slice;
     for (uint32_t j = 0; j < full; ++j, k += r) pc16_pair(ph.ti, S, k, ph.acc);
-    if (rem) pc16_pair(ph.ti, S, ph.slice < rem ? k : (uint32_t)kNullPair, ph.acc);
+    if (ph.slice < rem) pc16_pair(ph.ti, S, k, ph.acc);
 }
 
 // Write the FP16 half-record of cell k of the chunk (a far cell, or a hole
@@ -215,18 +225,18 @@ __device__ __forceinline__ void stage16(Far16Lds &S, uint32_t k, bool valid, con
     rec[kFphi + (k & 1u)] = __builtin_bit_cast(uint32_t, fp);
 }
 
-// Evaluate n (<= 64) staged sources for one phase; entries past n read the
-// null source (far away, zero mass) so every round is uniform.
+// Evaluate n (<= 64) staged sources for one phase.
 template <bool kIsPc, bool kEps0>
 __device__ __forceinline__ void eval_chunk(Phase &ph, uint32_t n, const WalkLds &L, float eps2) {
     const uint32_t r = ph.r;
     const uint32_t full = n / r, rem = n - full * r;
+    if (!ph.act) return;
     uint32_t j = 0;
     {
         // one induction variable: the lane's source record in stage[0]
         // (stage[1], stage[2] follow at fixed offsets)
         const float4 *src = &L.stage[0][ph.slice];
-        constexpr uint32_t kRow = kChunk + 1;
+        constexpr uint32_t kRow = kChunk;
         for (; j + 1u < full; j += 2u, src += 2u * r) {  // two sources per trip
             if (kIsPc) {
                 pc_term(ph.tgt, src[0], src[kRow], src[2 * kRow], eps2, ph.acc);
@@ -243,10 +253,9 @@ __device__ __forceinline__ void eval_chunk(Phase &ph, uint32_t n, const WalkLds 
         else pp_term<kEps0>(ph.tgt, L.stage[0][k], eps2, ph.acc);
         k += r;
     }
-    if (rem) {
-        const uint32_t kk = ph.slice < rem ? k : (uint32_t)kNull;
-        if (kIsPc) pc_term(ph.tgt, L.stage[0][kk], L.stage[1][kk], L.stage[2][kk], eps2, ph.acc);
-        else pp_term<kEps0>(ph.tgt, L.stage[0][kk], eps2, ph.acc);
+    if (ph.slice < rem) {
+        if (kIsPc) pc_term(ph.tgt, L.stage[0][k], L.stage[1][k], L.stage[2][k], eps2, ph.acc);
+        else pp_term<kEps0>(ph.tgt, L.stage[0][k], eps2, ph.acc);
     }
 }
 
@@ -285,7 +294,7 @@ template <bool kEps0, bool kF16, bool kSplit>
 __device__ void walk_group(const WalkArgs &a, uint32_t g, uint32_t w, uint32_t lane, WalkLds &L,
                            uint32_t *spill) {
     // the FP16 pair records share the FP32 staging area: a flush uses one
-    // or the other, and each flush rewrites its null source
+    // or the other
     static_assert(sizeof(Far16Lds) <= sizeof(L.stage), "pair records exceed the staging area");
     Far16Lds &S = *reinterpret_cast<Far16Lds *>(&L.stage[0][0]);
     const uint32_t gb = a.gbeg[g];
@@ -330,22 +339,9 @@ __device__ void walk_group(const WalkArgs &a, uint32_t g, uint32_t w, uint32_t l
         p2.ti[2] = hsplat((p2.tgt.z - b.cz) * sg);
     }
 
-    // the null source of the FP32 staging area (rewritten by every flush: in
-    // the FP16 walk the pair records share that area): massless and far
-    // enough that 1/r^5 underflows to zero while r^2 stays finite, so every
-    // product in its terms is an exact zero (M r^2 = 0 * inf would be NaN)
-    auto put_null = [&]() {
-        if (lane == 0) {
-            L.stage[0][kNull] = make_float4(1e18f, 1e18f, 1e18f, 0.f);
-            L.stage[1][kNull] = make_float4(0.f, 0.f, 0.f, 0.f);
-            L.stage[2][kNull] = make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-    };
-
     // evaluate the particle-cell list: stage 64 records at a time, loading
     // the next chunk while the current one is evaluated
     auto flush_pc32 = [&](uint32_t n) {
-        put_null();
         float4 r0, r1, r2;
         {
             const uint32_t c = L.T.pcidx[lane < n ? lane : 0u];
@@ -371,10 +367,6 @@ __device__ void walk_group(const WalkArgs &a, uint32_t g, uint32_t w, uint32_t l
     // to the front of the list (positions already consumed), to be
     // evaluated in FP32, in full chunks, after the far cells
     auto flush_pc16 = [&](uint32_t n) {
-        if (lane < 2) {  // the null pair
-            const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
-            stage16(S, kChunk + lane, false, z4, z4, z4, 0.f, 0.f, 0.f, 0, 0, 0.f);
-        }
         float4 r0, r1, r2;
         {
             const uint32_t c = L.T.pcidx[lane < n ? lane : 0u];
@@ -416,7 +408,6 @@ __device__ void walk_group(const WalkArgs &a, uint32_t g, uint32_t w, uint32_t l
         else flush_pc32(n);
     };
     auto flush_pp = [&](uint32_t n) {
-        put_null();
         float4 r0 = a.sxyzm[L.T.ppidx[lane < n ? lane : 0u]];
         for (uint32_t base = 0; base < n; base += kChunk) {
             const uint32_t m = n - base < (uint32_t)kChunk ? n - base : (uint32_t)kChunk;

@@ -35,7 +35,6 @@ constexpr int kPcFlush = kPcCap - 128;  // a pass appends at most 128 cells
 constexpr int kPpCap = 512;  // particle-particle index list
 constexpr int kChunk = 64;   // sources staged per evaluation round
 constexpr uint32_t kDealRanges = 64;  // stack ranges at which the waves of a split walk part
-constexpr int kNull = kChunk;  // staging slot of the null source
 
 struct TravLds {
     uint32_t ring[kRing];
