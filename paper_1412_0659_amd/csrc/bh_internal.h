@@ -286,19 +286,36 @@ struct WalkOut {
 void launch_walk_view(bh_ctx *c, const SrcView &v, float eps, bool remote, bool accum,
                       const WalkOut &out, hipStream_t st);
 int walk_blocks_per_cu();
-// A small set has fewer groups than the chip has wave slots, and the longest
-// walk (a wide group on the outskirts) sets the time, so 2^logw waves share
-// each group's walk.  Splitting costs throughput (every wave repeats the top
-// of the walk, lists are shorter), so fewer waves share as the groups become
-// more.  Measured, force of a disk + halo set at theta 0.4 in us by waves per
-// group (1 / 2 / 4 / 8): n = 1000: 77 / 58 / 49 / 48; 4096: 235 / 147 / 97 /
-// 90; 16384: 475 / 295 / 231 / 233; 32768: 581 / 429 / 407 / 448; 65536: 666 /
-// 601 / 564 / 663; 131072: 964 / 865 / 835 / 900; 262144: 1483 / 1393 / 1378;
-// at theta 0.6 two waves are as fast as one at 131072 (495 against 486) and 4%
-// slower at 262144, four 25% slower at 196608.
-constexpr int64_t kSplit8 = 4096, kSplit4 = 40960, kSplit2 = 147456;
-inline uint32_t split_logw(int64_t n) {
-    return n <= kSplit8 ? 3u : (n <= kSplit4 ? 2u : (n <= kSplit2 ? 1u : 0u));
+// Waves that share a group's walk: 2^logw for a group of more than t1 targets,
+// half as many for one of more than t2, a quarter as many for a smaller one.
+//
+// A set of up to a million particles has few groups for each wave slot of the
+// chip, and the longest walks set the time: those of the groups with the most
+// targets (a wave evaluates its lists in about as many rounds as the group has
+// targets; at 16384 the mean walk of a quarter of a group took 64 us, that of
+// 54 to 64 targets 150 to 174).  Splitting costs throughput (every wave repeats
+// the top of the walk, lists are shorter), so fewer waves share as the groups
+// become more.  Walk in us, all groups alike (the best number of waves) / this
+// rule, disk + halo at theta 0.4: n = 1000 36 / 36 (Plummer); 4096 79 / 73;
+// 16384 219 / 179; 40000 498 / 466; 65536 553 / 464; 131072 811 / 762; 262144
+// 1384 / 1259; 700000 3382 / 3194; 1M 4637 / 4460 and 4768 with no split.  The
+// lines, by waves 8 / 4 or 4 / 2: at 16384 (Plummer, theta 0.5) 152 / 170, at
+// 24576 (0.6) 187 / 157, at 32768 (Plummer) 215 / 192; at 200000 (0.6) 539 / 557,
+// at 400000 994 / 946; two waves or one: 1M at theta 0.6 2142 / 2092, 2M at
+// theta 0.4 8614 / 8651, 4M 10800 / 10636.
+struct Split {
+    uint32_t logw, t1, t2;
+};
+__host__ __device__ inline uint32_t group_logw(const Split &s, uint32_t gn) {
+    return s.logw - (gn <= s.t1 ? 1u : 0u) - (gn <= s.t2 ? 1u : 0u);
+}
+constexpr int64_t kSplit8 = 20480, kSplit4 = 262144, kSplit2 = 1048576;
+inline Split walk_split(int64_t n) {
+    if (n <= 8192) return {3u, 32u, 0u};
+    if (n <= kSplit8) return {3u, 32u, 16u};
+    if (n <= kSplit4) return {2u, 32u, 16u};
+    if (n <= kSplit2) return {1u, 40u, 0u};
+    return {0u, 0u, 0u};
 }
 // entries (one row of n per wave) of the partial sums of a context of n_max
 inline int64_t split_rows(int64_t n_max) {

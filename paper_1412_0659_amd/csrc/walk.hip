@@ -38,9 +38,10 @@ struct WalkArgs {
     uint32_t ring;  // resident stack entries allowed: kRing, or 192 to exercise the spill path
     uint32_t remote;  // 1: the walked tree is another domain's (no self pair)
     uint32_t accum;   // 1: add to acc, npp, npc instead of overwriting them
-    // split walks: 2^logw waves per group; wave w's sums of sorted particle i
-    // at pacc[w * pstride + i], its counts (p-p, p-c) of group g at pcnt[w * pstride + g]
-    uint32_t logw, pstride;
+    // split walks: wave w's sums of sorted particle i at pacc[w * pstride + i],
+    // its counts (p-p, p-c) of group g at pcnt[w * pstride + g]
+    Split split;
+    uint32_t pstride;
     float4 *pacc;
     uint2 *pcnt;
     // caller-order outputs (null: none), kick of the velocities (null: none)
@@ -288,8 +289,8 @@ __device__ __forceinline__ void finish_target(const WalkArgs &a, uint32_t i, flo
     }
 }
 
-// Walk group g (kSplit: as wave w of 2^a.logw, leaving the partial sums for
-// k_walk_combine).
+// Walk group g (kSplit: as wave w of those that share it, leaving the partial
+// sums for k_walk_combine).
 template <bool kEps0, bool kF16, bool kSplit>
 __device__ void walk_group(const WalkArgs &a, uint32_t g, uint32_t w, uint32_t lane, WalkLds &L,
                            uint32_t *spill) {
@@ -304,8 +305,15 @@ __device__ void walk_group(const WalkArgs &a, uint32_t g, uint32_t w, uint32_t l
         return;
     }
 
-    // ---- group box
     const bool own = lane < gn;
+    const uint32_t logw = kSplit ? group_logw(a.split, gn) : 0u;
+    if (w >> logw) {  // fewer waves share this group: none of the sums are this one's
+        if (own) a.pacc[(size_t)w * a.pstride + gb + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (lane == 0) a.pcnt[(size_t)w * a.pstride + g] = make_uint2(0u, 0u);
+        return;
+    }
+
+    // ---- group box
     const float4 me = a.xyzm[gb + (own ? lane : 0u)];
     const GroupBox b = group_box(me, own);
     if (lane == 0 && w == 0u) {
@@ -427,7 +435,7 @@ __device__ void walk_group(const WalkArgs &a, uint32_t g, uint32_t w, uint32_t l
     uint32_t cnt_pc, cnt_pp;
     const TreeView tv{a.wA, a.wN, a.ring, a.status};
     traverse<false, kSplit>(tv, b, lane, L.T, spill, cnt_pc, cnt_pp, flush_pc, flush_pp,
-                            Share{w, a.logw});
+                            Share{w, logw});
 
     // ---- sum the slices of each target (staging area reused)
     float4 res = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -469,7 +477,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 4))) void
     __shared__ WalkLds L;
     const uint32_t lane = threadIdx.x;
     uint32_t *spill = a.spill + (size_t)blockIdx.x * kStackMax;
-    for_each_group(*a.ngroups, a.work, lane, kSplit ? a.logw : 0u, [&](uint32_t g, uint32_t w) {
+    for_each_group(*a.ngroups, a.work, lane, kSplit ? a.split.logw : 0u, [&](uint32_t g, uint32_t w) {
         walk_group<kEps0, kF16, kSplit>(a, g, w, lane, L, spill);
     });
 }
@@ -480,7 +488,7 @@ template <bool kEps0>
 __global__ __launch_bounds__(256) void k_walk_combine(WalkArgs a, uint32_t n) {
     __shared__ unsigned long long part[4][2];
     const uint32_t i = blockIdx.x * 256 + threadIdx.x;
-    const uint32_t W = 1u << a.logw;
+    const uint32_t W = 1u << a.split.logw;
     if (i < n) {
         float4 res = a.pacc[i];
         for (uint32_t w = 1; w < W; ++w) {
@@ -572,13 +580,13 @@ void launch_walk_view(bh_ctx *c, const SrcView &v, float eps, bool remote, bool 
     a.totals = out.totals ? c->totals : nullptr;
     const bool own = !remote && !accum;  // the timed walk of the context's own tree
     if (own) record_event(c, 4, st);
-    a.logw = split_logw(c->n);
+    a.split = walk_split(c->n);
     a.pstride = (uint32_t)c->n;
     a.pacc = c->pacc; a.pcnt = c->pcnt;
-    if (a.logw) launch_walk_k<true>(c, a, eps, st);
+    if (a.split.logw) launch_walk_k<true>(c, a, eps, st);
     else launch_walk_k<false>(c, a, eps, st);
     if (own) record_event(c, 5, st);
-    if (!a.logw && out.totals) launch_totals(c, (uint32_t)c->n, st);
+    if (!a.split.logw && out.totals) launch_totals(c, (uint32_t)c->n, st);
 }
 
 SrcView own_view(const bh_ctx *c) {

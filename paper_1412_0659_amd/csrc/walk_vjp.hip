@@ -68,7 +68,8 @@ struct VjpArgs {
     const float4 *P0, *P1, *P2;
     const uint32_t *gbeg, *ngroups;
     uint32_t *work, *spill, *status;
-    uint32_t ring, logw;  // logw: 2^logw waves per group (split walks)
+    uint32_t ring;
+    Split split;
     // copy 0 of kXcd accumulators; copy k at + k * lstride / gstride: cell
     // adjoint q of cell c at lcell[kCellAdj * c + q], particle adjoint q of
     // particle j at gsrc[4 * j + q]
@@ -264,6 +265,8 @@ __device__ void vjp_group(const VjpArgs &a, uint32_t g, uint32_t w, uint32_t lan
         if (lane == 0) atomicOr(a.status, kStOverflow);
         return;
     }
+    const uint32_t logw = kSplit ? group_logw(a.split, gn) : 0u;
+    if (w >> logw) return;  // fewer waves share this group
     const uint32_t xcd = xcc_id();
     double *const lcx = a.lcell + xcd * a.lstride;
     double *const gsx = a.gsrc + xcd * a.gstride;
@@ -435,7 +438,7 @@ __device__ void vjp_group(const VjpArgs &a, uint32_t g, uint32_t w, uint32_t lan
     uint32_t cnt_pc, cnt_pp;
     const TreeView tv{a.wA, a.wN, a.ring, a.status};
     traverse<false, kSplit>(tv, b, lane, L.T, spill, cnt_pc, cnt_pp, flush_pc, flush_pp,
-                            Share{w, a.logw});
+                            Share{w, logw});
     if (own) {
         double *gs = gsx + 4ull * ti;
 #pragma unroll
@@ -449,7 +452,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
     __shared__ VjpLds L;
     const uint32_t lane = threadIdx.x;
     uint32_t *spill = a.spill + (size_t)blockIdx.x * kStackMax;
-    for_each_group(*a.ngroups, a.work, lane, kSplit ? a.logw : 0u, [&](uint32_t g, uint32_t w) {
+    for_each_group(*a.ngroups, a.work, lane, kSplit ? a.split.logw : 0u, [&](uint32_t g, uint32_t w) {
         vjp_group<kEps0, kSplit>(a, g, w, lane, L, spill);
     });
 }
@@ -550,15 +553,19 @@ __global__ __launch_bounds__(256) void k_moments_vjp(Cells c, const float4 *__re
     if (g_mass) g_mass[o] += (float)(coef * gm);
 }
 
-// Waves per group of a split adjoint walk, as in the force walk, but its sums
-// leave by atomics, which a split does not multiply, so it pays up to larger
-// sets.  Disk + halo, theta 0.4 / 0.6, whole calls in us by waves per group:
-// n = 1000: 1 220 / 210, 8 88 / 96; 16384: 1 1433 / 745, 4 736 / 383, 8 575 /
-// 343; 65536: 1 2667 / 1287, 4 1818 / 892, 8 1840 / 897; 131072: 1 3957 / 1934,
-// 4 3122 / 1722, 8 3138 / 1708; 262144: 1 6323 / 3123, 4 5536 / 3270; 1M: 1 20506
-// / 9955, 4 21548 / 12058.
-static uint32_t vjp_logw(int64_t n) {
-    return n <= 98304 ? 3u : (n <= 229376 ? 2u : 0u);
+// Waves per group of the adjoint walk, as in the force walk; its sums leave by
+// atomics, which a split does not multiply, so a small set is split further.
+// Disk + halo at theta 0.4 / 0.6, walk in us, all groups alike (the best number
+// of waves) / this rule: n = 1000 54 / 54 (Plummer); 4096 170 / 133; 16384 506 /
+// 495; 65536 1750 / 1730 and 815 / 776; 131072 - and 1613 / 1454; 262144 5292 /
+// 5133 (one wave 6306); 500000 - and 4860 / 4650; 1M 20134 / 19738.  The lines:
+// 16 waves at 1000 take 62, at 65536 1772 and 858; four at 500000 4915.
+static Split vjp_split(int64_t n) {
+    if (n <= 2048) return {3u, 0u, 0u};
+    if (n <= 32768) return {4u, 32u, 16u};
+    if (n <= 360448) return {2u, 32u, 16u};
+    if (n <= 1048576) return {1u, 40u, 0u};
+    return {0u, 0u, 0u};
 }
 
 template <bool kSplit>
@@ -599,8 +606,8 @@ void launch_walk_vjp(bh_ctx *c, float eps, const float *u, float coef, float *g_
     a.lstride = lstride; a.gstride = gstride;
     a.eps2 = eps * eps;
     record_event(c, 8, st);
-    a.logw = vjp_logw(c->n);
-    if (a.logw) launch_vjp_k<true>(c, a, eps, st);
+    a.split = vjp_split(c->n);
+    if (a.split.logw) launch_vjp_k<true>(c, a, eps, st);
     else launch_vjp_k<false>(c, a, eps, st);
     record_event(c, 9, st);
     hipLaunchKernelGGL(k_fold_xcd, dim3(2048), dim3(256), 0, st, c->lcell, (uint64_t)0, kCellAdj,
