@@ -13,12 +13,12 @@
 // Bound, large sets: power.  At 13M (theta 0.4) the vector units issue an
 // instruction every 2.8 cycles of a SIMD and the clock is held at 2.1 GHz
 // (2.45 in the other kernels), so what pays is work not done at all: lanes
-// without a target or without an entry left are switched off (57.1 ms) where
-// they repeated a slice or read a null source (57.6 ms).  Neither five waves
-// per SIMD instead of four (58.8), nor two targets per lane and half the LDS
-// reads (56.9, but 5% slower with the FP16 far field, which it leaves three
+// without a target or without an entry left are switched off (57.5 -> 57.0 ms
+// where they repeated a slice or read a null source).  Then neither five
+// waves per SIMD instead of four (58.8), nor two targets per lane and half the
+// LDS reads (56.9, but 5% slower with the FP16 far field, which it leaves three
 // waves), nor d and Q d by 4 x 4 x 1 matrix products (75.4; they do not
-// overlap the vector units) does better.
+// overlap the vector units) did better.
 #include "walk_common.h"
 
 namespace bh {
@@ -188,7 +188,7 @@ __device__ __forceinline__ void pc16_pair(const h2 ti[3], const Far16Lds &S, uin
 // Evaluate n staged pairs for one phase.
 __device__ __forceinline__ void eval16_chunk(Phase &ph, uint32_t n, const Far16Lds &S) {
     const uint32_t r = ph.r;
-    const uint32_t full = n / r, rem = n - full * r;
+    const uint32_t full = uniform(small_div(n, r)), rem = n - full * r;
     if (!ph.act) return;
     uint32_t k = ph.slice;
     for (uint32_t j = 0; j < full; ++j, k += r) pc16_pair(ph.ti, S, k, ph.acc);
@@ -230,7 +230,7 @@ __device__ __forceinline__ void stage16(Far16Lds &S, uint32_t k, bool valid, con
 template <bool kIsPc, bool kEps0>
 __device__ __forceinline__ void eval_chunk(Phase &ph, uint32_t n, const WalkLds &L, float eps2) {
     const uint32_t r = ph.r;
-    const uint32_t full = n / r, rem = n - full * r;
+    const uint32_t full = uniform(small_div(n, r)), rem = n - full * r;
     if (!ph.act) return;
     uint32_t j = 0;
     {
@@ -325,12 +325,12 @@ __device__ void walk_group(const WalkArgs &a, uint32_t g, uint32_t w, uint32_t l
     Phase p1, p2;
     plan_phases(gn, p1.T, p1.r, p2.T, p2.r);
     p1.act = lane < p1.T * p1.r;
-    p1.slice = p1.act ? lane / p1.T : 0u;
-    p1.tgt = a.xyzm[gb + (p1.act ? lane % p1.T : 0u)];
+    p1.slice = p1.act ? small_div(lane, p1.T) : 0u;
+    p1.tgt = a.xyzm[gb + (p1.act ? lane - p1.slice * p1.T : 0u)];
     p1.acc = make_float4(0.f, 0.f, 0.f, 0.f);
     p2.act = p2.T && lane < p2.T * p2.r;
-    p2.slice = p2.act ? lane / p2.T : 0u;
-    p2.tgt = a.xyzm[gb + (p2.act ? p1.T + lane % p2.T : 0u)];
+    p2.slice = p2.act ? small_div(lane, p2.T) : 0u;
+    p2.tgt = a.xyzm[gb + (p2.act ? p1.T + lane - p2.slice * p2.T : 0u)];
     p2.acc = make_float4(0.f, 0.f, 0.f, 0.f);
     const bool two = p2.T != 0u;
 

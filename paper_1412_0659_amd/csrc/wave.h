@@ -18,7 +18,7 @@ __device__ __forceinline__ uint64_t mask_le(uint32_t lane) {
     return ~0ull >> (63 - lane);
 }
 
-__device__ __forceinline__ uint64_t ballot(bool p) { return __ballot(p); }
+__device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 
 // popcount of the set bits of m below this lane (v_mbcnt)
 __device__ __forceinline__ uint32_t count_below(uint64_t m) {
@@ -26,8 +26,10 @@ __device__ __forceinline__ uint32_t count_below(uint64_t m) {
                                      __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-__device__ __forceinline__ uint32_t shfl(uint32_t v, int src) { return __shfl(v, src, 64); }
-__device__ __forceinline__ float shfl(float v, int src) { return __shfl(v, src, 64); }
+// value of v in lane src (modulo 64)
+__device__ __forceinline__ uint32_t shfl(uint32_t v, uint32_t src) {
+    return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(src << 2), (int)v);
+}
 
 // inclusive prefix sum over the 64 lanes (all lanes active): a Hillis-Steele
 // scan inside each row of 16 lanes with DPP row shifts (lanes whose source is
@@ -55,16 +57,31 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
     return v;
 }
 
-__device__ __forceinline__ float wave_min(float v) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v = fminf(v, __shfl_xor(v, d, 64));
-    return v;
+// minimum / maximum over the 64 lanes (all lanes active), uniform: the steps
+// of the scan above, a lane without a source keeping its own value
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ float dpp_or_own(float v) {
+    const int i = __float_as_int(v);
+    return __int_as_float(__builtin_amdgcn_update_dpp(i, i, kCtrl, kRowMask, 0xf, false));
 }
-
+__device__ __forceinline__ float last_lane(float v) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+__device__ __forceinline__ float wave_min(float v) {
+    v = fminf(v, dpp_or_own<0x111, 0xf>(v));
+    v = fminf(v, dpp_or_own<0x112, 0xf>(v));
+    v = fminf(v, dpp_or_own<0x114, 0xf>(v));
+    v = fminf(v, dpp_or_own<0x118, 0xf>(v));
+    v = fminf(v, dpp_or_own<0x142, 0xa>(v));
+    return last_lane(fminf(v, dpp_or_own<0x143, 0xc>(v)));
+}
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v = fmaxf(v, __shfl_xor(v, d, 64));
-    return v;
+    v = fmaxf(v, dpp_or_own<0x111, 0xf>(v));
+    v = fmaxf(v, dpp_or_own<0x112, 0xf>(v));
+    v = fmaxf(v, dpp_or_own<0x114, 0xf>(v));
+    v = fmaxf(v, dpp_or_own<0x118, 0xf>(v));
+    v = fmaxf(v, dpp_or_own<0x142, 0xa>(v));
+    return last_lane(fmaxf(v, dpp_or_own<0x143, 0xc>(v)));
 }
 
 // Order the LDS accesses of one wave: the DS unit runs a wave's accesses in
@@ -74,6 +91,12 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// a / b for a <= 128, 1 <= b <= 128: (a + 1/2) / b is at least 1/256 from the
+// next whole number, and the approximate quotient off by 4e-5 at most
+__device__ __forceinline__ uint32_t small_div(uint32_t a, uint32_t b) {
+    return (uint32_t)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)b));
 }
 
 // uniform value from lane 0 held in a scalar register
