@@ -39,8 +39,9 @@
 // (1.9e11 adds where eight lanes fill a request): 2.0e9 adds of the cells at 1M
 // (theta 0.4) take 18.5 ms with the pairs left out, everything but the adds 13.9
 // ms (84 VALU instructions and a reciprocal root per particle-cell pair).
-// Measured at 1M, theta 0.4: 19.9 ms, where lane sums by DPP, accumulators
-// field by field and particle pairs evaluated once per side took 23.0.
+// Measured at 1M, theta 0.4: 23.0 ms with lane sums by DPP, accumulators field by
+// field and particle pairs evaluated once per side; 19.4 with a source's sums
+// added once per 32 targets; 17.4 now that they are added once per group.
 #include "walk_common.h"
 
 namespace bh {
@@ -256,7 +257,7 @@ __device__ __forceinline__ void take_targets(const TargetSums &s, VjpLds &L, uin
     wave_sync();
 }
 
-template <bool kEps0, bool kSplit>
+template <bool kEps0>
 __device__ void vjp_group(const VjpArgs &a, uint32_t g, uint32_t w, uint32_t lane, VjpLds &L,
                           uint32_t *spill) {
     const uint32_t gb = a.gbeg[g];
@@ -265,7 +266,7 @@ __device__ void vjp_group(const VjpArgs &a, uint32_t g, uint32_t w, uint32_t lan
         if (lane == 0) atomicOr(a.status, kStOverflow);
         return;
     }
-    const uint32_t logw = kSplit ? group_logw(a.split, gn) : 0u;
+    const uint32_t logw = group_logw(a.split, gn);
     if (w >> logw) return;  // fewer waves share this group
     const uint32_t xcd = xcc_id();
     double *const lcx = a.lcell + xcd * a.lstride;
@@ -314,6 +315,10 @@ __device__ void vjp_group(const VjpArgs &a, uint32_t g, uint32_t w, uint32_t lan
         }
     };
 
+    // More targets than the tiles hold at once: their sums are taken after each
+    // chunk, so that a source's sums still leave once (else once per list).
+    const bool wide = gn > kTiles * kTile;
+
     // particle-cell list; lanes past it hold a null cell (zero mass and
     // moments, far away)
     auto flush_pc = [&](uint32_t n) {
@@ -331,52 +336,56 @@ __device__ void vjp_group(const VjpArgs &a, uint32_t g, uint32_t w, uint32_t lan
                 C.z = tr * a.eps2;
             }
         };
-        for (uint32_t tb = 0; tb < gn; tb += kTiles * kTile) {
-            TargetSums ts{};
-            for (uint32_t base = 0; base < n; base += kChunk) {
-                const uint32_t m = n - base < (uint32_t)kChunk ? n - base : (uint32_t)kChunk;
-                load(base);
-                CellSums cs{};
-                trips(tb, ts, [&](uint32_t t, float wv[3]) {
-                    float T[3], U[3];
-                    target(t, T, U);
-                    pc_adj(T, U, A, B, C, a.eps2, wv, cs);
-                });
-                pc_adj_finish(cs.Q, cs.t);
-                const float v[kCellAdj] = {cs.M,    cs.w[0], cs.w[1], cs.w[2], cs.Q[0],
-                                           cs.Q[1], cs.Q[2], cs.Q[3], cs.Q[4], cs.Q[5]};
-                for (uint32_t half = 0; half < m; half += 32u) {
-                    wave_sync();
-                    if ((lane & 32u) == half) {
+        CellSums cs;
+        auto pair = [&](uint32_t t, float wv[3]) {
+            float T[3], U[3];
+            target(t, T, U);
+            pc_adj(T, U, A, B, C, a.eps2, wv, cs);
+        };
+        TargetSums ts{};
+        for (uint32_t base = 0; base < n; base += kChunk) {
+            const uint32_t m = n - base < (uint32_t)kChunk ? n - base : (uint32_t)kChunk;
+            load(base);
+            cs = CellSums{};
+            for (uint32_t tb = 0; tb < gn; tb += kTiles * kTile) {
+                if (wide) ts = TargetSums{};
+                trips(tb, ts, pair);
+                if (!wide) continue;
+                const CellSums keep = cs;
+                if (sums_finite(ts)) take_targets(ts, L, lane, tb, gt);
+                else lane_sums(tb, pair);
+                cs = keep;
+            }
+            pc_adj_finish(cs.Q, cs.t);
+            const float v[kCellAdj] = {cs.M,    cs.w[0], cs.w[1], cs.w[2], cs.Q[0],
+                                       cs.Q[1], cs.Q[2], cs.Q[3], cs.Q[4], cs.Q[5]};
+            for (uint32_t half = 0; half < m; half += 32u) {
+                wave_sync();
+                if ((lane & 32u) == half) {
 #pragma unroll
-                        for (uint32_t q = 0; q < kCellAdj; ++q)
-                            L.turn[(lane & 31u) * kCellAdj + q] = v[q];
-                    }
-                    wave_sync();
-#pragma unroll
-                    for (uint32_t r = 0; r < kTurn / 64u; ++r) {
-                        const uint32_t f = r * 64u + lane, k = f / kCellAdj, q = f - k * kCellAdj;
-                        if (half + k < m) {
-                            const uint32_t c = L.T.pcidx[base + half + k];
-                            double *lc = c < kHotCells ? lhx : lcx;
-                            add_l2(lc + (size_t)c * kCellAdj + q, (double)L.turn[f]);
-                        }
-                    }
+                    for (uint32_t q = 0; q < kCellAdj; ++q)
+                        L.turn[(lane & 31u) * kCellAdj + q] = v[q];
                 }
                 wave_sync();
-            }
-            if (sums_finite(ts)) {
-                take_targets(ts, L, lane, tb, gt);
-            } else {
-                for (uint32_t base = 0; base < n; base += kChunk) {
-                    load(base);
-                    CellSums cs{};
-                    lane_sums(tb, [&](uint32_t t, float wv[3]) {
-                        float T[3], U[3];
-                        target(t, T, U);
-                        pc_adj(T, U, A, B, C, a.eps2, wv, cs);
-                    });
+#pragma unroll
+                for (uint32_t r = 0; r < kTurn / 64u; ++r) {
+                    const uint32_t f = r * 64u + lane, k = f / kCellAdj, q = f - k * kCellAdj;
+                    if (half + k < m) {
+                        const uint32_t c = L.T.pcidx[base + half + k];
+                        double *lc = c < kHotCells ? lhx : lcx;
+                        add_l2(lc + (size_t)c * kCellAdj + q, (double)L.turn[f]);
+                    }
                 }
+            }
+            wave_sync();
+        }
+        if (wide) return;
+        if (sums_finite(ts)) {
+            take_targets(ts, L, lane, 0u, gt);
+        } else {
+            for (uint32_t base = 0; base < n; base += kChunk) {
+                load(base);
+                lane_sums(0u, pair);
             }
         }
         wave_sync();
@@ -393,43 +402,45 @@ __device__ void vjp_group(const VjpArgs &a, uint32_t g, uint32_t w, uint32_t lan
                 P = a.xyzm[j];
             }
         };
-        for (uint32_t tb = 0; tb < gn; tb += kTiles * kTile) {
-            TargetSums ts{};
-            for (uint32_t base = 0; base < n; base += kChunk) {
-                const uint32_t m = n - base < (uint32_t)kChunk ? n - base : (uint32_t)kChunk;
-                load(base);
-                float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-                auto pair = [&](uint32_t t, float wv[3]) {
-                    float T[3], U[3], gm;
-                    target(t, T, U);
-                    pp_adj<kEps0>(T, U, P, a.eps2, wv, gm);
-                    if (gb + t == j) wv[0] = wv[1] = wv[2] = gm = 0.f;
-                    s.x += wv[0]; s.y += wv[1]; s.z += wv[2]; s.w += gm;
-                };
+        float4 s;  // the source's sums
+        auto pair = [&](uint32_t t, float wv[3]) {
+            float T[3], U[3], gm;
+            target(t, T, U);
+            pp_adj<kEps0>(T, U, P, a.eps2, wv, gm);
+            if (gb + t == j) wv[0] = wv[1] = wv[2] = gm = 0.f;
+            s.x += wv[0]; s.y += wv[1]; s.z += wv[2]; s.w += gm;
+        };
+        TargetSums ts{};
+        for (uint32_t base = 0; base < n; base += kChunk) {
+            const uint32_t m = n - base < (uint32_t)kChunk ? n - base : (uint32_t)kChunk;
+            load(base);
+            s = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (uint32_t tb = 0; tb < gn; tb += kTiles * kTile) {
+                if (wide) ts = TargetSums{};
                 trips(tb, ts, pair);
-                wave_sync();
-                reinterpret_cast<float4 *>(L.turn)[lane] = s;
-                wave_sync();
-#pragma unroll
-                for (uint32_t r = 0; r < 4u; ++r) {
-                    const uint32_t f = r * 64u + lane, k = f >> 2;
-                    if (k < m)
-                        add_l2(gsx + 4ull * L.T.ppidx[base + k] + (f & 3u), (double)L.turn[f]);
-                }
-                wave_sync();
+                if (!wide) continue;
+                const float4 keep = s;
+                if (sums_finite(ts)) take_targets(ts, L, lane, tb, gt);
+                else lane_sums(tb, pair);
+                s = keep;
             }
-            if (sums_finite(ts)) {
-                take_targets(ts, L, lane, tb, gt);
-            } else {
-                for (uint32_t base = 0; base < n; base += kChunk) {
-                    load(base);
-                    lane_sums(tb, [&](uint32_t t, float wv[3]) {
-                        float T[3], U[3], gm;
-                        target(t, T, U);
-                        pp_adj<kEps0>(T, U, P, a.eps2, wv, gm);
-                        if (gb + t == j) wv[0] = wv[1] = wv[2] = 0.f;
-                    });
-                }
+            wave_sync();
+            reinterpret_cast<float4 *>(L.turn)[lane] = s;
+            wave_sync();
+#pragma unroll
+            for (uint32_t r = 0; r < 4u; ++r) {
+                const uint32_t f = r * 64u + lane, k = f >> 2;
+                if (k < m) add_l2(gsx + 4ull * L.T.ppidx[base + k] + (f & 3u), (double)L.turn[f]);
+            }
+            wave_sync();
+        }
+        if (wide) return;
+        if (sums_finite(ts)) {
+            take_targets(ts, L, lane, 0u, gt);
+        } else {
+            for (uint32_t base = 0; base < n; base += kChunk) {
+                load(base);
+                lane_sums(0u, pair);
             }
         }
         wave_sync();
@@ -437,7 +448,7 @@ __device__ void vjp_group(const VjpArgs &a, uint32_t g, uint32_t w, uint32_t lan
 
     uint32_t cnt_pc, cnt_pp;
     const TreeView tv{a.wA, a.wN, a.ring, a.status};
-    traverse<false, kSplit>(tv, b, lane, L.T, spill, cnt_pc, cnt_pp, flush_pc, flush_pp,
+    traverse<false, true>(tv, b, lane, L.T, spill, cnt_pc, cnt_pp, flush_pc, flush_pp,
                             Share{w, logw});
     if (own) {
         double *gs = gsx + 4ull * ti;
@@ -447,13 +458,13 @@ __device__ void vjp_group(const VjpArgs &a, uint32_t g, uint32_t w, uint32_t lan
     wave_sync();
 }
 
-template <bool kEps0, bool kSplit>
+template <bool kEps0>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_walk_vjp(VjpArgs a) {
     __shared__ VjpLds L;
     const uint32_t lane = threadIdx.x;
     uint32_t *spill = a.spill + (size_t)blockIdx.x * kStackMax;
-    for_each_group(*a.ngroups, a.work, lane, kSplit ? a.split.logw : 0u, [&](uint32_t g, uint32_t w) {
-        vjp_group<kEps0, kSplit>(a, g, w, lane, L, spill);
+    for_each_group(*a.ngroups, a.work, lane, a.split.logw, [&](uint32_t g, uint32_t w) {
+        vjp_group<kEps0>(a, g, w, lane, L, spill);
     });
 }
 
@@ -556,25 +567,16 @@ __global__ __launch_bounds__(256) void k_moments_vjp(Cells c, const float4 *__re
 // Waves per group of the adjoint walk, as in the force walk; its sums leave by
 // atomics, which a split does not multiply, so a small set is split further.
 // Disk + halo at theta 0.4 / 0.6, walk in us, all groups alike (the best number
-// of waves) / this rule: n = 1000 54 / 54 (Plummer); 4096 170 / 133; 16384 506 /
-// 495; 65536 1750 / 1730 and 815 / 776; 131072 - and 1613 / 1454; 262144 5292 /
-// 5133 (one wave 6306); 500000 - and 4860 / 4650; 1M 20134 / 19738.  The lines:
-// 16 waves at 1000 take 62, at 65536 1772 and 858; four at 500000 4915.
+// of waves) / this rule: n = 1000 51 / 51 (Plummer); 4096 156 / 128; 16384 511 /
+// 468; 65536 1650 / 1484 and 759 / 676; 131072 - and 1452 / 1276; 262144 4881 /
+// 4610 (one wave 6001); 500000 - and 4401 / 4082; 1M 17816 / 16990; 2M 34749 /
+// 34514 and 16322 / 16167; 7M equal.  The lines: 16 waves at 1000 take 57, at
+// 65536 1566 and 802; four at 500000 4348.
 static Split vjp_split(int64_t n) {
     if (n <= 2048) return {3u, 0u, 0u};
     if (n <= 32768) return {4u, 32u, 16u};
     if (n <= 360448) return {2u, 32u, 16u};
-    if (n <= 1048576) return {1u, 40u, 0u};
-    return {0u, 0u, 0u};
-}
-
-template <bool kSplit>
-static void launch_vjp_k(bh_ctx *c, const VjpArgs &a, float eps, hipStream_t st) {
-    const dim3 grid(c->walk_grid), block(64);
-    if (eps == 0.f)
-        hipLaunchKernelGGL((k_walk_vjp<true, kSplit>), grid, block, 0, st, a);
-    else
-        hipLaunchKernelGGL((k_walk_vjp<false, kSplit>), grid, block, 0, st, a);
+    return {1u, 40u, 0u};
 }
 
 void launch_walk_vjp(bh_ctx *c, float eps, const float *u, float coef, float *g_pos,
@@ -607,8 +609,9 @@ void launch_walk_vjp(bh_ctx *c, float eps, const float *u, float coef, float *g_
     a.eps2 = eps * eps;
     record_event(c, 8, st);
     a.split = vjp_split(c->n);
-    if (a.split.logw) launch_vjp_k<true>(c, a, eps, st);
-    else launch_vjp_k<false>(c, a, eps, st);
+    const dim3 walks(c->walk_grid);
+    if (eps == 0.f) hipLaunchKernelGGL(k_walk_vjp<true>, walks, dim3(64), 0, st, a);
+    else hipLaunchKernelGGL(k_walk_vjp<false>, walks, dim3(64), 0, st, a);
     record_event(c, 9, st);
     hipLaunchKernelGGL(k_fold_xcd, dim3(2048), dim3(256), 0, st, c->lcell, (uint64_t)0, kCellAdj,
                        lstride, ls, (const double *)c->lhot);
