@@ -63,12 +63,6 @@ __device__ __forceinline__ uint32_t key_lower_bound(const uint64_t *__restrict__
     return lo;
 }
 
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, d, 64));
-    return v;
-}
-
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 // Levels of every particle and, per tile, the number of cells of each level
@@ -149,8 +143,8 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_levels(const uint64_t *__
         if (lane == 0 && gm) atomicAdd(&cnt[kGroupCh], (uint32_t)__popcll(gm));
         const bool starts = valid && lo <= hi;
         if (ballot(starts) == 0ull) continue;
-        const uint32_t l1 = wave_max_u32(starts ? hi : 0u),
-                       l0 = 31u - wave_max_u32(starts ? 31u - lo : 0u);
+        const uint32_t l1 = wave_max(starts ? hi : 0u),
+                       l0 = 31u - wave_max(starts ? 31u - lo : 0u);
         for (uint32_t l = l0; l <= l1; ++l) {
             const uint64_t m = ballot(starts && lo <= l && l <= hi);
             if (lane == 0 && m) atomicAdd(&cnt[l], (uint32_t)__popcll(m));
@@ -237,19 +231,21 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_write(
         if (lane == 0) mask[kGroupCh][word] = gm;
         const bool starts = lo <= hi;
         if (ballot(starts) == 0ull) continue;
-        const uint32_t l1 = wave_max_u32(starts ? hi : 0u),
-                       l0 = 31u - wave_max_u32(starts ? 31u - lo : 0u);
+        const uint32_t l1 = wave_max(starts ? hi : 0u),
+                       l0 = 31u - wave_max(starts ? 31u - lo : 0u);
         for (uint32_t l = l0; l <= l1; ++l) {
             const uint64_t m = ballot(starts && lo <= l && l <= hi);
             if (lane == 0) mask[l][word] = m;
         }
     }
     __syncthreads();
-    for (uint32_t q = threadIdx.x; q < (kLevels + 1) * kTreeWords; q += kTreeThreads) {
-        const uint32_t l = q / kTreeWords, word = q % kTreeWords;
-        uint32_t s = tcnt[(size_t)l * ntiles + blockIdx.x];
-        for (uint32_t k = 0; k < word; ++k) s += (uint32_t)__popcll(mask[l][k]);
-        pre[l][word] = s;
+    static_assert(kTreeWords == 16, "a level's words in a row of 16 lanes");
+    for (uint32_t q0 = 0; q0 < (kLevels + 1) * kTreeWords; q0 += kTreeThreads) {
+        const uint32_t q = q0 + threadIdx.x, l = q / kTreeWords, word = q % kTreeWords;
+        const bool have = l <= kLevels;
+        const uint32_t cnt = have ? (uint32_t)__popcll(mask[l][word]) : 0u;
+        const uint32_t s = row_incl_scan(cnt) - cnt;
+        if (have) pre[l][word] = tcnt[(size_t)l * ntiles + blockIdx.x] + s;
     }
     __syncthreads();
     // numbers of the cells of level l: those that start before particle
@@ -278,7 +274,7 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_write(
         const bool starts = valid && lo <= hi, ends = valid && ln[r] <= hi;
         if (ballot(starts || ends) == 0ull) continue;
         const uint32_t first = min(starts ? lo : 31u, ends ? ln[r] : 31u);
-        const uint32_t l1 = wave_max_u32(starts || ends ? hi : 0u), l0 = 31u - wave_max_u32(31u - first);
+        const uint32_t l1 = wave_max(starts || ends ? hi : 0u), l0 = 31u - wave_max(31u - first);
         for (uint32_t l = l0; l <= l1; ++l) {
             const uint32_t s0 = read_lane(lstart, l);
             const uint32_t s1 = read_lane(lend, l);  // the start of level l + 1

@@ -259,10 +259,11 @@ __global__ __launch_bounds__(kMomThreads, 4) void k_moments_tile(MomArgs a, uint
 #pragma unroll
     for (int s = 0; s < kOwn; ++s) {
         const uint32_t q = threadIdx.x + s * kMomThreads;
-        uint32_t l = 0;
         lev[s] = kNone;  // no cell
         if (q >= total) continue;
-        while (q >= ofs[l + 1u]) ++l;
+        uint32_t l = 0;
+#pragma unroll
+        for (int k = 1; k < kLevels; ++k) l += q >= ofs[k] ? 1u : 0u;
         if (q - ofs[l] >= inside[l]) continue;
         lev[s] = l;
         const uint32_t i = first[l] + (q - ofs[l]);
@@ -340,8 +341,7 @@ __global__ __launch_bounds__(kMomThreads, 4) void k_moments_tile(MomArgs a, uint
 }
 
 struct Across {
-    uint32_t i, b0, n0, k0, nch;  // i = kNone: none
-    uint32_t p0, p1;              // prefix
+    uint32_t i, k0, nch;  // i = kNone: none
 };
 
 constexpr int kAcrossThreads = 1024;
@@ -349,12 +349,22 @@ constexpr int kAcrossUnits = kAcrossThreads / 8;
 constexpr int kAcrossRow = kAcrossThreads + 2;  // (the eight lanes' rows in different banks)
 static_assert(kAcrossUnits >= kSpanTiles, "a span's tiles in one round");
 
-// A parent across an end, by eight lanes of a wave (have: these eight have
-// one): lane k reads child k, then each sum over the children runs in child
-// order in one lane, through the LDS rows ch.
-__device__ __forceinline__ void group_parent(const MomArgs &a, uint32_t lev, bool have,
-                                             const Across &o, double (*ch)[kAcrossRow]) {
-    const Cells &c = a.c;
+// row[b] = the sum of row[b .. b + n - 1], n <= 8, in that order (the eight
+// reads go out together)
+__device__ __forceinline__ void ordered_sum(double *row, uint32_t b, uint32_t n) {
+    double x[8], v = 0.0;
+#pragma unroll
+    for (uint32_t j = 0; j < 8u; ++j) x[j] = row[b + j];
+#pragma unroll
+    for (uint32_t j = 0; j < 8u; ++j) v = j < n ? v + x[j] : v;
+    row[b] = v;
+}
+
+// The moments of a parent across an end, by eight lanes of a wave (have:
+// these eight have one): lane k reads child k, then each sum over the children
+// runs in child order in one lane, through the LDS rows ch.
+__device__ __forceinline__ void group_parent(const Cells &c, bool have, const Across &o,
+                                             double (*ch)[kAcrossRow]) {
     const uint32_t t = threadIdx.x, k = t & 7u, b = t & ~7u;
     const double2 *Q2 = reinterpret_cast<const double2 *>(c.Q);
     const uint32_t nch = have ? o.nch : 0u;
@@ -368,15 +378,10 @@ __device__ __forceinline__ void group_parent(const MomArgs &a, uint32_t lev, boo
     }
     ch[0][t] = cm; ch[1][t] = s0; ch[2][t] = s1; ch[3][t] = s2;
     wave_sync();
-    if (k < 4u) {
-        double v = 0.0;
-        for (uint32_t j = 0; j < nch; ++j) v = v + ch[k][b + j];
-        ch[k][b] = v;
-    }
+    if (k < 4u) ordered_sum(ch[k], b, nch);
     wave_sync();
-    Mom r;
-    r.M = ch[0][b]; r.s0 = ch[1][b]; r.s1 = ch[2][b]; r.s2 = ch[3][b];
-    const double c0 = r.s0 / r.M, c1 = r.s1 / r.M, c2 = r.s2 / r.M;
+    const double M = ch[0][b];
+    const double c0 = ch[1][b] / M, c1 = ch[2][b] / M, c2 = ch[3][b] / M;
     const double d0 = s0 / cm - c0, d1 = s1 / cm - c1, d2 = s2 / cm - c2;
     ch[4][t] = qa.x + (cm * d0) * d0;
     ch[5][t] = qa.y + (cm * d1) * d1;
@@ -385,17 +390,13 @@ __device__ __forceinline__ void group_parent(const MomArgs &a, uint32_t lev, boo
     ch[8][t] = qc.x + (cm * d0) * d2;
     ch[9][t] = qc.y + (cm * d1) * d2;
     wave_sync();
-    if (k < 6u) {
-        double v = 0.0;
-        for (uint32_t j = 0; j < nch; ++j) v = v + ch[4u + k][b + j];
-        ch[4u + k][b] = v;
-    }
+    if (k < 6u) ordered_sum(ch[4u + k], b, nch);
     wave_sync();
-    if (have && k == 0u) {
-        r.q0 = ch[4][b]; r.q1 = ch[5][b]; r.q2 = ch[6][b];
-        r.q3 = ch[7][b]; r.q4 = ch[8][b]; r.q5 = ch[9][b];
-        cell_out(a, o.i, lev, ((uint64_t)o.p1 << 32) | o.p0, o.b0, o.n0, o.k0, o.nch, r, c0, c1,
-                 c2);
+    if (have) {  // what the next level reads
+        const size_t i = o.i;
+        if (k == 0u) c.M[i] = ch[0][b];
+        if (k < 3u) c.S[3 * i + k] = ch[1u + k][b];
+        if (k < 6u) c.Q[6 * i + k] = ch[4u + k][b];
     }
     wave_sync();
 }
@@ -456,14 +457,23 @@ __device__ __forceinline__ void across_pass(const MomArgs &a, uint32_t ntiles, u
             auto pick = [&](uint32_t v0, uint32_t v1, uint32_t v2) {
                 return shfl(l < 8u ? v0 : (l < 16u ? v1 : v2), src);
             };
-            Across o{pick(wi[0], wi[1], wi[2]), 0u, 0u, 0u, 0u, 0u, 0u};
+            Across o{pick(wi[0], wi[1], wi[2]), 0u, 0u};
             if (ballot(o.i != kNone) != 0ull) {
-                o.b0 = pick(wb[0], wb[1], wb[2]); o.n0 = pick(wn[0], wn[1], wn[2]);
                 o.k0 = pick(wk[0], wk[1], wk[2]); o.nch = pick(wc[0], wc[1], wc[2]);
-                o.p0 = pick(wp0[0], wp0[1], wp0[2]); o.p1 = pick(wp1[0], wp1[1], wp1[2]);
-                group_parent(a, l, o.i != kNone, o, ch);
+                group_parent(c, o.i != kNone, o, ch);
             }
             __syncthreads();  // the next level up reads these cells
+        }
+        // the rest of their records, off the chain of levels
+#pragma unroll
+        for (int s = 0; s < kOwn; ++s) {
+            const size_t i = wi[s];
+            if (wi[s] == kNone) continue;
+            const Mom r{c.M[i],     c.S[3 * i],     c.S[3 * i + 1], c.S[3 * i + 2], c.Q[6 * i],
+                        c.Q[6 * i + 1], c.Q[6 * i + 2], c.Q[6 * i + 3], c.Q[6 * i + 4],
+                        c.Q[6 * i + 5]};
+            cell_out(a, wi[s], k + 8u * (uint32_t)s, ((uint64_t)wp1[s] << 32) | wp0[s], wb[s],
+                     wn[s], wk[s], wc[s], r, r.s0 / r.M, r.s1 / r.M, r.s2 / r.M);
         }
         return;
     }

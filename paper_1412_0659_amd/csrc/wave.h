@@ -46,6 +46,16 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v, uint32_t lane) {
     return (uint32_t)s;
 }
 
+// inclusive prefix sum inside each row of 16 lanes
+__device__ __forceinline__ uint32_t row_incl_scan(uint32_t v) {
+    int s = (int)v;
+    s += __builtin_amdgcn_update_dpp(0, s, 0x111, 0xf, 0xf, false);
+    s += __builtin_amdgcn_update_dpp(0, s, 0x112, 0xf, 0xf, false);
+    s += __builtin_amdgcn_update_dpp(0, s, 0x114, 0xf, 0xf, false);
+    s += __builtin_amdgcn_update_dpp(0, s, 0x118, 0xf, 0xf, false);
+    return (uint32_t)s;
+}
+
 // value of v in lane src (src uniform across the wave)
 __device__ __forceinline__ uint32_t read_lane(uint32_t v, uint32_t src) {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)src);
@@ -82,6 +92,19 @@ __device__ __forceinline__ float wave_max(float v) {
     v = fmaxf(v, dpp_or_own<0x118, 0xf>(v));
     v = fmaxf(v, dpp_or_own<0x142, 0xa>(v));
     return last_lane(fmaxf(v, dpp_or_own<0x143, 0xc>(v)));
+}
+
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ uint32_t dpp_or_own(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, kCtrl, kRowMask, 0xf, false);
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+    v = max(v, dpp_or_own<0x111, 0xf>(v));
+    v = max(v, dpp_or_own<0x112, 0xf>(v));
+    v = max(v, dpp_or_own<0x114, 0xf>(v));
+    v = max(v, dpp_or_own<0x118, 0xf>(v));
+    v = max(v, dpp_or_own<0x142, 0xa>(v));
+    return read_lane(max(v, dpp_or_own<0x143, 0xc>(v)), 63u);
 }
 
 // Order the LDS accesses of one wave: the DS unit runs a wave's accesses in
