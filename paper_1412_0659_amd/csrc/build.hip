@@ -27,22 +27,21 @@
 //
 // Bound: memory, 16 B of keys and 4 B of levels per particle and 36 B per
 // cell; on small sets the latency of the three launches.  Measured at 13M
-// (disk + halo): 0.23 ms (levels 97, sums 14, cells 122 us), where splitting
-// level by level with binary searches (three launches per level) took 0.76 ms;
-// at 16384: 42 against 260 us.
+// (disk + halo): 0.20 ms, where splitting level by level with binary searches
+// (three launches per level) took 0.76 ms; at 16384: 18 against 260 us.
 //
 // A cell is a group iff (count <= ncrit or it is a leaf) and (it is the root
 // or its parent holds more than ncrit), so the group of particle i is the
 // cell of level g(i) = min(D_ncrit(i) + 1, hi(i)); groups are numbered in key
 // order as one more level.  A group cell larger than ncrit (a leaf, for
 // nleaf > ncrit or coincident keys) is cut into chunks of ncrit.
+#include <type_traits>
+
 #include "bh_internal.h"
 #include "wave.h"
 
 namespace bh {
 
-constexpr int kTreeThreads = 256;
-constexpr int kTreeItems = kTreeTile / kTreeThreads;
 constexpr int kTreeWords = kTreeTile / 64;
 constexpr int kHalo = 64;               // nleaf, ncrit <= 64
 constexpr int kGroupCh = kLevels;       // the groups' channel of the tile counts
@@ -69,23 +68,25 @@ typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 // (and of groups) that start in it.  Window maxima by doubling: entry j holds
 // max over [j, j + 2^k) of common(key[j], key[j + m]) + 1, for m = nleaf and
 // m = ncrit in the two halves of a word.
-__global__ __launch_bounds__(kTreeThreads) void k_tree_levels(const uint64_t *__restrict__ key,
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void k_tree_levels(const uint64_t *__restrict__ key,
                                                               uint32_t n, uint32_t nleaf,
                                                               uint32_t ncrit, uint32_t ntiles,
                                                               uint16_t *__restrict__ lev,
                                                               uint32_t *__restrict__ tcnt) {
+    constexpr int kItems = kTreeTile / kThreads;
     constexpr int kSpan = kTreeTile + kHalo;  // entries j = t0 - kHalo .. t0 + kTreeTile - 1
     __shared__ uint64_t k[kTreeTile + 2 * kHalo];
     __shared__ u16x2 win[2][kSpan];
     __shared__ uint32_t cnt[kLevels + 1];
     const int64_t t0 = (int64_t)blockIdx.x * kTreeTile;
-    for (int q = threadIdx.x; q < kTreeTile + 2 * kHalo; q += kTreeThreads) {
+    for (int q = threadIdx.x; q < kTreeTile + 2 * kHalo; q += kThreads) {
         const int64_t j = t0 - kHalo + q;
         k[q] = j >= 0 && j < (int64_t)n ? key[j] : 0ull;
     }
     if (threadIdx.x <= kLevels) cnt[threadIdx.x] = 0u;
     __syncthreads();
-    for (int q = threadIdx.x; q < kSpan; q += kTreeThreads) {
+    for (int q = threadIdx.x; q < kSpan; q += kThreads) {
         const int64_t j = t0 - kHalo + q;
         u16x2 v = {0, 0};
         if (j >= 0) {
@@ -97,13 +98,13 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_levels(const uint64_t *__
     __syncthreads();
     const int kl = 31 - __clz((int)nleaf + 1), kc = 31 - __clz((int)ncrit + 1);
     const int steps = max(kl, kc);
-    uint32_t dl[kTreeItems], dc[kTreeItems];  // D + 1 of this thread's particles
+    uint32_t dl[kItems], dc[kItems];  // D + 1 of this thread's particles
     for (int s = 0; s <= steps; ++s) {
         const u16x2 *w = win[s & 1];
         if (s == kl || s == kc) {
 #pragma unroll
-            for (int r = 0; r < kTreeItems; ++r) {
-                const int q = kHalo + r * kTreeThreads + (int)threadIdx.x;
+            for (int r = 0; r < kItems; ++r) {
+                const int q = kHalo + r * kThreads + (int)threadIdx.x;
                 if (s == kl)
                     dl[r] = max((uint32_t)w[q - (int)nleaf].x, (uint32_t)w[q - (1 << kl) + 1].x);
                 if (s == kc)
@@ -112,7 +113,7 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_levels(const uint64_t *__
         }
         if (s == steps) break;
         u16x2 *o = win[(s + 1) & 1];
-        for (int q = threadIdx.x; q < kSpan; q += kTreeThreads) {
+        for (int q = threadIdx.x; q < kSpan; q += kThreads) {
             const u16x2 a = w[q], b = q + (1 << s) < kSpan ? w[q + (1 << s)] : a;
             o[q] = __builtin_elementwise_max(a, b);
         }
@@ -120,8 +121,8 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_levels(const uint64_t *__
     }
     const uint32_t lane = lane_id();
 #pragma unroll
-    for (int r = 0; r < kTreeItems; ++r) {
-        const int q = kHalo + r * kTreeThreads + (int)threadIdx.x;
+    for (int r = 0; r < kItems; ++r) {
+        const int q = kHalo + r * kThreads + (int)threadIdx.x;
         const int64_t i = t0 + q - kHalo;
         const bool valid = i < (int64_t)n;
         uint32_t lo = 31u, hi = 0u;
@@ -196,16 +197,18 @@ __global__ __launch_bounds__(1024) void k_tree_scan(uint32_t *__restrict__ tcnt,
 // its last particle) is left in count and the end of its children (0 for a
 // leaf) in nchild: its first and last particle may lie in different tiles.
 // The moment pass turns both into counts.
-__global__ __launch_bounds__(kTreeThreads) void k_tree_write(
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void k_tree_write(
     Cells c, const uint64_t *__restrict__ key, const uint16_t *__restrict__ lev, uint32_t n,
     uint32_t ntiles, const uint32_t *__restrict__ tcnt, const uint32_t *__restrict__ tot,
     uint32_t cap, uint32_t *__restrict__ gbeg, uint32_t gcap, uint32_t *__restrict__ gpar,
     uint32_t *ngroups, uint32_t *status) {
+    constexpr int kItems = kTreeTile / kThreads;
     __shared__ uint64_t mask[kLevels + 1][kTreeWords];
     __shared__ uint32_t pre[kLevels + 1][kTreeWords];  // starts of the level before the word
     const uint32_t lane = lane_id(), w = threadIdx.x >> 6;
     const uint32_t t0 = blockIdx.x * kTreeTile;
-    for (uint32_t q = threadIdx.x; q < (kLevels + 1) * kTreeWords; q += kTreeThreads)
+    for (uint32_t q = threadIdx.x; q < (kLevels + 1) * kTreeWords; q += kThreads)
         (&mask[0][0])[q] = 0ull;
     // level starts (every wave for itself; lane l holds level l's)
     const uint32_t lt = lane < kLevels ? tot[lane] : 0u;
@@ -219,14 +222,14 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_write(
         }
     }
     __syncthreads();
-    uint32_t lv[kTreeItems], ln[kTreeItems];
+    uint32_t lv[kItems], ln[kItems];
 #pragma unroll
-    for (int r = 0; r < kTreeItems; ++r) {
-        const uint32_t i = t0 + r * kTreeThreads + threadIdx.x;
+    for (int r = 0; r < kItems; ++r) {
+        const uint32_t i = t0 + r * kThreads + threadIdx.x;
         lv[r] = i < n ? lev[i] : 31u;           // no cell
         ln[r] = i + 1u < n ? lv_lo(lev[i + 1u]) : 0u;  // every cell ends with the last particle
         const uint32_t lo = lv_lo(lv[r]), hi = lv_hi(lv[r]);
-        const uint32_t word = r * (kTreeThreads / 64) + w;
+        const uint32_t word = r * (kThreads / 64) + w;
         const uint64_t gm = ballot(i < n && lv_group(lv[r]));
         if (lane == 0) mask[kGroupCh][word] = gm;
         const bool starts = lo <= hi;
@@ -240,7 +243,7 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_write(
     }
     __syncthreads();
     static_assert(kTreeWords == 16, "a level's words in a row of 16 lanes");
-    for (uint32_t q0 = 0; q0 < (kLevels + 1) * kTreeWords; q0 += kTreeThreads) {
+    for (uint32_t q0 = 0; q0 < (kLevels + 1) * kTreeWords; q0 += kThreads) {
         const uint32_t q = q0 + threadIdx.x, l = q / kTreeWords, word = q % kTreeWords;
         const bool have = l <= kLevels;
         const uint32_t cnt = have ? (uint32_t)__popcll(mask[l][word]) : 0u;
@@ -257,9 +260,9 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_write(
         return pre[l][word] + (uint32_t)__popcll(mask[l][word] & mask_le(lane));
     };
 #pragma unroll
-    for (int r = 0; r < kTreeItems; ++r) {
-        const uint32_t i = t0 + r * kTreeThreads + threadIdx.x;
-        const uint32_t word = r * (kTreeThreads / 64) + w;
+    for (int r = 0; r < kItems; ++r) {
+        const uint32_t i = t0 + r * kThreads + threadIdx.x;
+        const uint32_t word = r * (kThreads / 64) + w;
         const uint32_t lo = lv_lo(lv[r]), hi = lv_hi(lv[r]);
         const bool valid = i < n;
         const uint64_t ky = valid ? key[i] : 0ull;
@@ -340,17 +343,28 @@ void launch_build(bh_ctx *ctx, uint32_t n, hipStream_t st) {
     Groups &g = ctx->groups;
     const uint64_t *key = ctx->sort.key[0];
     const uint32_t nt = cdiv(n, kTreeTile);
-    hipLaunchKernelGGL(k_tree_levels, dim3(nt), dim3(kTreeThreads), 0, st, key, n,
-                       (uint32_t)ctx->p.nleaf, (uint32_t)ctx->p.ncrit, nt, c.lev, c.tcnt);
-    hipLaunchKernelGGL(k_tree_scan, dim3(kLevels + 1), dim3(1024), 0, st, c.tcnt, nt, c.ttot);
     // paired target sets: the groups first go to the sort's second index
     // buffer, each group's parent cell to npp
     uint32_t *gbeg0 = ctx->pair_groups ? ctx->sort.idx[1] : g.begin;
     uint32_t *gpar = ctx->pair_groups ? g.npp : nullptr;
-    hipLaunchKernelGGL(k_tree_write, dim3(nt), dim3(kTreeThreads), 0, st, c, key,
-                       (const uint16_t *)c.lev, n, nt, (const uint32_t *)c.tcnt,
-                       (const uint32_t *)c.ttot, (uint32_t)ctx->cap_cells, gbeg0,
-                       ctx->pair_groups ? n : n + 1u, gpar, g.count_dev, ctx->status);
+    auto launch = [&](auto threads) {
+        constexpr int kThreads = decltype(threads)::value;
+        hipLaunchKernelGGL(k_tree_levels<kThreads>, dim3(nt), dim3(kThreads), 0, st, key, n,
+                           (uint32_t)ctx->p.nleaf, (uint32_t)ctx->p.ncrit, nt, c.lev, c.tcnt);
+        hipLaunchKernelGGL(k_tree_scan, dim3(kLevels + 1), dim3(1024), 0, st, c.tcnt, nt, c.ttot);
+        hipLaunchKernelGGL(k_tree_write<kThreads>, dim3(nt), dim3(kThreads), 0, st, c, key,
+                           (const uint16_t *)c.lev, n, nt, (const uint32_t *)c.tcnt,
+                           (const uint32_t *)c.ttot, (uint32_t)ctx->cap_cells, gbeg0,
+                           ctx->pair_groups ? n : n + 1u, gpar, g.count_dev, ctx->status);
+    };
+    // Threads of a tile.  Up to a tile a CU and beyond, a thread per particle
+    // keeps the chain of levels short; with many tiles the waves of other blocks
+    // fill the gaps and 16 waves waiting for each other are slower.  The three
+    // launches by 256 / 512 / 1024 threads, in us: 1000 27 / 20 / 17; 16384 29 / 22
+    // / 18; 65536 28 / 21 / 18; 1M 37 / 32 / 37; 13M 201 / 221 / 283.
+    if (n <= 524288u) launch(std::integral_constant<int, 1024>());
+    else if (n <= 4194304u) launch(std::integral_constant<int, 512>());
+    else launch(std::integral_constant<int, 256>());
     if (!ctx->pair_groups) return;
     hipLaunchKernelGGL(k_pair_flags, dim3(cdiv(n, 256)), dim3(256), 0, st,
                        (const uint32_t *)gbeg0, (const uint32_t *)g.count_dev,

@@ -27,13 +27,17 @@
 // number of particles and levels (one to kTreeTile particles, two to a span).
 //
 // Bound: memory, 16 B per particle and 200 B per cell; on small sets the
-// chain of levels (4 us a level in the spans).  Measured: 0.38 ms at 13M (tiles
-// 263, spans 52, top 67 us), 0.105 ms at 1M, where one launch per level took
-// 0.42 and 0.135 ms (22 launches on a new particle set); 16384: 50 against 95
-// us, 1000: 22 against 67.  Also measured: one lane per parent in the spans and
-// the top (its 27 FP64 divisions in a row): 54 and 135 us at 13M; eight parents
-// a wave with the sums by shuffles: 101 and 191 us; topology loaded again on
-// every level and records written from inside it: tiles 422 us.
+// chain of levels (0.6 us a level in a tile, 2.5 us in the spans).  Measured:
+// 0.36 ms at 13M, 0.092 ms at 1M, where one launch per level took 0.42 and
+// 0.135 ms (22 launches on a new particle set); 16384: 42 against 95 us, 1000:
+// 16 against 67.  A tile's parents by one lane each took 25 us at 1000 and 51 at
+// 16384 with the spans (a chain of 400 instructions a level against 120), with
+// eight lanes per parent split by child instead of by quantity the tile's LDS
+// would hold three blocks a CU instead of four.  Across tile ends, one lane per
+// parent (its 27 FP64 divisions in a row) took 54 and 135 us in the spans and
+// the top at 13M; sums by shuffles 101 and 191; LDS sums one read at a time with
+// all records written inside the chain of levels 52 and 67, 15 us more at 100003
+// than now.
 #include "bh_internal.h"
 #include "wave.h"
 
@@ -209,14 +213,28 @@ __device__ __forceinline__ uint32_t levels_across(const Cells &c, uint32_t i) {
     return min(lv_hi(c.lev[i - 1u]) + 1u, lv_lo(c.lev[i]));
 }
 
-constexpr int kMomThreads = 256;
-constexpr int kMomCells = 384;  // cells of a tile whose moments fit in LDS (235 on average)
+// v of the lane that kCtrl names in each quad
+template <int kCtrl>
+__device__ __forceinline__ double quad_lane(double v) {
+    const int2 i = __builtin_bit_cast(int2, v);
+    return __builtin_bit_cast(
+        double, make_int2(__builtin_amdgcn_update_dpp(0, i.x, kCtrl, 0xf, 0xf, false),
+                          __builtin_amdgcn_update_dpp(0, i.y, kCtrl, 0xf, 0xf, false)));
+}
 
-__global__ __launch_bounds__(kMomThreads, 4) void k_moments_tile(MomArgs a, uint32_t n,
+constexpr int kMomCells = 368;  // cells of a tile whose moments fit in LDS (235 on average)
+
+// (sixteen waves a CU either way)
+template <int kMomThreads>
+__global__ __launch_bounds__(kMomThreads, 1024 / kMomThreads) void k_moments_tile(MomArgs a, uint32_t n,
                                                               uint32_t ntiles) {
     // M, S xyz, com xyz, Q xx yy zz xy xz yz of the tile's cells
     __shared__ double mo[13][kMomCells];
     __shared__ uint32_t first[kLevels], ofs[kLevels + 1], inside[kLevels];
+    // the parents of level l: par[ofs[l] ..], npar[l] of them, each its cell, its
+    // first child and the number of its children
+    __shared__ uint32_t par[kMomCells], npar[kLevels];
+    static_assert(kMomCells <= 512, "nine bits for a cell");
     const Cells &c = a.c;
     const uint32_t lane = lane_id();
     if (threadIdx.x < 64) {
@@ -232,6 +250,7 @@ __global__ __launch_bounds__(kMomThreads, 4) void k_moments_tile(MomArgs a, uint
             first[lane] = c.ls[lane] + s0;
             // the last cell to start is left out where it holds the tile's end
             inside[lane] = cnt && lane < across ? cnt - 1u : cnt;
+            npar[lane] = 0u;
         }
     }
     __syncthreads();
@@ -274,6 +293,9 @@ __global__ __launch_bounds__(kMomThreads, 4) void k_moments_tile(MomArgs a, uint
         k0[s] = c.child0[i];
         prefix[s] = c.prefix[i];
         nch[s] = kend ? kend - k0[s] : 0u;
+        if (nch[s])
+            par[ofs[l] + atomicAdd(&npar[l], 1u)] =
+                q | (ofs[l + 1u] + (k0[s] - first[l + 1u])) << 9 | nch[s] << 18;
     }
 #pragma unroll
     for (int s = 0; s < kOwn; ++s) {
@@ -283,52 +305,44 @@ __global__ __launch_bounds__(kMomThreads, 4) void k_moments_tile(MomArgs a, uint
         leaf_sums(a, b0[s], n0[s], r, c0, c1, c2);
         keep(threadIdx.x + s * kMomThreads, r, c0, c1, c2);
     }
-    // ---- the parents, from the deepest level up
+    // ---- the parents, from the deepest level up, by eight lanes each: lane k
+    // sums quantity k mod 4 of (M, S), then entry k of Q, over the children in
+    // child order
+    const uint32_t k = lane & 7u, k4 = lane & 3u;
+    const uint32_t ra = k < 3u ? k : (k == 5u ? 1u : 0u), rb = k < 3u ? k : (k == 3u ? 1u : 2u);
+    __syncthreads();
     for (uint32_t l = kLevels - 1; l-- > 0u;) {
-        if (ofs[l + 1u] == ofs[l + 2u] || inside[l] == 0u) continue;  // no child starts here
-        __syncthreads();
+        const uint32_t np = npar[l];
+        if (np == 0u) continue;
+        for (uint32_t u = threadIdx.x >> 3; u < np; u += kMomThreads / 8) {
+            const uint32_t e = par[ofs[l] + u], q = e & 511u, q0 = (e >> 9) & 511u, m = e >> 18;
+            double x[8], v = 0.0;
 #pragma unroll
-        for (int s = 0; s < kOwn; ++s) {
-            if (lev[s] != l || nch[s] == 0u) continue;
-            const uint32_t q0 = ofs[l + 1u] + (k0[s] - first[l + 1u]);
-            Mom r{0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-            double vm[8], v0[8], v1[8], v2[8];
+            for (uint32_t j = 0; j < 8u; ++j) x[j] = mo[k4][q0 + (j < m ? j : 0u)];
 #pragma unroll
-            for (uint32_t k = 0; k < 8; ++k) {
-                const uint32_t j = q0 + (k < nch[s] ? k : 0u);
-                vm[k] = mo[0][j]; v0[k] = mo[1][j]; v1[k] = mo[2][j]; v2[k] = mo[3][j];
-            }
-#pragma unroll
-            for (uint32_t k = 0; k < 8; ++k) {
-                if (k < nch[s]) {
-                    r.M = r.M + vm[k];
-                    r.s0 = r.s0 + v0[k];
-                    r.s1 = r.s1 + v1[k];
-                    r.s2 = r.s2 + v2[k];
-                }
-            }
-            const double c0 = r.s0 / r.M, c1 = r.s1 / r.M, c2 = r.s2 / r.M;
+            for (uint32_t j = 0; j < 8u; ++j) v = j < m ? v + x[j] : v;
+            const double com = v / quad_lane<0x00>(v);
+            const double c0 = quad_lane<0x55>(com), c1 = quad_lane<0xaa>(com),
+                         c2 = quad_lane<0xff>(com);
+            const double ca = ra == 0u ? c0 : (ra == 1u ? c1 : c2),
+                         cb = rb == 0u ? c0 : (rb == 1u ? c1 : c2);
+            if (k < 4u) mo[k][q] = v;
+            if (k > 0u && k < 4u) mo[3u + k][q] = com;
+            if (k < 6u) {
+                double w = 0.0;
 #pragma unroll 4
-            for (uint32_t k = 0; k < 8; ++k) {
-                const uint32_t j = q0 + (k < nch[s] ? k : 0u);
-                const double mk = mo[0][j];
-                const double d0 = mo[4][j] - c0, d1 = mo[5][j] - c1, d2 = mo[6][j] - c2;
-                const double t0 = mo[7][j] + (mk * d0) * d0, t1 = mo[8][j] + (mk * d1) * d1,
-                             t2 = mo[9][j] + (mk * d2) * d2, t3 = mo[10][j] + (mk * d0) * d1,
-                             t4 = mo[11][j] + (mk * d0) * d2, t5 = mo[12][j] + (mk * d1) * d2;
-                if (k < nch[s]) {
-                    r.q0 = r.q0 + t0;
-                    r.q1 = r.q1 + t1;
-                    r.q2 = r.q2 + t2;
-                    r.q3 = r.q3 + t3;
-                    r.q4 = r.q4 + t4;
-                    r.q5 = r.q5 + t5;
+                for (uint32_t j = 0; j < 8u; ++j) {
+                    const uint32_t i = q0 + (j < m ? j : 0u);
+                    const double t = mo[7u + k][i] +
+                                     (mo[0][i] * (mo[4u + ra][i] - ca)) * (mo[4u + rb][i] - cb);
+                    w = j < m ? w + t : w;
                 }
+                mo[7u + k][q] = w;
             }
-            keep(threadIdx.x + s * kMomThreads, r, c0, c1, c2);
         }
+        __syncthreads();
     }
-    // ---- all of them written (each thread reads back its own)
+    // ---- all of them written
 #pragma unroll
     for (int s = 0; s < kOwn; ++s) {
         if (lev[s] == kNone) continue;
@@ -512,7 +526,11 @@ void launch_moments(bh_ctx *ctx, uint32_t n, hipStream_t st) {
     a.box = ctx->box;
     a.curve = (int)ctx->p.curve;
     const uint32_t nt = cdiv(n, kTreeTile), ns = cdiv(nt, kSpanTiles);
-    hipLaunchKernelGGL(k_moments_tile, dim3(nt), dim3(kMomThreads), 0, st, a, n, nt);
+    // Threads of a tile: one cell each while there is about a tile for each CU,
+    // else more tiles a CU.  The launches by 256 / 512, in us: 1000 18.5 / 16.3;
+    // 16384 44 / 42; 100003 59 / 57; 1M 92 / 99; 13M 364 / 422.
+    if (n <= 262144u) hipLaunchKernelGGL(k_moments_tile<512>, dim3(nt), dim3(512), 0, st, a, n, nt);
+    else hipLaunchKernelGGL(k_moments_tile<256>, dim3(nt), dim3(256), 0, st, a, n, nt);
     if (nt > 1) hipLaunchKernelGGL(k_moments_span, dim3(ns), dim3(kAcrossThreads), 0, st, a, nt);
     if (ns > 1) hipLaunchKernelGGL(k_moments_top, dim3(1), dim3(kAcrossThreads), 0, st, a, n, nt, ns);
 }
