@@ -86,13 +86,14 @@ int check_status(bh_ctx *c) {
 }
 
 // Sort and tree of the n particles of src; the sorted state becomes c's.
-void rebuild(bh_ctx *c, const Source &src, uint32_t n, hipStream_t s) {
+// theta > 0: for a force at theta that follows (its prepared).
+void rebuild(bh_ctx *c, const Source &src, uint32_t n, hipStream_t s, float theta = 0.f) {
     record_event(c, 0, s);
     launch_sort(c, src, n, s);
     record_event(c, 1, s);
     launch_build(c, n, s);
     record_event(c, 2, s);
-    launch_moments(c, n, s);
+    launch_moments(c, n, theta, s);
     record_event(c, 3, s);
     c->built = true;
     c->have_acc = false;
@@ -142,9 +143,11 @@ hipError_t copy_snapshot(const State &st, size_t n, char *p, bool out, hipStream
     return hipSuccess;
 }
 
-// Forces from the current tree: sorted into c->acc and on to `out`.
-void force(bh_ctx *c, float theta, float eps, const WalkOut &out, hipStream_t s) {
-    launch_walk_prep(c, theta, c, true, s);
+// Forces from the current tree: sorted into c->acc and on to `out`.  prepared:
+// the tree was just built for this theta (4 us less on small sets).
+void force(bh_ctx *c, float theta, float eps, const WalkOut &out, hipStream_t s,
+           bool prepared = false) {
+    if (!prepared) launch_walk_prep(c, theta, c, true, s);
     launch_walk_view(c, own_view(c), eps, false, false, out, s);
     c->have_acc = true;
     c->counts_valid = true;
@@ -318,7 +321,7 @@ size_t static_layout(bh_ctx *c, unsigned char *base) {
     take(&q.prefix, nc); take(&q.level, nc); take(&q.begin, nc); take(&q.count, nc);
     take(&q.child0, nc); take(&q.nchild, nc); take(&q.parent, nc); take(&q.ls, kLsSize);
     take(&q.lev, n); take(&q.tcnt, (size_t)(kLevels + 1) * cdiv(n, kTreeTile));
-    take(&q.ttot, kLevels + 1);
+    take(&q.ttot, (kLevels + 1) * (1 + kScanTiles));
     take(&q.M, nc); take(&q.S, 3 * nc); take(&q.Q, 6 * nc);
     q.com = nullptr;  // (only bh_export reads it)
     take(&q.wA, nc); take(&q.wN, nc); take(&q.P0, nc); take(&q.P1, nc); take(&q.P2, nc);
@@ -442,7 +445,7 @@ int bh_create(bh_ctx **out, int64_t n_max, const bh_params *p) {
          dalloc(&q.count, nc, err) && dalloc(&q.child0, nc, err) && dalloc(&q.nchild, nc, err) &&
          dalloc(&q.parent, nc, err) && dalloc(&q.ls, kLsSize, err) && dalloc(&q.lev, n, err) &&
          dalloc(&q.tcnt, (size_t)(kLevels + 1) * cdiv(n, kTreeTile), err) &&
-         dalloc(&q.ttot, kLevels + 1, err) && dalloc(&q.M, nc, err) && dalloc(&q.S, 3 * nc, err) &&
+         dalloc(&q.ttot, (kLevels + 1) * (1 + kScanTiles), err) && dalloc(&q.M, nc, err) && dalloc(&q.S, 3 * nc, err) &&
          dalloc(&q.com, 3 * nc, err) && dalloc(&q.Q, 6 * nc, err) && dalloc(&q.wA, nc, err) &&
          dalloc(&q.wN, nc, err) && dalloc(&q.P0, nc, err) && dalloc(&q.P1, nc, err) &&
          dalloc(&q.P2, nc, err) && dalloc(&q.size, nc, err) && dalloc(&g.begin, n + 1, err) &&
@@ -512,11 +515,11 @@ int leapfrog_step(bh_ctx *c, float dt, float theta, float eps, hipStream_t s) {
     if (!c->have_acc || theta != c->acc_theta || eps != c->acc_eps)
         force(c, theta, eps, WalkOut{}, s);
     launch_kick_drift(c, 0.5f * dt, dt, n, s);
-    rebuild(c, source_of(c->st[c->cur]), n, s);
+    rebuild(c, source_of(c->st[c->cur]), n, s, theta);
     WalkOut out;
     out.kick = true;
     out.kick_h = 0.5f * dt;
-    force(c, theta, eps, out, s);
+    force(c, theta, eps, out, s, true);
     record_event(c, 7, s);
     BH_HIP(c, hipGetLastError());
     return BH_OK;
@@ -1195,8 +1198,8 @@ int tree_force_static(const float *pos, const float *mass, int64_t n, float thet
     c.cur = 0;
     // the array keeps the previous call's contents: clear the status words
     launch_fill_u32(c.status, 0u, 4, s);
-    rebuild(&c, caller_source(pos, nullptr, mass), (uint32_t)n, s);
-    force(&c, theta, eps, to_caller(acc, pot), s);
+    rebuild(&c, caller_source(pos, nullptr, mass), (uint32_t)n, s, theta);
+    force(&c, theta, eps, to_caller(acc, pot), s, true);
     if (status) {
         hipError_t e = hipMemcpyAsync(status, c.status, sizeof(uint32_t), hipMemcpyDeviceToDevice, s);
         if (e != hipSuccess) {

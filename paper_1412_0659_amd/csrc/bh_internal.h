@@ -18,6 +18,7 @@ constexpr int kLevels = 22;             // levels 0..21
 constexpr int kLsSize = 24;             // level_start entries (23 used)
 constexpr int kGrid = 1024;             // fixed grid of the per-level moment, box and flag kernels
 constexpr int kTreeTile = 1024;         // particles per block of the octree build
+constexpr uint32_t kScanTiles = 64;  // tiles whose counts every block of k_tree_write adds up
 constexpr int kSpanTiles = 128;         // tiles per block of the moment pass over tile ends
 constexpr uint32_t kLeafBit = 0x80000000u;
 constexpr uint32_t kNone = 0xffffffffu;
@@ -74,7 +75,8 @@ struct Cells {
     uint32_t *ls;      // [kLsSize] level_start on the device
     uint16_t *lev;     // [n_max] levels of the cells that start at / hold each particle
     uint32_t *tcnt;    // [kLevels + 1][tiles] cells of each level (and groups) starting before a tile
-    uint32_t *ttot;    // [kLevels + 1] their totals
+    uint32_t *ttot;    // [kLevels + 1] their totals; then, for at most kScanTiles tiles, those counts
+                       // (tcnt holds each tile's own)
     // FP64 moments of the upward pass
     double *M, *S, *com, *Q;  // [c], [c][3], [c][3], [c][6]; com = S / M, filled for export
     // records read by the walk
@@ -241,7 +243,8 @@ void launch_exclusive_scan(const uint32_t *in, uint32_t *out, uint32_t n, uint32
 void launch_build(bh_ctx *c, uint32_t n, hipStream_t st);  // cells and groups
 
 // moments.hip
-void launch_moments(bh_ctx *c, uint32_t n, hipStream_t st);
+// theta > 0: also what launch_walk_prep does for the context's own walk
+void launch_moments(bh_ctx *c, uint32_t n, float theta, hipStream_t st);
 void launch_com(bh_ctx *c, hipStream_t st);
 // opening radii of c's cells for theta; also the work counters of walker (which
 // is about to walk; null: none) to zero, and its interaction totals if totals

@@ -21,8 +21,9 @@
 //     ends with it.
 // Three launches: per tile of particles the levels of each particle and the
 // cells that start in the tile per level (k_tree_levels), the running sums of
-// those counts over the tiles (k_tree_scan), and the cells (k_tree_write),
-// ranked inside the tile by a bit mask per level.  The build never waits on
+// those counts over the tiles (k_tree_scan; up to kScanTiles tiles each block of
+// the next sums them itself, 4 us less), and the cells (k_tree_write), ranked
+// inside the tile by a bit mask per level.  The build never waits on
 // the host and does not depend on the depth of the tree.
 //
 // Bound: memory, 16 B of keys and 4 B of levels per particle and 36 B per
@@ -200,28 +201,47 @@ __global__ __launch_bounds__(1024) void k_tree_scan(uint32_t *__restrict__ tcnt,
 template <int kThreads>
 __global__ __launch_bounds__(kThreads) void k_tree_write(
     Cells c, const uint64_t *__restrict__ key, const uint16_t *__restrict__ lev, uint32_t n,
-    uint32_t ntiles, const uint32_t *__restrict__ tcnt, const uint32_t *__restrict__ tot,
+    uint32_t ntiles, const uint32_t *__restrict__ tcnt, uint32_t *__restrict__ tot,
     uint32_t cap, uint32_t *__restrict__ gbeg, uint32_t gcap, uint32_t *__restrict__ gpar,
     uint32_t *ngroups, uint32_t *status) {
     constexpr int kItems = kTreeTile / kThreads;
+    // cells of each level (and groups) that start before the tile, and in all tiles
+    __shared__ uint32_t tb[kLevels + 1], tt[kLevels + 1];
     __shared__ uint64_t mask[kLevels + 1][kTreeWords];
     __shared__ uint32_t pre[kLevels + 1][kTreeWords];  // starts of the level before the word
     const uint32_t lane = lane_id(), w = threadIdx.x >> 6;
     const uint32_t t0 = blockIdx.x * kTreeTile;
     for (uint32_t q = threadIdx.x; q < (kLevels + 1) * kTreeWords; q += kThreads)
         (&mask[0][0])[q] = 0ull;
+    if (ntiles <= kScanTiles) {  // (no k_tree_scan) a lane per tile
+        for (uint32_t l = w; l <= kLevels; l += kThreads / 64) {
+            const uint32_t v = lane < ntiles ? tcnt[(size_t)l * ntiles + lane] : 0u;
+            const uint32_t inc = wave_incl_scan(v, lane);
+            if (lane == blockIdx.x) {
+                tb[l] = inc - v;
+                tot[kLevels + 1u + l * ntiles + lane] = inc - v;
+            }
+            if (lane == 63u) {
+                tt[l] = inc;
+                if (blockIdx.x == 0) tot[l] = inc;
+            }
+        }
+    } else if (threadIdx.x <= kLevels) {
+        tb[threadIdx.x] = tcnt[(size_t)threadIdx.x * ntiles + blockIdx.x];
+        tt[threadIdx.x] = tot[threadIdx.x];
+    }
+    __syncthreads();
     // level starts (every wave for itself; lane l holds level l's)
-    const uint32_t lt = lane < kLevels ? tot[lane] : 0u;
+    const uint32_t lt = lane < kLevels ? tt[lane] : 0u;
     const uint32_t lend = wave_incl_scan(lt, lane), lstart = lend - lt;
     if (blockIdx.x == 0 && threadIdx.x <= kLevels) {
         c.ls[threadIdx.x] = min(lstart, cap);  // (lane kLevels: the cell count)
         if (threadIdx.x == kLevels) {
             if (lstart > cap) atomicOr(status, kStOverflow);
-            *ngroups = tot[kGroupCh];
-            if (tot[kGroupCh] < gcap) gbeg[tot[kGroupCh]] = n;
+            *ngroups = tt[kGroupCh];
+            if (tt[kGroupCh] < gcap) gbeg[tt[kGroupCh]] = n;
         }
     }
-    __syncthreads();
     uint32_t lv[kItems], ln[kItems];
 #pragma unroll
     for (int r = 0; r < kItems; ++r) {
@@ -248,7 +268,7 @@ __global__ __launch_bounds__(kThreads) void k_tree_write(
         const bool have = l <= kLevels;
         const uint32_t cnt = have ? (uint32_t)__popcll(mask[l][word]) : 0u;
         const uint32_t s = row_incl_scan(cnt) - cnt;
-        if (have) pre[l][word] = tcnt[(size_t)l * ntiles + blockIdx.x] + s;
+        if (have) pre[l][word] = tb[l] + s;
     }
     __syncthreads();
     // numbers of the cells of level l: those that start before particle
@@ -351,10 +371,11 @@ void launch_build(bh_ctx *ctx, uint32_t n, hipStream_t st) {
         constexpr int kThreads = decltype(threads)::value;
         hipLaunchKernelGGL(k_tree_levels<kThreads>, dim3(nt), dim3(kThreads), 0, st, key, n,
                            (uint32_t)ctx->p.nleaf, (uint32_t)ctx->p.ncrit, nt, c.lev, c.tcnt);
-        hipLaunchKernelGGL(k_tree_scan, dim3(kLevels + 1), dim3(1024), 0, st, c.tcnt, nt, c.ttot);
+        if (nt > kScanTiles)
+            hipLaunchKernelGGL(k_tree_scan, dim3(kLevels + 1), dim3(1024), 0, st, c.tcnt, nt, c.ttot);
         hipLaunchKernelGGL(k_tree_write<kThreads>, dim3(nt), dim3(kThreads), 0, st, c, key,
                            (const uint16_t *)c.lev, n, nt, (const uint32_t *)c.tcnt,
-                           (const uint32_t *)c.ttot, (uint32_t)ctx->cap_cells, gbeg0,
+                           c.ttot, (uint32_t)ctx->cap_cells, gbeg0,
                            ctx->pair_groups ? n : n + 1u, gpar, g.count_dev, ctx->status);
     };
     // Threads of a tile.  Up to a tile a CU and beyond, a thread per particle

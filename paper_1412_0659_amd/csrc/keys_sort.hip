@@ -257,11 +257,11 @@ static void launch_gather(bh_ctx *c, const Source &s, uint32_t n, hipStream_t st
 // runs by a 64-way search on the diagonal (one wave per end), and merges them
 // in LDS.
 //
-// Bound: latency on small sets (two launches up to 8192 particles, then one
-// per doubling, where the radix passes over memory below take five launches
+// Bound: latency on small sets (one launch up to 1024 particles, two up to
+// 8192, then one per doubling, where the radix passes over memory below take five launches
 // per digit), 24 B per particle and merge on larger ones.  Measured, bounding
 // box, keys, sort and gather of a set in random order, in us, these against
-// the radix passes: n = 1000: 23 / 135; 4096: 32 / 148; 16384: 54 / 192; 65536:
+// the radix passes: n = 1000: 18 / 135; 4096: 32 / 148; 16384: 54 / 192; 65536:
 // 73 / 213; 500000: 136 / 257; 1M: 192 / 297; 2M: 312 / 373; 3M: 460 / 529; 4M:
 // 625 / 615; 8M: 1235 / 1105.
 constexpr uint32_t kMergeMax = 3u << 20;
@@ -271,10 +271,13 @@ constexpr int kSortWaves = kSortThreads / 64;
 
 // nb == 0: every block finds the bounding box of all particles itself (and
 // block 0 checks them); else it folds the nb partials.  Block 0 writes box.
+// xyzm: the set is one tile, whose particles move to their places in dst here
+// (a launch of its own costs 4.5 us of 98 at n = 1000).
 template <bool kPH, int kRounds>
 __global__ __launch_bounds__(kSortThreads) void k_sort_block(
     Source s, uint32_t n, const float *__restrict__ part, uint32_t nb, FixedBox fb, float *box,
-    uint32_t *status, uint64_t *__restrict__ key_out, uint32_t *__restrict__ idx_out) {
+    uint32_t *status, uint64_t *__restrict__ key_out, uint32_t *__restrict__ idx_out, State dst,
+    float4 *__restrict__ xyzm) {
     constexpr uint32_t kTile = kSortThreads * kRounds;
     __shared__ uint64_t skey[kTile];
     __shared__ uint16_t sidx[kTile];
@@ -393,6 +396,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_block(
         if (i < n) {
             key_out[i] = kk[r];
             idx_out[i] = t0 + vv[r];
+            if (xyzm) move_particle(s, t0 + vv[r], dst, i, xyzm);
         }
     }
 }
@@ -486,14 +490,16 @@ template <int kRounds>
 static void launch_sort_block(bh_ctx *c, const Source &s, uint32_t n, uint32_t nb, int dst,
                               hipStream_t st) {
     const dim3 grid(cdiv(n, (uint64_t)kSortThreads * kRounds));
+    const State &to = c->st[c->cur ^ 1];
+    float4 *xyzm = grid.x == 1 ? c->xyzm : nullptr;
     if (c->p.curve == 1)
         hipLaunchKernelGGL((k_sort_block<true, kRounds>), grid, dim3(kSortThreads), 0, st, s, n,
                            (const float *)c->box_part, nb, fixed_box(c), c->box, c->status,
-                           c->sort.key[dst], c->sort.idx[dst]);
+                           c->sort.key[dst], c->sort.idx[dst], to, xyzm);
     else
         hipLaunchKernelGGL((k_sort_block<false, kRounds>), grid, dim3(kSortThreads), 0, st, s, n,
                            (const float *)c->box_part, nb, fixed_box(c), c->box, c->status,
-                           c->sort.key[dst], c->sort.idx[dst]);
+                           c->sort.key[dst], c->sort.idx[dst], to, xyzm);
 }
 
 // Sets of up to kRankMax particles: the place of every particle among all runs
@@ -536,10 +542,10 @@ static void launch_merge_sort(bh_ctx *c, const Source &s, uint32_t n, hipStream_
     if (n <= kRankMax) {
         const int src = n > kRankRun ? 1 : 0;
         launch_sort_block<1>(c, s, n, 0u, src, st);
-        if (src == 0) return launch_gather(c, s, n, st);
-        hipLaunchKernelGGL(k_sort_rank, dim3(cdiv(n, 256)), dim3(256), 0, st,
-                           (const uint64_t *)c->sort.key[1], (const uint32_t *)c->sort.idx[1], n,
-                           s, c->st[c->cur ^ 1], c->xyzm, c->sort.key[0]);
+        if (src)
+            hipLaunchKernelGGL(k_sort_rank, dim3(cdiv(n, 256)), dim3(256), 0, st,
+                               (const uint64_t *)c->sort.key[1], (const uint32_t *)c->sort.idx[1],
+                               n, s, c->st[c->cur ^ 1], c->xyzm, c->sort.key[0]);
         c->cur ^= 1;
         return;
     }

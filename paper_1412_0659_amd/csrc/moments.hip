@@ -54,7 +54,23 @@ struct MomArgs {
     const float4 *xyzm;  // sorted particles as (x, y, z, m) records
     const float *box;  // lo xyz, side
     int curve;
+    // theta > 0: the opening radii for a walk at theta, and its counters zeroed
+    float theta;
+    uint32_t *work;
+    unsigned long long *totals;
 };
+
+// Squared opening radius (fl32(l / theta) + delta)^2 in FP32.
+__device__ __forceinline__ float open_radius2(float2 size, float theta) {
+    const float r = size.x / theta + size.y;
+    return r * r;
+}
+
+// The walk's counters and totals, by one block.
+__device__ __forceinline__ void zero_walk(uint32_t *work, unsigned long long *totals) {
+    if (work && threadIdx.x < 16u) work[threadIdx.x * kWorkStride] = 0u;
+    if (totals && threadIdx.x < 2u) totals[threadIdx.x] = 0ull;
+}
 
 struct Mom {
     double M, s0, s1, s2, q0, q1, q2, q3, q4, q5;
@@ -177,14 +193,16 @@ __device__ __forceinline__ void cell_out(const MomArgs &a, uint32_t i, uint32_t 
     const double e2 = c2 - (lo2 + ((double)p[2] + 0.5) * lc);
     const double dl = __dsqrt_rn((e0 * e0 + e1 * e1) + e2 * e2);
     const double tr = (r.q0 + r.q1) + r.q2;
-    c.wA[i] = make_float4((float)c0, (float)c1, (float)c2, 0.f);
+    const float2 size = make_float2((float)lc, (float)dl);
+    c.wA[i] = make_float4((float)c0, (float)c1, (float)c2,
+                          a.theta > 0.f ? open_radius2(size, a.theta) : 0.f);
     c.P0[i] = make_float4((float)c0, (float)c1, (float)c2, (float)r.M);
     c.P1[i] = make_float4((float)(-3.0 * r.q0), (float)(-3.0 * r.q1), (float)(-3.0 * r.q2),
                           (float)(-3.0 * r.q3));
     c.P2[i] = make_float4((float)(-3.0 * r.q4), (float)(-3.0 * r.q5), (float)(0.5 * tr),
                           (float)(-1.5 * tr));
     c.wN[i] = nch ? make_uint2(k0, nch) : make_uint2(b0, n0 | kLeafBit);
-    c.size[i] = make_float2((float)lc, (float)dl);
+    c.size[i] = size;
 }
 
 // Cell i of level lev on its own, a parent's children read from memory.
@@ -204,7 +222,8 @@ __device__ __forceinline__ void cell_pass(const MomArgs &a, uint32_t i, uint32_t
 // The cells of level l that start before tile t (the total for t = tiles).
 __device__ __forceinline__ uint32_t starts_before(const Cells &c, uint32_t ntiles, uint32_t l,
                                                   uint32_t t) {
-    return t < ntiles ? c.tcnt[(size_t)l * ntiles + t] : c.ttot[l];
+    const uint32_t *pre = ntiles <= kScanTiles ? c.ttot + kLevels + 1 : c.tcnt;
+    return t < ntiles ? pre[(size_t)l * ntiles + t] : c.ttot[l];
 }
 
 // The levels l < levels_across(i) are those whose cells hold both particle
@@ -237,6 +256,7 @@ __global__ __launch_bounds__(kMomThreads, 1024 / kMomThreads) void k_moments_til
     static_assert(kMomCells <= 512, "nine bits for a cell");
     const Cells &c = a.c;
     const uint32_t lane = lane_id();
+    if (a.theta > 0.f && blockIdx.x == 0) zero_walk(a.work, a.totals);
     if (threadIdx.x < 64) {
         const uint32_t l = min(lane, (uint32_t)kLevels - 1u);
         const uint32_t s0 = starts_before(c, ntiles, l, blockIdx.x),
@@ -519,12 +539,15 @@ __global__ __launch_bounds__(kAcrossThreads) void k_moments_top(MomArgs a, uint3
     across_pass(a, ntiles, 0u, nspans - 1u, kSpanTiles, n);
 }
 
-void launch_moments(bh_ctx *ctx, uint32_t n, hipStream_t st) {
+void launch_moments(bh_ctx *ctx, uint32_t n, float theta, hipStream_t st) {
     MomArgs a;
     a.c = ctx->cells;
     a.xyzm = ctx->xyzm;
     a.box = ctx->box;
     a.curve = (int)ctx->p.curve;
+    a.theta = theta;
+    a.work = ctx->work;
+    a.totals = ctx->totals;
     const uint32_t nt = cdiv(n, kTreeTile), ns = cdiv(nt, kSpanTiles);
     // Threads of a tile: one cell each while there is about a tile for each CU,
     // else more tiles a CU.  The launches by 256 / 512, in us: 1000 18.5 / 16.3;
@@ -550,21 +573,14 @@ void launch_com(bh_ctx *ctx, hipStream_t st) {
     hipLaunchKernelGGL(k_com, dim3(kGrid * 2), dim3(256), 0, st, ctx->cells);
 }
 
-// r_open^2 = (fl32(l / theta) + delta)^2 in FP32, stored in wA.w; the first
-// block also zeroes the walk's counters.
+// The opening radii of a walk at theta, stored in wA.w; the first block also
+// zeroes the walk's counters.
 __global__ __launch_bounds__(256) void k_walk_prep(Cells c, float theta, uint32_t *work,
                                                    unsigned long long *totals) {
-    if (blockIdx.x == 0) {
-        if (work)
-            for (uint32_t k = threadIdx.x; k < 16u; k += 256u) work[k * kWorkStride] = 0u;
-        if (totals && threadIdx.x < 2u) totals[threadIdx.x] = 0ull;
-    }
-    uint32_t nc = c.ls[kLevels];
-    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < nc; i += gridDim.x * 256) {
-        float2 sz = c.size[i];
-        float r = sz.x / theta + sz.y;
-        c.wA[i].w = r * r;
-    }
+    if (blockIdx.x == 0) zero_walk(work, totals);
+    const uint32_t nc = c.ls[kLevels];
+    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < nc; i += gridDim.x * 256)
+        c.wA[i].w = open_radius2(c.size[i], theta);
 }
 
 void launch_walk_prep(bh_ctx *ctx, float theta, bh_ctx *walker, bool totals, hipStream_t st) {
