@@ -709,8 +709,7 @@ int tree_force_vjp(bh_ctx *c, float theta, float eps, const float *u, float coef
     if (!c->p.adjoint) return fail(c, BH_EINVAL, "context created without adjoint = 1");
     if (!c->built) return fail(c, BH_ESTATE, "tree_force_vjp before tree_build");
     if (!g_pos && !g_mass) return BH_OK;
-    launch_walk_prep(c, theta, c, false, s);
-    launch_walk_vjp(c, eps, u, coef, g_pos, g_mass, s);
+    launch_walk_vjp(c, theta, eps, u, coef, g_pos, g_mass, s);
     BH_HIP(c, hipGetLastError());
     return BH_OK;
 }

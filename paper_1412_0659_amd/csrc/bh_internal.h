@@ -211,7 +211,7 @@ namespace bh {
 
 // walk_vjp.hip: coef * u^T d(acc)/d(x, m) accumulated into caller-order
 // g_pos [n][3] / g_mass [n] (either may be null); u is caller order [n][3]
-void launch_walk_vjp(bh_ctx *c, float eps, const float *u, float coef, float *g_pos,
+void launch_walk_vjp(bh_ctx *c, float theta, float eps, const float *u, float coef, float *g_pos,
                      float *g_mass, hipStream_t st);
 void launch_axpy3(const float *x, float *y, float a, uint32_t n, hipStream_t st);
 
@@ -243,6 +243,18 @@ void launch_exclusive_scan(const uint32_t *in, uint32_t *out, uint32_t n, uint32
 void launch_build(bh_ctx *c, uint32_t n, hipStream_t st);  // cells and groups
 
 // moments.hip
+// Squared opening radius (fl32(l / theta) + delta)^2 in FP32.
+__device__ __forceinline__ float open_radius2(float2 size, float theta) {
+    const float r = size.x / theta + size.y;
+    return r * r;
+}
+
+// The walk's counters and totals, by one block.
+__device__ __forceinline__ void zero_walk(uint32_t *work, unsigned long long *totals) {
+    if (work && threadIdx.x < 16u) work[threadIdx.x * kWorkStride] = 0u;
+    if (totals && threadIdx.x < 2u) totals[threadIdx.x] = 0ull;
+}
+
 // theta > 0: also what launch_walk_prep does for the context's own walk
 void launch_moments(bh_ctx *c, uint32_t n, float theta, hipStream_t st);
 void launch_com(bh_ctx *c, hipStream_t st);

@@ -60,18 +60,6 @@ struct MomArgs {
     unsigned long long *totals;
 };
 
-// Squared opening radius (fl32(l / theta) + delta)^2 in FP32.
-__device__ __forceinline__ float open_radius2(float2 size, float theta) {
-    const float r = size.x / theta + size.y;
-    return r * r;
-}
-
-// The walk's counters and totals, by one block.
-__device__ __forceinline__ void zero_walk(uint32_t *work, unsigned long long *totals) {
-    if (work && threadIdx.x < 16u) work[threadIdx.x * kWorkStride] = 0u;
-    if (totals && threadIdx.x < 2u) totals[threadIdx.x] = 0ull;
-}
-
 struct Mom {
     double M, s0, s1, s2, q0, q1, q2, q3, q4, q5;
 };

@@ -42,6 +42,8 @@
 // Measured at 1M, theta 0.4: 23.0 ms with lane sums by DPP, accumulators field by
 // field and particle pairs evaluated once per side; 19.4 with a source's sums
 // added once per 32 targets; 17.4 now that they are added once per group.
+#include <algorithm>
+
 #include "walk_common.h"
 
 namespace bh {
@@ -470,54 +472,57 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
 
 // ---- moments part, combination and unsorting --------------------------------
 
-__global__ __launch_bounds__(256) void k_leafof(Cells c, uint32_t *leafof) {
+// What the walk needs, in one launch (six of 4 to 5 us each on small sets):
+// opening radii and work counters, the accumulators' zeros, the leaf of every
+// particle, the cotangents in sorted order.
+__global__ __launch_bounds__(256) void k_vjp_prep(Cells c, float theta, uint32_t *work,
+                                                  const float *__restrict__ u,
+                                                  const uint32_t *__restrict__ cid, uint32_t n,
+                                                  float4 *__restrict__ us, uint32_t *leafof,
+                                                  double *lcell, uint64_t lstride, double *gsrc,
+                                                  uint64_t gstride, double *lhot) {
+    if (blockIdx.x == 0) zero_walk(work, nullptr);
     const uint32_t nc = c.ls[kLevels];
-    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < nc; i += gridDim.x * 256) {
+    const uint64_t t = (uint64_t)blockIdx.x * 256 + threadIdx.x, step = (uint64_t)gridDim.x * 256;
+    for (uint64_t i = t; i < nc; i += step) {
+        c.wA[i].w = open_radius2(c.size[i], theta);
         if (c.nchild[i] != 0) continue;
         const uint32_t b = c.begin[i], e = b + c.count[i];
-        for (uint32_t j = b; j < e; ++j) leafof[j] = i;
+        for (uint32_t j = b; j < e; ++j) leafof[j] = (uint32_t)i;
     }
+    for (uint64_t i = t; i < n; i += step) {
+        const size_t p = cid[i];
+        us[i] = make_float4(u[3 * p], u[3 * p + 1], u[3 * p + 2], 0.f);
+    }
+    // (cells in the hot copies leave their others unused)
+    const uint64_t all = (uint64_t)nc * kCellAdj, hot = (uint64_t)min(nc, kHotCells) * kCellAdj;
+    for (uint64_t i = t; i < hot; i += step)
+#pragma unroll 8
+        for (uint32_t k = 0; k < kHotCopies; ++k) lhot[i + k * kHotCopy] = 0.0;
+    for (uint64_t i = hot + t; i < all; i += step)
+#pragma unroll
+        for (uint32_t k = 0; k < kXcd; ++k) lcell[i + k * lstride] = 0.0;
+    for (uint64_t i = t; i < 4ull * n; i += step)
+#pragma unroll
+        for (uint32_t k = 0; k < kXcd; ++k) gsrc[i + k * gstride] = 0.0;
 }
 
-__global__ __launch_bounds__(256) void k_usort(const float *__restrict__ u,
-                                               const uint32_t *__restrict__ cid, uint32_t n,
-                                               float4 *__restrict__ us) {
-    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const size_t p = cid[i];
-    us[i] = make_float4(u[3 * p], u[3 * p + 1], u[3 * p + 2], 0.f);
-}
-
-// Zero `copies` copies (copy k at k * stride) of cnt entries of F values each
-// (cnt = the cell count of the current tree when ls is given, at most lim).
-__global__ __launch_bounds__(256) void k_zero_xcd(double *p, uint64_t cnt, uint32_t F,
-                                                  uint64_t stride, uint32_t copies,
-                                                  const uint32_t *ls, uint64_t lim) {
-    if (ls) cnt = ls[kLevels] < lim ? ls[kLevels] : lim;
-    const uint64_t total = cnt * F;
-    for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < total;
-         i += (uint64_t)gridDim.x * 256)
-        for (uint32_t k = 0; k < copies; ++k) p[i + k * stride] = 0.0;
-}
-
-// Fold the kXcd copies (same layout as k_zero_xcd) into copy 0; with hot, the
-// first kHotCells cells instead from their kHotCopies copies.
-__global__ __launch_bounds__(256) void k_fold_xcd(double *p, uint64_t cnt, uint32_t F,
-                                                  uint64_t stride, const uint32_t *ls,
-                                                  const double *__restrict__ hot) {
-    if (ls) cnt = ls[kLevels];
-    const uint64_t total = cnt * F;
+// Fold the copies of the cells' adjoints into copy 0 of lcell.
+__global__ __launch_bounds__(256) void k_fold_cells(const uint32_t *ls, double *lcell,
+                                                    uint64_t lstride,
+                                                    const double *__restrict__ lhot) {
+    const uint64_t total = (uint64_t)ls[kLevels] * kCellAdj;
     for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < total;
          i += (uint64_t)gridDim.x * 256) {
         double v = 0.0;
-        if (hot && i < (uint64_t)kHotCells * F) {
+        if (i < (uint64_t)kHotCells * kCellAdj) {
 #pragma unroll 8
-            for (uint32_t k = 0; k < kHotCopies; ++k) v += hot[i + k * kHotCopy];
+            for (uint32_t k = 0; k < kHotCopies; ++k) v += lhot[i + k * kHotCopy];
         } else {
 #pragma unroll
-            for (uint32_t k = 0; k < kXcd; ++k) v += p[i + k * stride];
+            for (uint32_t k = 0; k < kXcd; ++k) v += lcell[i + k * lstride];
         }
-        p[i] = v;
+        lcell[i] = v;
     }
 }
 
@@ -529,14 +534,20 @@ __global__ __launch_bounds__(256) void k_moments_vjp(Cells c, const float4 *__re
                                                      const uint32_t *__restrict__ cid,
                                                      const double *__restrict__ lcell,
                                                      const double *__restrict__ gsrc,
-                                                     uint32_t n, float coef, float *g_pos,
+                                                     uint64_t gstride, uint32_t n, float coef,
+                                                     float *g_pos,
                                                      float *g_mass) {
     const uint32_t k = blockIdx.x * 256 + threadIdx.x;
     if (k >= n) return;
     const float4 p = xyzm[k];
     const double xk = p.x, yk = p.y, zk = p.z, mk = p.w;
-    const double *gk = gsrc + 4ull * k;
-    double gx = gk[0], gy = gk[1], gz = gk[2], gm = gk[3];
+    double gx = 0.0, gy = 0.0, gz = 0.0, gm = 0.0;
+#pragma unroll
+    for (uint32_t x = 0; x < kXcd; ++x) {
+        const double2 *g = reinterpret_cast<const double2 *>(gsrc + x * gstride + 4ull * k);
+        const double2 a = g[0], b = g[1];
+        gx += a.x; gy += a.y; gz += b.x; gm += b.y;
+    }
     for (uint32_t cc = leafof[k]; cc != kNone; cc = c.parent[cc]) {
         const double *l = lcell + (size_t)cc * kCellAdj;
         const double lM = l[0], lx = l[1], ly = l[2], lz = l[3];
@@ -579,24 +590,16 @@ static Split vjp_split(int64_t n) {
     return {1u, 40u, 0u};
 }
 
-void launch_walk_vjp(bh_ctx *c, float eps, const float *u, float coef, float *g_pos,
+void launch_walk_vjp(bh_ctx *c, float theta, float eps, const float *u, float coef, float *g_pos,
                      float *g_mass, hipStream_t st) {
     const uint32_t n = (uint32_t)c->n;
     const uint32_t nb = cdiv(n, 256);
-    const uint32_t grid = nb < 4096u ? (nb ? nb : 1u) : 4096u;
-    const uint64_t cap = (uint64_t)c->cap_cells;
-    const uint64_t lstride = kCellAdj * cap, gstride = 4ull * (uint64_t)c->nmax;
+    const uint64_t lstride = kCellAdj * (uint64_t)c->cap_cells, gstride = 4ull * (uint64_t)c->nmax;
     const uint32_t *ls = c->cells.ls;
-    // (cells in the hot copies leave their first copies unused)
-    hipLaunchKernelGGL(k_zero_xcd, dim3(2048), dim3(256), 0, st, c->lcell, (uint64_t)0, kCellAdj,
-                       lstride, kXcd, ls, cap);
-    hipLaunchKernelGGL(k_zero_xcd, dim3(grid), dim3(256), 0, st, c->gsrc, (uint64_t)n, 4u,
-                       gstride, kXcd, (const uint32_t *)nullptr, (uint64_t)n);
-    hipLaunchKernelGGL(k_zero_xcd, dim3(640), dim3(256), 0, st, c->lhot, (uint64_t)0, kCellAdj,
-                       kHotCopy, kHotCopies, ls, (uint64_t)kHotCells);
-    hipLaunchKernelGGL(k_leafof, dim3(kGrid * 2), dim3(256), 0, st, c->cells, c->leafof);
-    hipLaunchKernelGGL(k_usort, dim3(nb), dim3(256), 0, st, u,
-                       (const uint32_t *)c->st[c->cur].cid, n, c->usort);
+    const uint32_t grid = std::min<uint32_t>(cdiv(4ull * n, 256), 4096u);
+    hipLaunchKernelGGL(k_vjp_prep, dim3(grid), dim3(256), 0, st, c->cells, theta, c->work, u,
+                       (const uint32_t *)c->st[c->cur].cid, n, c->usort, c->leafof, c->lcell,
+                       lstride, c->gsrc, gstride, c->lhot);
     VjpArgs a;
     a.xyzm = c->xyzm; a.u = c->usort;
     a.wA = c->cells.wA; a.wN = c->cells.wN;
@@ -613,14 +616,12 @@ void launch_walk_vjp(bh_ctx *c, float eps, const float *u, float coef, float *g_
     if (eps == 0.f) hipLaunchKernelGGL(k_walk_vjp<true>, walks, dim3(64), 0, st, a);
     else hipLaunchKernelGGL(k_walk_vjp<false>, walks, dim3(64), 0, st, a);
     record_event(c, 9, st);
-    hipLaunchKernelGGL(k_fold_xcd, dim3(2048), dim3(256), 0, st, c->lcell, (uint64_t)0, kCellAdj,
-                       lstride, ls, (const double *)c->lhot);
-    hipLaunchKernelGGL(k_fold_xcd, dim3(grid), dim3(256), 0, st, c->gsrc, (uint64_t)n, 4u,
-                       gstride, (const uint32_t *)nullptr, (const double *)nullptr);
+    hipLaunchKernelGGL(k_fold_cells, dim3(std::min<uint32_t>(cdiv(4ull * n, 256), 2048u)),
+                       dim3(256), 0, st, ls, c->lcell, lstride, (const double *)c->lhot);
     hipLaunchKernelGGL(k_moments_vjp, dim3(nb), dim3(256), 0, st, c->cells,
                        (const float4 *)c->xyzm, (const uint32_t *)c->leafof,
                        (const uint32_t *)c->st[c->cur].cid, (const double *)c->lcell,
-                       (const double *)c->gsrc, n, coef, g_pos, g_mass);
+                       (const double *)c->gsrc, gstride, n, coef, g_pos, g_mass);
 }
 
 // y += a x over n [3]-vectors (the drift's transpose in the adjoint step)
