@@ -146,12 +146,11 @@ struct Phase {
     h2 ti[3];  // FP16 far field: (x_i - gc) s_g, both halves equal
 };
 
-// One pair of particle-cell terms in FP16 (cells 2p and 2p+1 of the chunk).
-__device__ __forceinline__ void pc16_pair(const h2 ti[3], const Far16Lds &S, uint32_t p,
-                                          float4 &acc) {
-    const uint4 *R = reinterpret_cast<const uint4 *>(S.rec[p]);
+// One pair of particle-cell terms in FP16, of the two cells of a record.
+__device__ __forceinline__ void pc16_pair(const h2 ti[3], const uint32_t *rec, float4 &acc) {
+    const uint4 *R = reinterpret_cast<const uint4 *>(rec);
     const uint4 q0 = R[0], q1 = R[1], q2 = R[2], q3 = R[3];
-    const float fphi1 = __builtin_bit_cast(float, S.rec[p][kFphi + 1]);
+    const float fphi1 = __builtin_bit_cast(float, rec[kFphi + 1]);
     const h2 rho = as_h2(q0.w);
     const h2 dx = hfma(-rho, ti[0], as_h2(q0.x));
     const h2 dy = hfma(-rho, ti[1], as_h2(q0.y));
@@ -191,8 +190,10 @@ __device__ __forceinline__ void eval16_chunk(Phase &ph, uint32_t n, const Far16L
     const uint32_t full = uniform(small_div(n, r)), rem = n - full * r;
     if (!ph.act) return;
     uint32_t k = ph.slice;
-    for (uint32_t j = 0; j < full; ++j, k += r) pc16_pair(ph.ti, S, k, ph.acc);
-    if (ph.slice < rem) pc16_pair(ph.ti, S, k, ph.acc);
+    const uint32_t *rec = S.rec[k];  // (one induction variable: 4.86 -> 4.70 ms at 1M)
+    for (uint32_t j = 0; j < full; ++j, rec += r * kRec) pc16_pair(ph.ti, rec, ph.acc);
+    k += full * r;
+    if (ph.slice < rem) pc16_pair(ph.ti, S.rec[k], ph.acc);
 }
 
 // Write the FP16 half-record of cell k of the chunk (a far cell, or a hole
