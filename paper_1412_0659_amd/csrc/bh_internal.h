@@ -311,12 +311,12 @@ int walk_blocks_per_cu();
 // 54 to 64 targets 150 to 174).  Splitting costs throughput (every wave repeats
 // the top of the walk, lists are shorter), so fewer waves share as the groups
 // become more.  Walk in us, all groups alike (the best number of waves) / this
-// rule, disk + halo at theta 0.4: n = 1000 36 / 36 (Plummer); 4096 79 / 73;
-// 16384 219 / 179; 40000 498 / 466; 65536 553 / 464; 131072 811 / 762; 262144
-// 1384 / 1259; 700000 3382 / 3194; 1M 4637 / 4460 and 4768 with no split.  The
-// lines, by waves 8 / 4 or 4 / 2: at 16384 (Plummer, theta 0.5) 152 / 170, at
-// 24576 (0.6) 187 / 157, at 32768 (Plummer) 215 / 192; at 200000 (0.6) 539 / 557,
-// at 400000 994 / 946; two waves or one: 1M at theta 0.6 2142 / 2092, 2M at
+// rule, disk + halo at theta 0.4: n = 1000 31 / 32 (Plummer); 4099 74 / 63
+// (Plummer); 16384 194 / 175; 40000 388 / 307; 65536 472 / 387; 131072 834 / 677;
+// 1M 4637 / 4390 and 4768 with no split.  The lines, by up to 8 / 4 waves: at 16384
+// (Plummer, theta 0.5) 147 / 162, at 24576 (0.6) 171 / 153, at 32768 (Plummer) 228
+// / 187; 4 / 2: at 200000 933 / 1016, at 262144 1208 / 1264 and (0.6) 630 / 600, at
+// 500000 2281 / 2163 and 1199 / 1079; 2 / 1: 1M at theta 0.6 2142 / 2092, 2M at
 // theta 0.4 8614 / 8651, 4M 10800 / 10636.
 struct Split {
     uint32_t logw, t1, t2;

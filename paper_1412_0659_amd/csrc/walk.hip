@@ -29,6 +29,7 @@ struct WalkArgs {
                                          // unless the tree is another context's)
     const float4 *wA;                    // com, r_open^2
     const uint2 *wN;                     // (first, n | leaf bit)
+    const uint32_t *ls, *parent;         // of the walked cells, if it is the context's own tree
     const float4 *P0, *P1, *P2;          // particle-cell records
     const uint32_t *gbeg, *ngroups;
     uint32_t *work, *spill;
@@ -434,8 +435,8 @@ __device__ void walk_group(const WalkArgs &a, uint32_t g, uint32_t w, uint32_t l
     };
 
     uint32_t cnt_pc, cnt_pp;
-    const TreeView tv{a.wA, a.wN, a.ring, a.status};
-    traverse<false, kSplit>(tv, b, lane, L.T, spill, cnt_pc, cnt_pp, flush_pc, flush_pp,
+    const TreeView tv{a.wA, a.wN, a.ring, a.status, nullptr, a.ls, a.parent};
+    traverse<false, kSplit, kSplit>(tv, b, lane, L.T, spill, cnt_pc, cnt_pp, flush_pc, flush_pp,
                             Share{w, logw});
 
     // ---- sum the slices of each target (staging area reused)
@@ -562,6 +563,8 @@ void launch_walk_view(bh_ctx *c, const SrcView &v, float eps, bool remote, bool 
     a.xyzm = c->xyzm;
     a.sxyzm = v.xyzm;
     a.wA = v.wA; a.wN = v.wN;
+    a.ls = remote ? nullptr : c->cells.ls;
+    a.parent = remote ? nullptr : c->cells.parent;
     a.P0 = v.P0; a.P1 = v.P1; a.P2 = v.P2;
     a.gbeg = c->groups.begin; a.ngroups = c->groups.count_dev;
     a.work = c->work + (remote ? 8 * kWorkStride : 0);

@@ -34,7 +34,7 @@ constexpr int kPcCap = 752;  // particle-cell index list
 constexpr int kPcFlush = kPcCap - 128;  // a pass appends at most 128 cells
 constexpr int kPpCap = 512;  // particle-particle index list
 constexpr int kChunk = 64;   // sources staged per evaluation round
-constexpr uint32_t kDealRanges = 64;  // stack ranges at which the waves of a split walk part
+constexpr uint32_t kDealRanges = 96;  // stack ranges at which the waves of a split walk part
 
 struct TravLds {
     uint32_t ring[kRing];
@@ -50,6 +50,8 @@ struct TreeView {
     uint32_t ring;      // resident stack entries allowed: kRing, or 192 to exercise the spill path
     uint32_t *status;
     uint32_t *opened = nullptr;  // kLeafCells: opened internal cells are marked here
+    // level starts and parents of the cells (null: not known, the walk starts at the root)
+    const uint32_t *ls = nullptr, *parent = nullptr;
 };
 
 struct GroupBox {
@@ -138,8 +140,16 @@ __device__ __forceinline__ void deal(bool &a, bool &b, const Share &sh, uint32_t
 // holds kDealRanges ranges, the accepted cells and opened leaves of those
 // passes dealt out in list order; then wave w keeps every 2^logw-th range and
 // walks those subtrees alone.  Which wave takes what depends only on the tree
-// and the group, so the sums do not depend on scheduling.
-template <bool kLeafCells = false, bool kSplit = false, class FlushPc, class FlushPp>
+// and the group, so the sums do not depend on scheduling.  The more ranges are
+// dealt out, the more alike the shares: 96 against 64 (that is all the smaller
+// ring allows), walk in us: 16384 149 -> 144, 40000 228 -> 209, 65536 448 -> 393;
+// 128 no better.
+//
+// kTop: where the level starts are known, the first pass takes all cells of
+// the levels 0 to 2 (at most 73, each with its parent) instead of three passes
+// of 1, 8 and 64: 1000 32.5 -> 31.2 us, 4099 61.7 -> 60.2.
+template <bool kLeafCells = false, bool kSplit = false, bool kTop = false, class FlushPc,
+          class FlushPp>
 __device__ __forceinline__ void traverse(const TreeView &tv, const GroupBox &b, uint32_t lane,
                                          TravLds &L, uint32_t *spill, uint32_t &cnt_pc,
                                          uint32_t &cnt_pp, FlushPc &&flush_pc,
@@ -151,45 +161,63 @@ __device__ __forceinline__ void traverse(const TreeView &tv, const GroupBox &b, 
     cnt_pc = 0;
     cnt_pp = 0;
     bool common = kSplit;          // the waves still walk the same cells
+    const uint32_t deal_at = min(kDealRanges, tv.ring - 128u);
     uint32_t dealt_pc = 0, dealt_pp = 0;  // entries dealt out so far
+    bool top = kTop && tv.ls != nullptr;
+    const uint32_t top_n = top ? uniform(tv.ls[3]) : 0u, top_push = top ? uniform(tv.ls[2]) : 0u;
     if (lane == 0) L.ring[0] = 0u;  // the root: first cell 0, one cell
     wave_sync();
 
     while (sp > 0) {
-        // ---- refill the ring from the spill area when the top range is not resident
-        const uint32_t avail = sp < 64u ? sp : 64u;
-        if (sp - avail < lo) {
-            lo -= 64u;
-            L.ring[(lo + lane) & rmask] = spill[lo + lane];
+        uint32_t cell_a, cell_b, sp_new;
+        bool have_a, have_b;
+        uint32_t up_a = 0u, up_b = 0u;  // top: the cells' parents
+        if (kTop && top) {
+            have_a = lane < top_n;
+            have_b = 64u + lane < top_n;
+            cell_a = have_a ? lane : 0u;
+            cell_b = have_b ? 64u + lane : 0u;
+            up_a = tv.parent[cell_a];
+            up_b = tv.parent[cell_b];
+            sp_new = 0u;
+        } else {
+            // ---- refill the ring from the spill area when the top range is not resident
+            const uint32_t avail = sp < 64u ? sp : 64u;
+            if (sp - avail < lo) {
+                lo -= 64u;
+                L.ring[(lo + lane) & rmask] = spill[lo + lane];
+                wave_sync();
+            }
+            // ---- pop up to 128 cells from the top ranges (range lane = stack top - lane)
+            const uint32_t e = L.ring[(sp - 1 - lane) & rmask];
+            const uint32_t ne = lane < avail ? (e & 7u) + 1u : 0u;
+            const uint32_t incl = wave_incl_scan(ne, lane);
+            const uint32_t excl = incl - ne;
+            const uint32_t nfull = (uint32_t)__popcll(ballot(lane < avail && incl <= 128u));
+            const uint32_t tall = read_lane(incl, avail - 1u);
+            const uint32_t total = tall < 128u ? tall : 128u;
+            L.starts[lane] = 0u;
+            L.starts[64u + lane] = 0u;
             wave_sync();
-        }
-        // ---- pop up to 128 cells from the top ranges (range lane = stack top - lane)
-        const uint32_t e = L.ring[(sp - 1 - lane) & rmask];
-        const uint32_t ne = lane < avail ? (e & 7u) + 1u : 0u;
-        const uint32_t incl = wave_incl_scan(ne, lane);
-        const uint32_t excl = incl - ne;
-        const uint32_t nfull = (uint32_t)__popcll(ballot(lane < avail && incl <= 128u));
-        const uint32_t tall = read_lane(incl, avail - 1u);
-        const uint32_t total = tall < 128u ? tall : 128u;
-        L.starts[lane] = 0u;
-        L.starts[64u + lane] = 0u;
-        wave_sync();
-        if (lane < avail && excl < 128u) L.starts[excl] = 1u;
-        wave_sync();
-        const uint64_t sa = ballot(L.starts[lane] != 0u);
-        const uint64_t sb = ballot(L.starts[64u + lane] != 0u);
-        // range of each slot's cell (cell 0 starts range 0: both indices are in 0..63)
-        const uint32_t ja = (uint32_t)__popcll(sa & mask_le(lane)) - 1u;
-        const uint32_t jb = (uint32_t)__popcll(sa) + (uint32_t)__popcll(sb & mask_le(lane)) - 1u;
-        const uint32_t c0 = (e >> 3) - excl;  // a range's first cell less its slot
-        const uint32_t ra = shfl(c0, ja), rb = shfl(c0, jb);
-        const bool have_a = lane < total, have_b = 64u + lane < total;
-        const uint32_t cell_a = have_a ? ra + lane : 0u;
-        const uint32_t cell_b = have_b ? rb + 64u + lane : 0u;
-        const uint32_t sp_new = sp - nfull;
-        if (nfull < avail && lane == nfull && excl < 128u) {
-            const uint32_t taken = 128u - excl;  // the rest of this range stays on top
-            L.ring[(sp_new - 1) & rmask] = (((e >> 3) + taken) << 3) | (ne - taken - 1u);
+            if (lane < avail && excl < 128u) L.starts[excl] = 1u;
+            wave_sync();
+            const uint64_t sa = ballot(L.starts[lane] != 0u);
+            const uint64_t sb = ballot(L.starts[64u + lane] != 0u);
+            // range of each slot's cell (cell 0 starts range 0: both indices are in 0..63)
+            const uint32_t ja = (uint32_t)__popcll(sa & mask_le(lane)) - 1u;
+            const uint32_t jb =
+                (uint32_t)__popcll(sa) + (uint32_t)__popcll(sb & mask_le(lane)) - 1u;
+            const uint32_t c0 = (e >> 3) - excl;  // a range's first cell less its slot
+            const uint32_t ra = shfl(c0, ja), rb = shfl(c0, jb);
+            have_a = lane < total;
+            have_b = 64u + lane < total;
+            cell_a = have_a ? ra + lane : 0u;
+            cell_b = have_b ? rb + 64u + lane : 0u;
+            sp_new = sp - nfull;
+            if (nfull < avail && lane == nfull && excl < 128u) {
+                const uint32_t taken = 128u - excl;  // the rest of this range stays on top
+                L.ring[(sp_new - 1) & rmask] = (((e >> 3) + taken) << 3) | (ne - taken - 1u);
+            }
         }
 
         // ---- opening test (idle slots read cell 0: all four loads are in flight
@@ -198,9 +226,24 @@ __device__ __forceinline__ void traverse(const TreeView &tv, const GroupBox &b, 
         const float4 Aa = tv.wA[cell_a], Ab = tv.wA[cell_b];
         const bool far_a = box_d2(Aa, b) >= Aa.w, far_b = box_d2(Ab, b) >= Ab.w;
         const bool cut_a = (Na.y & kLeafBit) != 0u, cut_b = (Nb.y & kLeafBit) != 0u;
+        bool push_a = true, push_b = true;
+        if (kTop && top) {  // reached: the parent and its parent opened; pushed: the last level
+            L.starts[lane] = (uint8_t)(!far_a & !cut_a);
+            L.starts[64u + lane] = (uint8_t)(!far_b & !cut_b);
+            wave_sync();
+            const uint32_t root = L.starts[0];
+            const bool in_a = L.starts[up_a & 127u] != 0u, in_b = L.starts[up_b & 127u] != 0u;
+            wave_sync();
+            have_a &= lane == 0u || (root != 0u && in_a);
+            have_b &= root != 0u && in_b;
+            push_a = cell_a >= top_push;
+            push_b = cell_b >= top_push;
+            top = false;
+        }
         bool acc_a = have_a & far_a, acc_b = have_b & far_b;
         bool leaf_a = have_a & !far_a & cut_a, leaf_b = have_b & !far_b & cut_b;
-        const bool open_a = have_a & !far_a & !cut_a, open_b = have_b & !far_b & !cut_b;
+        const bool open_a = have_a & !far_a & !cut_a & push_a;
+        const bool open_b = have_b & !far_b & !cut_b & push_b;
 
         if (kSplit && common) {  // this wave's share of the entries, in list order
             deal(acc_a, acc_b, sh, dealt_pc);
@@ -244,7 +287,7 @@ __device__ __forceinline__ void traverse(const TreeView &tv, const GroupBox &b, 
             L.ring[(sp_new + nob - 1u - count_below(omb)) & rmask] = (Nb.x << 3) | (Nb.y - 1u);
         }
         sp = sp_new + npush;
-        if (kSplit && common && sp >= kDealRanges) {  // (at most 63 + 128 ranges, none spilled)
+        if (kSplit && common && sp >= deal_at) {  // (at most tv.ring - 1 ranges, none spilled)
             wave_sync();
             const uint32_t j0 = sh.w + (lane << sh.logw), j1 = sh.w + ((64u + lane) << sh.logw);
             const uint32_t e0 = j0 < sp ? L.ring[j0] : 0u;

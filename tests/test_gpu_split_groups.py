@@ -41,6 +41,31 @@ def test_walk(oracle, n, ncrit):
     _same(pot, opot)
 
 
+@pytest.mark.parametrize("kind", ["plummer", "coincident", "pairs"])
+@pytest.mark.parametrize("n", [1, 2, 16, 17, 18, 65, 400])
+def test_first_pass_of_few_levels(oracle, n, kind):
+    """Trees of one, two and more levels, chains of single cells down to the
+    last level: the pass that takes the levels 0 to 2 together."""
+    s = ics.plummer(max(n, 2), 87)
+    pos, mass = s.pos[:n].copy(), s.mass[:n].copy()
+    if kind == "coincident":
+        pos[:] = pos[0]
+    elif kind == "pairs":
+        pos[1::2] = pos[0]
+    for nleaf, theta in ((16, 0.5), (1, 1.0)):
+        print(f"{kind} n={n} nleaf={nleaf}", flush=True)
+        t = gpu_tree(pos, mass, nleaf)
+        acc, pot = gpu_force(t, theta, 0.05)
+        npp, npc = t.export("group_npp").astype(np.int64), t.export("group_npc").astype(np.int64)
+        t.close()
+        oacc, opot, onpp, onpc = oracle.walk(oracle.build_tree(pos, mass, nleaf), theta, 0.05)
+        assert np.array_equal(npp, onpp) and np.array_equal(npc, onpc)
+        scale = max(np.abs(oacc).max(), 1e-30)
+        assert np.abs(acc - oacc).max() <= 1e-5 * scale + 1e-6
+        if n > 1:
+            assert np.percentile(rel_err(pot, opot), 99) <= 1e-4
+
+
 @pytest.mark.parametrize("n", [2048, 2049, 32768, 32769])
 def test_vjp(oracle, n):
     import torch
