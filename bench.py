@@ -174,7 +174,7 @@ def write_build_traffic(out_path, fetch_db, write_db, bench_json, command):
             "# algorithmic bytes (hbm_phases): sort 376 B per particle (box 12, keys 24, 8 radix",
             "# passes x 32, gather 84); build: the keys read once per splitting level plus 40 B per",
             "# cell and 12 B per particle for the groups (what a per-level scan would move; the",
-            "# build's binary searches over cell ranges read less); moments: 16 B per particle +",
+            "# build reads the keys twice, whatever the depth); moments: 16 B per particle +",
             "# 260 B per cell (topology 20, FP64 M, S, Q written 80 and read by the parent 80, walk",
             "# records 80)."]
     text = "\n".join(hdr + rows + foot) + "\n"
@@ -668,7 +668,7 @@ def profile_kernels(meta_path=None, log=print):
     pos = torch.from_numpy(snap.pos).to(dev)
     mass = torch.from_numpy(snap.mass).to(dev)
     meta = {"workload": "disk_halo_13m", "theta": w["theta"], "eps": w["eps"], "kernels": {}}
-    for f16, key in ((False, "k_walk<false, false>"), (True, "k_walk<false, true>")):
+    for f16, key in ((False, "k_walk<false, false, false>"), (True, "k_walk<false, true, false>")):
         t = bh.Tree(snap.n, far_fp16=f16)
         t.build(pos, mass)
         for _ in range(2):
@@ -788,7 +788,7 @@ def write_traffic(out_path, fetch_db, write_db, copy_fetch_db, copy_write_db, co
     """The committed HBM traffic of the FP32 walk: FETCH_SIZE and WRITE_SIZE
     (KiB per dispatch, mean over the walk's dispatches) scaled by what the
     same counters read for the plain 1 GiB device copy of --copy-calibration."""
-    key = "k_walk<false, false>"
+    key = "k_walk<false, false, false>"
 
     def mean_of(db, counter, pat):
         rows = [r for n, r in pmc_summary([db]).items() if pat in n]
@@ -797,8 +797,8 @@ def write_traffic(out_path, fetch_db, write_db, copy_fetch_db, copy_write_db, co
         return (sum(v * r["dispatches"] for v, r in zip(vals, rows)) / disp if disp else None,
                 disp)
 
-    f, nf = mean_of(fetch_db, "FETCH_SIZE", "k_walk<false, false>")
-    w_, nw = mean_of(write_db, "WRITE_SIZE", "k_walk<false, false>")
+    f, nf = mean_of(fetch_db, "FETCH_SIZE", "k_walk<false, false, false>")
+    w_, nw = mean_of(write_db, "WRITE_SIZE", "k_walk<false, false, false>")
     cf, _ = mean_of(copy_fetch_db, "FETCH_SIZE", "copyBuffer")
     cw, _ = mean_of(copy_write_db, "WRITE_SIZE", "copyBuffer")
     gib = float(1 << 30)
@@ -1138,7 +1138,7 @@ def main(argv=None):
     del pos, vel, mass
     counters = load_counters()
     out["valu_counters"] = None if args.pair_groups else counter_report(
-        counters, "k_walk<false, false>", walk_tflops, paper_flops(n_pp, n_pc) / args.steps)
+        counters, "k_walk<false, false, false>", walk_tflops, paper_flops(n_pp, n_pc) / args.steps)
     anchors = []
     if not args.no_precision:
         out["precision"] = precision(snap, theta, eps, log=log)
@@ -1150,7 +1150,7 @@ def main(argv=None):
         a["name"] = f"{args.workload} theta {theta}"
         anchors.append(a)
         f16 = out["precision"]["fp16_far"]
-        f16["valu_counters"] = counter_report(counters, "k_walk<false, true>", f16["tflops_walk"],
+        f16["valu_counters"] = counter_report(counters, "k_walk<false, true, false>", f16["tflops_walk"],
                                               paper_flops(f16["n_pp"], f16["n_pc"]))
     if not args.no_c4:
         c4 = precision_sweep(log=log)
