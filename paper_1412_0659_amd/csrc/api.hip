@@ -1195,8 +1195,7 @@ int tree_force_static(const float *pos, const float *mass, int64_t n, float thet
     if (static_layout(&c, d.ptr) > kStaticBytes) return BH_ENOMEM;
     c.n = n;
     c.cur = 0;
-    // the array keeps the previous call's contents: clear the status words
-    launch_fill_u32(c.status, 0u, 4, s);
+    c.clear_status = true;  // the array keeps the previous call's contents
     rebuild(&c, caller_source(pos, nullptr, mass), (uint32_t)n, s, theta);
     force(&c, theta, eps, to_caller(acc, pot), s, true);
     if (status) {

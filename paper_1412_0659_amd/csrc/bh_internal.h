@@ -166,6 +166,7 @@ struct bh_ctx {
     float *box = nullptr;   // [8]: lo xyz, side, scale
     float *box_part = nullptr;
     uint32_t *status = nullptr;
+    bool clear_status = false;  // a build starts with clear status words (tree_force_static)
     uint32_t *work = nullptr;                // [2][8][kWorkStride] walk work counters, one per line
     unsigned long long *totals = nullptr;    // [4] n_pp, n_pc, leaves
     bh::Sort sort{};
