@@ -258,10 +258,10 @@ static void launch_gather(bh_ctx *c, const Source &s, uint32_t n, hipStream_t st
 // in LDS.
 //
 // Bound: latency on small sets (one launch up to 1024 particles, two up to
-// 8192, then one per doubling, where the radix passes over memory below take five launches
+// 12288, then one per doubling, where the radix passes over memory below take five launches
 // per digit), 24 B per particle and merge on larger ones.  Measured, bounding
 // box, keys, sort and gather of a set in random order, in us, these against
-// the radix passes: n = 1000: 18 / 135; 4096: 32 / 148; 16384: 54 / 192; 65536:
+// the radix passes: n = 1000: 18 / 135; 4096: 31 / 148; 16384: 54 / 192; 65536:
 // 73 / 213; 500000: 136 / 257; 1M: 192 / 297; 2M: 312 / 373; 3M: 460 / 529; 4M:
 // 625 / 615; 8M: 1235 / 1105.
 constexpr uint32_t kMergeMax = 3u << 20;
@@ -509,9 +509,13 @@ static void launch_sort_block(bh_ctx *c, const Source &s, uint32_t n, uint32_t n
 // Sets of up to kRankMax particles: the place of every particle among all runs
 // of 1024 in one launch, its place in its own run plus the keys before it in
 // each other run (ties from the earlier run first), found by binary searches
-// that do not wait for each other; the particle is moved there at once.
+// that do not wait for each other; the particle is moved there at once.  The
+// sort phase by four / eight / sixteen searches at once, in us: 4099 31.7 / 30.8 /
+// 31.7; 8192 42.6 / 40.2 / 41.2.  The line: 12000 particles 53.4 against 57.8 by
+// merges, 16384 57.2 against 54.2.
 constexpr uint32_t kRankRun = 1024;
-constexpr uint32_t kRankMax = 8 * kRankRun;
+constexpr uint32_t kRankAtOnce = 8;  // searches that do not wait for each other
+constexpr uint32_t kRankMax = 12 * kRankRun;
 
 __global__ __launch_bounds__(256) void k_sort_rank(const uint64_t *__restrict__ key,
                                                    const uint32_t *__restrict__ idx, uint32_t n,
@@ -522,12 +526,12 @@ __global__ __launch_bounds__(256) void k_sort_rank(const uint64_t *__restrict__ 
     if (i >= n) return;
     const uint64_t k = key[i];
     uint32_t rank = i - own * kRankRun;
-    for (uint32_t q0 = 0; q0 < runs; q0 += 4u) {
-        uint32_t pos[4] = {0u, 0u, 0u, 0u};
+    for (uint32_t q0 = 0; q0 < runs; q0 += kRankAtOnce) {
+        uint32_t pos[kRankAtOnce] = {};
 #pragma unroll
         for (uint32_t step = kRankRun; step > 0u; step >>= 1) {
 #pragma unroll
-            for (uint32_t q = 0; q < 4u; ++q) {
+            for (uint32_t q = 0; q < kRankAtOnce; ++q) {
                 const uint32_t r = q0 + q, base = r * kRankRun;
                 if (r >= runs || r == own) continue;
                 const uint32_t len = min(kRankRun, n - base), e = pos[q] + step;
@@ -535,7 +539,8 @@ __global__ __launch_bounds__(256) void k_sort_rank(const uint64_t *__restrict__ 
                 if (e <= len && (r < own ? v <= k : v < k)) pos[q] = e;
             }
         }
-        rank += pos[0] + pos[1] + pos[2] + pos[3];
+#pragma unroll
+        for (uint32_t q = 0; q < kRankAtOnce; ++q) rank += pos[q];
     }
     key_out[rank] = k;
     move_particle(a, idx[i], b, rank, xyzm);
