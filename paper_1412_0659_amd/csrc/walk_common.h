@@ -317,8 +317,12 @@ __device__ __forceinline__ void traverse(const TreeView &tv, const GroupBox &b, 
         // ---- particles of opened leaves -> particle-particle index list, 64
         // entries at a time: the leaves that begin among them are marked, and an
         // entry's leaf is the last to begin at or before it (leaves in the order
-        // of lanes, slot a first; each holds at least one particle)
-        const bool pa = !kLeafCells & leaf_a, pb = !kLeafCells & leaf_b;
+        // of lanes, slot a first).  A leaf without particles is left out: it would
+        // begin where the next one does.  Only a local essential tree has them
+        // (cells its boxes accept, kept without what is below); a paired target
+        // set, whose box reaches over two terminal cells, opens them.
+        const bool pa = !kLeafCells & leaf_a & (Na.y != kLeafBit);
+        const bool pb = !kLeafCells & leaf_b & (Nb.y != kLeafBit);
         const uint64_t la = ballot(pa), lb = ballot(pb);
         if ((la | lb) != 0ull) {
             const uint32_t ca = pa ? (Na.y & ~kLeafBit) : 0u;
