@@ -115,6 +115,20 @@ __device__ __forceinline__ void deal(bool &a, bool &b, const Share &sh, uint32_t
     dealt += na + (uint32_t)__popcll(mb);
 }
 
+// A leaf of more than a chunk of particles (coincident ones: others hold at
+// most 64) is not dealt to one wave: each takes its share of the particles, at
+// least four.  Dealt whole it made one wave of every group do all the work of
+// a coincident set, and those waves all in the same quarter of the CUs: force
+// of 50000 coincident particles 4.69 ms (in shares 1.37; one wave per group
+// 3.29), adjoint of 20000 9.73 (1.32; 6.41).
+constexpr uint32_t kBigLeaf = kLeafBit | (uint32_t)kChunk;
+__device__ __forceinline__ bool share_leaf(uint2 &N, const Share &sh) {
+    const uint32_t c = N.y & ~kLeafBit, q = c >> sh.logw, r = c & ((1u << sh.logw) - 1u);
+    N.x += q * sh.w + min(sh.w, r);
+    N.y = (q + (sh.w < r ? 1u : 0u)) | kLeafBit;
+    return true;
+}
+
 // Walk the tree for one group.  flush_pc(n) / flush_pp(n) evaluate the first
 // n entries of L.pcidx / L.ppidx (called with n > 0, all lanes, after a
 // barrier); both lists are empty when traverse returns.  Counts: accepted
@@ -138,7 +152,7 @@ __device__ __forceinline__ void deal(bool &a, bool &b, const Share &sh, uint32_t
 // kSplit: 2^logw waves walk the tree for the same group, each calling
 // traverse with its own share.  They run the same passes until the stack
 // holds kDealRanges ranges, the accepted cells and opened leaves of those
-// passes dealt out in list order; then wave w keeps every 2^logw-th range and
+// passes dealt out in list order (big leaves shared); then wave w keeps every 2^logw-th range and
 // walks those subtrees alone.  Which wave takes what depends only on the tree
 // and the group, so the sums do not depend on scheduling.  The more ranges are
 // dealt out, the more alike the shares: 96 against 64 (that is all the smaller
@@ -222,7 +236,7 @@ __device__ __forceinline__ void traverse(const TreeView &tv, const GroupBox &b, 
 
         // ---- opening test (idle slots read cell 0: all four loads are in flight
         // together, where branches around them made each wait for the last)
-        const uint2 Na = tv.wN[cell_a], Nb = tv.wN[cell_b];
+        uint2 Na = tv.wN[cell_a], Nb = tv.wN[cell_b];
         const float4 Aa = tv.wA[cell_a], Ab = tv.wA[cell_b];
         const bool far_a = box_d2(Aa, b) >= Aa.w, far_b = box_d2(Ab, b) >= Ab.w;
         const bool cut_a = (Na.y & kLeafBit) != 0u, cut_b = (Nb.y & kLeafBit) != 0u;
@@ -247,7 +261,12 @@ __device__ __forceinline__ void traverse(const TreeView &tv, const GroupBox &b, 
 
         if (kSplit && common) {  // this wave's share of the entries, in list order
             deal(acc_a, acc_b, sh, dealt_pc);
+            const bool all_a = leaf_a, all_b = leaf_b;
             deal(leaf_a, leaf_b, sh, dealt_pp);
+            if (ballot(max(Na.y, Nb.y) > kBigLeaf) != 0ull) {
+                if (all_a & (Na.y > kBigLeaf)) leaf_a = share_leaf(Na, sh);
+                if (all_b & (Nb.y > kBigLeaf)) leaf_b = share_leaf(Nb, sh);
+            }
         }
 
         // ---- accepted cells -> particle-cell index list
