@@ -116,16 +116,28 @@ Source caller_source(const float *pos, const float *vel, const float *mass) {
     return r;
 }
 
-// Whether a kernel of c can read or write a snapshot at p: memory of c's
-// device, aligned for its widest field (else it is copied field by field).
-bool in_place(const bh_ctx *c, const void *p) {
+// Bytes of a snapshot of n particles.
+int64_t state_bytes(const bh_ctx *c, int64_t n) {
+    return n * (int64_t)(7 * sizeof(float) + sizeof(uint32_t) +
+                         (c->p.pos_fp64 ? 3 * sizeof(double) : 0));
+}
+
+// Whether a kernel of c can read or write a snapshot of `bytes` at p: inside
+// one allocation on c's device, aligned for its widest field.  Else it is
+// copied field by field, and the runtime refuses what an allocation does not hold.
+bool in_place(const bh_ctx *c, const void *p, int64_t bytes) {
     if (reinterpret_cast<uintptr_t>(p) % sizeof(double)) return false;
     hipPointerAttribute_t at{};
-    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+    hipDeviceptr_t base{};
+    size_t size = 0;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess ||
+        hipMemGetAddressRange(&base, &size, const_cast<void *>(p)) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
-    return at.type == hipMemoryTypeDevice && at.device == c->device;
+    const size_t off = (size_t)(static_cast<const char *>(p) - static_cast<const char *>(base));
+    return at.type == hipMemoryTypeDevice && at.device == c->device && off <= size &&
+           (size_t)bytes <= size - off;
 }
 
 // Copy a snapshot of n particles to (out) or from st, field by field.
@@ -750,8 +762,7 @@ int leapfrog_vjp_segment(bh_ctx *c, const void *snap, int64_t n, int32_t k, int3
     int rc = check_n(c, n);
     if (rc) return rc;
     const size_t vec = 3 * sizeof(float) * (size_t)n;
-    const int64_t per = n * (int64_t)(7 * sizeof(float) + sizeof(uint32_t) +
-                                      (c->p.pos_fp64 ? 3 * sizeof(double) : 0));
+    const int64_t per = state_bytes(c, n);
     std::string err;
     if (k > 1 && !grow(&c->seg, c->seg_cap, (int64_t)(k - 1) * per, err))
         return fail(c, BH_ENOMEM, err);
@@ -785,8 +796,7 @@ int leapfrog_vjp_segment(bh_ctx *c, const void *snap, int64_t n, int32_t k, int3
 
 int64_t bh_state_bytes(const bh_ctx *c) {
     if (!c || !c->built) return 0;
-    return c->n * (int64_t)(7 * sizeof(float) + sizeof(uint32_t) +
-                            (c->p.pos_fp64 ? 3 * sizeof(double) : 0));
+    return state_bytes(c, c->n);
 }
 
 int bh_save_state(bh_ctx *c, void *dst, hipStream_t s) {
@@ -795,7 +805,7 @@ int bh_save_state(bh_ctx *c, void *dst, hipStream_t s) {
     if (!c->built) return fail(c, BH_ESTATE, "no state");
     const State &st = c->st[c->cur];
     const size_t n = (size_t)c->n;
-    if (in_place(c, dst)) {
+    if (in_place(c, dst, state_bytes(c, c->n))) {
         launch_save(st, (uint32_t)n, static_cast<char *>(dst), s);
         BH_HIP(c, hipGetLastError());
         return BH_OK;
@@ -812,7 +822,7 @@ int bh_load_state(bh_ctx *c, const void *src, int64_t n64, hipStream_t s) {
     const size_t n = (size_t)n64;
     c->n = n64;
     Source r = source_of(c->st[c->cur]);
-    if (in_place(c, src)) {
+    if (in_place(c, src, state_bytes(c, n64))) {
         const float *f = static_cast<const float *>(src);
         r.x = f; r.y = f + n; r.z = f + 2 * n; r.m = f + 3 * n;
         r.vx = f + 4 * n; r.vy = f + 5 * n; r.vz = f + 6 * n;
