@@ -35,13 +35,23 @@
 // addresses: the cells of a list come in runs of siblings, and 64 cells of ten
 // values are 40 to 60 cache lines instead of ten times the 15 or so runs.
 //
+// Sums: a source's over the group's targets and a target's over one flush of a
+// list are FP32 (the latter in 16 columns); flushes, lists and waves meet in
+// FP64.  (One FP32 sum over all flushes lost 1e-3 to 0.5 of the cells' part of
+// a target next to a pair 0.02 to 0.005 apart; the three wider sums cost 1 to 3%
+// on sets of up to 4096, nothing from 16384.)  B' below, the quadrupole with its
+// trace folded in, is rounded to FP32 once more than the two terms it stands
+// for.  Against FP64 on the same lists (300 to 40000 particles, theta 0.3 to
+// 0.8) the positions' gradient is 0.20 to 0.94 times as far off as with lane
+// sums and the trace apart, the masses' as far.
+//
 // Bound: the L2's atomics, which go at 2.35e10 requests of 64 bytes per second
-// (1.9e11 adds where eight lanes fill a request): 2.0e9 adds of the cells at 1M
-// (theta 0.4) take 18.5 ms with the pairs left out, everything but the adds 13.9
-// ms (84 VALU instructions and a reciprocal root per particle-cell pair).
-// Measured at 1M, theta 0.4: 23.0 ms with lane sums by DPP, accumulators field by
-// field and particle pairs evaluated once per side; 19.4 with a source's sums
-// added once per 32 targets; 17.4 now that they are added once per group.
+// (1.9e11 adds where eight lanes fill a request): at 1M (theta 0.4) 2.34e9 adds
+// leave in 3.46e8 requests, 14.7 ms at that rate.  The walk takes 16.9 ms, 15.9
+// with the pairs left out and 14.2 with the adds left out (84 VALU instructions
+// and a reciprocal root per particle-cell pair).  It took 23.0 ms with lane sums
+// by DPP, accumulators field by field and particle pairs evaluated once per
+// side; 19.4 with a source's sums added once per 32 targets.
 #include <algorithm>
 
 #include "walk_common.h"
@@ -241,7 +251,7 @@ __device__ __forceinline__ float row_total(float v) {
 
 // Take the sums from lane tb + t's target terms g, t < kTiles kTile.
 __device__ __forceinline__ void take_targets(const TargetSums &s, VjpLds &L, uint32_t lane,
-                                             uint32_t tb, float g[3]) {
+                                             uint32_t tb, double g[3]) {
 #pragma unroll
     for (uint32_t i = 0; i < kTiles; ++i)
 #pragma unroll
@@ -282,7 +292,7 @@ __device__ void vjp_group(const VjpArgs &a, uint32_t g, uint32_t w, uint32_t lan
     const float4 mu = a.u[ti];
     L.tp[lane] = make_float4(me.x, me.y, me.z, mu.x);
     L.tu[lane] = make_float2(mu.y, mu.z);
-    float gt[3] = {0.f, 0.f, 0.f};  // target terms of lane t's target
+    double gt[3] = {0.0, 0.0, 0.0};  // target terms of lane t's target
 
     // one trip: target t's position and cotangent
     auto target = [&](uint32_t t, float T[3], float U[3]) {
@@ -455,7 +465,7 @@ __device__ void vjp_group(const VjpArgs &a, uint32_t g, uint32_t w, uint32_t lan
     if (own) {
         double *gs = gsx + 4ull * ti;
 #pragma unroll
-        for (int k = 0; k < 3; ++k) add_l2(gs + k, (double)gt[k]);
+        for (int k = 0; k < 3; ++k) add_l2(gs + k, gt[k]);
     }
     wave_sync();
 }
