@@ -74,7 +74,9 @@ __global__ __launch_bounds__(256) void k_cic_deposit(const float *__restrict__ p
 // fifth selected), which the L2 runs one after another per address: 238 us
 // for the whole call there, 15 us with the blocks' own grids (8 x 8 cells: 1071
 // against 15 us; 64 x 128: 41 against 16; 128 x 256, adds straight to memory:
-// 38).
+// 38).  A block clears its grid and reads it all back for at most 4096
+// particles, so few particles on many cells take the other kernel
+// (own_grids).
 constexpr int kCicLds = 8192;
 constexpr int kCicThreads = 1024;
 
@@ -141,14 +143,23 @@ __global__ __launch_bounds__(256) void k_cic_vjp(const float *__restrict__ pos,
     if (g_mass) g_mass[k] += dm;
 }
 
+// Whether n particles on nb cells are summed on the blocks' own grids.
+// Deposit in us, straight to memory / on own grids, all selected: 64 cells, n = 1,
+// 4, 16 per cell 2.1 / 2.0, 2.5 / 1.9, 4.0 / 2.4; 256 cells 2.2 / 1.9, 2.7 / 2.4, 5.4 /
+// 5.2; 512 cells, n = 2, 8, 16 per cell 2.4 / 2.6, 4.0 / 5.2, 6.2 / 5.7; 2048 cells
+// 3.1 / 5.6, 4.8 / 6.0, 7.5 / 6.5; 8192 cells 3.9 / 7.2, 7.6 / 7.6, 12.6 / 8.1.  A
+// fifth selected (the host does not know how many): the lines come at 4 to 8.
+static bool own_grids(uint32_t n, uint32_t nb) {
+    return nb <= (uint32_t)kCicLds && n >= (nb <= 256u ? nb : 16u * nb);
+}
+
 void launch_cic(const float *pos, const float *mass, const uint8_t *sel, uint32_t n, float rmin,
                 float rmax, int nr, int nphi, double *scratch, float *density, hipStream_t st) {
     const CicGeom g{rmin, rmax, (rmax - rmin) / nr, 6.28318530717958647692f / nphi, nr, nphi};
     const uint32_t nb = (uint32_t)nr * (uint32_t)nphi;
     launch_fill_u32(reinterpret_cast<uint32_t *>(scratch), 0u, 2ull * nb, st);
-    // a block's own grid pays when its particles outnumber the grid's cells
     const uint32_t blocks = cdiv(n, 4 * kCicThreads);
-    if (nb <= (uint32_t)kCicLds && n >= nb)
+    if (own_grids(n, nb))
         hipLaunchKernelGGL(k_cic_deposit_lds, dim3(blocks < 256u ? blocks : 256u),
                            dim3(kCicThreads), nb * sizeof(double), st, pos, mass, sel, n, g,
                            scratch);
