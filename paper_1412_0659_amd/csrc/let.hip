@@ -204,11 +204,8 @@ struct LetBatch {
 // opening radii of the batch's sources for theta
 __global__ __launch_bounds__(256) void k_let_prep(LetBatch b, float theta) {
     const LetSrc &s = b.s[blockIdx.y];
-    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < s.nc; i += gridDim.x * 256) {
-        const float2 sz = s.size[i];
-        const float r = sz.x / theta + sz.y;
-        s.wA[i].w = r * r;
-    }
+    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < s.nc; i += gridDim.x * 256)
+        s.wA[i].w = open_radius2(s.size[i], theta);
 }
 
 // One wave per (source, target box): the force walk's traversal of the

@@ -283,7 +283,7 @@ __device__ __forceinline__ void traverse(const TreeView &tv, const GroupBox &b, 
         const uint64_t oma = ballot(open_a), omb = ballot(open_b);
         const uint32_t nob = (uint32_t)__popcll(omb);
         const uint32_t npush = (uint32_t)__popcll(oma) + nob;
-        const uint32_t top = sp_new + npush - 1u;
+        const uint32_t last = sp_new + npush - 1u;  // the new top of the stack
         if (sp_new + npush > (uint32_t)kStackMax) {  // cannot happen: 128 ranges per level
             if (lane == 0) atomicOr(tv.status, kStOverflow);
             break;
@@ -300,7 +300,7 @@ __device__ __forceinline__ void traverse(const TreeView &tv, const GroupBox &b, 
             if (open_b) tv.opened[cell_b] = 1u;
         }
         if (open_a) {
-            L.ring[(top - count_below(oma)) & rmask] = (Na.x << 3) | (Na.y - 1u);
+            L.ring[(last - count_below(oma)) & rmask] = (Na.x << 3) | (Na.y - 1u);
         }
         if (open_b) {
             L.ring[(sp_new + nob - 1u - count_below(omb)) & rmask] = (Nb.x << 3) | (Nb.y - 1u);
