@@ -85,7 +85,10 @@ typedef struct bh_params {
                          union (Sec. III.A walks a group of targets at a time;
                          the paper does not fix how targets are grouped).  Fewer
                          walks, more interactions per target: the forces are the
-                         same method's, with more particle-particle terms. */
+                         same method's, with more particle-particle terms.  A
+                         local essential tree (bh_let_build) is cut for the
+                         terminal cells' boxes: of a cell that they accept and
+                         a set's wider box opens it has nothing to give. */
     int32_t reserved;
 } bh_params;
 
@@ -93,7 +96,9 @@ typedef struct bh_ctx bh_ctx;
 
 /* Create a context on the current HIP device with room for up to n_max
  * particles.  The context owns every buffer the path needs (sorted particle
- * state, keys, cells, moments, groups); they are allocated here, once.
+ * state, keys, cells, moments, groups, and up to 50 MB of partial sums for the
+ * walks of up to 2^20 particles, whose groups several waves share); they are
+ * allocated here, once.
  * p == NULL selects nleaf = 16, ncrit = 64.  On success *out is set. */
 int bh_create(bh_ctx **out, int64_t n_max, const bh_params *p);
 

@@ -16,7 +16,7 @@ namespace bh {
 constexpr int kKeyBits = 21;            // bits per axis of a Morton key
 constexpr int kLevels = 22;             // levels 0..21
 constexpr int kLsSize = 24;             // level_start entries (23 used)
-constexpr int kGrid = 1024;             // fixed grid of the per-level moment, box and flag kernels
+constexpr int kGrid = 1024;             // grid of the strided kernels over the cells (boxes, flags, radii, centres)
 constexpr int kTreeTile = 1024;         // particles per block of the octree build
 constexpr uint32_t kScanTiles = 64;  // tiles whose counts every block of k_tree_write adds up
 constexpr int kSpanTiles = 128;         // tiles per block of the moment pass over tile ends
@@ -314,11 +314,22 @@ int walk_blocks_per_cu();
 // become more.  Walk in us, all groups alike (the best number of waves) / this
 // rule, disk + halo at theta 0.4: n = 1000 31 / 32 (Plummer); 4099 74 / 63
 // (Plummer); 16384 194 / 175; 40000 388 / 307; 65536 472 / 387; 131072 834 / 677;
-// 1M 4637 / 4390 and 4768 with no split.  The lines, by up to 8 / 4 waves: at 16384
-// (Plummer, theta 0.5) 147 / 162, at 24576 (0.6) 171 / 153, at 32768 (Plummer) 228
-// / 187; 4 / 2: at 200000 933 / 1016, at 262144 1208 / 1264 and (0.6) 630 / 600, at
-// 500000 2281 / 2163 and 1199 / 1079; 2 / 1: 1M at theta 0.6 2142 / 2092, 2M at
-// theta 0.4 8614 / 8651, 4M 10800 / 10636.
+// 1M 4637 / 4390 and 4768 with no split.  The lines, us by the rule below / above:
+//   8192 (4 or 2 waves for groups of up to 16 targets), forces at theta 0.4, 0.6,
+//   0.8: 4099 (Plummer) 71 / 76, 64 / 69, 61 / 62; 8192 111 / 118, 96 / 94, 88 / 84
+//   (disk + halo 123 / 130, 99 / 104, 89 / 87); 10000 125 / 135, 104 / 102, 89 / 88
+//   (134 / 131, 108 / 100, 94 / 86); 12000 146 / 145, 123 / 115, 108 / 100.
+//   20480 (up to 8 or 4): 16384 (Plummer, theta 0.5) 147 / 162, 24576 (0.6) 171 /
+//   153, 32768 (Plummer) 228 / 187.
+//   262144 (up to 4 or 2): 200000 933 / 1016, 262144 1208 / 1264 and (0.6) 630 /
+//   600, 500000 2281 / 2163 and 1199 / 1079.
+//   2^20 (up to 2 or 1), forces of a disk + halo at 0.4, 0.6, 0.8: 300000 1360 /
+//   1508, 690 / 735, 419 / 420; 700000 3015 / 3222, 1440 / 1462, 818 / 790; 1M 4252 /
+//   4478, 1992 / 1987, 1140 / 1071; 1.2M 5074 / 5284, 2385 / 2383, 1346 / 1270; 2M
+//   8537 / 8652, 3985 / 3940, 2183 / 2084; 3M 12937 / 12835, 6327 / 5982, 3487 /
+//   3194.  The longer walks of a small theta gain by two waves and the short
+//   ones of a large theta lose; the rule does not look at theta, and at a million
+//   the three come out even.
 struct Split {
     uint32_t logw, t1, t2;
 };

@@ -14,7 +14,7 @@
 // target are added with FP64 atomics, so their order (and the last bits of
 // the result) may vary between runs.
 //
-// Bound: FP64 VALU, 19 operations and one v_rsq_f64 per pair.  1 / r is the
+// Bound: FP64 VALU, 18 operations and one v_rsq_f64 per pair.  1 / r is the
 // hardware's estimate and one third-order step, y (1 + e (1/2 + 3/8 e)) with
 // e = 1 - r^2 y^2, which leaves only rounding; a square root and a division
 // cost more than the rest of the pair.  8192 targets of 1M sources: 5.38 ms,

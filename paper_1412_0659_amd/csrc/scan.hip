@@ -1,5 +1,6 @@
 // Exclusive prefix sum of u32 arrays (reduce, scan the block totals, scan
-// down).  Used for the radix-sort digit offsets and the group numbering.
+// down).  Used for the radix-sort digit offsets, the numbering of paired target
+// sets and that of boundary and LET cells.
 #include "bh_internal.h"
 #include "wave.h"
 
